@@ -124,25 +124,20 @@ moespec_status layer_forward(const moespec_desc *desc, const moespec_weights *we
     if (e != hipSuccess) return MOESPEC_ERR_HIP;
     mark(1);
     e = launch_expert_ffn(*desc, *weights, h, M, B, nullptr, nullptr, nullptr, tok_ids, tok_w, residual, out, w.act,
-                          w.y, w.items, false, w.list_count, budget_ids, nullptr, nullptr, st, tr ? tr + 2 : nullptr,
-                          w.lists, M, x_next);
+                          w.y, w.items, false, w.list_count, budget_ids, w.lists, M, st, tr ? tr + 2 : nullptr, x_next);
     return from_hip(e);
   }
-  // Other shapes: the expert passes derive their segments themselves where they can, and the budget stage groups
-  // the pairs only if the caller asked for the segment arrays or the passes need them.
-  const bool self_seg = expert_ffn_self_segmenting(*desc, M);
-  const bool want_segments = !self_seg || t.seg_off || t.perm || t.n_loaded;
+  // Other shapes: the budget stage groups the pairs into the segment arrays and work items of the expert passes.
   hipError_t e = mfma_route_ok(*desc, M)
-                     ? launch_mfma_route(*desc, *weights, h, M, w.partial, probs, w.done, 1 + desc->n_experts, st)
-                     : launch_route(*desc, *weights, h, M, probs, nullptr, nullptr, w.done, 1 + desc->n_experts, st);
+                     ? launch_mfma_route(*desc, *weights, h, M, w.partial, probs, st)
+                     : launch_route(*desc, *weights, h, M, probs, nullptr, nullptr, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   e = launch_budget(*desc, probs, M, B, policy, ext_shortlist, t.scores, budget_ids, tok_ids, tok_w, seg_expert,
-                    seg_off, perm, t.n_loaded, w.items, w.done, true, want_segments, w.scores, st);
+                    seg_off, perm, t.n_loaded, w.items, w.score_parts, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   mark(1);
   e = launch_expert_ffn(*desc, *weights, h, M, B, seg_expert, seg_off, perm, tok_ids, tok_w, residual, out, w.act,
-                        w.y, w.items, want_segments, self_seg ? w.done + 1 : nullptr, budget_ids, w.pub_items,
-                        w.pub_lists, st, tr ? tr + 2 : nullptr, nullptr, 0, x_next);
+                        w.y, w.items, true, nullptr, nullptr, nullptr, 0, st, tr ? tr + 2 : nullptr, x_next);
   return from_hip(e);
 }
 
@@ -178,7 +173,7 @@ moespec_status moespec_route(const moespec_desc *desc, const moespec_weights *we
   if ((s = check_weights(weights, true, false)) != MOESPEC_OK) return s;
   if (!h || !probs || !aligned16(h)) return MOESPEC_ERR_INVALID_ARG;
   return from_hip(
-      launch_route(*desc, *weights, h, M, probs, topk_ids, topk_w, nullptr, 0, static_cast<hipStream_t>(hip_stream)));
+      launch_route(*desc, *weights, h, M, probs, topk_ids, topk_w, static_cast<hipStream_t>(hip_stream)));
 }
 
 moespec_status moespec_budget(const moespec_desc *desc, const double *probs, int32_t M, int32_t B, int32_t policy,
@@ -192,8 +187,8 @@ moespec_status moespec_budget(const moespec_desc *desc, const double *probs, int
   Workspace w = carve_workspace(*desc, M, ws);
   return from_hip(launch_budget(*desc, probs, M, B, policy, ext_shortlist, scores,
                                 budget_ids ? budget_ids : w.budget_ids, tok_ids, tok_w,
-                                seg_expert, seg_off, perm, n_loaded, w.items, w.done, false, true,
-                                w.scores, static_cast<hipStream_t>(hip_stream)));
+                                seg_expert, seg_off, perm, n_loaded, w.items, w.score_parts,
+                                static_cast<hipStream_t>(hip_stream)));
 }
 
 moespec_status moespec_expert_ffn(const moespec_desc *desc, const moespec_weights *weights, const void *h, int32_t M,
@@ -208,7 +203,7 @@ moespec_status moespec_expert_ffn(const moespec_desc *desc, const moespec_weight
   if (!aligned16(h) || !aligned16(out) || (residual && !aligned16(residual))) return MOESPEC_ERR_INVALID_ARG;
   Workspace w = carve_workspace(*desc, M, ws);
   return from_hip(launch_expert_ffn(*desc, *weights, h, M, n_seg, seg_expert, seg_off, perm, tok_ids, tok_w, residual,
-                                    out, w.act, w.y, w.items, false, nullptr, nullptr, nullptr, nullptr,
+                                    out, w.act, w.y, w.items, false, nullptr, nullptr, nullptr, 0,
                                     static_cast<hipStream_t>(hip_stream)));
 }
 
@@ -334,15 +329,13 @@ moespec_status moespec_oracle_ranking(const moespec_desc *desc, const moespec_we
   Workspace w = carve_workspace(*desc, M, ws);
   const int N = desc->n_experts;
   // natural routing (Eq. (2)): the budgeted path with B = N and truncation keeps every token's top-k
-  const bool self_seg = expert_ffn_self_segmenting(*desc, M);
-  hipError_t e = launch_route(*desc, *weights, h, M, w.probs, nullptr, nullptr, w.done, 1 + N, st);
+  hipError_t e = launch_route(*desc, *weights, h, M, w.probs, nullptr, nullptr, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   e = launch_budget(*desc, w.probs, M, N, MOESPEC_TRUNCATE, nullptr, nullptr, w.budget_ids, w.tok_ids, w.tok_w,
-                    w.seg_expert, w.seg_off, w.perm, nullptr, w.items, w.done, true, !self_seg, w.scores, st);
+                    w.seg_expert, w.seg_off, w.perm, nullptr, w.items, w.score_parts, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   e = launch_expert_ffn(*desc, *weights, h, M, N, w.seg_expert, w.seg_off, w.perm, w.tok_ids, w.tok_w, nullptr,
-                        nullptr, w.act, w.y, w.items, !self_seg, self_seg ? w.done + 1 : nullptr, w.budget_ids,
-                        w.pub_items, w.pub_lists, st);
+                        nullptr, w.act, w.y, w.items, true, nullptr, nullptr, nullptr, 0, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   return from_hip(launch_oracle_ranking(*desc, w.y, down_splits(*desc, N), (size_t)M * desc->top_k * desc->d,
                                         w.tok_ids, w.tok_w, M, B, static_cast<double *>(w.act), w.gram, ranking, err,

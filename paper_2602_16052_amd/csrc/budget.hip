@@ -2,322 +2,360 @@
 // probability over the tree (Eq. (5)), top-B shortlist (Section 3.2), restriction of every token's
 // routing by truncation (Eq. (7)) or substitution (Eq. (8)), and the grouping of the surviving
 // (token, slot) pairs into per-expert segments.  All decisions in fp64, ties to the lowest id.
+//
+// Three launches, none of which has a workgroup that does the whole tree's work by itself:
+//   score_parts_kernel   column sums of blocks of rows (large trees only; the others add the rows in the next launch)
+//   budget_kernel        one WAVE per token: every workgroup adds the partial sums and ranks the experts itself
+//   group_pairs_kernel   one workgroup per shortlisted expert: its pairs, its offset, its work items
 #include "common.h"
 
 namespace moespec {
 
-constexpr int kBudgetThreads = 1024;
-constexpr int kRedundantScoreTokens = 256;
+// Up to this many tokens every workgroup of budget_kernel adds the rows of the table itself (127 rows of 128 experts:
+// 130 KB from L2, a quarter of a microsecond per 16 KB); above, the row blocks are summed once by a launch of its own.
+constexpr int kDirectScoreRows = 128;
+constexpr int kScoreLoads = 32;  // rows in flight per thread of those sums
 
-// s_i = sum over t = 0..M-1 of probs[t, i], added strictly in ascending t; the loads of up to 32 rows
-// are issued together so that the chain is bound by the adds, not by memory latency.
-__device__ __forceinline__ double column_sum(const double *__restrict__ probs, int M, int N, int i) {
-  double acc = 0.0;
-  for (int t = 0; t < M; t += 32) {
-    double v[32];
+// part[b, i] = sum of probs[t, i] over the rows t of block b, ascending.  Wave w of a workgroup adds the rows w, w + 16,
+// ... of the block, and thread i the 16 results in wave order.  N <= 1024.
+__global__ __launch_bounds__(kScoreThreads) void score_parts_kernel(const double *__restrict__ probs, int M, int N,
+                                                                    int rows, double *__restrict__ part) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  double *tab = reinterpret_cast<double *>(smem);  // [16][N]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t0 = blockIdx.x * rows, t1 = min(M, t0 + rows);
+  for (int i = lane; i < N; i += kWave) {
+    double a = 0.0;
+    for (int t = t0 + wave; t < t1; t += 4 * kScoreWaves) {
+      double v[4];
 #pragma unroll
-    for (int u = 0; u < 32; ++u) v[u] = t + u < M ? probs[(size_t)(t + u) * N + i] : 0.0;
+      for (int u = 0; u < 4; ++u) v[u] = t + u * kScoreWaves < t1 ? probs[(size_t)(t + u * kScoreWaves) * N + i] : 0.0;
 #pragma unroll
-    for (int u = 0; u < 32; ++u) acc += v[u];  // rows past M add +0.0, which leaves the sum unchanged
+      for (int u = 0; u < 4; ++u) a += v[u];  // rows past the end add +0.0, which leaves the sum unchanged
+    }
+    tab[wave * N + i] = a;
   }
-  return acc;
+  __syncthreads();
+  for (int i = threadIdx.x; i < N; i += kScoreThreads) {
+    double a = tab[i];
+    for (int w = 1; w < kScoreWaves; ++w) a += tab[w * N + i];
+    part[(size_t)blockIdx.x * N + i] = a;
+  }
 }
 
-// The same sums for all N columns by a whole workgroup (N <= blockDim.x): the rows are fetched `rows_per_chunk`
-// at a time with every thread loading (contiguous, one latency per chunk, the next chunk already in flight),
-// parked in LDS, and thread i then adds column i row by row - the additions keep the strict ascending order,
-// only the memory latency leaves the chain.  tab: rows_per_chunk * N doubles of LDS.  Synchronises.
-constexpr int kScoreLoads = 4;  // values per thread and chunk
-__device__ __forceinline__ double column_sums_staged(const double *__restrict__ probs, int M, int N,
-                                                     int rows_per_chunk, double *tab) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  double nxt[kScoreLoads];
-  auto fetch = [&](int t0) {
-    const int n = (M - t0 < rows_per_chunk ? M - t0 : rows_per_chunk) * N;
+// Threads of a budget_kernel workgroup: four tokens at a time, and more where the scores and the ranking of more
+// experts, which every workgroup repeats, need the threads (at most kScoreLoads rows per thread up to 128 tokens).
+inline int budget_threads(int N) { return N <= 64 ? 256 : N <= 128 ? 512 : 1024; }
+
+// c[u] += number of the values row[j0 .. j1) that go before candidate lane + 64 u with value v[u] in a ranking by (value
+// descending, index ascending).  j0 and j1 are multiples of 4; row is padded with values that rank behind everything.
+// Four values per step, the same address in every lane (an LDS broadcast).  Against a rival of another block of 64
+// experts the tie rule is the same for all lanes (>= or >): one comparison and one add with carry per rival.
+template <int NU>
+__device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, int lane, const double (&v)[NU],
+                                            int (&c)[NU]) {
+#pragma unroll (NU <= 4 ? NU : 1)
+  for (int b = 0; b < NU; ++b) {
+    const int hi = min(j1, kWave * (b + 1));
+#pragma unroll 2
+    for (int j = max(j0, kWave * b); j < hi; j += 4) {
+      double r[4];
 #pragma unroll
-    for (int u = 0; u < kScoreLoads; ++u) {
-      const int idx = tid + u * nt;
-      nxt[u] = idx < n ? probs[(size_t)t0 * N + idx] : 0.0;
+      for (int q = 0; q < 4; ++q) r[q] = row[j + q];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+          c[u] += u > b ? (int)(r[q] >= v[u]) : u < b ? (int)(r[q] > v[u])
+                        : (int)((r[q] > v[u]) | ((r[q] == v[u]) & (j + q < lane + kWave * u)));
     }
+  }
+}
+
+struct BudgetLds {
+  size_t s, red, rows, row_stride, S, rank, sel, inS, total;
+};
+__host__ __device__ inline BudgetLds budget_lds(int N, int B, int threads) {
+  BudgetLds L;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off += (bytes + 15) & ~(size_t)15;
+    return at;
   };
-  double acc = 0.0;
-  fetch(0);
-  for (int t0 = 0; t0 < M; t0 += rows_per_chunk) {
-    const int rows = M - t0 < rows_per_chunk ? M - t0 : rows_per_chunk;
-#pragma unroll
-    for (int u = 0; u < kScoreLoads; ++u) {
-      const int idx = tid + u * nt;
-      if (idx < rows * N) tab[idx] = nxt[u];
-    }
-    __syncthreads();
-    if (t0 + rows_per_chunk < M) fetch(t0 + rows_per_chunk);
-    if (tid < N)
-      for (int r = 0; r < rows; ++r) acc += tab[r * N + tid];
-    __syncthreads();
-  }
-  return acc;
+  L.row_stride = (size_t)((N + 3) & ~3);
+  L.s = take(sizeof(double) * L.row_stride);
+  L.red = take(sizeof(double) * threads);
+  L.rows = take(sizeof(double) * L.row_stride * (threads / kWave));
+  L.S = take(sizeof(int32_t) * B);
+  L.rank = take(sizeof(int32_t) * N);
+  L.sel = take(sizeof(int32_t) * kWave * (threads / kWave));
+  L.inS = take((size_t)N);
+  L.total = off;
+  return L;
 }
 
-// Groups the surviving (token, slot) pairs by expert: segment i holds the pairs routed to
-// seg_expert[i], tokens ascending.  Run by one whole workgroup; one wave per segment at a time,
-// 64 tokens per ballot.  The routing table is staged in LDS slot-major (lanes read consecutive
-// words) when it fits.  items receives the work items of the expert passes: the non-empty segments
-// ordered by size, largest first (ties: lower segment first), each cut into piece_count(size) pieces of
-// (almost) equal size; items[0].x = number of pieces, items[1 + r] = (segment, expert, offset, size) of
-// piece r - the order in which the expert passes hand them out.
-// lds: (3 B + 1 + (staged ? M k : 0)) int32.
-__device__ void build_segments(const int32_t *tok_ids, int M, int k, int B, int staged, const int32_t *seg_expert,
-                               int32_t *seg_off, int32_t *perm, int32_t *n_loaded, int4 *items, int32_t *lds) {
-  int32_t *cnt = lds;           // [B + 1] exclusive offsets
-  int32_t *sexp = cnt + B + 1;  // [B] seg_expert
-  int32_t *sz = sexp + B;       // [B] sizes
-  int32_t *copy = sz + B;       // [k][M] routing table, slot-major (if staged)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwave = blockDim.x >> 6;
-  for (int i = tid; i < B; i += blockDim.x) sexp[i] = seg_expert[i];
-  if (staged)
-    for (int i = tid; i < M * k; i += blockDim.x) copy[(i % k) * M + i / k] = tok_ids[i];
-  __syncthreads();
-  auto id_at = [&](int t, int j) { return staged ? copy[j * M + t] : tok_ids[(size_t)t * k + j]; };
-
-  for (int i = wave; i < B; i += nwave) {
-    const int e = sexp[i];
-    int c = 0;
-    for (int t0 = 0; e >= 0 && t0 < M; t0 += kWave) {
-      const int t = t0 + lane;
-      bool has = false;
-      if (t < M)
-        for (int j = 0; j < k; ++j) has |= (id_at(t, j) == e);
-      c += __popcll(__ballot(has));
-    }
-    if (lane == 0) sz[i] = c;
-  }
-  __syncthreads();
-  if (wave == 0) {  // exclusive scan of the sizes, 64 segments per step
-    int run = 0, loaded = 0, pieces = 0;
-    for (int i0 = 0; i0 < B; i0 += kWave) {
-      const int i = i0 + lane;
-      const int c = i < B ? sz[i] : 0;
-      pieces += piece_count(c);
-      int incl = c;
-#pragma unroll
-      for (int sft = 1; sft < kWave; sft <<= 1) {
-        const int v = __shfl_up(incl, sft, kWave);
-        if (lane >= sft) incl += v;
-      }
-      if (i < B) {
-        seg_off[i] = run + incl - c;
-        cnt[i] = run + incl - c;
-      }
-      run += __shfl(incl, kWave - 1, kWave);
-      loaded += __popcll(__ballot(c > 0));
-    }
-#pragma unroll
-    for (int sft = 32; sft >= 1; sft >>= 1) pieces += __shfl_xor(pieces, sft, kWave);
-    if (lane == 0) {
-      seg_off[B] = run;
-      items[0] = int4{pieces, 0, 0, 0};
-      if (n_loaded) *n_loaded = loaded;
-      cnt[B] = run;
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < B; i += blockDim.x) {
-    const int c = sz[i];
-    if (c > 0) {
-      int first = 0;  // pieces of the segments that rank before this one
-      for (int j = 0; j < B; ++j) first += (sz[j] > c || (sz[j] == c && j < i)) ? piece_count(sz[j]) : 0;
-      const int q = piece_count(c), len = (c + q - 1) / q;
-      for (int p = 0; p < q; ++p) items[1 + first + p] = int4{i, sexp[i], cnt[i] + p * len, min(len, c - p * len)};
-    }
-  }
-  const int P = cnt[B];
-  for (int p = P + tid; p < M * k; p += blockDim.x) perm[p] = -1;
-  for (int i = wave; i < B; i += nwave) {
-    const int e = sexp[i];
-    int base = cnt[i];
-    for (int t0 = 0; e >= 0 && t0 < M; t0 += kWave) {
-      const int t = t0 + lane;
-      int slot = -1;
-      if (t < M)
-        for (int j = 0; j < k; ++j)
-          if (id_at(t, j) == e) slot = j;
-      const unsigned long long mask = __ballot(slot >= 0);
-      if (slot >= 0) perm[base + __popcll(mask & ((1ull << lane) - 1ull))] = t * k + slot;
-      base += __popcll(mask);
-    }
-  }
-}
-
-// Bytes of the selection arrays at the start of the budget kernel's LDS (the score staging follows), and the
-// rows of one staging chunk: kBudgetThreads * kScoreLoads values, at most 64 rows.
-__host__ __device__ inline size_t budget_sel_bytes(int N, int k, int B) {
-  const size_t b = sizeof(double) * (2 * (size_t)N + ((k + 1) & ~1) + 2) + sizeof(int32_t) * ((size_t)k + B + 2 * N + 1) + N;
-  return (b + 15) & ~(size_t)15;
-}
-__host__ __device__ inline int budget_rows_per_chunk(int N) {
-  const int r = kBudgetThreads * kScoreLoads / N;
-  return r > 64 ? 64 : (r < 1 ? 1 : r);
-}
-
-// One workgroup per tree token.  Every workgroup recomputes the (tiny) scores and shortlist so that
-// no grid-wide synchronisation is needed; workgroup 0 also writes them out.  The workgroup that
-// finishes last (ticket counter done[0], zero at launch) builds the segments from everybody's rows,
-// if they are wanted.  done[1 + r] (zero at launch) receives the number of surviving pairs of the expert
-// with shortlist rank r.
-__global__ __launch_bounds__(kBudgetThreads) void budget_kernel(
-    const double *__restrict__ probs, int M, int N, int k, int B, int policy, int renorm,
-    const int32_t *__restrict__ ext_shortlist, double *__restrict__ scores, int32_t *__restrict__ budget_ids,
-    int32_t *__restrict__ seg_expert, int32_t *tok_ids, float *__restrict__ tok_w, int32_t *__restrict__ seg_off,
-    int32_t *__restrict__ perm, int32_t *__restrict__ n_loaded, int4 *__restrict__ items, int staged,
-    int want_segments, const double *__restrict__ scores_in, int32_t *done) {
+// One wave per tree token.  src holds n_src rows of N values whose column sums are the scores of Eq. (5): the
+// probabilities themselves or the sums of row blocks.  Every workgroup recomputes the (tiny) scores and shortlist so
+// that no grid-wide synchronisation is needed; workgroup 0 also writes them out.  NU = candidates per lane.
+// A token's selection is a rank count: lane i compares its candidates with the whole row, read from LDS four values at
+// a time (the same address in every lane: a broadcast).  k <= 64, N <= 64 NU.
+// What bounds it: the launch, two rounds of cold loads and the row's N / 4 LDS reads; the tokens are independent.
+// The kernel it replaces had one workgroup per token, whose last one to finish grouped the pairs of the whole tree
+// (MI355X: 973 us with the sum of the scores at 2048 tokens x 64 experts, 32 us at 127 x 128, 17 us at 63 x 64; the
+// three kernels here take 24, 17 and 13 us).
+template <int NU>
+__global__ __launch_bounds__(1024) void budget_kernel(
+    const double *__restrict__ probs, const double *__restrict__ src, int n_src, int M, int N, int k, int B, int policy,
+    int renorm, const int32_t *__restrict__ ext_shortlist, double *__restrict__ scores,
+    int32_t *__restrict__ budget_ids, int32_t *__restrict__ seg_expert, int32_t *__restrict__ tok_ids,
+    float *__restrict__ tok_w) {
   extern __shared__ __align__(16) unsigned char smem[];
-  double *s = reinterpret_cast<double *>(smem);                  // [N] aggregate scores
-  double *g = s + N;                                              // [N] this token's probabilities
-  double *wsel = g + N;                                           // [k, even] + denominator
-  int32_t *sel = reinterpret_cast<int32_t *>(wsel + ((k + 1) & ~1) + 2);  // [k]
-  int32_t *S = sel + k;                                           // [B] shortlist in rank order
-  int32_t *rank = S + B;                                          // [N] scratch of the selections
-  int32_t *pos = rank + N;                                        // [N] shortlist rank of every expert
-  int32_t *flag = pos + N;                                        // [1] "this workgroup is the last one"
-  uint8_t *inS = reinterpret_cast<uint8_t *>(flag + 1);           // [N] membership
-  double *tab = reinterpret_cast<double *>(smem + budget_sel_bytes(N, k, B));  // [rows_per_chunk, N] score staging
-  const int rows_per_chunk = budget_rows_per_chunk(N);
+  const int nt = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const BudgetLds L = budget_lds(N, B, nt);
+  double *s = reinterpret_cast<double *>(smem + L.s);      // [N] aggregate scores
+  double *red = reinterpret_cast<double *>(smem + L.red);  // [threads] partial column sums
+  double *row = reinterpret_cast<double *>(smem + L.rows) + wave * L.row_stride;  // this wave's token
+  int32_t *S = reinterpret_cast<int32_t *>(smem + L.S);    // [B] shortlist in rank order
+  int32_t *rank = reinterpret_cast<int32_t *>(smem + L.rank);
+  int32_t *sel = reinterpret_cast<int32_t *>(smem + L.sel) + wave * kWave;  // [k] this wave's selection
+  uint8_t *inS = smem + L.inS;
 
-  const int t = blockIdx.x, tid = threadIdx.x;
+  // the first token's row is requested before the shortlist is known
+  const int n_waves = gridDim.x * (nt / kWave);
+  int t = blockIdx.x * (nt / kWave) + wave;
+  double v[NU];
+  auto load_row = [&](int tok) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) v[u] = (tok < M && lane + kWave * u < N) ? probs[(size_t)tok * N + lane + kWave * u] : 0.0;
+  };
+  load_row(t);
 
-  for (int i = tid; i < N; i += blockDim.x) {
-    g[i] = probs[(size_t)t * N + i];
-    inS[i] = 0;
-    pos[i] = 0x7fffffff;
+  for (int i = tid; i < N; i += nt) inS[i] = 0;
+  if (ext_shortlist == nullptr || scores != nullptr) {
+    // Eq. (5).  The threads with the same index modulo a power of two >= N share a column, each a contiguous run of rows.
+    int np2 = 1, np2_log = 0;
+    while (np2 < N) np2 <<= 1, ++np2_log;
+    const int parts = nt >> np2_log > 0 ? nt >> np2_log : 1, per = (n_src + parts - 1) / parts;
+    const int i = tid & (np2 - 1), p = tid >> np2_log;
+    double a = 0.0;
+    if (i < N) {
+      const int r1 = min(n_src, (p + 1) * per);
+      for (int r = p * per; r < r1; r += kScoreLoads) {  // the loads of a block go out together: one memory latency
+        double x[kScoreLoads];
+#pragma unroll
+        for (int u = 0; u < kScoreLoads; ++u) x[u] = r + u < r1 ? src[(size_t)(r + u) * N + i] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kScoreLoads; ++u) a += x[u];
+      }
+    }
+    red[tid] = a;
+    __syncthreads();
+    if (tid < (int)L.row_stride) {
+      double sum = tid < N ? red[tid] : -1.0;
+      for (int q = 1; tid < N && q < parts; ++q) sum += red[q * np2 + tid];
+      s[tid] = sum;
+    }
   }
+  for (int i = tid; i < N; i += nt) rank[i] = 0;
+  for (int r = tid; r < B; r += nt) S[r] = -1;  // stays -1 where NaN scores leave a place of the shortlist unclaimed
+  __syncthreads();
   if (ext_shortlist == nullptr) {
-    // Eq. (5): s_i = sum over the M tree tokens of g_i(h_t), tokens in ascending order.
-    // (large trees: summed once by scores_kernel instead of by every workgroup)
-    if (scores_in) {
-      for (int i = tid; i < N; i += blockDim.x) s[i] = scores_in[i];
-    } else {
-      const double acc = column_sums_staged(probs, M, N, rows_per_chunk, tab);
-      if (tid < N) s[tid] = acc;
+    // Section 3.2: the B highest aggregate scores, ties to the lowest id.  Each wave ranks all experts against its share
+    // of the rivals; the shares add up through integer LDS atomics.
+    double sv[NU];
+    int c[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      c[u] = 0;
+      sv[u] = lane + kWave * u < N ? s[lane + kWave * u] : 0.0;
     }
+    const int quads = (int)L.row_stride / 4, n_w = nt / kWave;
+    rank_counts<NU>(s, quads * wave / n_w * 4, quads * (wave + 1) / n_w * 4, lane, sv, c);
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (lane + kWave * u < N && c[u]) atomicAdd(&rank[lane + kWave * u], c[u]);
     __syncthreads();
-    select_topk(s, nullptr, N, B, S, rank);
+    for (int i = tid; i < N; i += nt)
+      if (rank[i] < B) S[rank[i]] = i;
   } else {
-    for (int r = tid; r < B; r += blockDim.x) S[r] = ext_shortlist[r];
-    if (scores && t == 0)  // uniform in the workgroup
-      for (int i = tid; i < N; i += blockDim.x) s[i] = scores_in ? scores_in[i] : column_sum(probs, M, N, i);
+    for (int r = tid; r < B; r += nt) S[r] = ext_shortlist[r];
   }
   __syncthreads();
-  for (int r = tid; r < B; r += blockDim.x)
-    if ((uint32_t)S[r] < (uint32_t)N) {  // ids outside [0, N) in an external shortlist are ignored
-      inS[S[r]] = 1;
-      atomicMin(&pos[S[r]], r);  // an expert named twice counts at its first rank
-    }
+  for (int r = tid; r < B; r += nt)
+    if ((uint32_t)S[r] < (uint32_t)N) inS[S[r]] = 1;  // ids outside [0, N) in an external shortlist are ignored
   __syncthreads();
 
-  if (t == 0) {
-    for (int i = tid; i < N; i += blockDim.x) {
-      if (scores) scores[i] = s[i];
-      if (inS[i]) {  // position of expert i among the shortlisted experts in ascending id
-        int pos = 0;
-        for (int j = 0; j < i; ++j) pos += inS[j];
-        seg_expert[pos] = i;
+  if (blockIdx.x == 0) {
+    // every wave builds the membership mask of all experts, 64 at a time; the position of an expert among the
+    // shortlisted ones in ascending id is a population count
+    int n_member = 0;  // in the end < B only if an external shortlist repeats or misnames an expert
+    for (int i0 = 0; i0 < N; i0 += kWave) {
+      const int i = i0 + lane;
+      const bool in = i < N && inS[i] != 0;
+      const unsigned long long mask = __ballot(in);
+      if (wave == 0) {
+        if (scores && i < N) scores[i] = s[i];
+        if (in) seg_expert[n_member + __popcll(mask & ((1ull << lane) - 1ull))] = i;
       }
+      n_member += __popcll(mask);
     }
-    if (tid < B) {
-      int n_member = 0;  // < B only if an external shortlist repeats or misnames an expert
-      for (int j = 0; j < N; ++j) n_member += inS[j];
-      for (int r = tid; r < B; r += blockDim.x) {
-        if (r >= n_member) seg_expert[r] = -1;
-        budget_ids[r] = S[r];
-      }
+    for (int r = tid; r < B; r += nt) {
+      if (r >= n_member) seg_expert[r] = -1;
+      budget_ids[r] = S[r];
     }
   }
 
-  if (policy == MOESPEC_TRUNCATE) {
-    // Natural top-k and its weights, then drop the slots outside S; kept weights are unchanged.
-    select_topk(g, nullptr, N, k, sel, rank);
-    __syncthreads();
-    mixing_weights(g, sel, k, renorm, wsel, wsel + ((k + 1) & ~1));
-    __syncthreads();
-    for (int j = tid; j < k; j += blockDim.x) {
-      const bool keep = (uint32_t)sel[j] < (uint32_t)N && inS[sel[j]] != 0;  // an unfilled slot (NaN scores) is dropped
-      tok_ids[(size_t)t * k + j] = keep ? sel[j] : -1;
-      tok_w[(size_t)t * k + j] = keep ? (float)wsel[j] : 0.0f;
-      if (keep) atomicAdd(&done[1 + pos[sel[j]]], 1);
+  const bool truncate = policy == MOESPEC_TRUNCATE;
+  bool member[NU];  // candidates: every expert under truncation, the shortlist under substitution
+#pragma unroll
+  for (int u = 0; u < NU; ++u) member[u] = lane + kWave * u < N && (truncate || inS[lane + kWave * u] != 0);
+  for (; t < M; t += n_waves) {
+    wave_lds_sync();  // the previous token's reads are done
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (lane + kWave * u < (int)L.row_stride) row[lane + kWave * u] = member[u] ? v[u] : -1.0;  // -1 ranks behind all
+    sel[lane] = -1;  // stays -1 where an external shortlist names fewer than k experts or a NaN leaves a slot unclaimed
+    wave_lds_sync();
+    int c[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) c[u] = 0;
+    rank_counts<NU>(row, 0, N, lane, v, c);
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (member[u] && c[u] < k) sel[c[u]] = lane + kWave * u;
+    wave_lds_sync();
+    if (lane < k) {
+      double denom = 0.0;  // over the selected set in slot order, before any slot is dropped (Eq. (7))
+      for (int j = 0; j < k; ++j) denom += sel[j] >= 0 ? row[sel[j]] : 0.0;
+      const int e = sel[lane];
+      const bool keep = e >= 0 && inS[e] != 0;  // truncation drops the slots outside S; kept weights are unchanged
+      const double w = keep ? (renorm ? row[e] / denom : row[e]) : 0.0;
+      tok_ids[(size_t)t * k + lane] = keep ? e : -1;
+      tok_w[(size_t)t * k + lane] = (float)w;
     }
-  } else {
-    // Top-k inside S by g_i(h_t); weights over the constrained selection.  Slots stay unfilled (-1)
-    // only when an external shortlist names fewer than k valid experts.
-    select_topk(g, inS, N, k, sel, rank);
-    __syncthreads();
-    mixing_weights(g, sel, k, renorm, wsel, wsel + ((k + 1) & ~1));
-    __syncthreads();
-    for (int j = tid; j < k; j += blockDim.x) {
-      const bool filled = (uint32_t)sel[j] < (uint32_t)N;
-      tok_ids[(size_t)t * k + j] = filled ? sel[j] : -1;
-      tok_w[(size_t)t * k + j] = filled ? (float)wsel[j] : 0.0f;
-      if (filled) atomicAdd(&done[1 + pos[sel[j]]], 1);
-    }
+    load_row(t + n_waves);
   }
+}
 
-  if (!want_segments) return;
-  // Last workgroup to arrive groups the pairs of all tokens.  One thread publishes the workgroup's
-  // rows (the barrier before it orders everybody's stores first) and takes the ticket; device-scope
-  // fences are expensive, so they are not executed by every wave.
+// Groups the surviving (token, slot) pairs by expert: segment i = blockIdx.x holds the pairs routed to seg_expert[i],
+// tokens ascending.  Every workgroup counts the pairs of ALL experts itself (integer LDS atomics: order-independent),
+// which gives it its own offset and rank without any exchange, then collects its own pairs 64 tokens per ballot.
+// items receives the work items of the expert passes: the non-empty segments ordered by size, largest first (ties:
+// lower segment first), each cut into piece_count(size) pieces of (almost) equal size; items[0].x = number of pieces,
+// items[1 + r] = (segment, expert, offset, size) of piece r - the order in which the expert passes hand them out.
+__global__ __launch_bounds__(1024) void group_pairs_kernel(const int32_t *__restrict__ tok_ids, int M, int N, int k,
+                                                           int B, const int32_t *__restrict__ seg_expert,
+                                                           int32_t *__restrict__ seg_off, int32_t *__restrict__ perm,
+                                                           int32_t *__restrict__ n_loaded, int4 *__restrict__ items) {
+  __shared__ int32_t cnt[1024];        // pairs per expert (N <= 1024)
+  __shared__ int32_t tot[5];           // offset of this segment, its first item; all pairs, segments, pieces
+  __shared__ int32_t wave_cnt[2][16];  // routed tokens per wave, two rounds
+  const int nt = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = nt >> 6, i = blockIdx.x;
+  const int n_pairs = M * k;
+  for (int e = tid; e < N; e += nt) cnt[e] = 0;
+  if (tid < 5) tot[tid] = 0;
   __syncthreads();
+  for (int p0 = 0; p0 < n_pairs; p0 += 4 * nt) {
+    int id[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) id[u] = p0 + u * nt + tid < n_pairs ? tok_ids[p0 + u * nt + tid] : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (id[u] >= 0) atomicAdd(&cnt[id[u]], 1);
+  }
+  __syncthreads();
+  const int e = seg_expert[i], c = e >= 0 ? cnt[e] : 0;
+  for (int j0 = 0; j0 < B; j0 += nt) {  // uniform trip count
+    const int j = j0 + tid, ej = j < B ? seg_expert[j] : -1, cj = ej >= 0 ? cnt[ej] : 0, q = piece_count(cj);
+    int sum[5] = {j < i ? cj : 0, (cj > c || (cj == c && j < i)) ? q : 0, cj, cj > 0 ? 1 : 0, q};
+#pragma unroll
+    for (int x = 0; x < 5; ++x) {
+#pragma unroll
+      for (int sft = 32; sft >= 1; sft >>= 1) sum[x] += __shfl_xor(sum[x], sft, kWave);
+      if (lane == 0 && sum[x]) atomicAdd(&tot[x], sum[x]);
+    }
+  }
+  __syncthreads();
+  const int off = tot[0], total = tot[2];
   if (tid == 0) {
-    __threadfence();
-    const bool is_last = atomicAdd(done, 1) == (int)gridDim.x - 1;
-    if (is_last) __threadfence();
-    *flag = is_last;
+    seg_off[i] = off;
+    if (i == B - 1) {
+      seg_off[B] = total;
+      items[0] = int4{tot[4], 0, 0, 0};
+      if (n_loaded) *n_loaded = tot[3];
+    }
   }
-  __syncthreads();
-  const bool last = *flag != 0;
-  __syncthreads();  // everybody has read the flag before the LDS is reused below
-  if (!last) return;
-  build_segments(tok_ids, M, k, B, staged, seg_expert, seg_off, perm, n_loaded, items,
-                 reinterpret_cast<int32_t *>(smem));
+  for (int p = total + i * nt + tid; p < n_pairs; p += B * nt) perm[p] = -1;
+  if (c == 0) return;
+  const int q = piece_count(c), len = (c + q - 1) / q;
+  for (int p = tid; p < q; p += nt) items[1 + tot[1] + p] = int4{i, e, off + p * len, min(len, c - p * len)};
+  int base = 0;
+  for (int t0 = 0, round = 0; base < c && t0 < M; t0 += nt, round ^= 1) {
+    const int t = t0 + tid;
+    int slot = -1;
+    if (t < M) {
+#pragma unroll 8
+      for (int j = 0; j < k; ++j)
+        if (tok_ids[(size_t)t * k + j] == e) slot = j;
+    }
+    const unsigned long long mask = __ballot(slot >= 0);
+    if (lane == 0) wave_cnt[round][wave] = __popcll(mask);
+    __syncthreads();  // the two sets of counts alternate: one barrier a round
+    int at = base;
+    for (int w = 0; w < n_waves; ++w) {
+      const int cw = wave_cnt[round][w];
+      at += w < wave ? cw : 0;
+      base += cw;
+    }
+    if (slot >= 0) perm[off + at + __popcll(mask & ((1ull << lane) - 1ull))] = t * k + slot;
+  }
 }
 
-// Eq. (5) once for the whole tree (same order of additions): used when the tree is so large that recomputing
-// the scores in every workgroup of budget_kernel (M^2 N loads in total) would dominate.  One workgroup.
-__global__ __launch_bounds__(kBudgetThreads) void scores_kernel(const double *__restrict__ probs, int M, int N,
-                                                                double *__restrict__ scores) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const double acc = column_sums_staged(probs, M, N, budget_rows_per_chunk(N), reinterpret_cast<double *>(smem));
-  if ((int)threadIdx.x < N) scores[threadIdx.x] = acc;
-}
-
-__global__ void zero_words_kernel(int32_t *p, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
+hipError_t launch_score_parts(const double *probs, int M, int N, double *part, int *n_parts, hipStream_t st) {
+  const int rows = score_block_rows(M);
+  *n_parts = (M + rows - 1) / rows;
+  const size_t smem = sizeof(double) * kScoreWaves * N;
+  if (smem > 64 * 1024) {  // beyond the default limit of a launch
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_parts_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  score_parts_kernel<<<*n_parts, kScoreThreads, smem, st>>>(probs, M, N, rows, part);
+  return hipGetLastError();
 }
 
 hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int B, int policy,
                          const int32_t *ext_shortlist, double *scores, int32_t *budget_ids, int32_t *tok_ids,
                          float *tok_w, int32_t *seg_expert, int32_t *seg_off, int32_t *perm, int32_t *n_loaded,
-                         int4 *items, int32_t *done, bool done_is_zero, bool want_segments, double *score_scratch,
-                         hipStream_t st) {
+                         int4 *items, double *score_parts, hipStream_t st) {
   const int N = ds.n_experts, k = ds.top_k;
-  if (!done_is_zero) {
-    zero_words_kernel<<<1, 256, 0, st>>>(done, 1 + N);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  const double *src = probs;
+  int n_src = M;
+  hipError_t e;
+  if (M > kDirectScoreRows && (ext_shortlist == nullptr || scores != nullptr)) {
+    if ((e = launch_score_parts(probs, M, N, score_parts, &n_src, st)) != hipSuccess) return e;
+    src = score_parts;
   }
-  // above this many tokens the redundant per-workgroup scoring (M^2 N loads in total) is replaced by one pass
-  const double *scores_in = nullptr;
-  if (M > kRedundantScoreTokens && (ext_shortlist == nullptr || scores != nullptr)) {
-    scores_kernel<<<1, kBudgetThreads, sizeof(double) * budget_rows_per_chunk(N) * N, st>>>(probs, M, N,
-                                                                                           score_scratch);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    scores_in = score_scratch;
-  }
-  const int staged = (size_t)M * k <= 8192;
-  const size_t smem_sel = budget_sel_bytes(N, k, B) + sizeof(double) * budget_rows_per_chunk(N) * N;
-  const size_t smem_seg = sizeof(int32_t) * (3 * B + 1 + (staged ? (size_t)M * k : 0));
-  budget_kernel<<<M, kBudgetThreads, smem_sel > smem_seg ? smem_sel : smem_seg, st>>>(
-      probs, M, N, k, B, policy, ds.renorm, ext_shortlist, scores, budget_ids, seg_expert, tok_ids, tok_w, seg_off, perm,
-      n_loaded, items, staged, want_segments ? 1 : 0, scores_in, done);
+  const int nt = budget_threads(N), per_wg = nt / kWave;
+  // every workgroup ranks the experts again: no more of them than two per compute unit
+  const int want = (M + per_wg - 1) / per_wg, grid = want < 512 ? want : 512;
+  const size_t smem = budget_lds(N, B, nt).total;
+  auto run = [&](auto kern) -> hipError_t {
+    if (smem > 64 * 1024) {
+      hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (err != hipSuccess) return err;
+    }
+    kern<<<grid, nt, smem, st>>>(probs, src, n_src, M, N, k, B, policy, ds.renorm, ext_shortlist, scores, budget_ids,
+                                 seg_expert, tok_ids, tok_w);
+    return hipGetLastError();
+  };
+  e = N <= 64 ? run(budget_kernel<1>) : N <= 128 ? run(budget_kernel<2>) : N <= 256 ? run(budget_kernel<4>)
+                                                                                    : run(budget_kernel<16>);
+  if (e != hipSuccess) return e;
+  group_pairs_kernel<<<B, (int64_t)M * k <= 2048 ? 256 : 1024, 0, st>>>(tok_ids, M, N, k, B, seg_expert, seg_off, perm,
+                                                                       n_loaded, items);
   return hipGetLastError();
 }
 

@@ -80,6 +80,12 @@ __device__ inline float rms_scale_of_row(const float (&v)[kRmsChunks][4], int d,
   return 1.0f / sqrtf(part[0] / (float)d);
 }
 
+// Orders the LDS accesses of one wave: they execute in program order, so only the compiler has to keep it.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Rank-count selection of the k best of v[0..n) restricted to candidates with member[i] != 0
 // (member == nullptr: all).  sel[r] receives the index with rank r < k.  Equivalent to sorting by
 // (value descending, index ascending) and keeping the first k.  v, member, sel and the scratch
@@ -150,12 +156,18 @@ constexpr int kMaxLogitSlices = 8;    // slices of the hidden dimension in the f
 constexpr int kSelfMaxTokens = 1024;  // largest tree for which the expert passes derive their segments themselves
 constexpr int kSelfMaxExperts = 256;  // ... and the largest shortlist
 
+// Row blocks whose column sums are the first half of Eq. (5) on large trees: at most kScoreMaxParts of them, one
+// workgroup each, a multiple of its waves.
+constexpr int kScoreThreads = 1024, kScoreWaves = kScoreThreads / kWave, kScoreMaxParts = 64;
+inline int score_block_rows(int64_t M) {
+  return kScoreWaves * (int)((M + kScoreMaxParts * kScoreWaves - 1) / (kScoreMaxParts * kScoreWaves));
+}
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Workspace carve-up shared by all entry points (host).
 struct Workspace {
   double *probs;      // [M, N]
-  double *scores;     // [N]
   int32_t *budget_ids;  // [N]
   int32_t *tok_ids;   // [M, k]
   float *tok_w;       // [M, k]
@@ -163,13 +175,10 @@ struct Workspace {
   int32_t *seg_off;   // [N + 1]
   int32_t *perm;      // [M * k]
   int4 *items;        // [items_capacity(N, M, k) + 1] count, then (segment, expert, offset, size) of every piece
-  int4 *pub_items;    // [as items] the same table as published by a self-segmenting gate/up pass
-  int32_t *pub_lists; // [work items of that mode, kPiecePairs] its pair lists
-  int32_t *n_loaded;  // [1]
-  int32_t *done;      // [1 + N] ticket counter of the budget stage, then surviving pairs per shortlist rank
   void *act;          // [M * k, F] dtype
   float *y;           // [kMaxDownSplits][M * k, d]
   double *gram;       // [N, N + 3] scratch of the oracle ranking
+  double *score_parts;  // [kScoreMaxParts, N] column sums of row blocks (budget stage; shares the place of gram)
   double *partial;    // [kMaxLogitSlices, M, N] partial router projections of the fused prologue
   int32_t *list_count;  // [N] pairs per shortlist rank (fused prologue)
   int32_t *lists;     // [N, M] their pair lists (only for shapes the fused prologue covers)
@@ -189,7 +198,6 @@ inline Workspace carve_workspace(const moespec_desc &ds, int64_t M, void *base) 
   const int64_t N = ds.n_experts, k = ds.top_k, F = ds.d_ff, d = ds.d;
   const size_t es = ds.dtype == MOESPEC_BF16 ? 2 : 4;
   w.probs = static_cast<double *>(take(sizeof(double) * M * N));
-  w.scores = static_cast<double *>(take(sizeof(double) * N));
   w.budget_ids = static_cast<int32_t *>(take(sizeof(int32_t) * N));
   w.tok_ids = static_cast<int32_t *>(take(sizeof(int32_t) * M * k));
   w.tok_w = static_cast<float *>(take(sizeof(float) * M * k));
@@ -197,15 +205,10 @@ inline Workspace carve_workspace(const moespec_desc &ds, int64_t M, void *base) 
   w.seg_off = static_cast<int32_t *>(take(sizeof(int32_t) * (N + 1)));
   w.perm = static_cast<int32_t *>(take(sizeof(int32_t) * M * k));
   w.items = static_cast<int4 *>(take(sizeof(int4) * (items_capacity((int)N, M, k) + 1)));
-  w.pub_items = static_cast<int4 *>(take(sizeof(int4) * (items_capacity((int)N, M, k) + 1)));
-  w.pub_lists = static_cast<int32_t *>(
-      take(sizeof(int32_t) * kPiecePairs *
-           items_capacity((int)(N < kSelfMaxExperts ? N : kSelfMaxExperts), M < kSelfMaxTokens ? M : kSelfMaxTokens, k)));
-  w.n_loaded = static_cast<int32_t *>(take(sizeof(int32_t)));
-  w.done = static_cast<int32_t *>(take(sizeof(int32_t) * (1 + N)));
   w.act = take(es * M * k * F);
   w.y = static_cast<float *>(take(sizeof(float) * kMaxDownSplits * M * k * d));
-  w.gram = static_cast<double *>(take(sizeof(double) * N * (N + 3)));
+  w.gram = static_cast<double *>(take(sizeof(double) * N * (N + 3 > kScoreMaxParts ? N + 3 : kScoreMaxParts)));
+  w.score_parts = w.gram;
   const bool small = N <= kSelfMaxExperts && M <= kSelfMaxTokens;
   w.partial = static_cast<double *>(take(small ? sizeof(double) * kMaxLogitSlices * M * N : 0));
   w.list_count = static_cast<int32_t *>(take(sizeof(int32_t) * N));
@@ -216,27 +219,19 @@ inline Workspace carve_workspace(const moespec_desc &ds, int64_t M, void *base) 
 }
 
 // Launchers (defined in the .hip files).  Each returns hipGetLastError() after its launches.
-// zero_words (may be NULL): n_zero int32 that the route stage sets to 0 (the counters of the budget stage).
 hipError_t launch_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *probs,
-                        int32_t *topk_ids, float *topk_w, int32_t *zero_words, int n_zero, hipStream_t st);
-// done: [1 + N] counters (ticket, then the number of surviving pairs of the expert at each shortlist
-// rank), zero at launch or zeroed first (done_is_zero == false).  budget_ids must not be NULL.
-// want_segments == false skips seg_off / perm / n_loaded / items: the expert passes can then only run in
-// the mode that derives its segments from done + 1, budget_ids and tok_ids.  score_scratch: N doubles.
+                        int32_t *topk_ids, float *topk_w, hipStream_t st);
+// score_parts: [kScoreMaxParts, N] doubles of scratch.  scores and n_loaded may be NULL.
 hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int B, int policy,
                          const int32_t *ext_shortlist, double *scores, int32_t *budget_ids, int32_t *tok_ids,
                          float *tok_w, int32_t *seg_expert, int32_t *seg_off, int32_t *perm, int32_t *n_loaded,
-                         int4 *items, int32_t *done, bool done_is_zero, bool want_segments, double *score_scratch,
-                         hipStream_t st);
+                         int4 *items, double *score_parts, hipStream_t st);
 // items: table of the work items ([items_capacity(n_seg, M, k) + 1] int4 of scratch: the non-empty segments,
 // those above kPiecePairs pairs cut into pieces); items_ready says that the budget stage has already filled
 // it from the same segment arrays, otherwise it is built first.
-// rank_count, shortlist (may be NULL): the shortlist in rank order ([n_seg]) and the surviving pairs of each
-// of its experts, from the budget stage; when given and the shape allows (expert_ffn_self_segmenting),
-// every workgroup derives its segment from them and tok_ids itself, and seg_expert / seg_off / perm /
-// items are not read.  pub_items (like items) and pub_lists ([work items, kPiecePairs] int32) are scratch in
-// which the gate/up pass of that mode leaves its work items for the down pass (NULL: the down pass derives
-// them again).
+// rank_count, shortlist, lists (NULL, or all three from the fused prologue): the shortlist in rank order ([n_seg]), the
+// surviving pairs of each of its experts and their lists (rank r at lists + r * list_stride); every workgroup then
+// finds its work item in them (needs expert_ffn_self_segmenting) and seg_expert / seg_off / perm / items are not read.
 // trace (may be NULL): 3 events recorded after the gate/up pass, the down pass and the combine.
 // x_next (may be NULL): [M, d] dtype; the combine then also writes out scaled row by row to unit root-mean-square,
 // the next layer's input in a stack (d <= 8192).
@@ -244,9 +239,8 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
                              const int32_t *seg_expert, const int32_t *seg_off, const int32_t *perm,
                              const int32_t *tok_ids, const float *tok_w, const void *residual, void *out, void *act,
                              float *y, int4 *items, bool items_ready, const int32_t *rank_count,
-                             const int32_t *shortlist, int4 *pub_items, int32_t *pub_lists, hipStream_t st,
-                             void *const *trace = nullptr, const int32_t *lists = nullptr, int list_stride = 0,
-                             void *x_next = nullptr);
+                             const int32_t *shortlist, const int32_t *lists, int list_stride, hipStream_t st,
+                             void *const *trace = nullptr, void *x_next = nullptr);
 // The fused prologue of the layer call (prologue.hip): router projection on the fp64 matrix cores, then one
 // launch that leaves the shortlist (budget_ids), the restricted routing (tok_ids, tok_w) and, for every shortlist
 // rank r, the pairs routed to its expert (list_count[r]; lists[r * list_stride ..], flat ids t * k + slot, tokens
@@ -254,10 +248,10 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
 // perm, n_loaded are optional copies for the caller (the last three cost one more small launch).
 bool fused_prologue_ok(const moespec_desc &ds, int M);
 // Stage 1 on the matrix cores for bf16 layers of up to kSelfMaxExperts experts and kSelfMaxTokens tokens, whatever the
-// size of the table: probs [M, N] out, partial as above, zero_words cleared like launch_route does.
+// size of the table: probs [M, N] out, partial as above.
 bool mfma_route_ok(const moespec_desc &ds, int M);
 hipError_t launch_mfma_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *partial,
-                             double *probs, int32_t *zero_words, int n_zero, hipStream_t st);
+                             double *probs, hipStream_t st);
 int logit_slices(const moespec_desc &ds, int M, bool whole_table);
 hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int B,
                                  int policy, const int32_t *ext_shortlist, double *partial, double *probs_ws,

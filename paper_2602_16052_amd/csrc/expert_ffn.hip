@@ -22,10 +22,9 @@
 // Shapes whose K is not a multiple of 128 take a simpler direct-load variant of the same tiling.
 // The intermediate act and the per-pair outputs y are indexed by the flat pair id t * k + slot.
 //
-// Where its segment comes from: either from the segment arrays (seg_expert, seg_off, perm; any
-// caller), or - inside the fused layer, for small trees - every workgroup derives it from the
-// shortlist, the pair count of every shortlisted expert and the restricted routing table, which takes
-// no longer than reading perm and spares the budget stage its serial grouping step.
+// Where its segment comes from: either from the work items that the budget stage has built beside the segment
+// arrays (seg_expert, seg_off, perm; any caller), or - inside the fused layer, for small trees - from the pair lists
+// of the fused prologue.
 #include "common.h"
 
 namespace moespec {
@@ -142,19 +141,19 @@ __device__ __forceinline__ int4 xcd_item(int tiles, int cap, const int4 *__restr
 __global__ __launch_bounds__(256) void segment_items_kernel(const int32_t *__restrict__ seg_expert,
                                                             const int32_t *__restrict__ seg_off, int n_seg, int M,
                                                             int k, int cap, int4 *__restrict__ items) {
-  __shared__ int n_items;
+  __shared__ int n_items, sizes[1024];  // n_seg <= n_experts <= 1024
   if (threadIdx.x == 0) n_items = 0;
-  __syncthreads();
-  auto size_of = [&](int j) {
+  for (int j = threadIdx.x; j < n_seg; j += blockDim.x) {
     const int lo = seg_off[j], c = seg_off[j + 1] - lo;
-    return (lo >= 0 && c > 0 && c <= M && (long long)lo + c <= (long long)M * k) ? c : 0;
-  };
+    sizes[j] = (lo >= 0 && c > 0 && c <= M && (long long)lo + c <= (long long)M * k) ? c : 0;
+  }
+  __syncthreads();
   for (int i = threadIdx.x; i < n_seg; i += blockDim.x) {
-    const int c = size_of(i);
+    const int c = sizes[i];
     if (c > 0) {
       int first = 0;  // pieces of the segments that rank before this one
       for (int j = 0; j < n_seg; ++j) {
-        const int cj = size_of(j);
+        const int cj = sizes[j];
         first += (cj > c || (cj == c && j < i)) ? piece_count(cj) : 0;
       }
       const int q = piece_count(c), len = (c + q - 1) / q, lo = seg_off[i];
@@ -430,32 +429,17 @@ __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt
   __syncthreads();  // the LDS tiles may be reused by the caller's next pass
 }
 
-// The workgroup's work item derived on the spot (fused layer, small trees).  shortlist[r] = expert with
-// rank r in the shortlist (descending aggregate score, which is also roughly descending segment size),
-// rank_count[r] = number of its surviving pairs, tok_ids = restricted routing table [M, k].  The work items
-// are the pieces (piece_count per expert) of the shortlisted experts in rank order; the workgroup takes the
-// one that xcd_map assigns to it and collects that piece's pairs in token order into plist (LDS,
-// kPiecePairs entries).  The tables are read in one round of independent loads per 256 tokens.
-// Requires B <= kFfnThreads, k <= kSelfMaxK, M <= kSelfMaxTokens.  misc: 8 int32 of LDS scratch.
-// Called by every thread of the workgroup (it synchronises).  Returns the expert (-1: no work item) and the
-// number of work items.
-constexpr int kSelfMaxK = 16;
-// lists != NULL (the fused prologue has already written every shortlist rank's pairs, rank r at
-// lists + r * list_stride): nothing is collected, list receives the address of the piece inside that table.
-__device__ __forceinline__ int self_segment(const int32_t *__restrict__ rank_count,
-                                            const int32_t *__restrict__ shortlist, int B,
-                                            const int32_t *__restrict__ tok_ids, int M, int k, int tiles,
-                                            int32_t *misc, int32_t *plist, int &m, int &item, int &tile,
-                                            int &n_items, const int32_t *__restrict__ lists, int list_stride,
-                                            const int32_t *&list) {
+// The workgroup's work item found in the fused prologue's lists: shortlist[r] = expert with rank r in the shortlist
+// (descending aggregate score, which is also roughly descending segment size), rank_count[r] = number of its surviving
+// pairs, listed at lists + r * list_stride.  The work items are the pieces (piece_count per expert) of the shortlisted
+// experts in rank order; the workgroup takes the one that xcd_map assigns to it.  Requires B <= kFfnThreads.
+// misc: 8 int32 of LDS scratch.  Called by every thread of the workgroup (it synchronises).  Returns the expert (-1: no
+// work item), its piece of m pairs (list) and the work item's number.
+__device__ __forceinline__ int listed_segment(const int32_t *__restrict__ rank_count,
+                                              const int32_t *__restrict__ shortlist, int B, int tiles, int32_t *misc,
+                                              int &m, int &item, int &tile, const int32_t *__restrict__ lists,
+                                              int list_stride, const int32_t *&list) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int ids[kSelfMaxK];
-  auto load_ids = [&](int t) {
-#pragma unroll
-    for (int j = 0; j < kSelfMaxK; ++j) ids[j] = (j < k && t < M) ? tok_ids[(size_t)t * k + j] : -1;
-  };
-  list = plist;
-  if (!lists) load_ids(tid);
   const int c = tid < B ? rank_count[tid] : 0;
   const int ex = tid < B ? shortlist[tid] : -1;
   const int q = c > 0 ? piece_count(c) : 0;
@@ -468,8 +452,7 @@ __device__ __forceinline__ int self_segment(const int32_t *__restrict__ rank_cou
   if (lane == kWave - 1) misc[1 + wave] = incl;
   if (tid == 0) misc[0] = -1;
   __syncthreads();
-  int before = 0;
-  n_items = 0;
+  int before = 0, n_items = 0;
   for (int w = 0; w < kFfnWaves; ++w) {
     if (w < wave) before += misc[1 + w];
     n_items += misc[1 + w];
@@ -485,33 +468,8 @@ __device__ __forceinline__ int self_segment(const int32_t *__restrict__ rank_cou
   }
   __syncthreads();
   const int e = misc[0];
-  m = 0;
-  if (e < 0) return -1;
-  const int lo = misc[5];
-  m = misc[6];
-  if (lists) {
-    list = lists + (size_t)misc[7] * list_stride + lo;
-    return e;
-  }
-  int base = 0;
-  for (int t0 = 0; t0 < M && base < lo + m; t0 += kFfnThreads) {  // uniform trip count
-    const int t = t0 + tid;
-    if (t0 > 0) load_ids(t);
-    int slot = -1;
-#pragma unroll
-    for (int j = 0; j < kSelfMaxK; ++j)
-      if (ids[j] == e) slot = j;
-    const unsigned long long mask = __ballot(slot >= 0);
-    __syncthreads();  // everybody has read the wave counts of the previous round
-    if (lane == 0) misc[1 + wave] = __popcll(mask);
-    __syncthreads();
-    int pos = base;
-    for (int w = 0; w < wave; ++w) pos += misc[1 + w];
-    pos += __popcll(mask & ((1ull << lane) - 1ull)) - lo;
-    if (slot >= 0 && pos >= 0 && pos < m) plist[pos] = t * k + slot;
-    for (int w = 0; w < kFfnWaves; ++w) base += misc[1 + w];
-  }
-  __syncthreads();
+  m = e < 0 ? 0 : misc[6];
+  list = e < 0 ? lists : lists + (size_t)misc[7] * list_stride + misc[5];
   return e;
 }
 
@@ -565,36 +523,25 @@ __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *
   }
 }
 
-// rank_count != NULL: self-segmenting mode (items / perm unused; n_seg = B); otherwise items + perm.
+// rank_count != NULL: work items from the prologue's lists (items / perm unused; n_seg = B); otherwise items + perm.
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ w_gate, const uint16_t *__restrict__ w_up,
     const int4 *__restrict__ items, const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count,
-    const int32_t *__restrict__ shortlist, const int32_t *__restrict__ tok_ids, int n_seg, int cap, int M, int N,
-    int k, int d, int F, long long perm_len, int4 *__restrict__ pub_items, int32_t *__restrict__ pub_lists,
+    const int32_t *__restrict__ shortlist, int n_seg, int cap, int M, int N, int k, int d, int F,
     const int32_t *__restrict__ lists, int list_stride, uint16_t *__restrict__ act) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
-  __shared__ int32_t own_pairs[kPiecePairs];
   __shared__ int32_t misc[8];
   const int tiles = (F / 16 + kFfnWaves - 1) / kFfnWaves;
   int tile, rank, e, m;
   const int32_t *plist;
   if (rank_count) {
-    int n_items;
-    e = self_segment(rank_count, shortlist, n_seg, tok_ids, M, k, tiles, misc, own_pairs, m, rank, tile, n_items,
-                     lists, list_stride, plist);
-    // The work items found here are published for the down pass (same table format as the budget stage's):
-    // workgroup 0 writes the count, the first row tile of every item its entry and its pair list.
-    if (pub_items && blockIdx.x == 0 && threadIdx.x == 0) pub_items[0] = int4{n_items, 0, 0, 0};
+    e = listed_segment(rank_count, shortlist, n_seg, tiles, misc, m, rank, tile, lists, list_stride, plist);
     if (e < 0 || e >= N || m <= 0 || m > kPiecePairs) return;
-    if (pub_items && tile == 0) {
-      for (int p = threadIdx.x; p < m; p += kFfnThreads) pub_lists[(size_t)rank * kPiecePairs + p] = own_pairs[p];
-      if (threadIdx.x == 0) pub_items[1 + rank] = int4{rank, e, rank * kPiecePairs, m};
-    }
   } else {
     const int4 it = xcd_item(tiles, cap, items, tile, rank);
     e = it.y;
     m = it.w;
-    if (it.x < 0 || !segment_ok(e, it.z, m, perm_len, N)) return;
+    if (it.x < 0 || !segment_ok(e, it.z, m, (long long)M * k, N)) return;
     plist = perm + it.z;
   }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -658,10 +605,9 @@ __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
     const uint16_t *__restrict__ act, const uint16_t *__restrict__ w_down, const int4 *__restrict__ items,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
-    const int32_t *__restrict__ tok_ids, int n_seg, int cap, int M, int N, int k, int d, int F, int splits,
-    long long perm_len, const int32_t *__restrict__ lists, int list_stride, float *__restrict__ y) {
+    int n_seg, int cap, int M, int N, int k, int d, int F, int splits, const int32_t *__restrict__ lists,
+    int list_stride, float *__restrict__ y) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
-  __shared__ int32_t own_pairs[kPiecePairs];
   __shared__ int32_t misc[8];
   // a work item is (row tile, K split): split sp sums the 128-element chunks [sp n / splits, (sp + 1) n / splits)
   // of F into its own copy of y, which the combine adds up in split order
@@ -669,15 +615,13 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
   int tile, rank, e, m;
   const int32_t *plist;
   if (rank_count) {
-    int n_items;
-    e = self_segment(rank_count, shortlist, n_seg, tok_ids, M, k, tiles, misc, own_pairs, m, rank, tile, n_items,
-                     lists, list_stride, plist);
+    e = listed_segment(rank_count, shortlist, n_seg, tiles, misc, m, rank, tile, lists, list_stride, plist);
     if (e < 0 || e >= N || m <= 0 || m > kPiecePairs) return;
   } else {
     const int4 it = xcd_item(tiles, cap, items, tile, rank);
     e = it.y;
     m = it.w;
-    if (it.x < 0 || !segment_ok(e, it.z, m, perm_len, N)) return;
+    if (it.x < 0 || !segment_ok(e, it.z, m, (long long)M * k, N)) return;
     plist = perm + it.z;
   }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -870,11 +814,10 @@ static hipError_t launch_bf16(const moespec_desc &ds, const moespec_weights &wt,
   return hipGetLastError();
 }
 
-// The self-segmenting mode needs both passes on the LDS-tiled kernels and a tree small enough for
-// their LDS scratch.
+// Taking the work items from the prologue's lists needs both passes on the LDS-tiled kernels.
 bool expert_ffn_self_segmenting(const moespec_desc &ds, int M) {
   return ds.dtype == MOESPEC_BF16 && ds.d % 128 == 0 && ds.d_ff % 128 == 0 && ds.n_experts <= kSelfMaxExperts &&
-         M <= kSelfMaxTokens && ds.top_k <= kSelfMaxK;
+         M <= kSelfMaxTokens;
 }
 
 // K-split of the LDS-tiled down pass: when its (segment, row tile) items alone cannot give every compute
@@ -897,12 +840,12 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
                              const int32_t *seg_expert, const int32_t *seg_off, const int32_t *perm,
                              const int32_t *tok_ids, const float *tok_w, const void *residual, void *out, void *act,
                              float *y, int4 *items, bool items_ready, const int32_t *rank_count,
-                             const int32_t *shortlist, int4 *pub_items, int32_t *pub_lists, hipStream_t st,
-                             void *const *trace, const int32_t *lists, int list_stride, void *x_next) {
+                             const int32_t *shortlist, const int32_t *lists, int list_stride, hipStream_t st,
+                             void *const *trace, void *x_next) {
   const int d = ds.d, F = ds.d_ff, k = ds.top_k;
   hipError_t e;
-  if (lists) pub_items = nullptr;  // every pass reads the prologue's lists: nothing to publish
-  if (rank_count && !(shortlist && expert_ffn_self_segmenting(ds, M) && n_seg <= kFfnThreads)) rank_count = nullptr;
+  if (rank_count && !(shortlist && lists && expert_ffn_self_segmenting(ds, M) && n_seg <= kFfnThreads))
+    return hipErrorInvalidValue;
   if (!rank_count && !items_ready && !items) return hipErrorInvalidValue;
   const int cap = items_capacity(n_seg, M, k);  // work items of the LDS-tiled passes
   if (ds.dtype == MOESPEC_BF16 && !rank_count && !items_ready && (d % 128 == 0 || F % 128 == 0)) {
@@ -913,7 +856,6 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     if (trace && trace[i]) (void)hipEventRecord(static_cast<hipEvent_t>(trace[i]), st);
   };
   const int splits = down_splits(ds, n_seg);
-  const bool publish = rank_count && pub_items && pub_lists;
   const size_t split_stride = (size_t)M * k * d;
   if (ds.dtype == MOESPEC_BF16) {
     for (int pass = 1; pass <= 2; ++pass) {
@@ -922,17 +864,13 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
           const int grid = xcd_grid((F / 16 + kFfnWaves - 1) / kFfnWaves, cap);
           ffn_gateup_lds_kernel<<<grid, kFfnThreads, 0, st>>>(
               static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_gate),
-              static_cast<const uint16_t *>(wt.w_up), items, perm, rank_count, shortlist, tok_ids, n_seg, cap, M,
-              ds.n_experts, k, d, F, (long long)M * k, publish ? pub_items : nullptr, pub_lists,
-              rank_count ? lists : nullptr, list_stride, static_cast<uint16_t *>(act));
+              static_cast<const uint16_t *>(wt.w_up), items, perm, rank_count, shortlist, n_seg, cap, M, ds.n_experts, k, d,
+              F, lists, list_stride, static_cast<uint16_t *>(act));
         } else {
           const int grid = xcd_grid(((d / 32 + kFfnWaves - 1) / kFfnWaves) * splits, cap);
-          // after a self-segmenting gate/up pass the down pass reads the segments that pass has published
           ffn_down_lds_kernel<<<grid, kFfnThreads, 0, st>>>(
-              static_cast<const uint16_t *>(act), static_cast<const uint16_t *>(wt.w_down),
-              publish ? pub_items : items, publish ? pub_lists : perm, publish ? nullptr : rank_count, shortlist,
-              tok_ids, n_seg, cap, M, ds.n_experts, k, d, F, splits,
-              publish ? (long long)cap * kPiecePairs : (long long)M * k, rank_count ? lists : nullptr, list_stride, y);
+              static_cast<const uint16_t *>(act), static_cast<const uint16_t *>(wt.w_down), items, perm, rank_count,
+              shortlist, n_seg, cap, M, ds.n_experts, k, d, F, splits, lists, list_stride, y);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         mark(pass - 1);

@@ -1,0 +1,41 @@
+"""The budget stage at the sizes where its dispatch and its blocks change: tokens around the limit of the direct score
+sum and of a score block, experts around the candidates-per-lane steps, top-k of 1 and of a whole wave, more tokens
+than waves, ragged everything.  The probabilities are multiples of 2^-12, so that every sum is exact in any order and
+ties are frequent: scores, shortlist, routing and segments must equal the oracle's exactly."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moespec_oracle as O
+from paper_2602_16052_amd import binding as mb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,k,B", [(1, 1, 1, 1), (1, 64, 8, 9), (128, 64, 8, 33), (129, 65, 1, 2), (127, 128, 8, 64),
+                                     (130, 129, 6, 77), (257, 257, 5, 200), (1025, 5, 3, 4), (2100, 64, 8, 64),
+                                     (40, 1024, 64, 700), (300, 3, 3, 3)])
+@pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
+def test_budget_stage_edges(M, N, k, B, policy):
+    print(f"case M={M} N={N} k={k} B={B} policy={policy}", flush=True)
+    r = np.random.default_rng(M * 7 + N)
+    g = r.integers(0, 1 << 12, size=(M, N)).astype(np.float64) / (1 << 12)
+    g[:, : N // 2] *= r.integers(0, 2, size=(M, N // 2))  # exact zeros: experts that underflow
+    desc = mb.LayerDesc(32, N, k, 32, mb.BF16, True)
+    ws = mb.alloc_workspace(desc, M)
+    b = mb.moespec_budget(desc, torch.from_numpy(g).cuda(), B, policy, ws)
+    torch.cuda.synchronize()
+    ids = np.array([O.top_k(row, k) for row in g], dtype=np.int32)
+    w = np.array([O.mixing_weights(row, i, True) for row, i in zip(g, ids)])
+    ref = O.budget(g, ids, w, B, policy, k, True)
+    got = {key: val.cpu().numpy() for key, val in b.items()}
+    assert np.array_equal(got["scores"], ref["scores"])
+    assert np.array_equal(got["budget_ids"], ref["S"])
+    assert np.array_equal(got["tok_ids"], ref["tok_ids"])
+    assert np.array_equal(got["seg_expert"], ref["seg_expert"])
+    assert np.array_equal(got["seg_off"], ref["seg_off"])
+    P = int(ref["seg_off"][-1])
+    assert np.array_equal(got["perm"][:P], ref["perm"]) and np.all(got["perm"][P:] == -1)
+    assert int(got["n_loaded"][0]) == int(np.count_nonzero(np.diff(ref["seg_off"])))
+    # fp32 storage of an fp64 quotient: half an ulp
+    np.testing.assert_allclose(got["tok_w"], ref["tok_w"], rtol=2.0 ** -24, atol=0)
