@@ -9,13 +9,23 @@ namespace moespec {
 
 constexpr int kAnalysisThreads = 1024;
 
-// c_i += #{(t, slot) : topk_ids[t, slot] == i}.  Integer atomics: the result does not depend on order.
-__global__ __launch_bounds__(256) void calibration_count_kernel(const int32_t *__restrict__ topk_ids, int n, int N,
-                                                                unsigned long long *__restrict__ counts) {
+// c_i += #{(t, slot) : topk_ids[t, slot] == i}.  Integer atomics: the result does not depend on order.  Every workgroup
+// counts its share of the ids in LDS and adds one number per expert to memory (thousands of atomics on the few words of
+// the popular experts took 78 us for 32768 ids; 4 us this way).  N <= 1024.
+constexpr int kCountsPerThread = 4;
+__global__ __launch_bounds__(kAnalysisThreads) void calibration_count_kernel(const int32_t *__restrict__ topk_ids,
+                                                                             int n, int N,
+                                                                             unsigned long long *__restrict__ counts) {
+  __shared__ uint32_t c[1024];
+  for (int i = threadIdx.x; i < N; i += blockDim.x) c[i] = 0;
+  __syncthreads();
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const int e = topk_ids[i];
-    if ((uint32_t)e < (uint32_t)N) atomicAdd(&counts[e], 1ull);
+    if ((uint32_t)e < (uint32_t)N) atomicAdd(&c[e], 1u);
   }
+  __syncthreads();
+  for (int i = threadIdx.x; i < N; i += blockDim.x)
+    if (c[i]) atomicAdd(&counts[i], (unsigned long long)c[i]);
 }
 
 // shortlist[r] = expert with rank r < B when ordered by (count descending, id ascending).  One workgroup.
@@ -224,10 +234,10 @@ hipError_t launch_oracle_ranking(const moespec_desc &ds, const float *y, int spl
 }
 
 hipError_t launch_calibration_count(const int32_t *topk_ids, int M, int k, int N, int64_t *counts, hipStream_t st) {
-  const int n = M * k;
-  int blocks = (n + 255) / 256;
-  blocks = blocks > 1024 ? 1024 : blocks;
-  calibration_count_kernel<<<blocks, 256, 0, st>>>(topk_ids, n, N, reinterpret_cast<unsigned long long *>(counts));
+  const int n = M * k, per_wg = kAnalysisThreads * kCountsPerThread;
+  int blocks = (n + per_wg - 1) / per_wg;
+  blocks = blocks > 256 ? 256 : blocks;
+  calibration_count_kernel<<<blocks, kAnalysisThreads, 0, st>>>(topk_ids, n, N, reinterpret_cast<unsigned long long *>(counts));
   return hipGetLastError();
 }
 

@@ -47,31 +47,6 @@ __global__ __launch_bounds__(kScoreThreads) void score_parts_kernel(const double
 // experts, which every workgroup repeats, need the threads (at most kScoreLoads rows per thread up to 128 tokens).
 inline int budget_threads(int N) { return N <= 64 ? 256 : N <= 128 ? 512 : 1024; }
 
-// c[u] += number of the values row[j0 .. j1) that go before candidate lane + 64 u with value v[u] in a ranking by (value
-// descending, index ascending).  j0 and j1 are multiples of 4; row is padded with values that rank behind everything.
-// Four values per step, the same address in every lane (an LDS broadcast).  Against a rival of another block of 64
-// experts the tie rule is the same for all lanes (>= or >): one comparison and one add with carry per rival.
-template <int NU>
-__device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, int lane, const double (&v)[NU],
-                                            int (&c)[NU]) {
-#pragma unroll (NU <= 4 ? NU : 1)
-  for (int b = 0; b < NU; ++b) {
-    const int hi = min(j1, kWave * (b + 1));
-#pragma unroll 2
-    for (int j = max(j0, kWave * b); j < hi; j += 4) {
-      double r[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = row[j + q];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int u = 0; u < NU; ++u)
-          c[u] += u > b ? (int)(r[q] >= v[u]) : u < b ? (int)(r[q] > v[u])
-                        : (int)((r[q] > v[u]) | ((r[q] == v[u]) & (j + q < lane + kWave * u)));
-    }
-  }
-}
-
 struct BudgetLds {
   size_t s, red, rows, row_stride, S, rank, sel, inS, total;
 };

@@ -58,6 +58,59 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
+// ---- 16-lane all-reductions through DPP (no LDS, no barrier).  Every lane of a row of 16 ends with the same
+// bits: each step combines a value with its partner's, and the operations used are commutative.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+__device__ __forceinline__ double row16_max(double v) {
+  v = fmax(v, dpp_f64<kDppXor1>(v));
+  v = fmax(v, dpp_f64<kDppXor2>(v));
+  v = fmax(v, dpp_f64<kDppHalfMirror>(v));
+  return fmax(v, dpp_f64<kDppMirror>(v));
+}
+__device__ __forceinline__ double row16_sum(double v) {
+  v += dpp_f64<kDppXor1>(v);
+  v += dpp_f64<kDppXor2>(v);
+  v += dpp_f64<kDppHalfMirror>(v);
+  return v + dpp_f64<kDppMirror>(v);
+}
+__device__ __forceinline__ int row16_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, kDppXor1, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, kDppXor2, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, kDppHalfMirror, 0xf, 0xf, false);
+  return v + __builtin_amdgcn_update_dpp(0, v, kDppMirror, 0xf, 0xf, false);
+}
+
+// exp(x) for x <= 0 (the max-subtracted argument of a softmax): x = n ln 2 + r with |r| <= ln 2 / 2, the Taylor
+// polynomial of degree 12 in r (truncation error below 2e-16 relative) and a scaling by 2^n.  Every workgroup of
+// the kernel below evaluates the whole table, so the two dozen instructions of this form matter; arguments
+// below -800 give 0, NaN gives NaN further on (0 * inf in the normalisation).
+__device__ __forceinline__ double exp_nonpos(double x) {
+  x = fmax(x, -800.0);
+  const double n = rint(x * 1.4426950408889634);
+  double r = fma(n, -6.93147180369123816490e-01, x);
+  r = fma(n, -1.90821492927058770002e-10, r);
+  double p = 1.0 / 479001600.0;
+  p = fma(p, r, 1.0 / 39916800.0);
+  p = fma(p, r, 1.0 / 3628800.0);
+  p = fma(p, r, 1.0 / 362880.0);
+  p = fma(p, r, 1.0 / 40320.0);
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r, 1.0);
+  p = fma(p, r, 1.0);
+  return ldexp(p, (int)n);
+}
+
 // x = row / sqrt(mean of squares) in fp32 for one row held by a workgroup of kRmsThreads threads: thread i holds the
 // elements (c * kRmsThreads + i) * 4 .. + 3 of chunk c = 0 .. kRmsChunks-1 in v[c][0..3] (zeros past the row end;
 // the hidden size is at most 8192).  Squares are
@@ -84,6 +137,31 @@ __device__ inline float rms_scale_of_row(const float (&v)[kRmsChunks][4], int d,
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+}
+
+// c[u] += number of the values row[j0 .. j1) that go before candidate lane + 64 u with value v[u] in a ranking by (value
+// descending, index ascending).  j0 and j1 are multiples of 4; row is padded with values that rank behind everything.
+// Four values per step, the same address in every lane (an LDS broadcast).  Against a rival of another block of 64
+// experts the tie rule is the same for all lanes (>= or >): one comparison and one add with carry per rival.
+template <int NU>
+__device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, int lane, const double (&v)[NU],
+                                            int (&c)[NU]) {
+#pragma unroll (NU <= 4 ? NU : 1)
+  for (int b = 0; b < NU; ++b) {
+    const int hi = min(j1, kWave * (b + 1));
+#pragma unroll 2
+    for (int j = max(j0, kWave * b); j < hi; j += 4) {
+      double r[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) r[q] = row[j + q];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+          c[u] += u > b ? (int)(r[q] >= v[u]) : u < b ? (int)(r[q] > v[u])
+                        : (int)((r[q] > v[u]) | ((r[q] == v[u]) & (j + q < lane + kWave * u)));
+    }
+  }
 }
 
 // Rank-count selection of the k best of v[0..n) restricted to candidates with member[i] != 0
@@ -219,8 +297,10 @@ inline Workspace carve_workspace(const moespec_desc &ds, int64_t M, void *base) 
 }
 
 // Launchers (defined in the .hip files).  Each returns hipGetLastError() after its launches.
+// topk_ids / topk_w may be NULL.  partial: [kMaxLogitSlices, M, N] doubles of scratch where M <= kSelfMaxTokens and
+// N <= kSelfMaxExperts, unused otherwise.
 hipError_t launch_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *probs,
-                        int32_t *topk_ids, float *topk_w, hipStream_t st);
+                        int32_t *topk_ids, float *topk_w, double *partial, hipStream_t st);
 // score_parts: [kScoreMaxParts, N] doubles of scratch.  scores and n_loaded may be NULL.
 hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int B, int policy,
                          const int32_t *ext_shortlist, double *scores, int32_t *budget_ids, int32_t *tok_ids,
@@ -247,11 +327,14 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
 // ascending).  partial: [logit_slices, M, N] doubles of scratch.  probs_out, scores_out, seg_expert, seg_off,
 // perm, n_loaded are optional copies for the caller (the last three cost one more small launch).
 bool fused_prologue_ok(const moespec_desc &ds, int M);
-// Stage 1 on the matrix cores for bf16 layers of up to kSelfMaxExperts experts and kSelfMaxTokens tokens, whatever the
-// size of the table: probs [M, N] out, partial as above.
-bool mfma_route_ok(const moespec_desc &ds, int M);
-hipError_t launch_mfma_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *partial,
-                             double *probs, hipStream_t st);
+// The two halves of stage 1 for bf16 layers of up to kSelfMaxExperts experts (mfma_route_ok): the router projection on
+// the fp64 matrix cores (partial [slices, M, N] out), then bias, gate and - if wanted - the natural top-k, one wave per
+// token (partial may be probs itself when there is one slice).
+bool mfma_route_ok(const moespec_desc &ds);
+hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int slices,
+                         double *partial, hipStream_t st);
+hipError_t launch_gate_rows(const moespec_desc &ds, const moespec_weights &wt, int M, int slices, const double *partial,
+                            double *probs, int32_t *topk_ids, float *topk_w, hipStream_t st);
 int logit_slices(const moespec_desc &ds, int M, bool whole_table);
 hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int B,
                                  int policy, const int32_t *ext_shortlist, double *partial, double *probs_ws,

@@ -84,105 +84,6 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const u
   }
 }
 
-// ---- 16-lane all-reductions through DPP (no LDS, no barrier).  Every lane of a row of 16 ends with the same
-// bits: each step combines a value with its partner's, and the operations used are commutative.
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
-__device__ __forceinline__ double row16_max(double v) {
-  v = fmax(v, dpp_f64<kDppXor1>(v));
-  v = fmax(v, dpp_f64<kDppXor2>(v));
-  v = fmax(v, dpp_f64<kDppHalfMirror>(v));
-  return fmax(v, dpp_f64<kDppMirror>(v));
-}
-__device__ __forceinline__ double row16_sum(double v) {
-  v += dpp_f64<kDppXor1>(v);
-  v += dpp_f64<kDppXor2>(v);
-  v += dpp_f64<kDppHalfMirror>(v);
-  return v + dpp_f64<kDppMirror>(v);
-}
-__device__ __forceinline__ int row16_sum(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, kDppXor1, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, kDppXor2, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, kDppHalfMirror, 0xf, 0xf, false);
-  return v + __builtin_amdgcn_update_dpp(0, v, kDppMirror, 0xf, 0xf, false);
-}
-
-// exp(x) for x <= 0 (the max-subtracted argument of a softmax): x = n ln 2 + r with |r| <= ln 2 / 2, the Taylor
-// polynomial of degree 12 in r (truncation error below 2e-16 relative) and a scaling by 2^n.  Every workgroup of
-// the kernel below evaluates the whole table, so the two dozen instructions of this form matter; arguments
-// below -800 give 0, NaN gives NaN further on (0 * inf in the normalisation).
-__device__ __forceinline__ double exp_nonpos(double x) {
-  x = fmax(x, -800.0);
-  const double n = rint(x * 1.4426950408889634);
-  double r = fma(n, -6.93147180369123816490e-01, x);
-  r = fma(n, -1.90821492927058770002e-10, r);
-  double p = 1.0 / 479001600.0;
-  p = fma(p, r, 1.0 / 39916800.0);
-  p = fma(p, r, 1.0 / 3628800.0);
-  p = fma(p, r, 1.0 / 362880.0);
-  p = fma(p, r, 1.0 / 40320.0);
-  p = fma(p, r, 1.0 / 5040.0);
-  p = fma(p, r, 1.0 / 720.0);
-  p = fma(p, r, 1.0 / 120.0);
-  p = fma(p, r, 1.0 / 24.0);
-  p = fma(p, r, 1.0 / 6.0);
-  p = fma(p, r, 0.5);
-  p = fma(p, r, 1.0);
-  p = fma(p, r, 1.0);
-  return ldexp(p, (int)n);
-}
-
-// Eq. (1) row by row, for tables so large that rebuilding all of them in every workgroup of route_budget_kernel
-// would cost more than one more launch: probs[t, :] = gate(sum of the slices of the router projection + bias).
-// One wave per token; a lane holds up to 4 experts (N <= 256); 16-lane DPP reductions, then two cross-row steps.
-template <int Q>
-__global__ __launch_bounds__(kWave) void softmax_rows_kernel(const double *__restrict__ partial,
-                                                            const float *__restrict__ bias, int M, int N,
-                                                            int sigmoid_gate, double *__restrict__ probs) {
-  const int t = blockIdx.x, lane = threadIdx.x;
-  const size_t MN = (size_t)M * N;
-  double val[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i = lane + kWave * u;
-    double a = -INFINITY;
-    if (i < N) {
-      a = partial[(size_t)t * N + i];
-#pragma unroll
-      for (int q = 1; q < Q; ++q) a += partial[q * MN + (size_t)t * N + i];
-      a += bias ? (double)bias[i] : 0.0;
-    }
-    val[u] = a;
-  }
-  auto all_lanes = [](double v, auto op) {  // the 16-lane result of every row combined across the 4 rows
-    v = op(v, __shfl_xor(v, 16, kWave));
-    return op(v, __shfl_xor(v, 32, kWave));
-  };
-  if (sigmoid_gate) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (lane + kWave * u < N) probs[(size_t)t * N + lane + kWave * u] = 1.0 / (1.0 + exp(-val[u]));
-    return;
-  }
-  double m = fmax(fmax(val[0], val[1]), fmax(val[2], val[3]));
-  m = all_lanes(row16_max(m), [](double a, double b) { return fmax(a, b); });
-  double a = 0.0;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    val[u] = exp_nonpos(val[u] - m);  // lanes past the row end hold -inf: they come out as 0
-    a += val[u];
-  }
-  const double inv = 1.0 / all_lanes(row16_sum(a), [](double x, double y) { return x + y; });
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-    if (lane + kWave * u < N) probs[(size_t)t * N + lane + kWave * u] = val[u] * inv;
-}
-
 // LDS of route_budget_kernel.  Rows of the table are N + 1 doubles apart: lanes that walk down a column (one token
 // per lane) then touch different banks.
 struct PrologueLds {
@@ -592,26 +493,15 @@ int logit_slices(const moespec_desc &ds, int M, bool whole_table) {
   return best;
 }
 
-// Stage 1 alone for bf16 layers whose table does not fit the fused kernel's LDS: matrix-core projection, then the
-// row-wise gate.
-bool mfma_route_ok(const moespec_desc &ds, int M) {
-  return ds.dtype == MOESPEC_BF16 && ds.n_experts <= kSelfMaxExperts && M <= kSelfMaxTokens;
-}
-hipError_t launch_mfma_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *partial,
-                             double *probs, hipStream_t st) {
-  const int N = ds.n_experts, q = logit_slices(ds, M, false), sig = ds.gate == MOESPEC_GATE_SIGMOID ? 1 : 0;
-  dim3 grid(((M + 15) / 16) * ((N + 15) / 16), q);
+// Whether Eq. (1) runs on the matrix cores and row by row (bf16 layers of up to kSelfMaxExperts experts, any tree).
+bool mfma_route_ok(const moespec_desc &ds) { return ds.dtype == MOESPEC_BF16 && ds.n_experts <= kSelfMaxExperts; }
+
+hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int slices,
+                         double *partial, hipStream_t st) {
+  dim3 grid(((M + 15) / 16) * ((ds.n_experts + 15) / 16), slices);
   logits_mfma_kernel<<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const uint16_t *>(h),
-                                                          static_cast<const uint16_t *>(wt.w_router), M, N, ds.d, q,
-                                                          partial);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  switch (q) {
-    case 1: softmax_rows_kernel<1><<<M, kWave, 0, st>>>(partial, wt.b_router, M, N, sig, probs); break;
-    case 2: softmax_rows_kernel<2><<<M, kWave, 0, st>>>(partial, wt.b_router, M, N, sig, probs); break;
-    case 4: softmax_rows_kernel<4><<<M, kWave, 0, st>>>(partial, wt.b_router, M, N, sig, probs); break;
-    default: softmax_rows_kernel<8><<<M, kWave, 0, st>>>(partial, wt.b_router, M, N, sig, probs); break;
-  }
+                                                          static_cast<const uint16_t *>(wt.w_router), M, ds.n_experts,
+                                                          ds.d, slices, partial);
   return hipGetLastError();
 }
 
@@ -626,11 +516,7 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
   // only loads them; small tables: every workgroup of the last kernel rebuilds the table itself.
   const bool split = (long long)M * N > kSplitSoftmaxAbove;
   const int q = logit_slices(ds, M, !split);
-  dim3 grid(((M + 15) / 16) * ((N + 15) / 16), q);
-  logits_mfma_kernel<<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const uint16_t *>(h),
-                                                          static_cast<const uint16_t *>(wt.w_router), M, N, ds.d, q,
-                                                          partial);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_logits(ds, wt, h, M, q, partial, st);
   if (e != hipSuccess) return e;
   const size_t smem = prologue_lds(M, N, k, B).total;
   const int sig = ds.gate == MOESPEC_GATE_SIGMOID ? 1 : 0;
@@ -639,13 +525,7 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
   int slices = q;
   if (split) {
     double *probs = probs_out ? probs_out : probs_ws;
-    switch (q) {
-      case 1: softmax_rows_kernel<1><<<M, kWave, 0, st>>>(partial, wt.b_router, M, N, sig, probs); break;
-      case 2: softmax_rows_kernel<2><<<M, kWave, 0, st>>>(partial, wt.b_router, M, N, sig, probs); break;
-      case 4: softmax_rows_kernel<4><<<M, kWave, 0, st>>>(partial, wt.b_router, M, N, sig, probs); break;
-      default: softmax_rows_kernel<8><<<M, kWave, 0, st>>>(partial, wt.b_router, M, N, sig, probs); break;
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_gate_rows(ds, wt, M, q, partial, probs, nullptr, nullptr, st)) != hipSuccess) return e;
     table = probs;
     table_bias = nullptr;
     slices = 1;

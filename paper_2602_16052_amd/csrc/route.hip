@@ -1,11 +1,9 @@
 // Stage 1 of Algorithm 1: router projection, softmax over all N experts (Eq. (1)), per-token
 // top-k and mixing weights (Section 2.1).  Every decision in fp64.
 //
-// Two kernels.  The projection is spread over (token, group of 4 experts) workgroups so that the
-// whole chip takes part: converting bf16 operands to fp64 costs several vector instructions per
-// element, and one workgroup per token would leave that work on M compute units.  The softmax and
-// the top-k then need one small workgroup per token.  Cross-lane fp64 shuffles are slow on this
-// hardware (two 32-bit permutes per step), so all reductions go through LDS.
+// bf16 layers of up to 256 experts: the projection runs on the fp64 matrix cores (logits_mfma_kernel of prologue.hip)
+// and gate_rows_kernel takes one wave per token.  fp32 layers and more experts: logits_kernel, spread over (token,
+// group of 4 experts) workgroups so that the whole chip takes part, and softmax_topk_kernel, one workgroup per token.
 #include "common.h"
 
 namespace moespec {
@@ -14,6 +12,7 @@ constexpr int kLogitThreads = 256;
 constexpr int kRowsPerGroup = 4;                               // router rows per workgroup
 constexpr int kSlices = kLogitThreads / kRowsPerGroup;         // threads that share one row (= 64)
 constexpr int kSoftmaxThreads = 256;
+constexpr int kGateThreads = 256;
 
 // logits[t, i] = w_i . h_t (+ b_i).  Thread (el, sl) takes the 16-byte pieces sl, sl+64, ... of row
 // i = 4 blockIdx.x + el and of h_t; all loads of a batch are issued together (the router weights of a
@@ -130,9 +129,111 @@ __global__ __launch_bounds__(kSoftmaxThreads) void softmax_topk_kernel(double *_
   }
 }
 
+// Eq. (1) and, if wanted, the natural top-k of Section 2.1 row by row, one wave per token: probs[t, :] = gate(sum of the
+// Q slices of the router projection + bias), top-k by rank counts over the row in LDS.  A lane holds up to NU experts;
+// 16-lane DPP reductions, then two cross-row steps.  partial may be probs (a wave reads its whole row before it writes).
+// Bound by the launch and one round of cold loads up to a few hundred tokens, by the row's N / 4 LDS reads beyond (4096
+// tokens x 64 experts with top-8 and weights: 7.6 us, against 15 us of softmax_topk_kernel).
+template <int Q, int NU, bool kTopK>
+__global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *partial, const float *__restrict__ bias,
+                                                                 int M, int N, int sigmoid_gate, double *probs, int k,
+                                                                 int renorm, int32_t *__restrict__ topk_ids,
+                                                                 float *__restrict__ topk_w) {
+  __shared__ double rows[kTopK ? kGateThreads / kWave : 1][kTopK ? NU * kWave : 1];
+  __shared__ int32_t sels[kTopK ? kGateThreads / kWave : 1][kWave];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = blockIdx.x * (kGateThreads / kWave) + wave;
+  if (t >= M) return;
+  const size_t MN = (size_t)M * N;
+  double val[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int i = lane + kWave * u;
+    double a = -INFINITY;
+    if (i < N) {
+      a = partial[(size_t)t * N + i];
+#pragma unroll
+      for (int q = 1; q < Q; ++q) a += partial[q * MN + (size_t)t * N + i];
+      a += bias ? (double)bias[i] : 0.0;
+    }
+    val[u] = a;
+  }
+  if (sigmoid_gate) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) val[u] = 1.0 / (1.0 + exp(-val[u]));
+  } else {
+    auto all_lanes = [](double v, auto op) {  // the 16-lane result of every row combined across the 4 rows
+      v = op(v, __shfl_xor(v, 16, kWave));
+      return op(v, __shfl_xor(v, 32, kWave));
+    };
+    double m = val[0];
+#pragma unroll
+    for (int u = 1; u < NU; ++u) m = fmax(m, val[u]);
+    m = all_lanes(row16_max(m), [](double a, double b) { return fmax(a, b); });
+    double a = 0.0;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      val[u] = exp_nonpos(val[u] - m);  // lanes past the row end hold -inf: they come out as 0
+      a += val[u];
+    }
+    const double inv = 1.0 / all_lanes(row16_sum(a), [](double x, double y) { return x + y; });
+#pragma unroll
+    for (int u = 0; u < NU; ++u) val[u] *= inv;
+  }
+#pragma unroll
+  for (int u = 0; u < NU; ++u)
+    if (lane + kWave * u < N) probs[(size_t)t * N + lane + kWave * u] = val[u];
+  if constexpr (kTopK) {
+    double *row = rows[wave];
+    int32_t *sel = sels[wave];
+    int c[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      c[u] = 0;
+      row[lane + kWave * u] = lane + kWave * u < N ? val[u] : -1.0;
+    }
+    sel[lane] = -1;  // stays -1 where a NaN leaves a slot unclaimed
+    wave_lds_sync();
+    rank_counts<NU>(row, 0, N, lane, val, c);
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (lane + kWave * u < N && c[u] < k) sel[c[u]] = lane + kWave * u;
+    wave_lds_sync();
+    if (lane < k) {
+      double denom = 0.0;  // in slot order
+      for (int j = 0; j < k; ++j) denom += sel[j] >= 0 ? row[sel[j]] : 0.0;
+      const int e = sel[lane];
+      if (topk_ids) topk_ids[(size_t)t * k + lane] = e;
+      if (topk_w) topk_w[(size_t)t * k + lane] = (float)(e < 0 ? 0.0 : (renorm ? row[e] / denom : row[e]));
+    }
+  }
+}
+
+hipError_t launch_gate_rows(const moespec_desc &ds, const moespec_weights &wt, int M, int slices, const double *partial,
+                            double *probs, int32_t *topk_ids, float *topk_w, hipStream_t st) {
+  const int N = ds.n_experts, per_wg = kGateThreads / kWave, sig = ds.gate == MOESPEC_GATE_SIGMOID ? 1 : 0;
+  auto run = [&](auto kern) -> hipError_t {
+    kern<<<(M + per_wg - 1) / per_wg, kGateThreads, 0, st>>>(partial, wt.b_router, M, N, sig, probs, ds.top_k, ds.renorm,
+                                                             topk_ids, topk_w);
+    return hipGetLastError();
+  };
+  const bool topk = topk_ids || topk_w;
+#define MOESPEC_GATE(Q, NU) (topk ? run(gate_rows_kernel<Q, NU, true>) : run(gate_rows_kernel<Q, NU, false>))
+#define MOESPEC_GATE_Q(Q) (N <= 64 ? MOESPEC_GATE(Q, 1) : N <= 128 ? MOESPEC_GATE(Q, 2) : MOESPEC_GATE(Q, 4))
+  return slices == 1 ? MOESPEC_GATE_Q(1) : slices == 2 ? MOESPEC_GATE_Q(2) : slices == 4 ? MOESPEC_GATE_Q(4) : MOESPEC_GATE_Q(8);
+#undef MOESPEC_GATE_Q
+#undef MOESPEC_GATE
+}
+
 hipError_t launch_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *probs,
-                        int32_t *topk_ids, float *topk_w, hipStream_t st) {
+                        int32_t *topk_ids, float *topk_w, double *partial, hipStream_t st) {
   const int N = ds.n_experts, k = ds.top_k, d = ds.d;
+  if (mfma_route_ok(ds)) {
+    // beyond kSelfMaxTokens the output tiles alone fill the chip: one slice, accumulated in the caller's table
+    const int slices = M <= kSelfMaxTokens ? logit_slices(ds, M, false) : 1;
+    double *logits = slices == 1 ? probs : partial;
+    hipError_t e = launch_logits(ds, wt, h, M, slices, logits, st);
+    return e != hipSuccess ? e : launch_gate_rows(ds, wt, M, slices, logits, probs, topk_ids, topk_w, st);
+  }
   dim3 grid((N + kRowsPerGroup - 1) / kRowsPerGroup, M);
   if (ds.dtype == MOESPEC_BF16) {
     logits_kernel<uint16_t><<<grid, kLogitThreads, 0, st>>>(static_cast<const uint16_t *>(h),
