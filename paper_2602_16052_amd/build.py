@@ -10,7 +10,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libmoespec.so")
-SOURCES = ("api.hip", "route.hip", "budget.hip", "prologue.hip", "expert_ffn.hip", "analysis.hip", "stack.hip")
+SOURCES = ("api.hip", "route.hip", "budget.hip", "prologue.hip", "expert_ffn.hip", "expert_wide.hip", "analysis.hip", "stack.hip")
 
 # Packed-FP32 instructions are disabled for all device code (hipcc's host pass warns that it does
 # not know the feature; that warning is harmless).
@@ -41,11 +41,12 @@ def build_library(verbose: bool = False) -> str:
 
 def build_host_sanitizer_library(out_dir: str) -> str:
     """The library with AddressSanitizer and UndefinedBehaviorSanitizer instrumentation in its HOST code only
-    (GPU sanitizers are not used); the device code is compiled unoptimised to keep the build short.  For the
+    (GPU sanitizers are not used); the device code is compiled with -O1 to keep the build short (the scalar operands
+    of its inline assembly need an optimised build).  For the
     host-side checks in tests/; never loaded by the product path.  Returns the path of the library."""
     out = os.path.join(out_dir, "libmoespec_hostsan.so")
     flags = [f for f in HIPCC_FLAGS if f != "-O3"]
-    cmd = [hipcc_path(), *flags, "-Xarch_device", "-O0", "-Xarch_host", "-O1",
+    cmd = [hipcc_path(), *flags, "-Xarch_device", "-O1", "-Xarch_host", "-O1",
            "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
            "-Xarch_host", "-fno-sanitize-recover=undefined",
            "-I", os.path.join(ROOT, "include"), "-I", CSRC, *[os.path.join(CSRC, s) for s in SOURCES], "-o", out]

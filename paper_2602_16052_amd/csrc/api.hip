@@ -114,7 +114,7 @@ moespec_status layer_forward(const moespec_desc *desc, const moespec_weights *we
     if (tr && tr[i]) (void)hipEventRecord(static_cast<hipEvent_t>(tr[i]), st);
   };
   mark(0);
-  if (fused_prologue_ok(*desc, M) && expert_ffn_self_segmenting(*desc, M)) {
+  if (fused_prologue_ok(*desc, M) && expert_ffn_self_segmenting(*desc, M) && !expert_ffn_wide(*desc, M, B)) {
     // Small trees: two launches leave the shortlist, the restricted routing and every loaded expert's pair
     // list; the expert passes pick their work items from those lists.
     hipError_t e = launch_fused_prologue(*desc, *weights, h, M, B, policy, ext_shortlist, w.partial, w.probs, t.probs,
@@ -336,7 +336,7 @@ moespec_status moespec_oracle_ranking(const moespec_desc *desc, const moespec_we
   e = launch_expert_ffn(*desc, *weights, h, M, N, w.seg_expert, w.seg_off, w.perm, w.tok_ids, w.tok_w, nullptr,
                         nullptr, w.act, w.y, w.items, true, nullptr, nullptr, nullptr, 0, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
-  return from_hip(launch_oracle_ranking(*desc, w.y, down_splits(*desc, N), (size_t)M * desc->top_k * desc->d,
+  return from_hip(launch_oracle_ranking(*desc, w.y, down_splits(*desc, M, N), (size_t)M * desc->top_k * desc->d,
                                         w.tok_ids, w.tok_w, M, B, static_cast<double *>(w.act), w.gram, ranking, err,
                                         st));
 }

@@ -25,6 +25,8 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
   return static_cast<uint16_t>(u >> 16);
 }
 
+__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
   static __device__ __forceinline__ float load(const float *p) { return *p; }
@@ -146,7 +148,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 template <int NU>
 __device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, int lane, const double (&v)[NU],
                                             int (&c)[NU]) {
-#pragma unroll (NU <= 4 ? NU : 1)
+  constexpr int kBlocksUnrolled = NU <= 4 ? NU : 1;
+#pragma unroll kBlocksUnrolled
   for (int b = 0; b < NU; ++b) {
     const int hi = min(j1, kWave * (b + 1));
 #pragma unroll 2
@@ -345,7 +348,11 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
 bool expert_ffn_self_segmenting(const moespec_desc &ds, int M);
 // Number of K-split copies of y that launch_expert_ffn writes for n_seg segments; out == NULL there skips
 // the combine and leaves the per-pair expert outputs in y.
-int down_splits(const moespec_desc &ds, int n_seg);
+int down_splits(const moespec_desc &ds, int M, int n_seg);
+// The passes as a grouped GEMM (expert_wide.hip): whether they run in that form, and one of them.
+bool expert_ffn_wide(const moespec_desc &ds, int M, int n_seg);
+hipError_t launch_wide_pass(const moespec_desc &ds, const moespec_weights &wt, bool gate_up, const void *x, int M,
+                            const int4 *items, const int32_t *perm, int cap, void *out, hipStream_t st);
 // Analysis kernels (analysis.hip).  part: 2 M doubles of scratch.
 hipError_t launch_calibration_count(const int32_t *topk_ids, int M, int k, int N, int64_t *counts, hipStream_t st);
 hipError_t launch_static_shortlist(const int64_t *counts, int N, int B, int32_t *shortlist, hipStream_t st);

@@ -173,8 +173,6 @@ inline int xcd_grid(int tiles, int n_items) { return kXcds * tiles * ((n_items +
 // Start offset (elements) of a wave's walk over K: 128 elements (256 bytes) apart for consecutive waves.
 __device__ __forceinline__ int k_stagger(int wave_id, int K) { return (int)(((long long)wave_id * 128) % K); }
 
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
-
 // ---- pass 1 (bf16): gate/up projections + SwiGLU ---------------------------------------------
 template <int NT, int U>
 __device__ __forceinline__ void gateup_tiles(const uint16_t *a0, const uint16_t *a1, const uint16_t *__restrict__ h,
@@ -824,9 +822,9 @@ bool expert_ffn_self_segmenting(const moespec_desc &ds, int M) {
 // unit two workgroups, each item is cut along F into up to kMaxDownSplits parts with their own copy of y,
 // as long as a part keeps at least 16 chunks (shorter walks are dominated by their start-up: measured
 // slower at F = 1024, 1.6x to 2.7x faster at F = 14336 with 4 or 2 loaded experts).
-int down_splits(const moespec_desc &ds, int n_seg) {
+int down_splits(const moespec_desc &ds, int M, int n_seg) {
   int splits = 1;
-  if (ds.dtype == MOESPEC_BF16 && ds.d_ff % 128 == 0) {
+  if (!expert_ffn_wide(ds, M, n_seg) && ds.dtype == MOESPEC_BF16 && ds.d_ff % 128 == 0) {
     const int tiles = (ds.d / 32 + kFfnWaves - 1) / kFfnWaves;
     while (splits < kMaxDownSplits && (long long)n_seg * tiles * splits * 2 <= 512 && ds.d_ff / 128 >= 32 * splits)
       splits *= 2;
@@ -847,18 +845,26 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   if (rank_count && !(shortlist && lists && expert_ffn_self_segmenting(ds, M) && n_seg <= kFfnThreads))
     return hipErrorInvalidValue;
   if (!rank_count && !items_ready && !items) return hipErrorInvalidValue;
+  const bool wide = !rank_count && expert_ffn_wide(ds, M, n_seg);
   const int cap = items_capacity(n_seg, M, k);  // work items of the LDS-tiled passes
-  if (ds.dtype == MOESPEC_BF16 && !rank_count && !items_ready && (d % 128 == 0 || F % 128 == 0)) {
+  if (ds.dtype == MOESPEC_BF16 && !rank_count && !items_ready && (wide || d % 128 == 0 || F % 128 == 0)) {
     segment_items_kernel<<<1, 256, 0, st>>>(seg_expert, seg_off, n_seg, M, k, cap, items);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   auto mark = [&](int i) {
     if (trace && trace[i]) (void)hipEventRecord(static_cast<hipEvent_t>(trace[i]), st);
   };
-  const int splits = down_splits(ds, n_seg);
+  const int splits = down_splits(ds, M, n_seg);
   const size_t split_stride = (size_t)M * k * d;
   if (ds.dtype == MOESPEC_BF16) {
     for (int pass = 1; pass <= 2; ++pass) {
+      if (wide) {
+        e = launch_wide_pass(ds, wt, pass == 1, pass == 1 ? h : act, M, items, perm, cap,
+                             pass == 1 ? act : static_cast<void *>(y), st);
+        if (e != hipSuccess) return e;
+        mark(pass - 1);
+        continue;
+      }
       if ((pass == 1 ? d : F) % 128 == 0) {
         if (pass == 1) {
           const int grid = xcd_grid((F / 16 + kFfnWaves - 1) / kFfnWaves, cap);
