@@ -330,7 +330,7 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
 // ascending).  partial: [logit_slices, M, N] doubles of scratch.  probs_out, scores_out, seg_expert, seg_off,
 // perm, n_loaded are optional copies for the caller (the last three cost one more small launch).
 bool fused_prologue_ok(const moespec_desc &ds, int M);
-// The two halves of stage 1 for bf16 layers of up to kSelfMaxExperts experts (mfma_route_ok): the router projection on
+// The two halves of stage 1 for layers of up to kSelfMaxExperts experts (mfma_route_ok): the router projection on
 // the fp64 matrix cores (partial [slices, M, N] out), then bias, gate and - if wanted - the natural top-k, one wave per
 // token (partial may be probs itself when there is one slice).
 bool mfma_route_ok(const moespec_desc &ds);

@@ -643,52 +643,159 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
   }
 }
 
-// ---- fp32 path: one wave per weight row, lanes stride K (correctness path for small layers) ----
+// ---- fp32 path ------------------------------------------------------------------------------------------------
+// A wave owns 8 weight rows (gate/up: 4 gate rows and the same 4 up rows) and P pairs at a time: lane l adds the
+// products of the elements l, l + 64, ... of K in ascending order, 8 P sums side by side, and the 64 lanes of a sum are
+// folded in the order 32, 16, 8, 4, 2, 1.  The sums are folded together: in each step a lane keeps one half of them and
+// hands the other half over, so that 8 P sums cost 8 P - 1 exchanges in all and every lane ends with one of them.
+// What bounds it: fp32 multiply-adds (packed fp32 is not used) and their loads, 16 per 64 of them.  One wave per row that
+// walked over the pairs one by one, with 6 exchanges per sum, took 140 + 276 us for 8 experts of 512 x 1024 and 63 tokens.
+constexpr int kF32Rows = 8, kF32Pairs = 8;
+
+// v[0 .. n/2) = the sums of the half of v[0 .. n) that this lane keeps: lanes with bit MASK set keep the upper half
+template <int MASK, int N_>
+__device__ __forceinline__ void fold_half(float *v) {
+#pragma unroll
+  for (int a = 0; a < N_ / 2; ++a) {
+    if constexpr (MASK >= 16) {
+      // swaps the odd rows of 32 (16) lanes of one register with the even rows of the other
+      const auto r = MASK == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(v[a]), __float_as_uint(v[a + N_ / 2]), false, false)
+                                : __builtin_amdgcn_permlane16_swap(__float_as_uint(v[a]), __float_as_uint(v[a + N_ / 2]), false, false);
+      v[a] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+      const bool up = (threadIdx.x & MASK) != 0;
+      const float keep = up ? v[a + N_ / 2] : v[a], give = up ? v[a] : v[a + N_ / 2];
+      v[a] = keep + __shfl_xor(give, MASK, kWave);
+    }
+  }
+}
+// After it, lane l holds the complete sum number l / (64 / N_) in v[0].
+template <int N_>
+__device__ __forceinline__ float fold_sums(float (&v)[N_]) {
+  static_assert(N_ == 64 || N_ == 32, "one or two lanes per sum");
+  fold_half<32, N_>(v);
+  fold_half<16, N_ / 2>(v);
+  fold_half<8, N_ / 4>(v);
+  fold_half<4, N_ / 8>(v);
+  fold_half<2, N_ / 16>(v);
+  if constexpr (N_ == 64) fold_half<1, 2>(v);
+  else v[0] += __shfl_xor(v[0], 1, kWave);
+  return v[0];
+}
+
+// sums[r * P + p] = this lane's part of row[r] . x[p] over K
+template <int P>
+__device__ __forceinline__ void f32_dots(const float *const (&row)[kF32Rows], const float *const (&x)[P], int K,
+                                         float (&sums)[kF32Rows * P]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < kF32Rows * P; ++i) sums[i] = 0.f;
+#pragma unroll 2
+  for (int j0 = 0; j0 < K; j0 += kWave) {
+    const int j = j0 + lane;
+    const bool in = j < K;  // lanes past the end add +0 * +0
+    float w[kF32Rows], xv[P];
+#pragma unroll
+    for (int r = 0; r < kF32Rows; ++r) w[r] = in ? row[r][j] : 0.f;
+#pragma unroll
+    for (int p = 0; p < P; ++p) xv[p] = in ? x[p][j] : 0.f;
+#pragma unroll
+    for (int r = 0; r < kF32Rows; ++r)
+#pragma unroll
+      for (int p = 0; p < P; ++p) sums[r * P + p] = fmaf(w[r], xv[p], sums[r * P + p]);
+  }
+}
+
+// The segment of grid row `seg`: from the prologue's lists (shortlist rank seg) or from the segment arrays.
+__device__ __forceinline__ bool f32_segment(int seg, const int32_t *seg_expert, const int32_t *seg_off,
+                                            const int32_t *perm, const int32_t *rank_count, const int32_t *shortlist,
+                                            const int32_t *lists, int list_stride, int M, int N, int k, int &e, int &m,
+                                            const int32_t *&plist) {
+  if (rank_count) {
+    e = shortlist[seg];
+    m = rank_count[seg];
+    plist = lists + (size_t)seg * list_stride;
+    return e >= 0 && e < N && m > 0 && m <= M;
+  }
+  e = seg_expert[seg];
+  const int beg = seg_off[seg];
+  m = seg_off[seg + 1] - beg;
+  plist = perm + beg;
+  return segment_ok(e, beg, m, (long long)M * k, N);
+}
+
+template <int P>
+__device__ __forceinline__ void gateup_f32_tile(const float *__restrict__ h, const float *wg, const float *wu,
+                                                const int32_t *plist, int p0, int m, int n_pairs, int k, int d, int F,
+                                                int f0, float *__restrict__ act) {
+  const int lane = threadIdx.x & 63;
+  const float *row[kF32Rows], *x[P];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int f = min(f0 + r, F - 1);
+    row[r] = wg + (size_t)f * d;
+    row[4 + r] = wu + (size_t)f * d;
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p) x[p] = h + (size_t)(pair_at(plist, min(p0 + p, m - 1), n_pairs) / k) * d;
+  float sums[kF32Rows * P];
+  f32_dots<P>(row, x, d, sums);
+  const float g = fold_sums(sums), u = __shfl_xor(g, 32, kWave);
+  constexpr int LPS = 64 / (kF32Rows * P);  // lanes per sum
+  const int idx = lane / LPS, f = f0 + idx / P, p = p0 + idx % P;
+  if (lane < 32 && lane % LPS == 0 && f < F && p < m) act[(size_t)pair_at(plist, p, n_pairs) * F + f] = g / (1.0f + expf(-g)) * u;
+}
+
 __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
     const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
     const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm,
-    int M, int N, int k, int d, int F, float *__restrict__ act) {
-  const int seg = blockIdx.y;
-  const int e = seg_expert[seg];
-  const int beg = seg_off[seg], m = seg_off[seg + 1] - beg;
-  if (!segment_ok(e, beg, m, (long long)M * k, N)) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int f = blockIdx.x * kFfnWaves + wave;
-  if (f >= F) return;
-  const float *wg = w_gate + ((size_t)e * F + f) * d;
-  const float *wu = w_up + ((size_t)e * F + f) * d;
-  for (int p = 0; p < m; ++p) {
-    const float *x = h + (size_t)(pair_index(perm, beg + p, M, k) / k) * d;
-    float g = 0.f, u = 0.f;
-    for (int j = lane; j < d; j += kWave) {
-      const float xv = x[j];
-      g = fmaf(wg[j], xv, g);
-      u = fmaf(wu[j], xv, u);
-    }
-    g = wave_sum(g);
-    u = wave_sum(u);
-    if (lane == 0) act[(size_t)(beg + p) * F + f] = g / (1.0f + expf(-g)) * u;
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int M, int N, int k, int d, int F, float *__restrict__ act) {
+  int e, m;
+  const int32_t *plist;
+  if (!f32_segment(blockIdx.y, seg_expert, seg_off, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m, plist))
+    return;
+  const int f0 = (blockIdx.x * kFfnWaves + (int)(threadIdx.x >> 6)) * 4;
+  if (f0 >= F) return;
+  const float *wg = w_gate + (size_t)e * F * d, *wu = w_up + (size_t)e * F * d;
+  for (int p0 = blockIdx.z * kF32Pairs; p0 < m; p0 += gridDim.z * kF32Pairs) {
+    if (m - p0 <= kF32Pairs / 2) gateup_f32_tile<kF32Pairs / 2>(h, wg, wu, plist, p0, m, M * k, k, d, F, f0, act);
+    else gateup_f32_tile<kF32Pairs>(h, wg, wu, plist, p0, m, M * k, k, d, F, f0, act);
   }
+}
+
+template <int P>
+__device__ __forceinline__ void down_f32_tile(const float *__restrict__ act, const float *wd, const int32_t *plist, int p0,
+                                              int m, int n_pairs, int d, int F, int j0, float *__restrict__ y) {
+  const int lane = threadIdx.x & 63;
+  const float *row[kF32Rows], *x[P];
+#pragma unroll
+  for (int r = 0; r < kF32Rows; ++r) row[r] = wd + (size_t)min(j0 + r, d - 1) * F;
+#pragma unroll
+  for (int p = 0; p < P; ++p) x[p] = act + (size_t)pair_at(plist, min(p0 + p, m - 1), n_pairs) * F;
+  float sums[kF32Rows * P];
+  f32_dots<P>(row, x, F, sums);
+  const float v = fold_sums(sums);
+  constexpr int LPS = 64 / (kF32Rows * P);
+  const int idx = lane / LPS, j = j0 + idx / P, p = p0 + idx % P;
+  if (lane % LPS == 0 && j < d && p < m) y[(size_t)pair_at(plist, p, n_pairs) * d + j] = v;
 }
 
 __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
     const float *__restrict__ act, const float *__restrict__ w_down, const int32_t *__restrict__ seg_expert,
-    const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm, int M, int N, int k, int d, int F,
-    float *__restrict__ y) {
-  const int seg = blockIdx.y;
-  const int e = seg_expert[seg];
-  const int beg = seg_off[seg], m = seg_off[seg + 1] - beg;
-  if (!segment_ok(e, beg, m, (long long)M * k, N)) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int j = blockIdx.x * kFfnWaves + wave;
-  if (j >= d) return;
-  const float *wd = w_down + ((size_t)e * d + j) * F;
-  for (int p = 0; p < m; ++p) {
-    const float *a = act + (size_t)(beg + p) * F;
-    float acc = 0.f;
-    for (int f = lane; f < F; f += kWave) acc = fmaf(wd[f], a[f], acc);
-    acc = wave_sum(acc);
-    if (lane == 0) y[(size_t)pair_index(perm, beg + p, M, k) * d + j] = acc;
+    const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count,
+    const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists, int list_stride, int M, int N, int k, int d,
+    int F, float *__restrict__ y) {
+  int e, m;
+  const int32_t *plist;
+  if (!f32_segment(blockIdx.y, seg_expert, seg_off, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m, plist))
+    return;
+  const int j0 = (blockIdx.x * kFfnWaves + (int)(threadIdx.x >> 6)) * kF32Rows;
+  if (j0 >= d) return;
+  const float *wd = w_down + (size_t)e * d * F;
+  for (int p0 = blockIdx.z * kF32Pairs; p0 < m; p0 += gridDim.z * kF32Pairs) {
+    if (m - p0 <= kF32Pairs / 2) down_f32_tile<kF32Pairs / 2>(act, wd, plist, p0, m, M * k, d, F, j0, y);
+    else down_f32_tile<kF32Pairs>(act, wd, plist, p0, m, M * k, d, F, j0, y);
   }
 }
 
@@ -812,9 +919,10 @@ static hipError_t launch_bf16(const moespec_desc &ds, const moespec_weights &wt,
   return hipGetLastError();
 }
 
-// Taking the work items from the prologue's lists needs both passes on the LDS-tiled kernels.
+// Whether the passes can take their pairs from the prologue's lists: fp32 layers, and bf16 layers whose passes are both
+// LDS-tiled.
 bool expert_ffn_self_segmenting(const moespec_desc &ds, int M) {
-  return ds.dtype == MOESPEC_BF16 && ds.d % 128 == 0 && ds.d_ff % 128 == 0 && ds.n_experts <= kSelfMaxExperts &&
+  return (ds.dtype == MOESPEC_F32 || (ds.d % 128 == 0 && ds.d_ff % 128 == 0)) && ds.n_experts <= kSelfMaxExperts &&
          M <= kSelfMaxTokens;
 }
 
@@ -904,17 +1012,19 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     mark(2);
     return e;
   }
-  dim3 g1((F + kFfnWaves - 1) / kFfnWaves, n_seg);
-  ffn_gateup_f32_kernel<<<g1, kFfnThreads, 0, st>>>(static_cast<const float *>(h),
-                                                    static_cast<const float *>(wt.w_gate),
-                                                    static_cast<const float *>(wt.w_up), seg_expert, seg_off, perm, M,
-                                                    ds.n_experts, k, d, F, static_cast<float *>(act));
+  // up to 4 workgroups share the pairs of a segment: enough waves to hide the loads where rows are few
+  const int ptiles = (M + kF32Pairs - 1) / kF32Pairs, z = ptiles < 4 ? ptiles : 4;
+  dim3 g1((F + 4 * kFfnWaves - 1) / (4 * kFfnWaves), n_seg, z);
+  ffn_gateup_f32_kernel<<<g1, kFfnThreads, 0, st>>>(
+      static_cast<const float *>(h), static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up),
+      seg_expert, seg_off, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
+      static_cast<float *>(act));
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(0);
-  dim3 g2((d + kFfnWaves - 1) / kFfnWaves, n_seg);
+  dim3 g2((d + kF32Rows * kFfnWaves - 1) / (kF32Rows * kFfnWaves), n_seg, z);
   ffn_down_f32_kernel<<<g2, kFfnThreads, 0, st>>>(static_cast<const float *>(act),
-                                                  static_cast<const float *>(wt.w_down), seg_expert, seg_off, perm, M,
-                                                  ds.n_experts, k, d, F, y);
+                                                  static_cast<const float *>(wt.w_down), seg_expert, seg_off, perm,
+                                                  rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(1);
   if (!out) return hipSuccess;

@@ -27,19 +27,34 @@ constexpr int kSoftmaxSegs = 16;  // threads that share one row of the table in 
 // 0.6 us faster rebuilt in every workgroup, 8128 entries 0.9 us and 16256 entries 2.3 us faster with the extra launch).
 constexpr long long kSplitSoftmaxAbove = 6000;
 
-__device__ __forceinline__ double bf16_to_f64(uint32_t word, int hi) {
-  return (double)__uint_as_float(hi ? (word & 0xffff0000u) : (word << 16));
-}
+// 8 consecutive elements of a row, widened one by one
+template <typename T> struct LogitPiece;
+template <> struct LogitPiece<uint16_t> {
+  uint4 v;
+  __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint4 *>(p); }
+  __device__ __forceinline__ double get(int m) const {
+    const uint32_t word = reinterpret_cast<const uint32_t *>(&v)[m >> 1];
+    return (double)__uint_as_float(m & 1 ? (word & 0xffff0000u) : (word << 16));
+  }
+};
+template <> struct LogitPiece<float> {
+  float4 v[2];
+  __device__ __forceinline__ void load(const float *p) {
+    v[0] = reinterpret_cast<const float4 *>(p)[0];
+    v[1] = reinterpret_cast<const float4 *>(p)[1];
+  }
+  __device__ __forceinline__ double get(int m) const { return (double)reinterpret_cast<const float *>(v)[m]; }
+};
 
 // partial[q][t][e] = sum over the q-th slice of the hidden dimension of h[t][j] * w_r[e][j], in fp64.
 // Workgroup (x, q): x = output tile (16 tokens x 16 experts), q = slice; its 4 waves cut the slice again into
 // runs of 32-element blocks and add their results through LDS in wave order.  v_mfma_f64_16x16x4: lane (i, g)
 // = (lane % 16, lane / 16) supplies A[i][g] and B[g][i] and receives D[g + 4 r][i] in accumulator r.  A lane
-// loads 8 consecutive elements (16 bytes) of its token row and of its expert row per block; which of the 32
+// loads 8 consecutive elements of its token row and of its expert row per block; which of the 32
 // elements of a block meet in one instruction is immaterial, the sum over the block is complete after 8 of them.
-__global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const uint16_t *__restrict__ h,
-                                                                          const uint16_t *__restrict__ w_r, int M,
-                                                                          int N, int d, int n_slices,
+template <typename T>
+__global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T *__restrict__ h, const T *__restrict__ w_r,
+                                                                          int M, int N, int d, int n_slices,
                                                                           double *__restrict__ partial) {
   __shared__ double red[kLogitWaves][256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -49,28 +64,30 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const u
   const int t = min(tt * 16 + i, M - 1), e = min(et * 16 + i, N - 1);  // pad rows repeat the last one, never stored
   const int n_blocks = d / 32, parts = n_slices * kLogitWaves, part = q * kLogitWaves + wave;
   const int b0 = (int)((long long)part * n_blocks / parts), b1 = (int)((long long)(part + 1) * n_blocks / parts);
-  const uint16_t *ha = h + (size_t)t * d + g * 8, *wb = w_r + (size_t)e * d + g * 8;
+  const T *ha = h + (size_t)t * d + g * 8, *wb = w_r + (size_t)e * d + g * 8;
   f64x4 acc = {0.0, 0.0, 0.0, 0.0};
   constexpr int PB = 4;  // blocks in flight
   for (int b = b0; b < b1; b += PB) {
-    uint4 A[PB], Bv[PB];
+    LogitPiece<T> A[PB], Bv[PB];
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
       const int bb = min(b + u, b1 - 1);
-      A[u] = *reinterpret_cast<const uint4 *>(ha + (size_t)bb * 32);
-      Bv[u] = *reinterpret_cast<const uint4 *>(wb + (size_t)bb * 32);
+      A[u].load(ha + (size_t)bb * 32);
+      Bv[u].load(wb + (size_t)bb * 32);
     }
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
       if (b + u < b1) {  // uniform in the wave
-        const uint32_t *a = reinterpret_cast<const uint32_t *>(&A[u]);
-        const uint32_t *bw = reinterpret_cast<const uint32_t *>(&Bv[u]);
 #pragma unroll
         for (int m = 0; m < 8; ++m)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bf16_to_f64(a[m >> 1], m & 1), bf16_to_f64(bw[m >> 1], m & 1), acc,
-                                                     0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u].get(m), Bv[u].get(m), acc, 0, 0, 0);
       }
     }
+  }
+  if (d % 32 != 0 && part == parts - 1) {  // fp32 layers: the last 4 to 28 elements, 4 at a time, one per lane group
+    for (int j = n_blocks * 32; j < d; j += 4)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Elem<T>::load(h + (size_t)t * d + j + g),
+                                                 (double)Elem<T>::load(w_r + (size_t)e * d + j + g), acc, 0, 0, 0);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[wave][(g + 4 * r) * 16 + i] = acc[r];
@@ -464,10 +481,10 @@ __global__ __launch_bounds__(256) void lists_to_segments_kernel(const int32_t *_
   }
 }
 
-// The fused prologue covers bf16 layers whose M x N table of doubles fits the LDS of one workgroup beside the
+// The fused prologue covers layers whose M x N table of doubles fits the LDS of one workgroup beside the
 // selection scratch, with at most kSelfMaxExperts experts (one thread per shortlist rank in the expert passes).
 bool fused_prologue_ok(const moespec_desc &ds, int M) {
-  if (ds.dtype != MOESPEC_BF16 || ds.n_experts > kSelfMaxExperts || M > kSelfMaxTokens) return false;
+  if (ds.n_experts > kSelfMaxExperts || M > kSelfMaxTokens) return false;
   return prologue_lds(M, ds.n_experts, ds.top_k, ds.n_experts).total <= 160 * 1024;
 }
 
@@ -493,15 +510,20 @@ int logit_slices(const moespec_desc &ds, int M, bool whole_table) {
   return best;
 }
 
-// Whether Eq. (1) runs on the matrix cores and row by row (bf16 layers of up to kSelfMaxExperts experts, any tree).
-bool mfma_route_ok(const moespec_desc &ds) { return ds.dtype == MOESPEC_BF16 && ds.n_experts <= kSelfMaxExperts; }
+// Whether Eq. (1) runs on the matrix cores and row by row (layers of up to kSelfMaxExperts experts, any tree).
+bool mfma_route_ok(const moespec_desc &ds) { return ds.n_experts <= kSelfMaxExperts; }
 
 hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int slices,
                          double *partial, hipStream_t st) {
   dim3 grid(((M + 15) / 16) * ((ds.n_experts + 15) / 16), slices);
-  logits_mfma_kernel<<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const uint16_t *>(h),
-                                                          static_cast<const uint16_t *>(wt.w_router), M, ds.n_experts,
-                                                          ds.d, slices, partial);
+  if (ds.dtype == MOESPEC_BF16)
+    logits_mfma_kernel<uint16_t><<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const uint16_t *>(h),
+                                                                    static_cast<const uint16_t *>(wt.w_router), M,
+                                                                    ds.n_experts, ds.d, slices, partial);
+  else
+    logits_mfma_kernel<float><<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const float *>(h),
+                                                                 static_cast<const float *>(wt.w_router), M,
+                                                                 ds.n_experts, ds.d, slices, partial);
   return hipGetLastError();
 }
 

@@ -1,9 +1,9 @@
 // Stage 1 of Algorithm 1: router projection, softmax over all N experts (Eq. (1)), per-token
 // top-k and mixing weights (Section 2.1).  Every decision in fp64.
 //
-// bf16 layers of up to 256 experts: the projection runs on the fp64 matrix cores (logits_mfma_kernel of prologue.hip)
-// and gate_rows_kernel takes one wave per token.  fp32 layers and more experts: logits_kernel, spread over (token,
-// group of 4 experts) workgroups so that the whole chip takes part, and softmax_topk_kernel, one workgroup per token.
+// Up to 256 experts: the projection runs on the fp64 matrix cores (logits_mfma_kernel of prologue.hip) and
+// gate_rows_kernel takes one wave per token.  More experts: logits_kernel, spread over (token, group of 4 experts)
+// workgroups so that the whole chip takes part, and softmax_topk_kernel, one workgroup per token.
 #include "common.h"
 
 namespace moespec {
