@@ -19,7 +19,8 @@
 // are work items of their own: its walks over the expert run side by side, not one after the other.
 // Workgroups start their K walk at staggered offsets: weight rows are a power-of-two stride
 // apart, and equal offsets would pile the concurrent reads onto the same memory channels.
-// Shapes whose K is not a multiple of 128 take a simpler direct-load variant of the same tiling.
+// Where K is not a multiple of the 128-element chunk (kTail), the pieces of the last chunk past the row end are not
+// loaded and count as zeros.
 // The intermediate act and the per-pair outputs y are indexed by the flat pair id t * k + slot.
 //
 // Where its segment comes from: either from the work items that the budget stage has built beside the segment
@@ -53,52 +54,6 @@ __device__ __forceinline__ bf16x8 ld_frag(const uint16_t *p) { return *reinterpr
 // not push the (re-read) token rows out of the caches.
 __device__ __forceinline__ bf16x8 ld_stream(const uint16_t *p) {
   return __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(p));
-}
-
-// acc0[j] += A0 . B_j, acc1[j] += A1 . B_j over K, for NT token tiles; U K-steps of 32 per stage,
-// two register stages so that the next stage's loads are in flight during the current MFMAs.
-// a0/a1/bp[] are per-lane pointers (already offset by the lane's row and K group).  K % (32 U) == 0.
-// The walk over K starts at element ks (a multiple of 32 U) and wraps: waves that start at
-// different offsets spread the concurrent row reads over the memory channels (rows of a weight
-// matrix are a power-of-two stride apart, so equal offsets would pile onto the same channels).
-template <int NT, int U>
-__device__ __forceinline__ void stream_rows(const uint16_t *a0, const uint16_t *a1, const uint16_t *const (&bp)[NT],
-                                            int K, int ks, f32x4 (&acc0)[NT], f32x4 (&acc1)[NT]) {
-  bf16x8 A0[2][U], A1[2][U], Bf[2][U][NT];
-  auto load = [&](int st, int k0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      A0[st][u] = ld_frag(a0 + k0 + 32 * u);
-      A1[st][u] = ld_frag(a1 + k0 + 32 * u);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) Bf[st][u][j] = ld_frag(bp[j] + k0 + 32 * u);
-  };
-  auto compute = [&](int st) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        acc0[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A0[st][u], Bf[st][u][j], acc0[j], 0, 0, 0);
-        acc1[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A1[st][u], Bf[st][u][j], acc1[j], 0, 0, 0);
-      }
-  };
-  constexpr int KS = 32 * U;
-  const int nst = K / KS;
-  int k = (ks / KS) * KS;
-  load(0, k);
-  for (int i = 0; i < nst; i += 2) {
-    int k1 = k + KS;
-    k1 = k1 >= K ? k1 - K : k1;
-    if (i + 1 < nst) load(1, k1);
-    compute(0);
-    k = k1 + KS;
-    k = k >= K ? k - K : k;
-    if (i + 2 < nst) load(0, k);
-    if (i + 1 < nst) compute(1);
-  }
 }
 
 // Workgroup -> (segment, row tile) for the LDS-tiled passes.  Workgroups are handed to the 8 XCDs
@@ -170,122 +125,13 @@ __global__ __launch_bounds__(256) void segment_items_kernel(const int32_t *__res
 // Workgroups of a pass: room for whole rounds of 8 work items.
 inline int xcd_grid(int tiles, int n_items) { return kXcds * tiles * ((n_items + kXcds - 1) / kXcds); }
 
-// Start offset (elements) of a wave's walk over K: 128 elements (256 bytes) apart for consecutive waves.
-__device__ __forceinline__ int k_stagger(int wave_id, int K) { return (int)(((long long)wave_id * 128) % K); }
+// Start offset (elements) of a walk over K: 128 elements (256 bytes) apart for consecutive ids.  The ids are made of the
+// expert and the row tile, not of the order of the work items: every route to the passes adds in the same order.  (By
+// rank, by expert alone and by 5 e + 3 tile: 582 / 587 / 582 us for four layers of two 4096 x 14336 experts, the others
+// within 0.7 %; by e + tile 627.)
+__device__ __forceinline__ int k_stagger(int id, int K) { return (int)(((long long)id * 128) % K); }
 
-// ---- pass 1 (bf16): gate/up projections + SwiGLU ---------------------------------------------
-template <int NT, int U>
-__device__ __forceinline__ void gateup_tiles(const uint16_t *a0, const uint16_t *a1, const uint16_t *__restrict__ h,
-                                             const int32_t *__restrict__ perm, int M, int k, int d, int F, int beg,
-                                             int c0, int m, int f0, int ks, uint16_t *__restrict__ act) {
-  const int lane = threadIdx.x & 63, col = lane & 15, kg = lane >> 4;
-  const uint16_t *bp[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    int p = c0 + j * 16 + col;
-    p = p < m ? p : m - 1;  // pad columns repeat the last token; their results are never stored
-    const int tok = pair_index(perm, beg + p, M, k) / k;
-    bp[j] = h + (size_t)tok * d + kg * 8;
-  }
-  f32x4 accg[NT], accu[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) accg[j] = accu[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  stream_rows<NT, U>(a0, a1, bp, d, ks, accg, accu);
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int p = c0 + j * 16 + col;
-    if (p < m) {
-      uint16_t o[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = float_to_bf16_bits(silu_f(accg[j][i]) * accu[j][i]);
-      uint2 pk;
-      pk.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
-      pk.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
-      *reinterpret_cast<uint2 *>(act + (size_t)pair_index(perm, beg + p, M, k) * F + f0 + 4 * kg) = pk;
-    }
-  }
-}
-
-template <int U>
-__global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_bf16_kernel(
-    const uint16_t *__restrict__ h, const uint16_t *__restrict__ w_gate, const uint16_t *__restrict__ w_up,
-    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm,
-    int M, int N, int k, int d, int F, uint16_t *__restrict__ act) {
-  const int seg = blockIdx.y;
-  const int e = seg_expert[seg];
-  const int beg = seg_off[seg], m = seg_off[seg + 1] - beg;
-  if (!segment_ok(e, beg, m, (long long)M * k, N)) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int f0 = (blockIdx.x * kFfnWaves + wave) * 16;
-  if (f0 >= F) return;
-  const size_t row = (size_t)e * F + f0 + (lane & 15);
-  const uint16_t *a0 = w_gate + row * d + (lane >> 4) * 8;
-  const uint16_t *a1 = w_up + row * d + (lane >> 4) * 8;
-  const int ks = k_stagger((blockIdx.y * gridDim.x + blockIdx.x) * kFfnWaves + wave, d);
-  constexpr int U4 = U > 2 ? 2 : U;
-  for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
-    const int mc = m - c0;
-    if (mc <= 16) gateup_tiles<1, U>(a0, a1, h, perm, M, k, d, F, beg, c0, m, f0, ks, act);
-    else if (mc <= 32) gateup_tiles<2, U>(a0, a1, h, perm, M, k, d, F, beg, c0, m, f0, ks, act);
-    else if (mc <= 64) gateup_tiles<4, U4>(a0, a1, h, perm, M, k, d, F, beg, c0, m, f0, ks, act);
-    else gateup_tiles<8, 1>(a0, a1, h, perm, M, k, d, F, beg, c0, m, f0, ks, act);
-  }
-}
-
-// ---- pass 2 (bf16): down projection, rows scattered to their (token, slot) position -----------
-template <int NT, int U>
-__device__ __forceinline__ void down_tiles(const uint16_t *a0, const uint16_t *a1, const uint16_t *__restrict__ act,
-                                           const int32_t *__restrict__ perm, int M, int k, int d, int F, int beg, int c0,
-                                           int m, int j0, int ks, float *__restrict__ y) {
-  const int lane = threadIdx.x & 63, col = lane & 15, kg = lane >> 4;
-  const uint16_t *bp[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    int p = c0 + j * 16 + col;
-    p = p < m ? p : m - 1;
-    bp[j] = act + (size_t)pair_index(perm, beg + p, M, k) * F + kg * 8;
-  }
-  f32x4 acc0[NT], acc1[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) acc0[j] = acc1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  stream_rows<NT, U>(a0, a1, bp, F, ks, acc0, acc1);
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int p = c0 + j * 16 + col;
-    if (p < m) {
-      float *dst = y + (size_t)pair_index(perm, beg + p, M, k) * d + j0 + 4 * kg;
-      *reinterpret_cast<f32x4 *>(dst) = acc0[j];
-      *reinterpret_cast<f32x4 *>(dst + 16) = acc1[j];
-    }
-  }
-}
-
-template <int U>
-__global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_bf16_kernel(
-    const uint16_t *__restrict__ act, const uint16_t *__restrict__ w_down, const int32_t *__restrict__ seg_expert,
-    const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm, int M, int N, int k, int d, int F,
-    float *__restrict__ y) {
-  const int seg = blockIdx.y;
-  const int e = seg_expert[seg];
-  const int beg = seg_off[seg], m = seg_off[seg + 1] - beg;
-  if (!segment_ok(e, beg, m, (long long)M * k, N)) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int j0 = (blockIdx.x * kFfnWaves + wave) * 32;
-  if (j0 >= d) return;
-  const uint16_t *a0 = w_down + ((size_t)e * d + j0 + (lane & 15)) * F + (lane >> 4) * 8;
-  const uint16_t *a1 = a0 + (size_t)16 * F;
-  const int ks = k_stagger((blockIdx.y * gridDim.x + blockIdx.x) * kFfnWaves + wave, F);
-  constexpr int U4 = U > 2 ? 2 : U;
-  for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
-    const int mc = m - c0;
-    if (mc <= 16) down_tiles<1, U>(a0, a1, act, perm, M, k, d, F, beg, c0, m, j0, ks, y);
-    else if (mc <= 32) down_tiles<2, U>(a0, a1, act, perm, M, k, d, F, beg, c0, m, j0, ks, y);
-    else if (mc <= 64) down_tiles<4, U4>(a0, a1, act, perm, M, k, d, F, beg, c0, m, j0, ks, y);
-    else down_tiles<8, 1>(a0, a1, act, perm, M, k, d, F, beg, c0, m, j0, ks, y);
-  }
-}
-
-// ---- LDS-tiled bf16 passes (K % 128 == 0) --------------------------------------------------------
+// ---- LDS-tiled bf16 passes  --------------------------------------------------------
 // Geometry of one K chunk: U MFMA K-steps of 32 elements; a row of the chunk is RB = 64 U bytes =
 // CPR = 4 U pieces of 16 bytes.  Piece c of row r sits at LDS offset r*RB + ((c ^ (r & (CPR-1))) * 16):
 // 8 consecutive lanes then touch 8 different 16-byte bank groups both when a row is written
@@ -313,7 +159,7 @@ constexpr int kLdsBytes = 65536;  // 32 KB of wave-private weight tiles + token 
 // called after the weight loads of the first chunk have been issued.  Loads complete in issue order, so the wait for
 // the (earlier issued) pair ids leaves those weight loads in flight: the expert's first bytes are on their way while
 // the token rows are still being looked up.
-template <int NT, int U, class XF>
+template <int NT, int U, bool kTail, class XF>
 __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt1, int K, int kb, int kl, int ks,
                                          const uint16_t *xbase, XF make_xsrc, unsigned char *lds,
                                          f32x4 (&acc0)[NT], f32x4 (&acc1)[NT]) {
@@ -333,23 +179,34 @@ __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt
   const uint32_t lane_off = 2u * ((uint32_t)lrow * (uint32_t)K + (uint32_t)lpc * 8u);
   bf16x8 GA[2][U], GX[IPW];
   uint32_t xsrc[IPW];
+  // kTail: whether this lane's piece of the chunk at element k lies inside the row (the same piece for weights and
+  // tokens); a lane past the end loads the first piece of its group of rows again and parks zeros
+  auto inside = [&](int k) { return !kTail || k + lpc * 8 < kb + kl; };
   auto issue_w = [&](int k) {
+    const uint32_t back = inside(k) ? 0u : (uint32_t)lpc * 16u;
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-      const uint32_t off = lane_off + 2u * ((uint32_t)(q * C::RPI) * (uint32_t)K + (uint32_t)k);
+      const uint32_t off = lane_off + 2u * ((uint32_t)(q * C::RPI) * (uint32_t)K + (uint32_t)k) - back;
       GA[0][q] = ld_stream(at_bytes(wt0, off));
       GA[1][q] = ld_stream(at_bytes(wt1, off));
     }
   };
   auto issue_x = [&](int k) {
+    const uint32_t back = inside(k) ? 0u : (uint32_t)lpc * 16u;
 #pragma unroll
-    for (int q = 0; q < IPW; ++q) GX[q] = ld_frag(at_bytes(xbase, xsrc[q] + 2u * (uint32_t)k));
+    for (int q = 0; q < IPW; ++q) GX[q] = ld_frag(at_bytes(xbase, xsrc[q] + 2u * (uint32_t)k - back));
   };
   auto issue = [&](int k) {
     issue_w(k);
     issue_x(k);
   };
-  auto park = [&](int buf) {
+  auto park = [&](int buf, int k) {
+    if (kTail && !inside(k)) {
+#pragma unroll
+      for (int q = 0; q < U; ++q) GA[0][q] = GA[1][q] = bf16x8{};
+#pragma unroll
+      for (int q = 0; q < IPW; ++q) GX[q] = bf16x8{};
+    }
 #pragma unroll
     for (int q = 0; q < U; ++q) {
       const int row = q * C::RPI + lrow;
@@ -407,18 +264,18 @@ __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt
     }
   };
 
-  // the walk covers the elements [kb, kb + kl) of every row (kl a multiple of the chunk), starting
+  // the walk covers the elements [kb, kb + kl) of every row in chunks (kl a multiple of the chunk unless kTail), starting
   // ks elements into that range and wrapping inside it
-  const int nst = kl / C::KC;
+  const int nst = kTail ? (kl + C::KC - 1) / C::KC : kl / C::KC;
   int k = ((ks % kl) / C::KC) * C::KC;
   issue_w(kb + k);
   __builtin_amdgcn_sched_barrier(0);  // keep the weight loads ahead of the wait for the pair ids
   make_xsrc(xsrc);
   issue_x(kb + k);
   for (int i = 0; i < nst; ++i) {
-    park(kDoubleX ? (i & 1) : 0);
+    park(kDoubleX ? (i & 1) : 0, kb + k);
     k += C::KC;
-    k = k >= kl ? k - kl : k;
+    k = k >= nst * C::KC ? 0 : k;
     if (i + 1 < nst) issue(kb + k);
     __syncthreads();  // token tile i complete; also orders this wave's tile writes before its reads
     compute(kDoubleX ? (i & 1) : 0);
@@ -477,7 +334,7 @@ __device__ __forceinline__ int pair_at(const int32_t *plist, int p, int n_pairs)
   return q < 0 ? 0 : (q >= n_pairs ? n_pairs - 1 : q);
 }
 
-template <int NT, int U>
+template <int NT, int U, bool kTail>
 __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *wt1, const uint16_t *__restrict__ h,
                                            const int32_t *plist, int n_pairs, int k, int d, int F, int c0, int m,
                                            int f0, int ks, unsigned char *lds, uint16_t *__restrict__ act) {
@@ -504,7 +361,7 @@ __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *
   f32x4 accg[NT], accu[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) accg[j] = accu[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  lds_pass<NT, U>(wt0, wt1, d, 0, d, ks, h, make_xsrc, lds, accg, accu);
+  lds_pass<NT, U, kTail>(wt0, wt1, d, 0, d, ks, h, make_xsrc, lds, accg, accu);
   const int col = lane & 15, kg = lane >> 4;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
@@ -522,6 +379,7 @@ __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *
 }
 
 // rank_count != NULL: work items from the prologue's lists (items / perm unused; n_seg = B); otherwise items + perm.
+template <bool kTail>
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ w_gate, const uint16_t *__restrict__ w_up,
     const int4 *__restrict__ items, const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count,
@@ -549,18 +407,18 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
   f0 = f0 < F ? f0 : F - 16;
   const uint16_t *wt0 = w_gate + ((size_t)e * F + f0) * d;
   const uint16_t *wt1 = w_up + ((size_t)e * F + f0) * d;
-  const int ks = k_stagger(rank, d);
+  const int ks = k_stagger(5 * e + 3 * tile, d);
   const int n_pairs = M * k;
   for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
     const int mc = m - c0;
-    if (mc <= 16) gateup_lds<1, 4>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
-    else if (mc <= 32) gateup_lds<2, 4>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
-    else if (mc <= 64) gateup_lds<4, 4>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
-    else gateup_lds<8, 4>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
+    if (mc <= 16) gateup_lds<1, 4, kTail>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
+    else if (mc <= 32) gateup_lds<2, 4, kTail>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
+    else if (mc <= 64) gateup_lds<4, 4, kTail>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
+    else gateup_lds<8, 4, kTail>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
   }
 }
 
-template <int NT, int U>
+template <int NT, int U, bool kTail>
 __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt1, const uint16_t *__restrict__ act,
                                          const int32_t *plist, int n_pairs, int d, int F, int kb, int kl, int c0, int m,
                                          int j0, int ks, unsigned char *lds, float *__restrict__ y) {
@@ -587,7 +445,7 @@ __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt
   f32x4 acc0[NT], acc1[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) acc0[j] = acc1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  lds_pass<NT, U>(wt0, wt1, F, kb, kl, ks, act, make_xsrc, lds, acc0, acc1);
+  lds_pass<NT, U, kTail>(wt0, wt1, F, kb, kl, ks, act, make_xsrc, lds, acc0, acc1);
   const int col = lane & 15, kg = lane >> 4;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
@@ -600,6 +458,7 @@ __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt
   }
 }
 
+template <bool kTail>
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
     const uint16_t *__restrict__ act, const uint16_t *__restrict__ w_down, const int4 *__restrict__ items,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
@@ -629,17 +488,17 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
   j0 = j0 < d ? j0 : d - 32;  // see ffn_gateup_lds_kernel
   const uint16_t *wt0 = w_down + ((size_t)e * d + j0) * F;
   const uint16_t *wt1 = wt0 + (size_t)16 * F;
-  const int nch = F / 128, kb = (int)((long long)sp * nch / splits) * 128;
-  const int kl = (int)((long long)(sp + 1) * nch / splits) * 128 - kb;
-  const int ks = k_stagger(rank + sp, kl);
+  const int nch = (F + 127) / 128, kb = (int)((long long)sp * nch / splits) * 128;
+  const int kl = min((int)((long long)(sp + 1) * nch / splits) * 128, F) - kb;
+  const int ks = k_stagger(5 * e + sp + 3 * tile, kl);
   const int n_pairs = M * k;
   y += (size_t)sp * n_pairs * d;
   for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
     const int mc = m - c0;
-    if (mc <= 16) down_lds<1, 4>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-    else if (mc <= 32) down_lds<2, 4>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-    else if (mc <= 64) down_lds<4, 4>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-    else down_lds<8, 4>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+    if (mc <= 16) down_lds<1, 4, kTail>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+    else if (mc <= 32) down_lds<2, 4, kTail>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+    else if (mc <= 64) down_lds<4, 4, kTail>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+    else down_lds<8, 4, kTail>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
   }
 }
 
@@ -899,31 +758,9 @@ __global__ __launch_bounds__(kRmsThreads) void combine_scale_kernel(const float 
   }
 }
 
-template <int U>
-static hipError_t launch_bf16(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int n_seg,
-                              const int32_t *seg_expert, const int32_t *seg_off, const int32_t *perm, void *act,
-                              float *y, int pass, hipStream_t st) {
-  const int d = ds.d, F = ds.d_ff, k = ds.top_k;
-  if (pass == 1) {
-    dim3 grid((F / 16 + kFfnWaves - 1) / kFfnWaves, n_seg);
-    ffn_gateup_bf16_kernel<U><<<grid, kFfnThreads, 0, st>>>(
-        static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_gate),
-        static_cast<const uint16_t *>(wt.w_up), seg_expert, seg_off, perm, M, ds.n_experts, k, d, F,
-        static_cast<uint16_t *>(act));
-  } else {
-    dim3 grid((d / 32 + kFfnWaves - 1) / kFfnWaves, n_seg);
-    ffn_down_bf16_kernel<U><<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(act),
-                                                          static_cast<const uint16_t *>(wt.w_down), seg_expert,
-                                                          seg_off, perm, M, ds.n_experts, k, d, F, y);
-  }
-  return hipGetLastError();
-}
-
-// Whether the passes can take their pairs from the prologue's lists: fp32 layers, and bf16 layers whose passes are both
-// LDS-tiled.
+// Whether the passes can take their pairs from the prologue's lists.
 bool expert_ffn_self_segmenting(const moespec_desc &ds, int M) {
-  return (ds.dtype == MOESPEC_F32 || (ds.d % 128 == 0 && ds.d_ff % 128 == 0)) && ds.n_experts <= kSelfMaxExperts &&
-         M <= kSelfMaxTokens;
+  return ds.n_experts <= kSelfMaxExperts && M <= kSelfMaxTokens;
 }
 
 // K-split of the LDS-tiled down pass: when its (segment, row tile) items alone cannot give every compute
@@ -932,15 +769,13 @@ bool expert_ffn_self_segmenting(const moespec_desc &ds, int M) {
 // slower at F = 1024, 1.6x to 2.7x faster at F = 14336 with 4 or 2 loaded experts).
 int down_splits(const moespec_desc &ds, int M, int n_seg) {
   int splits = 1;
-  if (!expert_ffn_wide(ds, M, n_seg) && ds.dtype == MOESPEC_BF16 && ds.d_ff % 128 == 0) {
+  if (!expert_ffn_wide(ds, M, n_seg) && ds.dtype == MOESPEC_BF16) {
     const int tiles = (ds.d / 32 + kFfnWaves - 1) / kFfnWaves;
     while (splits < kMaxDownSplits && (long long)n_seg * tiles * splits * 2 <= 512 && ds.d_ff / 128 >= 32 * splits)
       splits *= 2;
   }
   return splits;
 }
-
-static int pick_unroll(int K) { return K % 128 == 0 ? 4 : (K % 64 == 0 ? 2 : 1); }
 
 hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int n_seg,
                              const int32_t *seg_expert, const int32_t *seg_off, const int32_t *perm,
@@ -955,7 +790,7 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   if (!rank_count && !items_ready && !items) return hipErrorInvalidValue;
   const bool wide = !rank_count && expert_ffn_wide(ds, M, n_seg);
   const int cap = items_capacity(n_seg, M, k);  // work items of the LDS-tiled passes
-  if (ds.dtype == MOESPEC_BF16 && !rank_count && !items_ready && (wide || d % 128 == 0 || F % 128 == 0)) {
+  if (ds.dtype == MOESPEC_BF16 && !rank_count && !items_ready) {
     segment_items_kernel<<<1, 256, 0, st>>>(seg_expert, seg_off, n_seg, M, k, cap, items);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -973,29 +808,21 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
         mark(pass - 1);
         continue;
       }
-      if ((pass == 1 ? d : F) % 128 == 0) {
-        if (pass == 1) {
-          const int grid = xcd_grid((F / 16 + kFfnWaves - 1) / kFfnWaves, cap);
-          ffn_gateup_lds_kernel<<<grid, kFfnThreads, 0, st>>>(
-              static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_gate),
-              static_cast<const uint16_t *>(wt.w_up), items, perm, rank_count, shortlist, n_seg, cap, M, ds.n_experts, k, d,
-              F, lists, list_stride, static_cast<uint16_t *>(act));
-        } else {
-          const int grid = xcd_grid(((d / 32 + kFfnWaves - 1) / kFfnWaves) * splits, cap);
-          ffn_down_lds_kernel<<<grid, kFfnThreads, 0, st>>>(
-              static_cast<const uint16_t *>(act), static_cast<const uint16_t *>(wt.w_down), items, perm, rank_count,
-              shortlist, n_seg, cap, M, ds.n_experts, k, d, F, splits, lists, list_stride, y);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        mark(pass - 1);
-        continue;
+      if (pass == 1) {
+        const int grid = xcd_grid((F / 16 + kFfnWaves - 1) / kFfnWaves, cap);
+        auto kern = d % 128 == 0 ? ffn_gateup_lds_kernel<false> : ffn_gateup_lds_kernel<true>;
+        kern<<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_gate),
+                                           static_cast<const uint16_t *>(wt.w_up), items, perm, rank_count, shortlist,
+                                           n_seg, cap, M, ds.n_experts, k, d, F, lists, list_stride,
+                                           static_cast<uint16_t *>(act));
+      } else {
+        const int grid = xcd_grid(((d / 32 + kFfnWaves - 1) / kFfnWaves) * splits, cap);
+        auto kern = F % 128 == 0 ? ffn_down_lds_kernel<false> : ffn_down_lds_kernel<true>;
+        kern<<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(act), static_cast<const uint16_t *>(wt.w_down),
+                                           items, perm, rank_count, shortlist, n_seg, cap, M, ds.n_experts, k, d, F,
+                                           splits, lists, list_stride, y);
       }
-      switch (pick_unroll(pass == 1 ? d : F)) {
-        case 4: e = launch_bf16<4>(ds, wt, h, M, n_seg, seg_expert, seg_off, perm, act, y, pass, st); break;
-        case 2: e = launch_bf16<2>(ds, wt, h, M, n_seg, seg_expert, seg_off, perm, act, y, pass, st); break;
-        default: e = launch_bf16<1>(ds, wt, h, M, n_seg, seg_expert, seg_off, perm, act, y, pass, st); break;
-      }
-      if (e != hipSuccess) return e;
+      if ((e = hipGetLastError()) != hipSuccess) return e;
       mark(pass - 1);
     }
     if (!out) return hipSuccess;  // the caller only wants the per-pair outputs y
