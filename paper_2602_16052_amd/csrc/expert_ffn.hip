@@ -159,18 +159,21 @@ constexpr int kLdsBytes = 65536;  // 32 KB of wave-private weight tiles + token 
 // called after the weight loads of the first chunk have been issued.  Loads complete in issue order, so the wait for
 // the (earlier issued) pair ids leaves those weight loads in flight: the expert's first bytes are on their way while
 // the token rows are still being looked up.
-template <int NT, int U, bool kTail, class XF>
+// kPrivate: the waves of the workgroup walk over different parts of K and share nothing: each has token tiles of its own,
+// and nothing in the walk waits for another wave (the caller adds up the waves' sums).
+template <int NT, int U, bool kTail, bool kPrivate, class XF>
 __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt1, int K, int kb, int kl, int ks,
                                          const uint16_t *xbase, XF make_xsrc, unsigned char *lds,
                                          f32x4 (&acc0)[NT], f32x4 (&acc1)[NT]) {
   using C = Chunk<U>;
-  constexpr int IPW = NT * U / 4;  // token-tile loads per wave per chunk (4 waves share the tile)
+  constexpr int IPW = kPrivate ? NT * U : NT * U / 4;  // token-tile loads per wave per chunk (or 4 waves share the tile)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned char *a_lds = lds + wave * 2 * C::TILE;                 // wave-private: two weight tiles
-  unsigned char *x_lds = lds + kFfnWaves * 2 * C::TILE;            // shared: 2 buffers of NT*16 rows
   constexpr int XBUF = NT * 16 * C::RB;
+  unsigned char *x_lds = lds + kFfnWaves * 2 * C::TILE + (kPrivate ? wave * XBUF : 0);  // shared: 2 buffers of NT*16 rows
+  static_assert(!kPrivate || kFfnWaves * (2 * C::TILE + XBUF) <= kLdsBytes, "private token tiles fit the LDS");
   // two token-tile buffers if they fit beside the weight tiles, else one (and a second barrier per chunk)
-  constexpr bool kDoubleX = kFfnWaves * 2 * C::TILE + 2 * XBUF <= kLdsBytes;
+  constexpr bool kDoubleX = !kPrivate && kFfnWaves * 2 * C::TILE + 2 * XBUF <= kLdsBytes;
 
   // global -> register staging
   // uniform base + 32-bit byte offset per lane (a tile is 16 rows of at most 2^20 elements): the loads need
@@ -215,7 +218,7 @@ __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt
     }
 #pragma unroll
     for (int q = 0; q < IPW; ++q) {
-      const int g = (wave * IPW + q) * 64 + lane;
+      const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
       *reinterpret_cast<bf16x8 *>(x_lds + buf * XBUF + C::swz(g / C::CPR, g % C::CPR)) = GX[q];
     }
   };
@@ -277,9 +280,11 @@ __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt
     k += C::KC;
     k = k >= nst * C::KC ? 0 : k;
     if (i + 1 < nst) issue(kb + k);
-    __syncthreads();  // token tile i complete; also orders this wave's tile writes before its reads
+    if constexpr (kPrivate) wave_lds_sync();
+    else __syncthreads();  // token tile i complete; also orders this wave's tile writes before its reads
     compute(kDoubleX ? (i & 1) : 0);
-    if (!kDoubleX) __syncthreads();  // everybody has read the single token tile before it is overwritten
+    if constexpr (kPrivate) wave_lds_sync();
+    else if (!kDoubleX) __syncthreads();  // everybody has read the single token tile before it is overwritten
   }
   __syncthreads();  // the LDS tiles may be reused by the caller's next pass
 }
@@ -334,17 +339,43 @@ __device__ __forceinline__ int pair_at(const int32_t *plist, int p, int n_pairs)
   return q < 0 ? 0 : (q >= n_pairs ? n_pairs - 1 : q);
 }
 
-template <int NT, int U, bool kTail>
+// The sums of the 4 waves added in wave order; wave j gets the total of token tile j.  Synchronises; the caller may use the
+// LDS again afterwards.
+template <int NT>
+__device__ __forceinline__ void add_waves(unsigned char *lds, f32x4 (&a0)[NT], f32x4 (&a1)[NT]) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  f32x4 *part = reinterpret_cast<f32x4 *>(lds);  // [wave][tile][2][lane]
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    part[((wave * NT + j) * 2 + 0) * 64 + lane] = a0[j];
+    part[((wave * NT + j) * 2 + 1) * 64 + lane] = a1[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+    if (j == wave) {
+      a0[j] = part[(j * 2 + 0) * 64 + lane];
+      a1[j] = part[(j * 2 + 1) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < kFfnWaves; ++w) {
+        a0[j] += part[((w * NT + j) * 2 + 0) * 64 + lane];
+        a1[j] += part[((w * NT + j) * 2 + 1) * 64 + lane];
+      }
+    }
+  __syncthreads();
+}
+
+template <int NT, int U, bool kTail, bool kPrivate>
 __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *wt1, const uint16_t *__restrict__ h,
-                                           const int32_t *plist, int n_pairs, int k, int d, int F, int c0, int m,
-                                           int f0, int ks, unsigned char *lds, uint16_t *__restrict__ act) {
+                                           const int32_t *plist, int n_pairs, int k, int d, int F, int kb, int kl, int c0,
+                                           int m, int f0, int ks, unsigned char *lds, uint16_t *__restrict__ act) {
   using C = Chunk<U>;
-  constexpr int IPW = NT * U / 4;
+  constexpr int IPW = kPrivate ? NT * U : NT * U / 4;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int pair[IPW];  // this lane's pair ids, loaded now and turned into row offsets inside lds_pass
 #pragma unroll
   for (int q = 0; q < IPW; ++q) {
-    const int g = (wave * IPW + q) * 64 + lane;
+    const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
     int p = c0 + g / C::CPR;
     p = p < m ? p : m - 1;  // pad rows repeat the last token; their columns are never stored
     pair[q] = plist[p];
@@ -353,7 +384,7 @@ __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *
   auto make_xsrc = [&](uint32_t (&xsrc)[IPW]) {
 #pragma unroll
     for (int q = 0; q < IPW; ++q) {
-      const int g = (wave * IPW + q) * 64 + lane;
+      const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
       const int pr = pair[q] < 0 ? 0 : (pair[q] >= n_pairs ? n_pairs - 1 : pair[q]);
       xsrc[q] = 2u * ((uint32_t)(pr / k) * (uint32_t)d + (uint32_t)(g % C::CPR) * 8u);
     }
@@ -361,12 +392,13 @@ __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *
   f32x4 accg[NT], accu[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) accg[j] = accu[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  lds_pass<NT, U, kTail>(wt0, wt1, d, 0, d, ks, h, make_xsrc, lds, accg, accu);
+  lds_pass<NT, U, kTail, kPrivate>(wt0, wt1, d, kb, kl, ks, h, make_xsrc, lds, accg, accu);
+  if constexpr (kPrivate) add_waves<NT>(lds, accg, accu);
   const int col = lane & 15, kg = lane >> 4;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int p = c0 + j * 16 + col;
-    if (p < m) {
+    if (p < m && (!kPrivate || j == wave)) {
       uint16_t o[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) o[i] = float_to_bf16_bits(silu_f(accg[j][i]) * accu[j][i]);
@@ -379,7 +411,8 @@ __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *
 }
 
 // rank_count != NULL: work items from the prologue's lists (items / perm unused; n_seg = B); otherwise items + perm.
-template <bool kTail>
+// kPrivate: a workgroup takes 16 gate and the same 16 up rows (down: 32 rows) and its 4 waves a quarter of K each.
+template <bool kTail, bool kPrivate>
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ w_gate, const uint16_t *__restrict__ w_up,
     const int4 *__restrict__ items, const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count,
@@ -387,7 +420,7 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
     const int32_t *__restrict__ lists, int list_stride, uint16_t *__restrict__ act) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
   __shared__ int32_t misc[8];
-  const int tiles = (F / 16 + kFfnWaves - 1) / kFfnWaves;
+  const int tiles = kPrivate ? F / 16 : (F / 16 + kFfnWaves - 1) / kFfnWaves;
   int tile, rank, e, m;
   const int32_t *plist;
   if (rank_count) {
@@ -403,32 +436,45 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // F is a multiple of 32 but a workgroup covers 64 gate rows: the waves of a last, partial workgroup
   // redo rows of the previous tile (same values, same destination) so that every wave reaches the barriers.
-  int f0 = (tile * kFfnWaves + wave) * 16;
+  int f0 = kPrivate ? tile * 16 : (tile * kFfnWaves + wave) * 16;
   f0 = f0 < F ? f0 : F - 16;
   const uint16_t *wt0 = w_gate + ((size_t)e * F + f0) * d;
   const uint16_t *wt1 = w_up + ((size_t)e * F + f0) * d;
-  const int ks = k_stagger(5 * e + 3 * tile, d);
+  int kb = 0, kl = d;
+  if (kPrivate) {
+    const int nch = (d + 127) / 128;
+    kb = wave * nch / kFfnWaves * 128;
+    kl = min((wave + 1) * nch / kFfnWaves * 128, d) - kb;
+  }
+  const int ks = k_stagger(5 * e + 3 * tile, kl);
   const int n_pairs = M * k;
-  for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
-    const int mc = m - c0;
-    if (mc <= 16) gateup_lds<1, 4, kTail>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
-    else if (mc <= 32) gateup_lds<2, 4, kTail>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
-    else if (mc <= 64) gateup_lds<4, 4, kTail>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
-    else gateup_lds<8, 4, kTail>(wt0, wt1, h, plist, n_pairs, k, d, F, c0, m, f0, ks, lds, act);
+  if constexpr (kPrivate) {
+    for (int c0 = 0; c0 < m; c0 += 32) {
+      if (m - c0 <= 16) gateup_lds<1, 4, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
+      else gateup_lds<2, 4, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
+    }
+  } else {
+    for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
+      const int mc = m - c0;
+      if (mc <= 16) gateup_lds<1, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
+      else if (mc <= 32) gateup_lds<2, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
+      else if (mc <= 64) gateup_lds<4, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
+      else gateup_lds<8, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
+    }
   }
 }
 
-template <int NT, int U, bool kTail>
+template <int NT, int U, bool kTail, bool kPrivate>
 __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt1, const uint16_t *__restrict__ act,
                                          const int32_t *plist, int n_pairs, int d, int F, int kb, int kl, int c0, int m,
                                          int j0, int ks, unsigned char *lds, float *__restrict__ y) {
   using C = Chunk<U>;
-  constexpr int IPW = NT * U / 4;
+  constexpr int IPW = kPrivate ? NT * U : NT * U / 4;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int pair[IPW];  // this lane's pair ids, loaded now and turned into row offsets inside lds_pass
 #pragma unroll
   for (int q = 0; q < IPW; ++q) {
-    const int g = (wave * IPW + q) * 64 + lane;
+    const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
     int p = c0 + g / C::CPR;
     p = p < m ? p : m - 1;
     pair[q] = plist[p];
@@ -437,7 +483,7 @@ __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt
   auto make_xsrc = [&](uint32_t (&xsrc)[IPW]) {
 #pragma unroll
     for (int q = 0; q < IPW; ++q) {
-      const int g = (wave * IPW + q) * 64 + lane;
+      const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
       const int pr = pair[q] < 0 ? 0 : (pair[q] >= n_pairs ? n_pairs - 1 : pair[q]);
       xsrc[q] = 2u * ((uint32_t)pr * (uint32_t)F + (uint32_t)(g % C::CPR) * 8u);
     }
@@ -445,12 +491,13 @@ __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt
   f32x4 acc0[NT], acc1[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) acc0[j] = acc1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  lds_pass<NT, U, kTail>(wt0, wt1, F, kb, kl, ks, act, make_xsrc, lds, acc0, acc1);
+  lds_pass<NT, U, kTail, kPrivate>(wt0, wt1, F, kb, kl, ks, act, make_xsrc, lds, acc0, acc1);
+  if constexpr (kPrivate) add_waves<NT>(lds, acc0, acc1);
   const int col = lane & 15, kg = lane >> 4;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int p = c0 + j * 16 + col;
-    if (p < m) {
+    if (p < m && (!kPrivate || j == wave)) {
       float *dst = y + (size_t)pair_at(plist, p, n_pairs) * d + j0 + 4 * kg;
       *reinterpret_cast<f32x4 *>(dst) = acc0[j];
       *reinterpret_cast<f32x4 *>(dst + 16) = acc1[j];
@@ -458,7 +505,7 @@ __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt
   }
 }
 
-template <bool kTail>
+template <bool kTail, bool kPrivate>
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
     const uint16_t *__restrict__ act, const uint16_t *__restrict__ w_down, const int4 *__restrict__ items,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
@@ -468,7 +515,7 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
   __shared__ int32_t misc[8];
   // a work item is (row tile, K split): split sp sums the 128-element chunks [sp n / splits, (sp + 1) n / splits)
   // of F into its own copy of y, which the combine adds up in split order
-  const int tiles = ((d / 32 + kFfnWaves - 1) / kFfnWaves) * splits;
+  const int tiles = kPrivate ? d / 32 : ((d / 32 + kFfnWaves - 1) / kFfnWaves) * splits;  // kPrivate: splits == 1
   int tile, rank, e, m;
   const int32_t *plist;
   if (rank_count) {
@@ -484,21 +531,29 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sp = tile % splits;
   tile /= splits;
-  int j0 = (tile * kFfnWaves + wave) * 32;
+  int j0 = kPrivate ? tile * 32 : (tile * kFfnWaves + wave) * 32;
   j0 = j0 < d ? j0 : d - 32;  // see ffn_gateup_lds_kernel
   const uint16_t *wt0 = w_down + ((size_t)e * d + j0) * F;
   const uint16_t *wt1 = wt0 + (size_t)16 * F;
-  const int nch = (F + 127) / 128, kb = (int)((long long)sp * nch / splits) * 128;
-  const int kl = min((int)((long long)(sp + 1) * nch / splits) * 128, F) - kb;
+  const int part = kPrivate ? wave : sp, parts = kPrivate ? kFfnWaves : splits;
+  const int nch = (F + 127) / 128, kb = (int)((long long)part * nch / parts) * 128;
+  const int kl = min((int)((long long)(part + 1) * nch / parts) * 128, F) - kb;
   const int ks = k_stagger(5 * e + sp + 3 * tile, kl);
   const int n_pairs = M * k;
   y += (size_t)sp * n_pairs * d;
-  for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
-    const int mc = m - c0;
-    if (mc <= 16) down_lds<1, 4, kTail>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-    else if (mc <= 32) down_lds<2, 4, kTail>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-    else if (mc <= 64) down_lds<4, 4, kTail>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-    else down_lds<8, 4, kTail>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+  if constexpr (kPrivate) {
+    for (int c0 = 0; c0 < m; c0 += 32) {
+      if (m - c0 <= 16) down_lds<1, 4, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+      else down_lds<2, 4, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+    }
+  } else {
+    for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
+      const int mc = m - c0;
+      if (mc <= 16) down_lds<1, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+      else if (mc <= 32) down_lds<2, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+      else if (mc <= 64) down_lds<4, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+      else down_lds<8, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
+    }
   }
 }
 
@@ -777,6 +832,17 @@ int down_splits(const moespec_desc &ds, int M, int n_seg) {
   return splits;
 }
 
+// Whether the 4 waves of a workgroup take a quarter of K each instead of a quarter of its rows: the same bytes are in
+// flight, but a walk is a quarter as long and there are four times as many workgroups, for up to 32 pairs at a time.
+// That pays where the workgroups are few: always with one for every fourth compute unit, and up to one for every second
+// if no segment can need a second round of pairs.  Measured per layer, by rows / by K, us (2048 hidden, top-2 to top-8):
+// 4 experts of width 2048, 32 tokens (128 workgroups) 50 / 41; 4 of 1024, 128 tokens (64) 77 / 68; but 8 of 1024, 64 tokens
+// (128) 54 / 60; 2 of 4096, 128 tokens (128) 92 / 104; 15 of 1024, 63 tokens (240) 60 / 81.
+static bool walk_is_cut(int K, int M, int n_seg, int row_tiles, int splits) {
+  const long long wgs = (long long)n_seg * row_tiles;
+  return splits == 1 && K >= 4 * 128 && (wgs <= 64 || (wgs <= 128 && M <= 32));
+}
+
 hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int n_seg,
                              const int32_t *seg_expert, const int32_t *seg_off, const int32_t *perm,
                              const int32_t *tok_ids, const float *tok_w, const void *residual, void *out, void *act,
@@ -808,16 +874,22 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
         mark(pass - 1);
         continue;
       }
+      // with few workgroups a pass takes as long as one walk over K: cut it in four
+      const int K = pass == 1 ? d : F, row_tiles = pass == 1 ? (F / 16 + kFfnWaves - 1) / kFfnWaves
+                                                             : (d / 32 + kFfnWaves - 1) / kFfnWaves * splits;
+      const bool split_k = walk_is_cut(K, M, n_seg, row_tiles, pass == 1 ? 1 : splits), tail = K % 128 != 0;
       if (pass == 1) {
-        const int grid = xcd_grid((F / 16 + kFfnWaves - 1) / kFfnWaves, cap);
-        auto kern = d % 128 == 0 ? ffn_gateup_lds_kernel<false> : ffn_gateup_lds_kernel<true>;
+        const int grid = xcd_grid(split_k ? F / 16 : row_tiles, cap);
+        auto kern = split_k ? (tail ? ffn_gateup_lds_kernel<true, true> : ffn_gateup_lds_kernel<false, true>)
+                            : (tail ? ffn_gateup_lds_kernel<true, false> : ffn_gateup_lds_kernel<false, false>);
         kern<<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_gate),
                                            static_cast<const uint16_t *>(wt.w_up), items, perm, rank_count, shortlist,
                                            n_seg, cap, M, ds.n_experts, k, d, F, lists, list_stride,
                                            static_cast<uint16_t *>(act));
       } else {
-        const int grid = xcd_grid(((d / 32 + kFfnWaves - 1) / kFfnWaves) * splits, cap);
-        auto kern = F % 128 == 0 ? ffn_down_lds_kernel<false> : ffn_down_lds_kernel<true>;
+        const int grid = xcd_grid(split_k ? d / 32 : row_tiles, cap);
+        auto kern = split_k ? (tail ? ffn_down_lds_kernel<true, true> : ffn_down_lds_kernel<false, true>)
+                            : (tail ? ffn_down_lds_kernel<true, false> : ffn_down_lds_kernel<false, false>);
         kern<<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(act), static_cast<const uint16_t *>(wt.w_down),
                                            items, perm, rank_count, shortlist, n_seg, cap, M, ds.n_experts, k, d, F,
                                            splits, lists, list_stride, y);

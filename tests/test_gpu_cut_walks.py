@@ -1,0 +1,47 @@
+"""Expert passes with so few workgroups that the waves of a workgroup share K instead of the rows: K of exactly four chunks,
+chunks that do not divide by four, a tail in the last wave's part, one and two token tiles, more pairs than one round takes,
+either pass alone in that form; and the shapes just beyond the rule."""
+import pytest
+import torch
+
+from oracle import moespec_oracle as O
+from paper_2602_16052_amd import binding as mb
+from paper_2602_16052_amd import workloads as wl
+
+from gpu_common import (assert_out_close, assert_routing_equal, desc_of, oracle_weights, out_to_numpy, to_device,
+                        upload_weights)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,N,k,F,M,B", [(512, 2, 2, 512, 16, 2), (640, 2, 2, 800, 17, 2), (1056, 3, 1, 544, 33, 3),
+                                         (512, 2, 2, 64, 128, 2), (64, 2, 2, 1440, 100, 2), (544, 4, 2, 2048, 32, 4),
+                                         (544, 4, 2, 2048, 33, 4), (2080, 20, 3, 96, 1, 20)])
+def test_cut_walks(d, N, k, F, M, B):
+    print(f"case d={d} N={N} k={k} F={F} M={M} B={B}", flush=True)
+    cfg = wl.small_config("cut", "bf16", d=d, n_experts=N, top_k=k, d_ff=F, M=M, bias_alpha=0.4, seed=d + F + M)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    h_d, W_d, ws = to_device(h), upload_weights(W), mb.alloc_workspace(desc, M)
+    ref = O.layer_forward(wl.as_f32(h), oracle_weights(W), k, cfg.renorm, B, mb.SUBSTITUTE)
+    out, taps = mb.moespec_layer_forward(desc, W_d, h_d, B, mb.SUBSTITUTE, ws, taps=True)
+    staged = mb.moespec_expert_ffn(desc, W_d, h_d, taps["seg_expert"], taps["seg_off"], taps["perm"], taps["tok_ids"],
+                                   taps["tok_w"], ws)
+    torch.cuda.synchronize()
+    assert_routing_equal(taps, ref, B)
+    assert_out_close(out_to_numpy(out), ref["out"], "bf16")
+    assert torch.equal(staged, out)
+
+
+@pytest.mark.parametrize("M,B", [(1, 64), (7, 16), (15, 16), (16, 16)])
+@pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
+def test_fewer_tokens_than_shortlist_ranks(M, B, policy):
+    """The fused prologue then has workgroups without a token, which only build pair lists."""
+    print(f"case M={M} B={B} policy={policy}", flush=True)
+    cfg = wl.small_config("ranks", "bf16", d=128, n_experts=64, top_k=8, d_ff=128, M=M, bias_alpha=0.6, seed=M)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    out, taps = mb.moespec_layer_forward(desc, upload_weights(W), to_device(h), B, policy, mb.alloc_workspace(desc, M),
+                                         taps=True)
+    torch.cuda.synchronize()
+    ref = O.layer_forward(wl.as_f32(h), oracle_weights(W), 8, cfg.renorm, B, policy)
+    assert_routing_equal(taps, ref, B)
+    assert_out_close(out_to_numpy(out), ref["out"], "bf16")
