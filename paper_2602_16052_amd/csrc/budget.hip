@@ -11,8 +11,8 @@
 
 namespace moespec {
 
-// Up to this many tokens every workgroup of budget_kernel adds the rows of the table itself (127 rows of 128 experts:
-// 130 KB from L2, a quarter of a microsecond per 16 KB); above, the row blocks are summed once by a launch of its own.
+// Up to this many tokens every workgroup of budget_kernel adds the rows of the table itself, one round of loads; above, the
+// row blocks are summed once by a launch of its own (4.8 us at 511 and at 2048 tokens).
 constexpr int kDirectScoreRows = 128;
 constexpr int kScoreLoads = 32;  // rows in flight per thread of those sums
 
@@ -78,7 +78,7 @@ __host__ __device__ inline BudgetLds budget_lds(int N, int B, int threads) {
 // What bounds it: the launch, two rounds of cold loads and the row's N / 4 LDS reads; the tokens are independent.
 // The kernel it replaces had one workgroup per token, whose last one to finish grouped the pairs of the whole tree
 // (MI355X: 973 us with the sum of the scores at 2048 tokens x 64 experts, 32 us at 127 x 128, 17 us at 63 x 64; the
-// three kernels here take 24, 17 and 13 us).
+// three kernels here take 22, 17 and 13 us).
 template <int NU>
 __global__ __launch_bounds__(1024) void budget_kernel(
     const double *__restrict__ probs, const double *__restrict__ src, int n_src, int M, int N, int k, int B, int policy,

@@ -44,22 +44,6 @@ __device__ __forceinline__ bool ranks_before(double vj, int j, double vi, int i)
   return vj > vi || (vj == vi && j < i);
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s, kWave);
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s, kWave);
-  return v;
-}
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) v = fmax(v, __shfl_xor(v, s, kWave));
-  return v;
-}
-
 // ---- 16-lane all-reductions through DPP (no LDS, no barrier).  Every lane of a row of 16 ends with the same
 // bits: each step combines a value with its partner's, and the operations used are commutative.
 template <int CTRL>

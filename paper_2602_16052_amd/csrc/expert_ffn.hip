@@ -35,16 +35,11 @@ static_assert(kSelfMaxExperts <= kFfnThreads, "one thread per shortlist rank");
 constexpr int kFfnWaves = kFfnThreads / kWave;
 constexpr int kMaxTiles = 8;  // token tiles of 16 per pass over the weights
 
-// A segment is processed only if it names a real expert and lies inside the pair table; pair
-// indices are clamped into [0, M*k) so that malformed tables cannot address outside the buffers.
+// A segment is processed only if it names a real expert and lies inside the pair table; the passes clamp
+// pair indices into [0, M*k) so that malformed tables cannot address outside the buffers.
 __device__ __forceinline__ bool segment_ok(int e, int beg, int m, long long list_len, int N) {
   return e >= 0 && e < N && m > 0 && beg >= 0 && (long long)beg + m <= list_len;
 }
-__device__ __forceinline__ int pair_index(const int32_t *perm, int pos, int M, int k) {
-  const int q = perm[pos];
-  return q < 0 ? 0 : (q >= M * k ? M * k - 1 : q);
-}
-
 // base + a 32-bit byte offset: with a uniform base the load needs one offset register, not a 64-bit address
 __device__ __forceinline__ const uint16_t *at_bytes(const uint16_t *base, uint32_t bytes) {
   return reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + bytes);

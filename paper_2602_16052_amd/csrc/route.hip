@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kSoftmaxThreads) void softmax_topk_kernel(double *_
 // Q slices of the router projection + bias), top-k by rank counts over the row in LDS.  A lane holds up to NU experts;
 // 16-lane DPP reductions, then two cross-row steps.  partial may be probs (a wave reads its whole row before it writes).
 // Bound by the launch and one round of cold loads up to a few hundred tokens, by the row's N / 4 LDS reads beyond (4096
-// tokens x 64 experts with top-8 and weights: 7.6 us, against 15 us of softmax_topk_kernel).
+// tokens x 64 experts with top-8 and weights: 8.2 us, against 15 us of softmax_topk_kernel).
 template <int Q, int NU, bool kTopK>
 __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *partial, const float *__restrict__ bias,
                                                                  int M, int N, int sigmoid_gate, double *probs, int k,

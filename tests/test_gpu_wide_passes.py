@@ -40,3 +40,31 @@ def test_wide_passes(d, N, k, F, M, B, alpha):
     again = mb.moespec_layer_forward(desc, W_d, h_d, B, mb.SUBSTITUTE, ws)
     torch.cuda.synchronize()
     assert torch.equal(staged, out) and torch.equal(again, out)
+
+
+@pytest.mark.parametrize("dtype,d,F,M,B", [("bf16", 128, 192, 300, 4), ("bf16", 128, 128, 600, 16), ("f32", 68, 36, 40, 6)])
+def test_staged_and_wide_layers_replay_from_a_graph(dtype, d, F, M, B):
+    """Captured once and replayed on other inputs with eager calls in between: every replay equals the eager result."""
+    print(f"case {dtype} d={d} F={F} M={M} B={B}", flush=True)
+    cfg = wl.small_config("graph", dtype, d=d, n_experts=16, top_k=4, d_ff=F, M=M, bias_alpha=0.8)
+    desc, W_d = desc_of(cfg), upload_weights(wl.layer_weights(cfg))
+    ws = mb.alloc_workspace(desc, M)
+    inputs = [to_device(wl.hidden_states(cfg, seed=s)) for s in (0, 1, 2)]
+    eager = [mb.moespec_layer_forward(desc, W_d, h, B, mb.SUBSTITUTE, ws).clone() for h in inputs]
+    h_static, out_static = inputs[0].clone(), torch.empty_like(eager[0])
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        mb.LayerForwardCall(desc, W_d, h_static, B, mb.SUBSTITUTE, ws, out_static, stream=side)()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mb.LayerForwardCall(desc, W_d, h_static, B, mb.SUBSTITUTE, ws, out_static)()
+    for rep in range(3):
+        for h, want in zip(inputs, eager):
+            h_static.copy_(h)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out_static, want), f"replay {rep} differs from the eager call"
+            assert torch.equal(mb.moespec_layer_forward(desc, W_d, h, B, mb.SUBSTITUTE, ws), want)
