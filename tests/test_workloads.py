@@ -115,3 +115,23 @@ def test_tracked_counter_summaries_were_measured_on_the_current_kernel_sources()
         ids = re.findall(r"csrc_sha256_16:\s*([0-9a-f]{16})", open(f).read())
         assert ids and all(i == current for i in ids), (os.path.basename(f), ids, current)
     assert bench.stored_traffic()[0] > 0 and bench.stored_kernel_trace() > 0
+
+
+def test_tracked_bandwidths_and_traffic_ratios_are_possible():
+    """The algorithmic bytes of a gate/up launch are 2 d F weights of 2 bytes per loaded expert; no pass is faster than the
+    8 TB/s of the memory, and a launch cannot fetch less than the weights it needs (1 % for the calibration of the counter)."""
+    import os
+    import re
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    text = open(os.path.join(root, "profiles", "bench_other_workloads_kernel_trace_and_traffic.md")).read()
+    sections = re.split(r"^## ", text, flags=re.M)[1:]
+    assert len(sections) >= 5
+    for s in sections:
+        name = s.split(",")[0]
+        d, F = (int(re.search(rf"\b{key}=(\d+)", s).group(1)) for key in ("d", "F"))
+        m = re.search(r"fetched ([\d.]+) MB per launch against ([\d.]+) MB algorithmic \(([\d.]+) loaded experts\): "
+                      r"ratio ([\d.]+); .* = (\d+) GB/s \(([\d.]+) of peak\), down pass (\d+) GB/s", s)
+        fetched, algorithmic, loaded, ratio, gateup, share, down = (float(x) for x in m.groups())
+        assert abs(algorithmic - loaded * 4 * d * F / 1e6) < 0.001 * algorithmic + 0.1, (name, algorithmic, loaded)
+        assert abs(ratio - fetched / algorithmic) < 0.002 and ratio > 0.99, (name, ratio)
+        assert gateup < 8000 and down < 8000 and abs(share - gateup / 8000) < 0.001, (name, gateup, down, share)
