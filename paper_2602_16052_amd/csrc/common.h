@@ -73,13 +73,13 @@ __device__ __forceinline__ int row16_sum(int v) {
 }
 
 // exp(x) for x <= 0 (the max-subtracted argument of a softmax): x = n ln 2 + r with |r| <= ln 2 / 2, the Taylor
-// polynomial of degree 12 in r (truncation error below 2e-16 relative) and a scaling by 2^n.  Every workgroup of
-// the kernel below evaluates the whole table, so the two dozen instructions of this form matter; arguments
-// below -800 give 0, NaN gives NaN further on (0 * inf in the normalisation).
+// polynomial of degree 12 in r (truncation error below 2.4e-16 relative) and a scaling by 2^n.  Every workgroup of
+// route_budget_kernel evaluates the whole table, so the two dozen instructions of this form matter.  Arguments below -800
+// give 0; a NaN stays NaN and so makes its whole row NaN through the normalisation.
 __device__ __forceinline__ double exp_nonpos(double x) {
-  x = fmax(x, -800.0);
-  const double n = rint(x * 1.4426950408889634);
-  double r = fma(n, -6.93147180369123816490e-01, x);
+  const double c = fmax(x, -800.0);  // drops a NaN: put back at the end
+  const double n = rint(c * 1.4426950408889634);
+  double r = fma(n, -6.93147180369123816490e-01, c);
   r = fma(n, -1.90821492927058770002e-10, r);
   double p = 1.0 / 479001600.0;
   p = fma(p, r, 1.0 / 39916800.0);
@@ -94,7 +94,7 @@ __device__ __forceinline__ double exp_nonpos(double x) {
   p = fma(p, r, 0.5);
   p = fma(p, r, 1.0);
   p = fma(p, r, 1.0);
-  return ldexp(p, (int)n);
+  return x != x ? x : ldexp(p, (int)n);
 }
 
 // x = row / sqrt(mean of squares) in fp32 for one row held by a workgroup of kRmsThreads threads: thread i holds the

@@ -58,3 +58,37 @@ def test_underflowing_softmax_keeps_parity(dtype, d, N, k, F, M, gate):
         assert seen_zero, "the case was meant to underflow"
     if gate == "softmax" and cfg.renorm:
         assert seen_nan, "the case was meant to reach a zero-mass substitution set"
+
+
+@pytest.mark.parametrize("dtype,N,M,gate", [("bf16", 64, 7, "softmax"), ("bf16", 64, 1030, "softmax"), ("f32", 40, 33, "softmax"),
+                                            ("f32", 250, 9, "softmax"), ("bf16", 257, 5, "softmax"), ("bf16", 40, 20, "sigmoid")])
+def test_one_nan_logit_is_not_swallowed(dtype, N, M, gate):
+    """A NaN in one expert's router bias (one in a router row: every token) makes the softmax of every token NaN, whatever
+    kernel evaluates it; with the sigmoid gate it is that expert's score alone.  An expert masked with -inf gets 0."""
+    print(f"case {dtype} N={N} M={M} {gate}", flush=True)
+    cfg = wl.small_config("nan_bias", dtype, d=64, n_experts=N, top_k=3, d_ff=32, M=M, seed=M, gate=gate)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    W["b_router"][1] = -np.inf
+    h_d, ws = to_device(h), mb.alloc_workspace(desc, M)
+    W_o = oracle_weights(W)
+    want, ids, _ = O.route(wl.as_f32(h), W_o["w_router"], W_o["b_router"], 3, cfg.renorm, gate)
+    assert np.all(want[:, 1] == 0.0)
+    masked = mb.moespec_route(desc, upload_weights(W), h_d, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(masked["probs"].cpu().numpy(), want, rtol=1e-11, atol=1e-300)
+    assert np.array_equal(masked["topk_ids"].cpu().numpy(), ids)
+    bad = N // 2
+    W_nan = dict(W, b_router=W["b_router"].copy())
+    W_nan["b_router"][bad] = np.nan
+    W_row = dict(W, w_router=W["w_router"].copy())
+    W_row["w_router"][bad, 5] = 0x7FC0 if dtype == "bf16" else np.nan
+    for W_bad in (W_nan, W_row):
+        W_d = upload_weights(W_bad)
+        r = mb.moespec_route(desc, W_d, h_d, ws)
+        _, taps = mb.moespec_layer_forward(desc, W_d, h_d, N, mb.TRUNCATE, ws, taps=True)
+        torch.cuda.synchronize()
+        for g in (r["probs"].cpu().numpy(), taps["probs"].cpu().numpy()):
+            if gate == "softmax":
+                assert np.all(np.isnan(g))
+            else:
+                assert np.all(np.isnan(g[:, bad])) and np.all(np.isfinite(np.delete(g, bad, axis=1)))
