@@ -127,7 +127,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
     red[tid] = a;
     __syncthreads();
     if (tid < (int)L.row_stride) {
-      double sum = tid < N ? red[tid] : -1.0;
+      double sum = tid < N ? red[tid] : kNoRival;
       for (int q = 1; tid < N && q < parts; ++q) sum += red[q * np2 + tid];
       s[tid] = sum;
     }
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
     wave_lds_sync();  // the previous token's reads are done
 #pragma unroll
     for (int u = 0; u < NU; ++u)
-      if (lane + kWave * u < (int)L.row_stride) row[lane + kWave * u] = member[u] ? v[u] : -1.0;  // -1 ranks behind all
+      if (lane + kWave * u < (int)L.row_stride) row[lane + kWave * u] = member[u] ? v[u] : kNoRival;
     sel[lane] = -1;  // stays -1 where an external shortlist names fewer than k experts or a NaN leaves a slot unclaimed
     wave_lds_sync();
     int c[NU];

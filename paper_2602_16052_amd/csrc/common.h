@@ -125,8 +125,12 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Ranks before nothing: every comparison with it is false, whatever the other value (also an infinity or a log-probability).
+constexpr double kNoRival = __builtin_nan("");
+
 // c[u] += number of the values row[j0 .. j1) that go before candidate lane + 64 u with value v[u] in a ranking by (value
-// descending, index ascending).  j0 and j1 are multiples of 4; row is padded with values that rank behind everything.
+// descending, index ascending).  j0 is a multiple of 4; row is padded to a multiple of 4 with kNoRival,
+// which also stands for the entries that are no rivals.
 // Four values per step, the same address in every lane (an LDS broadcast).  Against a rival of another block of 64
 // experts the tie rule is the same for all lanes (>= or >): one comparison and one add with carry per rival.
 template <int NU>

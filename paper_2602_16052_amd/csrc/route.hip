@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       c[u] = 0;
-      row[lane + kWave * u] = lane + kWave * u < N ? val[u] : -1.0;
+      row[lane + kWave * u] = lane + kWave * u < N ? val[u] : kNoRival;
     }
     sel[lane] = -1;  // stays -1 where a NaN leaves a slot unclaimed
     wave_lds_sync();

@@ -39,3 +39,32 @@ def test_budget_stage_edges(M, N, k, B, policy):
     assert int(got["n_loaded"][0]) == int(np.count_nonzero(np.diff(ref["seg_off"])))
     # fp32 storage of an fp64 quotient: half an ulp
     np.testing.assert_allclose(got["tok_w"], ref["tok_w"], rtol=2.0 ** -24, atol=0)
+
+
+@pytest.mark.parametrize("M,N,k,B", [(5, 6, 2, 3), (63, 64, 8, 20), (130, 65, 3, 7), (40, 130, 6, 40), (300, 257, 5, 90),
+                                     (9, 1000, 17, 130)])
+@pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
+def test_scores_of_any_size_rank_the_same(M, N, k, B, policy):
+    """Log-probabilities or raw scores instead of probabilities: values far below zero, infinities of either sign and the
+    lowest double, in which nothing that pads a row or marks an expert outside the shortlist may take part."""
+    print(f"case M={M} N={N} k={k} B={B} policy={policy}", flush=True)
+    r = np.random.default_rng(M + N)
+    g = r.integers(-(1 << 15), 1 << 12, size=(M, N)).astype(np.float64) / (1 << 12)
+    g[:, r.permutation(N)[: N // 3]] -= 64.0
+    g[r.integers(0, M, M), r.integers(0, N - 1, M)] = -np.inf
+    g[r.integers(0, M, M // 2 + 1), r.integers(0, N - 1, M // 2 + 1)] = np.finfo(np.float64).min
+    g[r.integers(0, M), N - 1] = np.inf
+    desc = mb.LayerDesc(32, N, k, 32, mb.BF16, False)
+    b = mb.moespec_budget(desc, torch.from_numpy(g).cuda(), B, policy, mb.alloc_workspace(desc, M))
+    torch.cuda.synchronize()
+    ids = np.array([O.top_k(row, k) for row in g], dtype=np.int32)
+    w = np.array([O.mixing_weights(row, i, False) for row, i in zip(g, ids)])
+    with np.errstate(over="ignore"):
+        ref = O.budget(g, ids, w, B, policy, k, False)
+        got = {key: val.cpu().numpy() for key, val in b.items()}
+        assert np.array_equal(got["scores"], ref["scores"])
+        assert np.array_equal(got["budget_ids"], ref["S"])
+        assert np.array_equal(got["tok_ids"], ref["tok_ids"])
+        assert np.array_equal(got["seg_expert"], ref["seg_expert"])
+        assert np.array_equal(got["seg_off"], ref["seg_off"])
+        assert np.array_equal(got["tok_w"], ref["tok_w"].astype(np.float32))
