@@ -6,6 +6,7 @@
 // Three launches, none of which has a workgroup that does the whole tree's work by itself:
 //   score_parts_kernel   column sums of blocks of rows (large trees only; the others add the rows in the next launch)
 //   budget_kernel        one WAVE per token: every workgroup adds the partial sums and ranks the experts itself
+//                        (above 256 experts one WORKGROUP per token: budget_many_kernel)
 //   group_pairs_kernel   one workgroup per shortlisted expert: its pairs, its offset, its work items
 #include "common.h"
 
@@ -50,7 +51,8 @@ inline int budget_threads(int N) { return N <= 64 ? 256 : N <= 128 ? 512 : 1024;
 struct BudgetLds {
   size_t s, red, rows, row_stride, S, rank, sel, inS, total;
 };
-__host__ __device__ inline BudgetLds budget_lds(int N, int B, int threads) {
+// tokens: how many the workgroup has at a time
+__host__ __device__ inline BudgetLds budget_lds(int N, int B, int threads, int tokens) {
   BudgetLds L;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -61,20 +63,74 @@ __host__ __device__ inline BudgetLds budget_lds(int N, int B, int threads) {
   L.row_stride = (size_t)((N + 3) & ~3);
   L.s = take(sizeof(double) * L.row_stride);
   L.red = take(sizeof(double) * threads);
-  L.rows = take(sizeof(double) * L.row_stride * (threads / kWave));
+  L.rows = take(sizeof(double) * L.row_stride * tokens);
   L.S = take(sizeof(int32_t) * B);
   L.rank = take(sizeof(int32_t) * N);
-  L.sel = take(sizeof(int32_t) * kWave * (threads / kWave));
+  L.sel = take(sizeof(int32_t) * kWave * tokens);
   L.inS = take((size_t)N);
   L.total = off;
   return L;
+}
+
+// s[i] = sum of column i of src [n_src, N], i < N <= nt; kNoRival up to row_stride.  The threads with the same index modulo
+// a power of two >= N share a column, each a contiguous run of rows.  Called by the whole workgroup (it synchronises once;
+// the caller does before it reads s).
+__device__ __forceinline__ void tree_scores(const double *__restrict__ src, int n_src, int N, int row_stride, double *red,
+                                            double *s) {
+  const int nt = blockDim.x, tid = threadIdx.x;
+  int np2 = 1, np2_log = 0;
+  while (np2 < N) np2 <<= 1, ++np2_log;
+  const int parts = nt >> np2_log > 0 ? nt >> np2_log : 1, per = (n_src + parts - 1) / parts;
+  const int i = tid & (np2 - 1), p = tid >> np2_log;
+  double a = 0.0;
+  if (i < N) {
+    const int r1 = min(n_src, (p + 1) * per);
+    for (int r = p * per; r < r1; r += kScoreLoads) {  // the loads of a block go out together: one memory latency
+      double x[kScoreLoads];
+#pragma unroll
+      for (int u = 0; u < kScoreLoads; ++u) x[u] = r + u < r1 ? src[(size_t)(r + u) * N + i] : 0.0;
+#pragma unroll
+      for (int u = 0; u < kScoreLoads; ++u) a += x[u];
+    }
+  }
+  red[tid] = a;
+  __syncthreads();
+  if (tid < row_stride) {
+    double sum = tid < N ? red[tid] : kNoRival;
+    for (int q = 1; tid < N && q < parts; ++q) sum += red[q * np2 + tid];
+    s[tid] = sum;
+  }
+}
+
+// The copies of one workgroup for the caller: scores, the shortlist in rank order and in ascending id.  Every wave builds
+// the membership mask of all experts, 64 at a time; the position of an expert among the shortlisted ones is a population
+// count.
+__device__ __forceinline__ void publish_shortlist(int N, int B, const uint8_t *inS, const int32_t *S, const double *s,
+                                                  double *__restrict__ scores, int32_t *__restrict__ seg_expert,
+                                                  int32_t *__restrict__ budget_ids) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int n_member = 0;  // in the end < B only if an external shortlist repeats or misnames an expert
+  for (int i0 = 0; i0 < N; i0 += kWave) {
+    const int i = i0 + lane;
+    const bool in = i < N && inS[i] != 0;
+    const unsigned long long mask = __ballot(in);
+    if (wave == 0) {
+      if (scores && i < N) scores[i] = s[i];
+      if (in) seg_expert[n_member + __popcll(mask & ((1ull << lane) - 1ull))] = i;
+    }
+    n_member += __popcll(mask);
+  }
+  for (int r = tid; r < B; r += blockDim.x) {
+    if (r >= n_member) seg_expert[r] = -1;
+    budget_ids[r] = S[r];
+  }
 }
 
 // One wave per tree token.  src holds n_src rows of N values whose column sums are the scores of Eq. (5): the
 // probabilities themselves or the sums of row blocks.  Every workgroup recomputes the (tiny) scores and shortlist so
 // that no grid-wide synchronisation is needed; workgroup 0 also writes them out.  NU = candidates per lane.
 // A token's selection is a rank count: lane i compares its candidates with the whole row, read from LDS four values at
-// a time (the same address in every lane: a broadcast).  k <= 64, N <= 64 NU.
+// a time (the same address in every lane: a broadcast).  k <= 64, N <= 64 NU, NU <= 4.
 // What bounds it: the launch, two rounds of cold loads and the row's N / 4 LDS reads; the tokens are independent.
 // The kernel it replaces had one workgroup per token, whose last one to finish grouped the pairs of the whole tree
 // (MI355X: 973 us with the sum of the scores at 2048 tokens x 64 experts, 32 us at 127 x 128, 17 us at 63 x 64; the
@@ -87,7 +143,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
     float *__restrict__ tok_w) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int nt = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const BudgetLds L = budget_lds(N, B, nt);
+  const BudgetLds L = budget_lds(N, B, nt, nt / kWave);
   double *s = reinterpret_cast<double *>(smem + L.s);      // [N] aggregate scores
   double *red = reinterpret_cast<double *>(smem + L.red);  // [threads] partial column sums
   double *row = reinterpret_cast<double *>(smem + L.rows) + wave * L.row_stride;  // this wave's token
@@ -108,29 +164,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
 
   for (int i = tid; i < N; i += nt) inS[i] = 0;
   if (ext_shortlist == nullptr || scores != nullptr) {
-    // Eq. (5).  The threads with the same index modulo a power of two >= N share a column, each a contiguous run of rows.
-    int np2 = 1, np2_log = 0;
-    while (np2 < N) np2 <<= 1, ++np2_log;
-    const int parts = nt >> np2_log > 0 ? nt >> np2_log : 1, per = (n_src + parts - 1) / parts;
-    const int i = tid & (np2 - 1), p = tid >> np2_log;
-    double a = 0.0;
-    if (i < N) {
-      const int r1 = min(n_src, (p + 1) * per);
-      for (int r = p * per; r < r1; r += kScoreLoads) {  // the loads of a block go out together: one memory latency
-        double x[kScoreLoads];
-#pragma unroll
-        for (int u = 0; u < kScoreLoads; ++u) x[u] = r + u < r1 ? src[(size_t)(r + u) * N + i] : 0.0;
-#pragma unroll
-        for (int u = 0; u < kScoreLoads; ++u) a += x[u];
-      }
-    }
-    red[tid] = a;
-    __syncthreads();
-    if (tid < (int)L.row_stride) {
-      double sum = tid < N ? red[tid] : kNoRival;
-      for (int q = 1; tid < N && q < parts; ++q) sum += red[q * np2 + tid];
-      s[tid] = sum;
-    }
+    tree_scores(src, n_src, N, (int)L.row_stride, red, s);
   }
   for (int i = tid; i < N; i += nt) rank[i] = 0;
   for (int r = tid; r < B; r += nt) S[r] = -1;  // stays -1 where NaN scores leave a place of the shortlist unclaimed
@@ -146,7 +180,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
       sv[u] = lane + kWave * u < N ? s[lane + kWave * u] : 0.0;
     }
     const int quads = (int)L.row_stride / 4, n_w = nt / kWave;
-    rank_counts<NU>(s, quads * wave / n_w * 4, quads * (wave + 1) / n_w * 4, lane, sv, c);
+    rank_counts<NU>(s, quads * wave / n_w * 4, quads * (wave + 1) / n_w * 4, lane, 0, sv, c);
 #pragma unroll
     for (int u = 0; u < NU; ++u)
       if (lane + kWave * u < N && c[u]) atomicAdd(&rank[lane + kWave * u], c[u]);
@@ -162,23 +196,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
   __syncthreads();
 
   if (blockIdx.x == 0) {
-    // every wave builds the membership mask of all experts, 64 at a time; the position of an expert among the
-    // shortlisted ones in ascending id is a population count
-    int n_member = 0;  // in the end < B only if an external shortlist repeats or misnames an expert
-    for (int i0 = 0; i0 < N; i0 += kWave) {
-      const int i = i0 + lane;
-      const bool in = i < N && inS[i] != 0;
-      const unsigned long long mask = __ballot(in);
-      if (wave == 0) {
-        if (scores && i < N) scores[i] = s[i];
-        if (in) seg_expert[n_member + __popcll(mask & ((1ull << lane) - 1ull))] = i;
-      }
-      n_member += __popcll(mask);
-    }
-    for (int r = tid; r < B; r += nt) {
-      if (r >= n_member) seg_expert[r] = -1;
-      budget_ids[r] = S[r];
-    }
+    publish_shortlist(N, B, inS, S, s, scores, seg_expert, budget_ids);
   }
 
   const bool truncate = policy == MOESPEC_TRUNCATE;
@@ -195,7 +213,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
     int c[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) c[u] = 0;
-    rank_counts<NU>(row, 0, N, lane, v, c);
+    rank_counts<NU>(row, 0, N, lane, 0, v, c);
 #pragma unroll
     for (int u = 0; u < NU; ++u)
       if (member[u] && c[u] < k) sel[c[u]] = lane + kWave * u;
@@ -210,6 +228,84 @@ __global__ __launch_bounds__(1024) void budget_kernel(
       tok_w[(size_t)t * k + lane] = (float)w;
     }
     load_row(t + n_waves);
+  }
+}
+
+// More than 256 experts (N <= 1024 = blockDim.x): one workgroup per token.  A wave counts one block of 64 candidates
+// against its share of the rivals, and the shares add up through integer LDS atomics, for the shortlist as for a token.
+// Bound by the N^2 / 1024 comparisons per thread, once for the shortlist and once per token.  One wave per token, as above,
+// would hold 16 candidates per lane: its registers spill, and the stage took 405 us for 63 tokens x 300 experts (680 for
+// 512) against 20 us (25) this way.
+__device__ __forceinline__ void rank_in_workgroup(const double *row, int N, int32_t *rank) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int blocks = (N + kWave - 1) / kWave, parts = (int)(blockDim.x >> 6) / blocks;
+  const int block = wave % blocks, part = wave / blocks, quads = (N + 3) / 4, i = block * kWave + lane;
+  if (part >= parts) return;
+  const double v[1] = {i < N ? row[i] : 0.0};
+  int c[1] = {0};
+  rank_counts<1>(row, quads * part / parts * 4, quads * (part + 1) / parts * 4, lane, block, v, c);
+  if (i < N && c[0]) atomicAdd(&rank[i], c[0]);
+}
+
+__global__ __launch_bounds__(1024) void budget_many_kernel(
+    const double *__restrict__ probs, const double *__restrict__ src, int n_src, int M, int N, int k, int B, int policy,
+    int renorm, const int32_t *__restrict__ ext_shortlist, double *__restrict__ scores,
+    int32_t *__restrict__ budget_ids, int32_t *__restrict__ seg_expert, int32_t *__restrict__ tok_ids,
+    float *__restrict__ tok_w) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int nt = blockDim.x, tid = threadIdx.x;
+  const BudgetLds L = budget_lds(N, B, nt, 1);
+  double *s = reinterpret_cast<double *>(smem + L.s);
+  double *red = reinterpret_cast<double *>(smem + L.red);
+  double *row = reinterpret_cast<double *>(smem + L.rows);
+  int32_t *S = reinterpret_cast<int32_t *>(smem + L.S);
+  int32_t *rank = reinterpret_cast<int32_t *>(smem + L.rank);
+  int32_t *sel = reinterpret_cast<int32_t *>(smem + L.sel);
+  uint8_t *inS = smem + L.inS;
+
+  int t = blockIdx.x;
+  double v = tid < N ? probs[(size_t)t * N + tid] : 0.0;  // grid <= M; requested before the shortlist is known
+  for (int i = tid; i < N; i += nt) {
+    inS[i] = 0;
+    rank[i] = 0;
+  }
+  for (int r = tid; r < B; r += nt) S[r] = -1;  // see budget_kernel
+  if (ext_shortlist == nullptr || scores != nullptr) tree_scores(src, n_src, N, (int)L.row_stride, red, s);
+  __syncthreads();
+  if (ext_shortlist == nullptr) {
+    rank_in_workgroup(s, N, rank);
+    __syncthreads();
+    if (tid < N && rank[tid] < B) S[rank[tid]] = tid;
+  } else {
+    for (int r = tid; r < B; r += nt) S[r] = ext_shortlist[r];
+  }
+  __syncthreads();
+  for (int r = tid; r < B; r += nt)
+    if ((uint32_t)S[r] < (uint32_t)N) inS[S[r]] = 1;
+  __syncthreads();
+  if (blockIdx.x == 0) publish_shortlist(N, B, inS, S, s, scores, seg_expert, budget_ids);
+
+  const bool truncate = policy == MOESPEC_TRUNCATE, member = tid < N && (truncate || inS[tid] != 0);
+  for (; t < M; t += gridDim.x) {
+    if (tid < (int)L.row_stride) row[tid] = member ? v : kNoRival;
+    if (tid < N) rank[tid] = 0;
+    if (tid < kWave) sel[tid] = -1;
+    __syncthreads();
+    rank_in_workgroup(row, N, rank);
+    __syncthreads();
+    if (member && rank[tid] < k) sel[rank[tid]] = tid;
+    __syncthreads();
+    if (tid < k) {
+      double denom = 0.0;  // over the selected set in slot order, before any slot is dropped (Eq. (7))
+      for (int j = 0; j < k; ++j) denom += sel[j] >= 0 ? row[sel[j]] : 0.0;
+      const int e = sel[tid];
+      const bool keep = e >= 0 && inS[e] != 0;
+      const double w = keep ? (renorm ? row[e] / denom : row[e]) : 0.0;
+      tok_ids[(size_t)t * k + tid] = keep ? e : -1;
+      tok_w[(size_t)t * k + tid] = (float)w;
+    }
+    if (tid < N && t + (int)gridDim.x < M) v = probs[(size_t)(t + gridDim.x) * N + tid];
+    __syncthreads();  // the row and the selection have been read
   }
 }
 
@@ -312,22 +408,18 @@ hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int
     if ((e = launch_score_parts(probs, M, N, score_parts, &n_src, st)) != hipSuccess) return e;
     src = score_parts;
   }
-  const int nt = budget_threads(N), per_wg = nt / kWave;
   // every workgroup ranks the experts again: no more of them than two per compute unit
-  const int want = (M + per_wg - 1) / per_wg, grid = want < 512 ? want : 512;
-  const size_t smem = budget_lds(N, B, nt).total;
+  const bool many = N > 4 * kWave;
+  const int nt = budget_threads(N), tokens = many ? 1 : nt / kWave;
+  const int want = (M + tokens - 1) / tokens, grid = want < 512 ? want : 512;
+  const size_t smem = budget_lds(N, B, nt, tokens).total;
   auto run = [&](auto kern) -> hipError_t {
-    if (smem > 64 * 1024) {
-      hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (err != hipSuccess) return err;
-    }
     kern<<<grid, nt, smem, st>>>(probs, src, n_src, M, N, k, B, policy, ds.renorm, ext_shortlist, scores, budget_ids,
                                  seg_expert, tok_ids, tok_w);
     return hipGetLastError();
   };
-  e = N <= 64 ? run(budget_kernel<1>) : N <= 128 ? run(budget_kernel<2>) : N <= 256 ? run(budget_kernel<4>)
-                                                                                    : run(budget_kernel<16>);
+  e = N <= 64 ? run(budget_kernel<1>) : N <= 128 ? run(budget_kernel<2>) : !many ? run(budget_kernel<4>)
+                                                                                 : run(budget_many_kernel);
   if (e != hipSuccess) return e;
   group_pairs_kernel<<<B, (int64_t)M * k <= 2048 ? 256 : 1024, 0, st>>>(tok_ids, M, N, k, B, seg_expert, seg_off, perm,
                                                                        n_loaded, items);

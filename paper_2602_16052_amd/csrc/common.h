@@ -128,20 +128,20 @@ __device__ __forceinline__ void wave_lds_sync() {
 // Ranks before nothing: every comparison with it is false, whatever the other value (also an infinity or a log-probability).
 constexpr double kNoRival = __builtin_nan("");
 
-// c[u] += number of the values row[j0 .. j1) that go before candidate lane + 64 u with value v[u] in a ranking by (value
-// descending, index ascending).  j0 is a multiple of 4; row is padded to a multiple of 4 with kNoRival,
-// which also stands for the entries that are no rivals.
+// c[u] += number of the values row[j0 .. j1) that go before candidate lane + 64 (first + u) with value v[u] in a ranking by
+// (value descending, index ascending).  j0 is a multiple of 4; row is padded to a multiple of 4 with kNoRival, which also
+// stands for the entries that are no rivals.  first is uniform in the wave.
 // Four values per step, the same address in every lane (an LDS broadcast).  Against a rival of another block of 64
 // experts the tie rule is the same for all lanes (>= or >): one comparison and one add with carry per rival.
 template <int NU>
-__device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, int lane, const double (&v)[NU],
+__device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, int lane, int first, const double (&v)[NU],
                                             int (&c)[NU]) {
-  constexpr int kBlocksUnrolled = NU <= 4 ? NU : 1;
-#pragma unroll kBlocksUnrolled
-  for (int b = 0; b < NU; ++b) {
-    const int hi = min(j1, kWave * (b + 1));
+  // rivals in front of all candidates' blocks (b = -1), in block first + b, behind all (b = NU)
+#pragma unroll
+  for (int b = -1; b <= NU; ++b) {
+    const int lo = b < 0 ? j0 : max(j0, kWave * (first + b)), hi = b == NU ? j1 : min(j1, kWave * (first + b + 1));
 #pragma unroll 2
-    for (int j = max(j0, kWave * b); j < hi; j += 4) {
+    for (int j = lo; j < hi; j += 4) {
       double r[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) r[q] = row[j + q];
@@ -150,7 +150,7 @@ __device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, i
 #pragma unroll
         for (int u = 0; u < NU; ++u)
           c[u] += u > b ? (int)(r[q] >= v[u]) : u < b ? (int)(r[q] > v[u])
-                        : (int)((r[q] > v[u]) | ((r[q] == v[u]) & (j + q < lane + kWave * u)));
+                        : (int)((r[q] > v[u]) | ((r[q] == v[u]) & (j + q < lane + kWave * (first + u))));
     }
   }
 }

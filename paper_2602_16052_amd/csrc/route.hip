@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
     }
     sel[lane] = -1;  // stays -1 where a NaN leaves a slot unclaimed
     wave_lds_sync();
-    rank_counts<NU>(row, 0, N, lane, val, c);
+    rank_counts<NU>(row, 0, N, lane, 0, val, c);
 #pragma unroll
     for (int u = 0; u < NU; ++u)
       if (lane + kWave * u < N && c[u] < k) sel[c[u]] = lane + kWave * u;
