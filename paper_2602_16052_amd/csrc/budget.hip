@@ -6,7 +6,7 @@
 // Three launches, none of which has a workgroup that does the whole tree's work by itself:
 //   score_parts_kernel   column sums of blocks of rows (large trees only; the others add the rows in the next launch)
 //   budget_kernel        one WAVE per token: every workgroup adds the partial sums and ranks the experts itself
-//                        (above 256 experts one WORKGROUP per token: budget_many_kernel)
+//                        (many experts: one WORKGROUP per token, budget_many_kernel)
 //   group_pairs_kernel   one workgroup per shortlisted expert: its pairs, its offset, its work items
 #include "common.h"
 
@@ -47,6 +47,8 @@ __global__ __launch_bounds__(kScoreThreads) void score_parts_kernel(const double
 // Threads of a budget_kernel workgroup: four tokens at a time, and more where the scores and the ranking of more
 // experts, which every workgroup repeats, need the threads (at most kScoreLoads rows per thread up to 128 tokens).
 inline int budget_threads(int N) { return N <= 64 ? 256 : N <= 128 ? 512 : 1024; }
+
+constexpr int kMaxBudgetGroups = 512;
 
 struct BudgetLds {
   size_t s, red, rows, row_stride, S, rank, sel, inS, total;
@@ -231,11 +233,11 @@ __global__ __launch_bounds__(1024) void budget_kernel(
   }
 }
 
-// More than 256 experts (N <= 1024 = blockDim.x): one workgroup per token.  A wave counts one block of 64 candidates
+// Many experts (N <= 1024 = blockDim.x): one workgroup per token.  A wave counts one block of 64 candidates
 // against its share of the rivals, and the shares add up through integer LDS atomics, for the shortlist as for a token.
 // Bound by the N^2 / 1024 comparisons per thread, once for the shortlist and once per token.  One wave per token, as above,
-// would hold 16 candidates per lane: its registers spill, and the stage took 405 us for 63 tokens x 300 experts (680 for
-// 512) against 20 us (25) this way.
+// would hold 16 candidates per lane for 1024 experts: its registers spill, and the stage took 405 us for 63 tokens x 300
+// experts (680 for 512) against 20 us (25) this way.
 __device__ __forceinline__ void rank_in_workgroup(const double *row, int N, int32_t *rank) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blocks = (N + kWave - 1) / kWave, parts = (int)(blockDim.x >> 6) / blocks;
@@ -408,10 +410,14 @@ hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int
     if ((e = launch_score_parts(probs, M, N, score_parts, &n_src, st)) != hipSuccess) return e;
     src = score_parts;
   }
-  // every workgroup ranks the experts again: no more of them than two per compute unit
-  const bool many = N > 4 * kWave;
+  // Every workgroup ranks the experts again: no more of them than two per compute unit.  One wave per token leaves most
+  // compute units idle on small trees, one workgroup per token repeats the barriers of a token on large ones.  Whole stage,
+  // us, wave / workgroup per token: 256 experts, 63 tokens 37 / 17, 511 tokens 40 / 30, 2048 tokens 43 / 57; 130 experts
+  // 26 / 14, 29 / 25, 32 / 42 (1024 tokens: 41 / 40 and 30 / 31).  Up to 128 experts a row takes two candidates per lane,
+  // and the wave is within 3 us at any size.
+  const bool many = N > 4 * kWave || (N > 2 * kWave && M <= kMaxBudgetGroups);
   const int nt = budget_threads(N), tokens = many ? 1 : nt / kWave;
-  const int want = (M + tokens - 1) / tokens, grid = want < 512 ? want : 512;
+  const int want = (M + tokens - 1) / tokens, grid = want < kMaxBudgetGroups ? want : kMaxBudgetGroups;
   const size_t smem = budget_lds(N, B, nt, tokens).total;
   auto run = [&](auto kern) -> hipError_t {
     kern<<<grid, nt, smem, st>>>(probs, src, n_src, M, N, k, B, policy, ds.renorm, ext_shortlist, scores, budget_ids,

@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,N,k,B", [(1, 1, 1, 1), (1, 64, 8, 9), (128, 64, 8, 33), (129, 65, 1, 2), (127, 128, 8, 64),
                                      (130, 129, 6, 77), (257, 257, 5, 200), (1025, 5, 3, 4), (2100, 64, 8, 64),
-                                     (40, 1024, 64, 700), (300, 3, 3, 3), (1, 257, 1, 1), (129, 513, 8, 300), (600, 320, 9, 60),
-                                     (1040, 1024, 64, 700)])
+                                     (40, 1024, 64, 700), (300, 3, 3, 3), (1, 257, 1, 1), (129, 513, 8, 300), (600, 320, 9, 60), (512, 129, 4, 40), (513, 129, 4, 40),
+                                     (63, 256, 8, 64),                                      (1040, 1024, 64, 700)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_budget_stage_edges(M, N, k, B, policy):
     print(f"case M={M} N={N} k={k} B={B} policy={policy}", flush=True)
@@ -71,23 +71,43 @@ def test_scores_of_any_size_rank_the_same(M, N, k, B, policy):
         assert np.array_equal(got["tok_w"], ref["tok_w"].astype(np.float32))
 
 
+def best_us(N, M):
+    """Time of one budget stage on the GPU: replayed 20 times from a graph, so that the host's calls do not count."""
+    desc = mb.LayerDesc(512, N, 8, 32, mb.BF16, True)
+    ws = mb.alloc_workspace(desc, M)
+    probs = torch.softmax(torch.randn(M, N, dtype=torch.float64, device="cuda"), dim=1)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        mb.moespec_budget(desc, probs, N // 2, mb.SUBSTITUTE, ws)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(20):
+            mb.moespec_budget(desc, probs, N // 2, mb.SUBSTITUTE, ws)
+    times = []
+    for _ in range(8):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        graph.replay()
+        end.record()
+        end.synchronize()
+        times.append(start.elapsed_time(end) * 50.0)
+    return min(times)
+
+
 def test_one_expert_more_than_a_wave_per_token_takes_costs_no_multiple():
     """The selection has another form above 256 experts; 300 of them may cost the square of the ratio and the other form's
     overhead, not the eleven times that a wave with 16 candidates per lane took (63 tokens: 405 us against 37)."""
-    def best_us(N):
-        desc = mb.LayerDesc(512, N, 8, 32, mb.BF16, True)
-        ws = mb.alloc_workspace(desc, 63)
-        probs = torch.softmax(torch.randn(63, N, dtype=torch.float64, device="cuda"), dim=1)
-        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        times = []
-        for _ in range(6):
-            start.record()
-            for _ in range(20):
-                mb.moespec_budget(desc, probs, 75, mb.SUBSTITUTE, ws)
-            end.record()
-            end.synchronize()
-            times.append(start.elapsed_time(end) * 50.0)
-        return min(times)
-    few, many = best_us(256), best_us(300)
+    few, many = best_us(256, 63), best_us(300, 63)
     print(f"256 experts {few:.1f} us, 300 experts {many:.1f} us", flush=True)
     assert many < 4 * few
+
+
+def test_a_small_tree_does_not_queue_its_tokens_on_a_few_compute_units():
+    """63 tokens x 256 experts at 16 waves per workgroup would be four workgroups (37 us for the stage against 12 for 64
+    experts); with a workgroup per token the N^2 comparisons of the shortlist are the difference (17 us)."""
+    few, many = best_us(64, 63), best_us(256, 63)
+    print(f"64 experts {few:.1f} us, 256 experts {many:.1f} us", flush=True)
+    assert many < 2.2 * few
