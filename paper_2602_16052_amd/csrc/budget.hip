@@ -12,9 +12,12 @@
 
 namespace moespec {
 
-// Up to this many tokens every workgroup of budget_kernel adds the rows of the table itself, one round of loads; above, the
-// row blocks are summed once by a launch of its own (4.8 us at 511 and at 2048 tokens).
-constexpr int kDirectScoreRows = 128;
+// Up to this many tokens every workgroup of the budget kernel adds the rows of the table itself: one round of loads at 128
+// tokens and up to 256 experts, two at 256 tokens and up to 128 experts, where a second round still costs less than a launch
+// (whole stage, us, rows / row blocks first: 256 tokens x 8 experts 9.8 / 12.3, x 64 13.9 / 14.8, x 128 19.0 / 18.8, but
+// x 256 22.6 / 20.1, x 300 27.9 / 22.5).  Above, the row blocks are summed once by a launch of its own (4.8 us at 511 and at
+// 2048 tokens).
+inline int direct_score_rows(int N) { return N <= 2 * kWave ? 256 : 128; }
 constexpr int kScoreLoads = 32;  // rows in flight per thread of those sums
 
 // part[b, i] = sum of probs[t, i] over the rows t of block b, ascending.  Wave w of a workgroup adds the rows w, w + 16,
@@ -45,7 +48,7 @@ __global__ __launch_bounds__(kScoreThreads) void score_parts_kernel(const double
 }
 
 // Threads of a budget_kernel workgroup: four tokens at a time, and more where the scores and the ranking of more
-// experts, which every workgroup repeats, need the threads (at most kScoreLoads rows per thread up to 128 tokens).
+// experts, which every workgroup repeats, need the threads (at most kScoreLoads rows per thread at 128 tokens and up to 256 experts).
 inline int budget_threads(int N) { return N <= 64 ? 256 : N <= 128 ? 512 : 1024; }
 
 constexpr int kMaxBudgetGroups = 512;
@@ -406,7 +409,7 @@ hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int
   const double *src = probs;
   int n_src = M;
   hipError_t e;
-  if (M > kDirectScoreRows && (ext_shortlist == nullptr || scores != nullptr)) {
+  if (M > direct_score_rows(N) && (ext_shortlist == nullptr || scores != nullptr)) {
     if ((e = launch_score_parts(probs, M, N, score_parts, &n_src, st)) != hipSuccess) return e;
     src = score_parts;
   }

@@ -2,6 +2,8 @@
 sum and of a score block, experts around the candidates-per-lane steps, top-k of 1 and of a whole wave, more tokens
 than waves, ragged everything.  The probabilities are multiples of 2^-12, so that every sum is exact in any order and
 ties are frequent: scores, shortlist, routing and segments must equal the oracle's exactly."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -14,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,N,k,B", [(1, 1, 1, 1), (1, 64, 8, 9), (128, 64, 8, 33), (129, 65, 1, 2), (127, 128, 8, 64),
                                      (130, 129, 6, 77), (257, 257, 5, 200), (1025, 5, 3, 4), (2100, 64, 8, 64),
-                                     (40, 1024, 64, 700), (300, 3, 3, 3), (1, 257, 1, 1), (129, 513, 8, 300), (600, 320, 9, 60), (512, 129, 4, 40), (513, 129, 4, 40),
+                                     (40, 1024, 64, 700), (300, 3, 3, 3), (1, 257, 1, 1), (129, 513, 8, 300), (600, 320, 9, 60), (512, 129, 4, 40), (256, 64, 8, 20), (257, 128, 2, 30), (256, 128, 8, 90), (513, 129, 4, 40),
                                      (63, 256, 8, 64),                                      (1040, 1024, 64, 700)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_budget_stage_edges(M, N, k, B, policy):
@@ -111,3 +113,18 @@ def test_a_small_tree_does_not_queue_its_tokens_on_a_few_compute_units():
     few, many = best_us(64, 63), best_us(256, 63)
     print(f"64 experts {few:.1f} us, 256 experts {many:.1f} us", flush=True)
     assert many < 2.2 * few
+
+
+@pytest.mark.parametrize("M,N,launches", [(128, 64, 2), (129, 64, 2), (256, 128, 2), (257, 64, 3), (129, 129, 3)])
+def test_launches_of_a_budget_stage(M, N, launches):
+    """The rows are summed by a launch of its own only where that is cheaper: a caller pays the host's share of each."""
+    desc = mb.LayerDesc(32, N, 1, 32, mb.BF16, True)
+    ws, probs = mb.alloc_workspace(desc, M), torch.rand(M, N, dtype=torch.float64, device="cuda")
+    mb.moespec_budget(desc, probs, 1, mb.SUBSTITUTE, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        mb.moespec_budget(desc, probs, 1, mb.SUBSTITUTE, ws)
+    n = ctypes.c_size_t()
+    assert ctypes.CDLL("libamdhip64.so").hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value == launches
