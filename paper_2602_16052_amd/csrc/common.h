@@ -337,8 +337,11 @@ bool expert_ffn_self_segmenting(const moespec_desc &ds, int M);
 // Number of K-split copies of y that launch_expert_ffn writes for n_seg segments; out == NULL there skips
 // the combine and leaves the per-pair expert outputs in y.
 int down_splits(const moespec_desc &ds, int M, int n_seg);
-// The passes as a grouped GEMM (expert_wide.hip): whether they run in that form, and one of them.
+int streaming_down_splits(const moespec_desc &ds, int n_seg);  // what the streaming form of the down pass takes
+// The passes as a grouped GEMM (expert_wide.hip): whether the gate/up pass runs in that form (the layer call then takes the
+// staged prologue), whether the down pass does too, and one of them.
 bool expert_ffn_wide(const moespec_desc &ds, int M, int n_seg);
+bool expert_down_wide(const moespec_desc &ds, int M, int n_seg);
 hipError_t launch_wide_pass(const moespec_desc &ds, const moespec_weights &wt, bool gate_up, const void *x, int M,
                             const int4 *items, const int32_t *perm, int cap, void *out, hipStream_t st);
 // Analysis kernels (analysis.hip).  part: 2 M doubles of scratch.

@@ -817,14 +817,17 @@ bool expert_ffn_self_segmenting(const moespec_desc &ds, int M) {
 // unit two workgroups, each item is cut along F into up to kMaxDownSplits parts with their own copy of y,
 // as long as a part keeps at least 16 chunks (shorter walks are dominated by their start-up: measured
 // slower at F = 1024, 1.6x to 2.7x faster at F = 14336 with 4 or 2 loaded experts).
-int down_splits(const moespec_desc &ds, int M, int n_seg) {
+int streaming_down_splits(const moespec_desc &ds, int n_seg) {
   int splits = 1;
-  if (!expert_ffn_wide(ds, M, n_seg) && ds.dtype == MOESPEC_BF16) {
+  if (ds.dtype == MOESPEC_BF16) {
     const int tiles = (ds.d / 32 + kFfnWaves - 1) / kFfnWaves;
     while (splits < kMaxDownSplits && (long long)n_seg * tiles * splits * 2 <= 512 && ds.d_ff / 128 >= 32 * splits)
       splits *= 2;
   }
   return splits;
+}
+int down_splits(const moespec_desc &ds, int M, int n_seg) {
+  return expert_down_wide(ds, M, n_seg) ? 1 : streaming_down_splits(ds, n_seg);
 }
 
 // Whether the 4 waves of a workgroup take a quarter of K each instead of a quarter of its rows: the same bytes are in
@@ -849,7 +852,8 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   if (rank_count && !(shortlist && lists && expert_ffn_self_segmenting(ds, M) && n_seg <= kFfnThreads))
     return hipErrorInvalidValue;
   if (!rank_count && !items_ready && !items) return hipErrorInvalidValue;
-  const bool wide = !rank_count && expert_ffn_wide(ds, M, n_seg);
+  const bool wide_gate_up = !rank_count && expert_ffn_wide(ds, M, n_seg);
+  const bool wide_down = !rank_count && expert_down_wide(ds, M, n_seg);
   const int cap = items_capacity(n_seg, M, k);  // work items of the LDS-tiled passes
   if (ds.dtype == MOESPEC_BF16 && !rank_count && !items_ready) {
     segment_items_kernel<<<1, 256, 0, st>>>(seg_expert, seg_off, n_seg, M, k, cap, items);
@@ -862,7 +866,7 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   const size_t split_stride = (size_t)M * k * d;
   if (ds.dtype == MOESPEC_BF16) {
     for (int pass = 1; pass <= 2; ++pass) {
-      if (wide) {
+      if (pass == 1 ? wide_gate_up : wide_down) {
         e = launch_wide_pass(ds, wt, pass == 1, pass == 1 ? h : act, M, items, perm, cap,
                              pass == 1 ? act : static_cast<void *>(y), st);
         if (e != hipSuccess) return e;

@@ -15,6 +15,8 @@
 // A row of a stage is 128 bytes = 8 pieces of 16; piece c of row r sits in slot c ^ (r & 7), so that 8 lanes that read
 // the same piece of 8 consecutive rows touch all 32 banks.  The lane that fetches a slot applies the permutation to its
 // global address (the DMA writes lane after lane).
+#include <math.h>
+
 #include <type_traits>
 
 #include "common.h"
@@ -230,10 +232,47 @@ __global__ __launch_bounds__(kWideThreads, 2) void ffn_wide_kernel(
 // pay for 256 workgroups whose last round is partly empty.  Measured per layer, streaming / grouped, us (64 experts of
 // 2048 x 1024, top-8): 127 tokens over 16 segments 85 / 92; 255 over 32 124 / 139, over 16 114 / 98; 383 over 64
 // 168 / 154; 511 over 64 198 / 190, over 32 190 / 163; 2048 over 64 511 / 425.
+//
+// How many pairs a segment really has is known on the device only: between pairs / n_seg (substitution keeps them all) and
+// pairs / N (truncation of a flat routing).  segment_mean is the geometric mean of the two; with the segments that large:
+//   - up to 256 tokens, a layer of a few units keeps the streaming form and the fused prologue in front of it (8 experts of
+//     512 x 128, 2 to 4 shortlisted, 160 to 200 tokens: 34 to 38 / 39 to 43 us);
+//   - weight rows of more than 4 KB: a unit is one walk over a long row at one workgroup per compute unit, and the weights
+//     stream slower than to two.  Where they are many (more than 8e7 elements a matrix) the segments have to be larger to
+//     make up for it (16 of 4096 x 2048, top-2: 300 tokens 202 / 240 us, 2048 tokens 487 / 378; 32 of 4096 x 1024, top-4,
+//     383 tokens 200 / 245); most of all where the streaming form would cut F in four (2 of 8 experts of 4096 x 14336, 160
+//     tokens: 147 / 191 under truncation, 320 / 343 under substitution; 511 tokens 651 / 525).
+static double segment_mean(const moespec_desc &ds, int M, int n_seg) {
+  return (double)M * ds.top_k / sqrt((double)n_seg * ds.n_experts);
+}
+static long long expected_pieces(const moespec_desc &ds, int M, int n_seg) {
+  const double mean = segment_mean(ds, M, n_seg);
+  return (long long)n_seg * piece_count((int)ceil(mean < M ? mean : M));
+}
 bool expert_ffn_wide(const moespec_desc &ds, int M, int n_seg) {
   if (ds.dtype != MOESPEC_BF16 || ds.d < kWideK || ds.d_ff < kWideK) return false;
   const long long pairs = (long long)M * ds.top_k;
-  return (M > 2 * kPiecePairs && pairs >= 32ll * n_seg) || (M > kPiecePairs && pairs >= 96ll * n_seg);
+  if (!((M > 2 * kPiecePairs && pairs >= 32ll * n_seg) || (M > kPiecePairs && pairs >= 96ll * n_seg))) return false;
+  const int tiles = (ds.d_ff + kWideRows / 2 - 1) / (kWideRows / 2) + (ds.d + kWideRows - 1) / kWideRows;  // both passes
+  if (M <= 2 * kPiecePairs && expected_pieces(ds, M, n_seg) * tiles < 48) return false;
+  if (ds.d > 2048) {
+    const double mean = segment_mean(ds, M, n_seg);
+    if (streaming_down_splits(ds, n_seg) == kMaxDownSplits ? mean < 160.0
+                                                           : mean < 80.0 && (long long)n_seg * ds.d * ds.d_ff > 80000000ll)
+      return false;
+  }
+  return true;
+}
+
+// Whether the down pass takes the grouped form as well.  It has no split of K, so where the streaming form cuts F in two or
+// four (long rows, few row tiles) the grouped pass lasts as long as one walk over F, 0.85 us per stage of 64, unless its
+// units fill a good part of the 256 workgroups.  Down pass alone, streaming with splits / grouped, us: one of 4 experts of
+// 1024 x 8192, 300 tokens 40 less; 2 of 8 of 4096 x 14336, 160 tokens 130 less; but 2 of 8 of 4096 x 4096, 1023 tokens (256
+// units) 67 more, 3 of 6 of 3072 x 8192 (216 units) 104 more.
+bool expert_down_wide(const moespec_desc &ds, int M, int n_seg) {
+  return expert_ffn_wide(ds, M, n_seg) &&
+         (streaming_down_splits(ds, n_seg) == 1 ||
+          expected_pieces(ds, M, n_seg) * ((ds.d + kWideRows - 1) / kWideRows) >= 96);
 }
 
 hipError_t launch_wide_pass(const moespec_desc &ds, const moespec_weights &wt, bool gate_up, const void *x, int M,

@@ -17,8 +17,12 @@ pytestmark = pytest.mark.gpu
 CASES = [(64, 2, 2, 64, 384, 2, 0.2),      # one stage; three pieces of 128
          (96, 5, 2, 160, 288, 4, 0.2),     # half a last stage in both passes, rows inside a tile
          (192, 2, 2, 96, 291, 2, 0.2),     # pieces of 97
-         (128, 2, 2, 64, 129, 2, 0.2),     # two uneven pieces, smallest tree
+         (128, 2, 2, 64, 129, 2, 0.2),     # two uneven pieces, too few units for a tree of this size: streaming form
+         (1024, 2, 2, 1024, 129, 2, 0.2),  # the same with enough units, smallest tree
          (128, 2, 2, 64, 128, 2, 0.2),     # streaming form
+         (64, 2, 2, 4096, 300, 2, 0.2),    # gate/up grouped, down streaming with its K cut in two
+         (96, 2, 2, 8288, 260, 2, 0.2),    # ... in four, with a tail
+         (2048, 2, 2, 4096, 768, 2, 0.2),  # both grouped: enough units for the long rows
          (320, 12, 3, 416, 400, 12, 1.6),  # segments of every size
          (256, 40, 4, 256, 520, 33, 1.2),  # more than one round of items per XCD
          (32, 4, 2, 32, 300, 4, 0.2)]      # too narrow: streaming form
@@ -68,3 +72,36 @@ def test_staged_and_wide_layers_replay_from_a_graph(dtype, d, F, M, B):
             torch.cuda.synchronize()
             assert torch.equal(out_static, want), f"replay {rep} differs from the eager call"
             assert torch.equal(mb.moespec_layer_forward(desc, W_d, h, B, mb.SUBSTITUTE, ws), want)
+
+
+@pytest.mark.parametrize("M,B", [(160, 2), (255, 4)])
+def test_few_large_experts_keep_their_pace_above_128_tokens(M, B):
+    """2 or 4 of 8 experts of 4096 x 14336: a down pass without a split of its long rows took 316 us for what 128 tokens
+    take 147 us; the passes read the same experts, twice where a segment exceeds 128 pairs."""
+    d, N, k, F = 4096, 8, 2, 14336
+    desc = mb.LayerDesc(d, N, k, F, mb.BF16, True)
+    gen = torch.Generator(device="cuda").manual_seed(0)
+
+    def normal(*shape, sigma):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, sigma, generator=gen)
+
+    W = dict(w_router=normal(N, d, sigma=0.02), b_router=torch.zeros(N, device="cuda"), w_gate=normal(N, F, d, sigma=0.02),
+             w_up=normal(N, F, d, sigma=0.02), w_down=normal(N, d, F, sigma=0.02))
+
+    def best_us(m):
+        h, ws = normal(m, d, sigma=1.0), mb.alloc_workspace(desc, m)
+        call = mb.LayerForwardCall(desc, W, h, B, mb.TRUNCATE, ws, torch.empty_like(h))
+        times = []
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                call()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) * 100.0)
+        return min(times)
+
+    base, large = best_us(128), best_us(M)
+    print(f"B={B}: 128 tokens {base:.0f} us, {M} tokens {large:.0f} us", flush=True)
+    assert large < 1.35 * base
