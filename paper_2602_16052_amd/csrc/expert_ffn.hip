@@ -581,12 +581,14 @@ __device__ __forceinline__ void fold_half(float *v) {
 // After it, lane l holds the complete sum number l / (64 / N_) in v[0].
 template <int N_>
 __device__ __forceinline__ float fold_sums(float (&v)[N_]) {
-  static_assert(N_ == 64 || N_ == 32, "one or two lanes per sum");
+  static_assert(N_ == 8 || N_ == 16 || N_ == 32 || N_ == 64, "one to eight lanes per sum");
   fold_half<32, N_>(v);
   fold_half<16, N_ / 2>(v);
   fold_half<8, N_ / 4>(v);
-  fold_half<4, N_ / 8>(v);
-  fold_half<2, N_ / 16>(v);
+  if constexpr (N_ >= 16) fold_half<4, N_ / 8>(v);
+  else v[0] += __shfl_xor(v[0], 4, kWave);
+  if constexpr (N_ >= 32) fold_half<2, N_ / 16>(v);
+  else v[0] += __shfl_xor(v[0], 2, kWave);
   if constexpr (N_ == 64) fold_half<1, 2>(v);
   else v[0] += __shfl_xor(v[0], 1, kWave);
   return v[0];
@@ -599,7 +601,8 @@ __device__ __forceinline__ void f32_dots(const float *const (&row)[kF32Rows], co
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int i = 0; i < kF32Rows * P; ++i) sums[i] = 0.f;
-#pragma unroll 2
+  constexpr int kUnroll = P <= 2 ? 4 : 2;  // about as many loads in flight with few pairs as with many
+#pragma unroll kUnroll
   for (int j0 = 0; j0 < K; j0 += kWave) {
     const int j = j0 + lane;
     const bool in = j < K;  // lanes past the end add +0 * +0
@@ -655,6 +658,11 @@ __device__ __forceinline__ void gateup_f32_tile(const float *__restrict__ h, con
   if (lane < 32 && lane % LPS == 0 && f < F && p < m) act[(size_t)pair_at(plist, p, n_pairs) * F + f] = g / (1.0f + expf(-g)) * u;
 }
 
+// kFew: every segment has at most two pairs (trees of one or two tokens), so that the passes are a stream of weights: 8 rows
+// against a tile of 4 pairs spent a third of the loads and three quarters of the sums on pairs that are not there (one token,
+// 2 experts of 4096 x 14336: 340 us per layer against 300; 8 of 1024 x 2048: 69 / 64).  A kernel of its own, because in one
+// kernel with the larger tiles each costs the other its registers (63 tokens, 8 experts of 512 x 1024: 65 -> 74 us).
+template <bool kFew>
 __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
     const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
     const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm,
@@ -667,9 +675,15 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
   const int f0 = (blockIdx.x * kFfnWaves + (int)(threadIdx.x >> 6)) * 4;
   if (f0 >= F) return;
   const float *wg = w_gate + (size_t)e * F * d, *wu = w_up + (size_t)e * F * d;
-  for (int p0 = blockIdx.z * kF32Pairs; p0 < m; p0 += gridDim.z * kF32Pairs) {
-    if (m - p0 <= kF32Pairs / 2) gateup_f32_tile<kF32Pairs / 2>(h, wg, wu, plist, p0, m, M * k, k, d, F, f0, act);
-    else gateup_f32_tile<kF32Pairs>(h, wg, wu, plist, p0, m, M * k, k, d, F, f0, act);
+  constexpr int kPairs = kFew ? 2 : kF32Pairs;
+  for (int p0 = blockIdx.z * kPairs; p0 < m; p0 += gridDim.z * kPairs) {
+    if constexpr (kFew) {
+      if (m - p0 == 1) gateup_f32_tile<1>(h, wg, wu, plist, p0, m, M * k, k, d, F, f0, act);
+      else gateup_f32_tile<2>(h, wg, wu, plist, p0, m, M * k, k, d, F, f0, act);
+    } else {
+      if (m - p0 <= kF32Pairs / 2) gateup_f32_tile<kF32Pairs / 2>(h, wg, wu, plist, p0, m, M * k, k, d, F, f0, act);
+      else gateup_f32_tile<kF32Pairs>(h, wg, wu, plist, p0, m, M * k, k, d, F, f0, act);
+    }
   }
 }
 
@@ -690,6 +704,7 @@ __device__ __forceinline__ void down_f32_tile(const float *__restrict__ act, con
   if (lane % LPS == 0 && j < d && p < m) y[(size_t)pair_at(plist, p, n_pairs) * d + j] = v;
 }
 
+template <bool kFew>
 __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
     const float *__restrict__ act, const float *__restrict__ w_down, const int32_t *__restrict__ seg_expert,
     const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count,
@@ -702,9 +717,15 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
   const int j0 = (blockIdx.x * kFfnWaves + (int)(threadIdx.x >> 6)) * kF32Rows;
   if (j0 >= d) return;
   const float *wd = w_down + (size_t)e * d * F;
-  for (int p0 = blockIdx.z * kF32Pairs; p0 < m; p0 += gridDim.z * kF32Pairs) {
-    if (m - p0 <= kF32Pairs / 2) down_f32_tile<kF32Pairs / 2>(act, wd, plist, p0, m, M * k, d, F, j0, y);
-    else down_f32_tile<kF32Pairs>(act, wd, plist, p0, m, M * k, d, F, j0, y);
+  constexpr int kPairs = kFew ? 2 : kF32Pairs;
+  for (int p0 = blockIdx.z * kPairs; p0 < m; p0 += gridDim.z * kPairs) {
+    if constexpr (kFew) {
+      if (m - p0 == 1) down_f32_tile<1>(act, wd, plist, p0, m, M * k, d, F, j0, y);
+      else down_f32_tile<2>(act, wd, plist, p0, m, M * k, d, F, j0, y);
+    } else {
+      if (m - p0 <= kF32Pairs / 2) down_f32_tile<kF32Pairs / 2>(act, wd, plist, p0, m, M * k, d, F, j0, y);
+      else down_f32_tile<kF32Pairs>(act, wd, plist, p0, m, M * k, d, F, j0, y);
+    }
   }
 }
 
@@ -912,17 +933,19 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   }
   // up to 4 workgroups share the pairs of a segment: enough waves to hide the loads where rows are few
   const int ptiles = (M + kF32Pairs - 1) / kF32Pairs, z = ptiles < 4 ? ptiles : 4;
+  const bool few = M <= 2;
   dim3 g1((F + 4 * kFfnWaves - 1) / (4 * kFfnWaves), n_seg, z);
-  ffn_gateup_f32_kernel<<<g1, kFfnThreads, 0, st>>>(
+  auto gate_up = few ? ffn_gateup_f32_kernel<true> : ffn_gateup_f32_kernel<false>;
+  gate_up<<<g1, kFfnThreads, 0, st>>>(
       static_cast<const float *>(h), static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up),
       seg_expert, seg_off, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
       static_cast<float *>(act));
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(0);
   dim3 g2((d + kF32Rows * kFfnWaves - 1) / (kF32Rows * kFfnWaves), n_seg, z);
-  ffn_down_f32_kernel<<<g2, kFfnThreads, 0, st>>>(static_cast<const float *>(act),
-                                                  static_cast<const float *>(wt.w_down), seg_expert, seg_off, perm,
-                                                  rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
+  auto down = few ? ffn_down_f32_kernel<true> : ffn_down_f32_kernel<false>;
+  down<<<g2, kFfnThreads, 0, st>>>(static_cast<const float *>(act), static_cast<const float *>(wt.w_down), seg_expert, seg_off,
+                                   perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(1);
   if (!out) return hipSuccess;
