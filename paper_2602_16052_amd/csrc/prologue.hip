@@ -482,9 +482,14 @@ __global__ __launch_bounds__(256) void lists_to_segments_kernel(const int32_t *_
 }
 
 // The fused prologue covers layers whose M x N table of doubles fits the LDS of one workgroup beside the
-// selection scratch, with at most kSelfMaxExperts experts (one thread per shortlist rank in the expert passes).
+// selection scratch, with at most kSelfMaxExperts experts (one thread per shortlist rank in the expert passes) and at most
+// one token per compute unit.  With more tokens the workgroups, each of which loads the whole table and ranks its experts
+// again, come in rounds, while the staged kernels grow with the tokens alone.  Whole fp32 layer of 4 experts, us, fused
+// less staged: 128 tokens -4, 160 -2, 200 to 256 +1, 300 +2, 400 +5, 512 +16, 1024 +68; of 64 experts, top-8: 128 -5, 256 -5,
+// 300 0; bf16 within 4 up to 256.
+constexpr int kFusedMaxTokens = 256;
 bool fused_prologue_ok(const moespec_desc &ds, int M) {
-  if (ds.n_experts > kSelfMaxExperts || M > kSelfMaxTokens) return false;
+  if (ds.n_experts > kSelfMaxExperts || M > kFusedMaxTokens) return false;
   return prologue_lds(M, ds.n_experts, ds.top_k, ds.n_experts).total <= 160 * 1024;
 }
 

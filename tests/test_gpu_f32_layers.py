@@ -1,6 +1,6 @@
 """fp32 layers where their kernels can go wrong: rows that are no multiple of a wave's 8 (4 gate) rows, K below and just
 above a wave's 64 elements, hidden sizes that end inside a block of the router projection, segments of 1, 4, 5, 8, 9 and
-more pairs, more pair tiles than workgroups share, and a table beyond the fused prologue."""
+more pairs, more pair tiles than workgroups share, and trees on both sides of the fused prologue's limits (experts and tokens)."""
 import pytest
 import torch
 
@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d,N,k,F,M,B", [(4, 3, 1, 4, 1, 2), (36, 2, 2, 12, 4, 2), (60, 2, 2, 68, 5, 2),
                                          (64, 2, 2, 64, 8, 2), (68, 2, 2, 132, 9, 2), (132, 7, 3, 28, 33, 5),
                                          (100, 4, 2, 52, 300, 3), (48, 300, 5, 20, 11, 40),
+                                         (64, 4, 2, 32, 256, 3), (64, 4, 2, 32, 257, 3),
                                          (300, 5, 3, 332, 1, 4), (260, 3, 3, 516, 2, 3), (256, 2, 2, 256, 3, 2)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_f32_layers(d, N, k, F, M, B, policy):
@@ -64,3 +65,31 @@ def test_one_token_is_a_stream_of_weights():
     one, seven = best_us(1), best_us(7)
     print(f"one token {one:.0f} us, seven {seven:.0f} us", flush=True)
     assert one < 0.91 * seven
+
+
+def test_a_large_tree_costs_no_rounds_of_its_whole_table():
+    """With a workgroup per token that loads the whole table, 1024 tokens over 4 small experts were four rounds of 1024
+    rows each (78 us against 20 for 256 tokens, on a shortlist of one expert with few pairs; 21 row by row)."""
+    d, N, F = 64, 4, 64
+    desc = mb.LayerDesc(d, N, 1, F, mb.F32, True)
+    cfg = wl.small_config("table", "f32", d=d, n_experts=N, top_k=1, d_ff=F, M=1024, bias_alpha=0.0)
+    W, ext = upload_weights(wl.layer_weights(cfg)), torch.zeros(1, dtype=torch.int32, device="cuda")
+    W["b_router"][0] = -3.0
+
+    def best_us(M):
+        h, ws = to_device(wl.hidden_states(cfg))[:M].contiguous(), mb.alloc_workspace(desc, M)
+        call = mb.LayerForwardCall(desc, W, h, 1, mb.TRUNCATE, ws, torch.empty_like(h), ext_shortlist=ext)
+        times = []
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                call()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) * 50.0)
+        return min(times)
+
+    small, large = best_us(256), best_us(1024)
+    print(f"256 tokens {small:.0f} us, 1024 tokens {large:.0f} us", flush=True)
+    assert large < 1.8 * small
