@@ -13,6 +13,7 @@ constexpr int kRowsPerGroup = 4;                               // router rows pe
 constexpr int kSlices = kLogitThreads / kRowsPerGroup;         // threads that share one row (= 64)
 constexpr int kSoftmaxThreads = 256;
 constexpr int kGateThreads = 256;
+constexpr int kSharedGateTokens = 512;
 
 // logits[t, i] = w_i . h_t (+ b_i).  Thread (el, sl) takes the 16-byte pieces sl, sl+64, ... of row
 // i = 4 blockIdx.x + el and of h_t; all loads of a batch are issued together (the router weights of a
@@ -129,19 +130,22 @@ __global__ __launch_bounds__(kSoftmaxThreads) void softmax_topk_kernel(double *_
   }
 }
 
-// Eq. (1) and, if wanted, the natural top-k of Section 2.1 row by row, one wave per token: probs[t, :] = gate(sum of the
-// Q slices of the router projection + bias), top-k by rank counts over the row in LDS.  A lane holds up to NU experts;
-// 16-lane DPP reductions, then two cross-row steps.  partial may be probs (a wave reads its whole row before it writes).
-// Bound by the launch and one round of cold loads up to a few hundred tokens, by the row's N / 4 LDS reads beyond (4096
-// tokens x 64 experts with top-8 and weights: 8.2 us, against 15 us of softmax_topk_kernel).
-template <int Q, int NU, bool kTopK>
+// Eq. (1) and, if wanted, the natural top-k of Section 2.1 row by row: probs[t, :] = gate(sum of the Q slices of the router
+// projection + bias), top-k by rank counts over the row in LDS.  A lane holds up to NU experts; 16-lane DPP reductions, then
+// two cross-row steps.  partial may be probs (a wave reads its whole row before anybody writes it).
+// One wave per token, or (kShare) the 4 waves of a workgroup: all of them evaluate the row, each counts against a quarter of
+// the rivals.  Bound by the launch and one round of cold loads, by the row's N / 4 LDS reads (or a quarter of them) where
+// experts are many (4096 tokens x 64 experts with top-8 and weights: 8.2 us, against 15 us of softmax_topk_kernel).
+template <int Q, int NU, bool kTopK, bool kShare>
 __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *partial, const float *__restrict__ bias,
                                                                  int M, int N, int sigmoid_gate, double *probs, int k,
                                                                  int renorm, int32_t *__restrict__ topk_ids,
                                                                  float *__restrict__ topk_w) {
-  __shared__ double rows[kTopK ? kGateThreads / kWave : 1][kTopK ? NU * kWave : 1];
-  __shared__ int32_t sels[kTopK ? kGateThreads / kWave : 1][kWave];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = blockIdx.x * (kGateThreads / kWave) + wave;
+  constexpr int kWaves = kGateThreads / kWave, kRows = kTopK ? (kShare ? 1 : kWaves) : 1;
+  __shared__ double rows[kRows][kTopK ? NU * kWave : 1];
+  __shared__ int32_t sels[kRows][kWave];
+  __shared__ int32_t rank[kShare ? NU * kWave : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = kShare ? blockIdx.x : blockIdx.x * kWaves + wave;
   if (t >= M) return;
   const size_t MN = (size_t)M * N;
   double val[NU];
@@ -179,21 +183,45 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
 #pragma unroll
     for (int u = 0; u < NU; ++u) val[u] *= inv;
   }
+  if constexpr (kShare) {
+    for (int i = threadIdx.x; i < NU * kWave; i += kGateThreads) rank[i] = 0;
+    if (wave == 0) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) rows[0][lane + kWave * u] = lane + kWave * u < N ? val[u] : kNoRival;
+    }
+    __syncthreads();  // also: every wave has read its row of partial
+    int c[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) c[u] = 0;
+    const int quads = (N + 3) / 4;
+    rank_counts<NU>(rows[0], quads * wave / kWaves * 4, quads * (wave + 1) / kWaves * 4, lane, 0, val, c);
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (lane + kWave * u < N && c[u]) atomicAdd(&rank[lane + kWave * u], c[u]);
+    __syncthreads();
+    if (wave > 0) return;
+  }
 #pragma unroll
   for (int u = 0; u < NU; ++u)
     if (lane + kWave * u < N) probs[(size_t)t * N + lane + kWave * u] = val[u];
   if constexpr (kTopK) {
-    double *row = rows[wave];
-    int32_t *sel = sels[wave];
+    double *row = rows[kShare ? 0 : wave];
+    int32_t *sel = sels[kShare ? 0 : wave];
     int c[NU];
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      c[u] = 0;
-      row[lane + kWave * u] = lane + kWave * u < N ? val[u] : kNoRival;
-    }
     sel[lane] = -1;  // stays -1 where a NaN leaves a slot unclaimed
-    wave_lds_sync();
-    rank_counts<NU>(row, 0, N, lane, 0, val, c);
+    if constexpr (kShare) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) c[u] = rank[lane + kWave * u];
+      wave_lds_sync();
+    } else {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        c[u] = 0;
+        row[lane + kWave * u] = lane + kWave * u < N ? val[u] : kNoRival;
+      }
+      wave_lds_sync();
+      rank_counts<NU>(row, 0, N, lane, 0, val, c);
+    }
 #pragma unroll
     for (int u = 0; u < NU; ++u)
       if (lane + kWave * u < N && c[u] < k) sel[c[u]] = lane + kWave * u;
@@ -210,14 +238,20 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
 
 hipError_t launch_gate_rows(const moespec_desc &ds, const moespec_weights &wt, int M, int slices, const double *partial,
                             double *probs, int32_t *topk_ids, float *topk_w, hipStream_t st) {
-  const int N = ds.n_experts, per_wg = kGateThreads / kWave, sig = ds.gate == MOESPEC_GATE_SIGMOID ? 1 : 0;
+  const int N = ds.n_experts, sig = ds.gate == MOESPEC_GATE_SIGMOID ? 1 : 0;
+  const bool topk = topk_ids || topk_w;
+  // a workgroup per token where the counts take longer than the launch and the tokens leave compute units idle (projection
+  // and gate, wave / workgroup per token, us: 7 tokens x 256 experts 20.8 / 11.6, x 128 11.5 / 8.6; 511 x 256 31 / 23)
+  const bool share = topk && N > kWave && M <= kSharedGateTokens;
+  const int per_wg = share ? 1 : kGateThreads / kWave;
   auto run = [&](auto kern) -> hipError_t {
     kern<<<(M + per_wg - 1) / per_wg, kGateThreads, 0, st>>>(partial, wt.b_router, M, N, sig, probs, ds.top_k, ds.renorm,
                                                              topk_ids, topk_w);
     return hipGetLastError();
   };
-  const bool topk = topk_ids || topk_w;
-#define MOESPEC_GATE(Q, NU) (topk ? run(gate_rows_kernel<Q, NU, true>) : run(gate_rows_kernel<Q, NU, false>))
+#define MOESPEC_GATE(Q, NU)                                              \
+  (!topk ? run(gate_rows_kernel<Q, NU, false, false>)                    \
+         : share ? run(gate_rows_kernel<Q, NU, true, (NU > 1)>) : run(gate_rows_kernel<Q, NU, true, false>))
 #define MOESPEC_GATE_Q(Q) (N <= 64 ? MOESPEC_GATE(Q, 1) : N <= 128 ? MOESPEC_GATE(Q, 2) : MOESPEC_GATE(Q, 4))
   return slices == 1 ? MOESPEC_GATE_Q(1) : slices == 2 ? MOESPEC_GATE_Q(2) : slices == 4 ? MOESPEC_GATE_Q(4) : MOESPEC_GATE_Q(8);
 #undef MOESPEC_GATE_Q
