@@ -128,7 +128,7 @@ moespec_status layer_forward(const moespec_desc *desc, const moespec_weights *we
     return from_hip(e);
   }
   // Other shapes: the budget stage groups the pairs into the segment arrays and work items of the expert passes.
-  hipError_t e = launch_route(*desc, *weights, h, M, probs, nullptr, nullptr, w.partial, st);
+  hipError_t e = launch_route(*desc, *weights, h, M, probs, nullptr, nullptr, w.partial, w.partial_slices, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   e = launch_budget(*desc, probs, M, B, policy, ext_shortlist, t.scores, budget_ids, tok_ids, tok_w, seg_expert,
                     seg_off, perm, t.n_loaded, w.items, w.score_parts, st);
@@ -172,7 +172,8 @@ moespec_status moespec_route(const moespec_desc *desc, const moespec_weights *we
   if (!h || !probs || !aligned16(h)) return MOESPEC_ERR_INVALID_ARG;
   Workspace w = carve_workspace(*desc, M, ws);
   return from_hip(
-      launch_route(*desc, *weights, h, M, probs, topk_ids, topk_w, w.partial, static_cast<hipStream_t>(hip_stream)));
+      launch_route(*desc, *weights, h, M, probs, topk_ids, topk_w, w.partial, w.partial_slices,
+                               static_cast<hipStream_t>(hip_stream)));
 }
 
 moespec_status moespec_budget(const moespec_desc *desc, const double *probs, int32_t M, int32_t B, int32_t policy,
@@ -328,7 +329,7 @@ moespec_status moespec_oracle_ranking(const moespec_desc *desc, const moespec_we
   Workspace w = carve_workspace(*desc, M, ws);
   const int N = desc->n_experts;
   // natural routing (Eq. (2)): the budgeted path with B = N and truncation keeps every token's top-k
-  hipError_t e = launch_route(*desc, *weights, h, M, w.probs, nullptr, nullptr, w.partial, st);
+  hipError_t e = launch_route(*desc, *weights, h, M, w.probs, nullptr, nullptr, w.partial, w.partial_slices, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   e = launch_budget(*desc, w.probs, M, N, MOESPEC_TRUNCATE, nullptr, nullptr, w.budget_ids, w.tok_ids, w.tok_w,
                     w.seg_expert, w.seg_off, w.perm, nullptr, w.items, w.score_parts, st);

@@ -248,7 +248,8 @@ struct Workspace {
   float *y;           // [kMaxDownSplits][M * k, d]
   double *gram;       // [N, N + 3] scratch of the oracle ranking
   double *score_parts;  // [kScoreMaxParts, N] column sums of row blocks (budget stage; shares the place of gram)
-  double *partial;    // [kMaxLogitSlices, M, N] partial router projections of the fused prologue
+  double *partial;    // [partial_slices, M, N] partial router projections
+  int partial_slices;  // kMaxLogitSlices, or what fits the place of y, which later stages fill
   int32_t *list_count;  // [N] pairs per shortlist rank (fused prologue)
   int32_t *lists;     // [N, M] their pair lists (only for shapes the fused prologue covers)
   void *xnorm;        // [M, d] dtype: the scaled layer input of the layer stack
@@ -279,7 +280,13 @@ inline Workspace carve_workspace(const moespec_desc &ds, int64_t M, void *base) 
   w.gram = static_cast<double *>(take(sizeof(double) * N * (N + 3 > kScoreMaxParts ? N + 3 : kScoreMaxParts)));
   w.score_parts = w.gram;
   const bool small = N <= kSelfMaxExperts && M <= kSelfMaxTokens;
-  w.partial = static_cast<double *>(take(small ? sizeof(double) * kMaxLogitSlices * M * N : 0));
+  if (small) {
+    w.partial = static_cast<double *>(take(sizeof(double) * kMaxLogitSlices * M * N));
+    w.partial_slices = kMaxLogitSlices;
+  } else {
+    w.partial = reinterpret_cast<double *>(w.y);
+    w.partial_slices = (int)(sizeof(float) * kMaxDownSplits * k * d / (sizeof(double) * N));
+  }
   w.list_count = static_cast<int32_t *>(take(sizeof(int32_t) * N));
   w.lists = static_cast<int32_t *>(take(small ? sizeof(int32_t) * N * M : 0));
   w.xnorm = take(es * M * d);
@@ -288,10 +295,9 @@ inline Workspace carve_workspace(const moespec_desc &ds, int64_t M, void *base) 
 }
 
 // Launchers (defined in the .hip files).  Each returns hipGetLastError() after its launches.
-// topk_ids / topk_w may be NULL.  partial: [kMaxLogitSlices, M, N] doubles of scratch where M <= kSelfMaxTokens and
-// N <= kSelfMaxExperts, unused otherwise.
+// topk_ids / topk_w may be NULL.  partial: [partial_slices, M, N] doubles of scratch (partial_slices may be 0).
 hipError_t launch_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *probs,
-                        int32_t *topk_ids, float *topk_w, double *partial, hipStream_t st);
+                        int32_t *topk_ids, float *topk_w, double *partial, int partial_slices, hipStream_t st);
 // score_parts: [kScoreMaxParts, N] doubles of scratch.  scores and n_loaded may be NULL.
 hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int B, int policy,
                          const int32_t *ext_shortlist, double *scores, int32_t *budget_ids, int32_t *tok_ids,
@@ -326,7 +332,7 @@ hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, cons
                          double *partial, hipStream_t st);
 hipError_t launch_gate_rows(const moespec_desc &ds, const moespec_weights &wt, int M, int slices, const double *partial,
                             double *probs, int32_t *topk_ids, float *topk_w, hipStream_t st);
-int logit_slices(const moespec_desc &ds, int M, bool whole_table);
+int logit_slices(const moespec_desc &ds, int M, bool whole_table, int most);
 hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int B,
                                  int policy, const int32_t *ext_shortlist, double *partial, double *probs_ws,
                                  double *probs_out,

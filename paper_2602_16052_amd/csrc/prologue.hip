@@ -493,16 +493,16 @@ bool fused_prologue_ok(const moespec_desc &ds, int M) {
   return prologue_lds(M, ds.n_experts, ds.top_k, ds.n_experts).total <= 160 * 1024;
 }
 
-// Slices of the hidden dimension (1, 2, 4 or 8): more slices spread the matrix work over more compute units
+// Slices of the hidden dimension (1, 2, 4 or 8, at most `most`): more slices spread the matrix work over more compute units
 // (a wave issues one fp64 matrix instruction per 64 cycles), but the consumer re-reads one partial table per
 // slice: every workgroup of the fused kernel the whole table (whole_table), the row-wise gate kernel one row.
 // Picks the count with the smallest estimated sum of the two (rates measured on MI355X: 2.4 GHz, about 150 GB/s
 // from L2 into one compute unit).
-int logit_slices(const moespec_desc &ds, int M, bool whole_table) {
+int logit_slices(const moespec_desc &ds, int M, bool whole_table, int most) {
   const double tiles = ((M + 15) / 16) * ((ds.n_experts + 15) / 16), n_blocks = ds.d / 32;
   int best = 1;
   double best_us = 1e30;
-  for (int q = 1; q <= kMaxLogitSlices; q *= 2) {
+  for (int q = 1; q <= kMaxLogitSlices && (q == 1 || q <= most); q *= 2) {
     if (q > 1 && n_blocks < 2.0 * q * kLogitWaves) break;  // at least two 32-element blocks per wave
     const double waves_per_simd = tiles * q * kLogitWaves / 1024.0;  // 256 compute units x 4 SIMDs
     const double mfma_us = (n_blocks / (q * kLogitWaves)) * 8 * 64 / 2400.0 * (waves_per_simd > 1 ? waves_per_simd : 1);
@@ -542,7 +542,7 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
   // Large tables: the routing probabilities are finished row by row in a launch of their own and the last kernel
   // only loads them; small tables: every workgroup of the last kernel rebuilds the table itself.
   const bool split = (long long)M * N > kSplitSoftmaxAbove;
-  const int q = logit_slices(ds, M, !split);
+  const int q = logit_slices(ds, M, !split, kMaxLogitSlices);
   hipError_t e = launch_logits(ds, wt, h, M, q, partial, st);
   if (e != hipSuccess) return e;
   const size_t smem = prologue_lds(M, N, k, B).total;

@@ -259,11 +259,12 @@ hipError_t launch_gate_rows(const moespec_desc &ds, const moespec_weights &wt, i
 }
 
 hipError_t launch_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *probs,
-                        int32_t *topk_ids, float *topk_w, double *partial, hipStream_t st) {
+                        int32_t *topk_ids, float *topk_w, double *partial, int partial_slices, hipStream_t st) {
   const int N = ds.n_experts, k = ds.top_k, d = ds.d;
   if (mfma_route_ok(ds)) {
-    // beyond kSelfMaxTokens the output tiles alone fill the chip: one slice, accumulated in the caller's table
-    const int slices = M <= kSelfMaxTokens ? logit_slices(ds, M, false) : 1;
+    // one slice is accumulated in the caller's table (above kSelfMaxTokens a table of several has the place of y: 1025 tokens
+    // x 8 experts of d = 4096 19.3 -> 11.2 us, where the output tiles do not fill the chip)
+    const int slices = logit_slices(ds, M, false, partial_slices);
     double *logits = slices == 1 ? probs : partial;
     hipError_t e = launch_logits(ds, wt, h, M, slices, logits, st);
     return e != hipSuccess ? e : launch_gate_rows(ds, wt, M, slices, logits, probs, topk_ids, topk_w, st);
