@@ -31,7 +31,11 @@ constexpr int kWideGrid = 256;  // one workgroup per compute unit
 constexpr int kWideXcds = 8, kWideBlock = 4;  // consecutive work items that run side by side on one XCD
 
 // 64 lanes x 16 bytes from base + voff (per lane) to LDS bytes [lds, lds + 1024), lane after lane.  Completion is
-// counted by vmcnt in issue order; the compiler does not see the load, so the waits are written by hand.
+// counted by vmcnt in issue order; the compiler does not see the load, so the waits are written by hand.  m0 is a register
+// that the compiler reserves for sequences of its own, and warns about in a clobber list; named there, it keeps a value of
+// its own in m0 from being carried across.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void dma_to_lds(uint32_t lds, const void *base, uint32_t voff) {
   const uint64_t b = reinterpret_cast<uint64_t>(base);  // uniform, and the compiler is told so
   const uint64_t ub = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32 |
@@ -39,8 +43,9 @@ __device__ __forceinline__ void dma_to_lds(uint32_t lds, const void *base, uint3
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(
                    __builtin_amdgcn_readfirstlane(lds)),
                "v"(voff), "s"(ub)
-               : "memory");
+               : "m0", "memory");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");

@@ -225,3 +225,21 @@ def test_stack_calls_reject_bad_arguments(lib):
     assert g(ctypes.byref(cd), None, 8, P, None) == mb.ERR_INVALID_ARG
     assert g(ctypes.byref(cd), P, 0, P, None) == mb.ERR_INVALID_ARG
     assert g(ctypes.byref(cd), P, 8, P + 4, None) == mb.ERR_INVALID_ARG
+
+
+def test_inline_assembly_declares_the_registers_it_writes():
+    """A fixed register that an asm statement of the kernels writes has to be in its clobber list (the generic operands
+    declare themselves): the compiler is free to keep something there otherwise."""
+    import glob
+    import os
+    import re
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    seen = 0
+    for path in glob.glob(os.path.join(root, "paper_2602_16052_amd", "csrc", "*.h*")):
+        for stmt in re.findall(r"\basm\s+volatile\s*\((.*?)\);", open(path).read(), flags=re.S):
+            text = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', stmt.split("::")[0].split('" :')[0]))
+            written = set(re.findall(r"(?:^|\\n\\t)\s*[sv]_\w+\s+(m0|vcc|exec|[sv]\d+|[sv]\[\d+:\d+\])\b", text))
+            seen += len(written)
+            for reg in written:
+                assert f'"{reg}"' in stmt.rsplit(":", 1)[1], (os.path.basename(path), reg, stmt)
+    assert seen >= 1
