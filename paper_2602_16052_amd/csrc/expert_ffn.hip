@@ -601,7 +601,7 @@ __device__ __forceinline__ void f32_dots(const float *const (&row)[kF32Rows], co
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int i = 0; i < kF32Rows * P; ++i) sums[i] = 0.f;
-  constexpr int kUnroll = P <= 2 ? 4 : 2;  // about as many loads in flight with few pairs as with many
+  constexpr int kUnroll = P <= 2 ? 8 : 2;  // few pairs leave the registers for more loads in flight (8 against 4: 2 to 5 %)
 #pragma unroll kUnroll
   for (int j0 = 0; j0 < K; j0 += kWave) {
     const int j = j0 + lane;
@@ -660,7 +660,7 @@ __device__ __forceinline__ void gateup_f32_tile(const float *__restrict__ h, con
 
 // kFew: every segment has at most two pairs (trees of one or two tokens), so that the passes are a stream of weights: 8 rows
 // against a tile of 4 pairs spent a third of the loads and three quarters of the sums on pairs that are not there (one token,
-// 2 experts of 4096 x 14336: 340 us per layer against 300; 8 of 1024 x 2048: 69 / 64).  A kernel of its own, because in one
+// 2 experts of 4096 x 14336: 340 us per layer against 290; 8 of 1024 x 2048: 69 / 62).  A kernel of its own, because in one
 // kernel with the larger tiles each costs the other its registers (63 tokens, 8 experts of 512 x 1024: 65 -> 74 us).
 template <bool kFew>
 __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
