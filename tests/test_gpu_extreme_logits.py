@@ -15,10 +15,11 @@ from gpu_common import TOL, assert_routing_equal, desc_of, oracle_weights, out_t
 pytestmark = pytest.mark.gpu
 
 CASES = [("bf16", 256, 64, 8, 128, 48, "softmax"),     # fused prologue, every workgroup rebuilds the table
-         ("bf16", 128, 130, 4, 128, 200, "softmax"),   # fused prologue, row-wise gate kernel, ragged expert count
-         ("f32", 64, 16, 2, 32, 20, "softmax"),        # staged fp32 path
+         ("bf16", 128, 130, 4, 128, 200, "softmax"),   # table beyond the LDS, ragged expert count: staged kernels
+         ("f32", 64, 16, 2, 32, 20, "softmax"),        # fp32 operands
          ("bf16", 256, 40, 6, 256, 130, "sigmoid"),
-         ("bf16", 128, 64, 8, 128, 600, "softmax")]    # table beyond the LDS: staged budget kernel
+         ("bf16", 128, 64, 8, 128, 600, "softmax"),    # more tokens than the fused prologue takes: staged kernels
+         ("bf16", 128, 70, 4, 128, 100, "softmax")]    # fused prologue, row-wise gate kernel, ragged expert count
 
 
 @pytest.mark.parametrize("dtype,d,N,k,F,M,gate", CASES)

@@ -1,6 +1,6 @@
-"""GPU parity on seeded random layer shapes: every combination of kernel variant (LDS-tiled or direct passes,
-self-derived or grouped segments, K-split down pass, pieces of long segments), dtype, gate, policy and budget
-that a fixed seed reaches, each compared with the CPU oracle like the hand-picked cases."""
+"""GPU parity on seeded random layer shapes: every combination of kernel variant (fused or staged prologue, streaming
+passes with and without a K tail, waves that share K, K-split down pass, grouped passes, pieces of long segments, fp32),
+dtype, gate, policy and budget that a fixed seed reaches, each compared with the CPU oracle like the hand-picked cases."""
 import numpy as np
 import pytest
 import torch

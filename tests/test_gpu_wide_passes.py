@@ -1,6 +1,8 @@
 """The grouped form of the expert passes (trees whose experts serve many pairs) at the sizes where it can go wrong:
-rows that end inside a tile, K of one stage, K that ends with half a stage, pieces of exactly 96 / 97 / 128 pairs, segments
-from a few pairs to several pieces; the smallest tree that takes it and the largest that does not."""
+rows that end inside a tile, K of one stage, K that ends with half a stage, pieces on both sides of every step of its token
+tiles (32, 64, 96, 128 pairs), segments from a few pairs to several pieces; the smallest tree that takes it and the largest
+that does not; either pass alone in it."""
+import numpy as np
 import pytest
 import torch
 
@@ -16,6 +18,7 @@ pytestmark = pytest.mark.gpu
 #        d    N   k   F   M    B  alpha
 CASES = [(64, 2, 2, 64, 384, 2, 0.2),      # one stage; three pieces of 128
          (96, 5, 2, 160, 288, 4, 0.2),     # half a last stage in both passes, rows inside a tile
+         (192, 2, 2, 96, 288, 2, 0.2),     # pieces of 96
          (192, 2, 2, 96, 291, 2, 0.2),     # pieces of 97
          (128, 2, 2, 64, 129, 2, 0.2),     # two uneven pieces, too few units for a tree of this size: streaming form
          (1024, 2, 2, 1024, 129, 2, 0.2),  # the same with enough units, smallest tree
@@ -44,6 +47,39 @@ def test_wide_passes(d, N, k, F, M, B, alpha):
     again = mb.moespec_layer_forward(desc, W_d, h_d, B, mb.SUBSTITUTE, ws)
     torch.cuda.synchronize()
     assert torch.equal(staged, out) and torch.equal(again, out)
+
+
+@pytest.mark.parametrize("d,F", [(64, 160), (224, 64), (96, 96)])
+def test_pieces_on_both_sides_of_every_step(d, F):
+    """Hand-made segment tables for a tree that takes the grouped form: the sizes where a wave's number of token tiles
+    changes, a piece of one pair, and segments that are cut into pieces of those sizes."""
+    M, N, k = 450, 12, 3
+    slots = [[1, 32, 33, 64, 65, 95, 160], [96, 97, 127, 130], [128]]  # pairs per expert, expert after expert, of each slot
+    sizes = [n for slot in slots for n in slot]
+    assert len(sizes) == N and all(sum(s) <= M for s in slots)
+    cut = [-(-n // -(-n // 128)) for n in sizes]  # the longest piece of each segment
+    assert {1, 32, 33, 64, 65, 80, 95, 96, 97, 127, 128} == set(cut) and sum(sizes) <= M * k and M * k >= 32 * N and M > 256
+    cfg = wl.small_config("pieces", "bf16", d=d, n_experts=N, top_k=k, d_ff=F, M=M, seed=d + F)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    tok_ids, e = np.full((M, k), -1, dtype=np.int32), 0
+    for s, slot in enumerate(slots):
+        t0 = 7 * s
+        for n in slot:
+            tok_ids[np.arange(t0, t0 + n) % M, s] = e
+            t0, e = t0 + n, e + 1
+    tok_w = np.where(tok_ids >= 0, np.random.default_rng(d).uniform(0.1, 1.0, (M, k)), 0.0).astype(np.float32)
+    pairs = [np.flatnonzero(tok_ids.ravel() == i) for i in range(N)]
+    assert [p.size for p in pairs] == sizes
+    perm = np.full(M * k, -1, dtype=np.int32)
+    perm[: sum(sizes)] = np.concatenate(pairs)
+    seg_off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    out = mb.moespec_expert_ffn(desc, upload_weights(W), to_device(h), dev(np.arange(N, dtype=np.int32)), dev(seg_off), dev(perm),
+                                dev(tok_ids), dev(tok_w), mb.alloc_workspace(desc, M))
+    torch.cuda.synchronize()
+    W_o = oracle_weights(W)
+    want = O.combine(wl.as_f32(h), tok_ids, tok_w, W_o["w_gate"], W_o["w_up"], W_o["w_down"])
+    assert_out_close(out_to_numpy(out), want, "bf16")
 
 
 @pytest.mark.parametrize("dtype,d,F,M,B", [("bf16", 128, 192, 300, 4), ("bf16", 128, 128, 600, 16), ("f32", 68, 36, 40, 6)])
