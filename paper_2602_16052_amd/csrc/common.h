@@ -155,16 +155,14 @@ __device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, i
   }
 }
 
-// Rank-count selection of the k best of v[0..n) restricted to candidates with member[i] != 0
-// (member == nullptr: all).  sel[r] receives the index with rank r < k.  Equivalent to sorting by
-// (value descending, index ascending) and keeping the first k.  v, member, sel and the scratch
-// rank[n] live in LDS.  Called by every thread of the workgroup (it synchronises); the caller
-// synchronises again before reading sel.  The n x n comparisons are spread over the whole workgroup:
-// thread (i, part) counts the rivals of candidate i inside its part of the index range and adds its
-// count to rank[i] with an integer LDS atomic (order-independent, hence deterministic).
+// Rank-count selection of the k best of v[0..n).  sel[r] receives the index with rank r < k.  Equivalent to sorting by
+// (value descending, index ascending) and keeping the first k.  v, sel and the scratch rank[n] live in LDS.  Called by
+// every thread of the workgroup (it synchronises); the caller synchronises again before reading sel.  The n x n
+// comparisons are spread over the whole workgroup: thread (i, part) counts the rivals of candidate i inside its part of
+// the index range and adds its count to rank[i] with an integer LDS atomic (order-independent, hence deterministic).
 // Every slot of sel is first set to -1: when a value is NaN no comparison holds, several candidates then
 // count rank 0 and some slots are never claimed; those stay -1 (an unfilled slot) instead of stale LDS.
-__device__ inline void select_topk(const double *v, const uint8_t *member, int n, int k, int32_t *sel, int32_t *rank) {
+__device__ inline void select_topk(const double *v, int n, int k, int32_t *sel, int32_t *rank) {
   const int nt = blockDim.x, tid = threadIdx.x;
   int np2 = 1;
   while (np2 < n) np2 <<= 1;
@@ -175,22 +173,16 @@ __device__ inline void select_topk(const double *v, const uint8_t *member, int n
   const int chunk = (n + parts - 1) / parts;
   for (int i = np2 <= nt ? (tid & (np2 - 1)) : tid; i < n; i += np2 <= nt ? n : nt) {
     const int part = np2 <= nt ? tid / np2 : 0;
-    if (member && !member[i]) continue;
     const int j0 = part * chunk, j1 = min(n, j0 + chunk);
     const double vi = v[i];
     int cnt = 0;
-    if (member) {
 #pragma unroll 4
-      for (int j = j0; j < j1; ++j) cnt += (member[j] && ranks_before(v[j], j, vi, i)) ? 1 : 0;
-    } else {
-#pragma unroll 4
-      for (int j = j0; j < j1; ++j) cnt += ranks_before(v[j], j, vi, i) ? 1 : 0;
-    }
+    for (int j = j0; j < j1; ++j) cnt += ranks_before(v[j], j, vi, i) ? 1 : 0;
     if (cnt) atomicAdd(&rank[i], cnt);
   }
   __syncthreads();
   for (int x = tid; x < n; x += nt)
-    if ((!member || member[x]) && rank[x] < k) sel[rank[x]] = x;
+    if (rank[x] < k) sel[rank[x]] = x;
 }
 
 // Mixing weights of the slots sel[0..k): raw g or g / sum over the slots (summed in slot order).
@@ -222,8 +214,8 @@ inline int items_capacity(int n_seg, int64_t M, int64_t k) {
   return (int)(a < b ? a : b);
 }
 constexpr int kMaxLogitSlices = 8;    // slices of the hidden dimension in the fused prologue's router projection
-constexpr int kSelfMaxTokens = 1024;  // largest tree for which the expert passes derive their segments themselves
-constexpr int kSelfMaxExperts = 256;  // ... and the largest shortlist
+constexpr int kSelfMaxTokens = 1024;  // largest tree with a place of its own for partial projections and pair lists
+constexpr int kSelfMaxExperts = 256;  // ... and the most experts; also the limit of the matrix-core router projection
 
 // Row blocks whose column sums are the first half of Eq. (5) on large trees: at most kScoreMaxParts of them, one
 // workgroup each, a multiple of its waves.

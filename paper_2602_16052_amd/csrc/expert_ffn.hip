@@ -33,7 +33,7 @@ namespace moespec {
 constexpr int kFfnThreads = 256;
 static_assert(kSelfMaxExperts <= kFfnThreads, "one thread per shortlist rank");
 constexpr int kFfnWaves = kFfnThreads / kWave;
-constexpr int kMaxTiles = 8;  // token tiles of 16 per pass over the weights
+static_assert(kPiecePairs == 128, "8 token tiles of 16 per pass over the weights");
 
 // A segment is processed only if it names a real expert and lies inside the pair table; the passes clamp
 // pair indices into [0, M*k) so that malformed tables cannot address outside the buffers.
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
     const int4 it = xcd_item(tiles, cap, items, tile, rank);
     e = it.y;
     m = it.w;
-    if (it.x < 0 || !segment_ok(e, it.z, m, (long long)M * k, N)) return;
+    if (it.x < 0 || m > kPiecePairs || !segment_ok(e, it.z, m, (long long)M * k, N)) return;
     plist = perm + it.z;
   }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -449,13 +449,10 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
       else gateup_lds<2, 4, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
     }
   } else {
-    for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
-      const int mc = m - c0;
-      if (mc <= 16) gateup_lds<1, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
-      else if (mc <= 32) gateup_lds<2, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
-      else if (mc <= 64) gateup_lds<4, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
-      else gateup_lds<8, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
-    }
+    if (m <= 16) gateup_lds<1, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, 0, m, f0, ks, lds, act);
+    else if (m <= 32) gateup_lds<2, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, 0, m, f0, ks, lds, act);
+    else if (m <= 64) gateup_lds<4, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, 0, m, f0, ks, lds, act);
+    else gateup_lds<8, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, 0, m, f0, ks, lds, act);
   }
 }
 
@@ -520,7 +517,7 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
     const int4 it = xcd_item(tiles, cap, items, tile, rank);
     e = it.y;
     m = it.w;
-    if (it.x < 0 || !segment_ok(e, it.z, m, (long long)M * k, N)) return;
+    if (it.x < 0 || m > kPiecePairs || !segment_ok(e, it.z, m, (long long)M * k, N)) return;
     plist = perm + it.z;
   }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -542,13 +539,10 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
       else down_lds<2, 4, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
     }
   } else {
-    for (int c0 = 0; c0 < m; c0 += 16 * kMaxTiles) {
-      const int mc = m - c0;
-      if (mc <= 16) down_lds<1, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-      else if (mc <= 32) down_lds<2, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-      else if (mc <= 64) down_lds<4, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-      else down_lds<8, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-    }
+    if (m <= 16) down_lds<1, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, 0, m, j0, ks, lds, y);
+    else if (m <= 32) down_lds<2, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, 0, m, j0, ks, lds, y);
+    else if (m <= 64) down_lds<4, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, 0, m, j0, ks, lds, y);
+    else down_lds<8, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, 0, m, j0, ks, lds, y);
   }
 }
 

@@ -12,8 +12,8 @@
 //                         expert the (token, slot) pairs routed to it, tokens ascending, which is what the
 //                         expert passes consume.
 //
-// Every decision in fp64, ties to the lowest expert id, as in the staged kernels of route.hip / budget.hip,
-// which remain the path of the stage calls, of fp32 layers and of trees whose table does not fit the LDS.
+// Every decision in fp64, ties to the lowest expert id, as in the staged kernels of route.hip / budget.hip, which remain
+// the path of the stage calls, of larger trees (fused_prologue_ok) and of layers whose passes take the grouped form.
 #include "common.h"
 
 namespace moespec {
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   };
   bool token_done = false;
 
-  // Pair lists of the shortlist ranks own, own + M, ...: token t is routed to expert e = S[r] iff e ranks among the
+  // Pair lists of the shortlist ranks own, own + gridDim.x, ...: token t is routed to expert e = S[r] iff e ranks among the
   // first k of t's candidates; its rank is the slot.  16 lanes share a token and split its rivals; 64 tokens per
   // round; the routed tokens of a round are compacted in token order with one ballot per wave.
   for (int r = own; r < B; r += gridDim.x) {

@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kSoftmaxThreads) void softmax_topk_kernel(double *_
   }
 
   if (topk_ids == nullptr && topk_w == nullptr) return;
-  select_topk(g, nullptr, N, k, sel, rank);
+  select_topk(g, N, k, sel, rank);
   __syncthreads();
   mixing_weights(g, sel, k, renorm, wsel, wsel + ((k + 1) & ~1));
   __syncthreads();
