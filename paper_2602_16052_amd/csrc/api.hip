@@ -160,7 +160,10 @@ moespec_status moespec_check_desc(const moespec_desc *desc) { return check_desc(
 
 size_t moespec_workspace_bytes(const moespec_desc *desc, int32_t M_max) {
   if (check_desc(desc) != MOESPEC_OK || M_max < 1 || M_max > kMaxTokens) return 0;
-  return carve_workspace(*desc, M_max, nullptr).bytes;
+  // a tree of up to kSelfMaxTokens has areas that larger ones do without, and M_max covers those trees too
+  const size_t bytes = carve_workspace(*desc, M_max, nullptr).bytes;
+  const size_t small = M_max > kSelfMaxTokens ? carve_workspace(*desc, kSelfMaxTokens, nullptr).bytes : 0;
+  return bytes > small ? bytes : small;
 }
 
 moespec_status moespec_route(const moespec_desc *desc, const moespec_weights *weights, const void *h, int32_t M,

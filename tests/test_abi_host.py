@@ -243,3 +243,21 @@ def test_inline_assembly_declares_the_registers_it_writes():
             for reg in written:
                 assert f'"{reg}"' in stmt.rsplit(":", 1)[1], (os.path.basename(path), reg, stmt)
     assert seen >= 1
+
+
+def test_a_workspace_for_larger_trees_serves_smaller_ones():
+    """moespec_workspace_bytes(desc, M_max) covers every tree of up to M_max tokens: it never falls as M_max grows, and a call
+    with fewer tokens is not refused for its size."""
+    lib = mb.load_library()
+    sizes = (1, 2, 63, 128, 129, 1000, 1024, 1025, 1026, 1100, 2000, 65535)
+    for dtype, mult in ((mb.BF16, 32), (mb.F32, 4)):
+        for d in (mult, 8 * mult, 2048):
+            for n, k in ((1, 1), (64, 1), (64, 8), (256, 2), (300, 8)):
+                desc = mb.LayerDesc(d, n, k, mult, dtype, True)
+                need = [mb.workspace_bytes(desc, m) for m in sizes]
+                assert all(a <= b for a, b in zip(need, need[1:])), (dtype, d, n, k, need)
+    desc = mb.LayerDesc(64, 64, 1, 64, mb.BF16, True)
+    ws_bytes = mb.workspace_bytes(desc, 1025)
+    # a null shortlist budget is refused after the workspace's size has been accepted
+    assert _call_layer(lib, desc, M=1024, B=0, ws_bytes=ws_bytes) == mb.ERR_INVALID_ARG
+    assert _call_layer(lib, desc, M=1024, B=8, ws_bytes=1) == mb.ERR_WORKSPACE_TOO_SMALL
