@@ -612,8 +612,11 @@ __device__ __forceinline__ void f32_dots(const float *const (&row)[kF32Rows], co
   }
 }
 
-// The segment of grid row `seg`: from the prologue's lists (shortlist rank seg) or from the segment arrays.
-__device__ __forceinline__ bool f32_segment(int seg, const int32_t *seg_expert, const int32_t *seg_off,
+// The work of grid row `seg`: a shortlist rank of the prologue's lists, a work item of the budget stage or a segment of the
+// caller's arrays.  Ranks and work items come largest first, so that the last round of workgroups is a short one, and work
+// items end at 128 pairs, so that more of them run side by side.  Whole layer of 300 tokens, us, by rank / by ascending
+// segment / by work item: 40 experts of 1024 x 512, top-6, 329 / 349 / 289; 8 of 256 x 1024, top-2, 159 / 155 / 91.
+__device__ __forceinline__ bool f32_segment(int seg, const int32_t *seg_expert, const int32_t *seg_off, const int4 *items,
                                             const int32_t *perm, const int32_t *rank_count, const int32_t *shortlist,
                                             const int32_t *lists, int list_stride, int M, int N, int k, int &e, int &m,
                                             const int32_t *&plist) {
@@ -623,9 +626,18 @@ __device__ __forceinline__ bool f32_segment(int seg, const int32_t *seg_expert, 
     plist = lists + (size_t)seg * list_stride;
     return e >= 0 && e < N && m > 0 && m <= M;
   }
-  e = seg_expert[seg];
-  const int beg = seg_off[seg];
-  m = seg_off[seg + 1] - beg;
+  int beg;
+  if (items) {
+    if (seg >= items[0].x) return false;
+    const int4 it = items[1 + seg];  // gridDim.y does not exceed the table
+    e = it.y;
+    beg = it.z;
+    m = it.w;
+  } else {
+    e = seg_expert[seg];
+    beg = seg_off[seg];
+    m = seg_off[seg + 1] - beg;
+  }
   plist = perm + beg;
   return segment_ok(e, beg, m, (long long)M * k, N);
 }
@@ -659,12 +671,13 @@ __device__ __forceinline__ void gateup_f32_tile(const float *__restrict__ h, con
 template <bool kFew>
 __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
     const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
-    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm,
-    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
-    int list_stride, int M, int N, int k, int d, int F, float *__restrict__ act) {
+    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int4 *__restrict__ items,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
+    const int32_t *__restrict__ lists, int list_stride, int M, int N, int k, int d, int F, float *__restrict__ act) {
   int e, m;
   const int32_t *plist;
-  if (!f32_segment(blockIdx.y, seg_expert, seg_off, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m, plist))
+  if (!f32_segment(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
+                   plist))
     return;
   const int f0 = (blockIdx.x * kFfnWaves + (int)(threadIdx.x >> 6)) * 4;
   if (f0 >= F) return;
@@ -701,12 +714,13 @@ __device__ __forceinline__ void down_f32_tile(const float *__restrict__ act, con
 template <bool kFew>
 __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
     const float *__restrict__ act, const float *__restrict__ w_down, const int32_t *__restrict__ seg_expert,
-    const int32_t *__restrict__ seg_off, const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count,
-    const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists, int list_stride, int M, int N, int k, int d,
-    int F, float *__restrict__ y) {
+    const int32_t *__restrict__ seg_off, const int4 *__restrict__ items, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int M, int N, int k, int d, int F, float *__restrict__ y) {
   int e, m;
   const int32_t *plist;
-  if (!f32_segment(blockIdx.y, seg_expert, seg_off, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m, plist))
+  if (!f32_segment(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
+                   plist))
     return;
   const int j0 = (blockIdx.x * kFfnWaves + (int)(threadIdx.x >> 6)) * kF32Rows;
   if (j0 >= d) return;
@@ -928,18 +942,20 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   // up to 4 workgroups share the pairs of a segment: enough waves to hide the loads where rows are few
   const int ptiles = (M + kF32Pairs - 1) / kF32Pairs, z = ptiles < 4 ? ptiles : 4;
   const bool few = M <= 2;
-  dim3 g1((F + 4 * kFfnWaves - 1) / (4 * kFfnWaves), n_seg, z);
+  const int4 *work = !rank_count && items_ready ? items : nullptr;
+  const int rows = work ? cap : n_seg;
+  dim3 g1((F + 4 * kFfnWaves - 1) / (4 * kFfnWaves), rows, z);
   auto gate_up = few ? ffn_gateup_f32_kernel<true> : ffn_gateup_f32_kernel<false>;
   gate_up<<<g1, kFfnThreads, 0, st>>>(
       static_cast<const float *>(h), static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up),
-      seg_expert, seg_off, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
+      seg_expert, seg_off, work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
       static_cast<float *>(act));
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(0);
-  dim3 g2((d + kF32Rows * kFfnWaves - 1) / (kF32Rows * kFfnWaves), n_seg, z);
+  dim3 g2((d + kF32Rows * kFfnWaves - 1) / (kF32Rows * kFfnWaves), rows, z);
   auto down = few ? ffn_down_f32_kernel<true> : ffn_down_f32_kernel<false>;
   down<<<g2, kFfnThreads, 0, st>>>(static_cast<const float *>(act), static_cast<const float *>(wt.w_down), seg_expert, seg_off,
-                                   perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
+                                   work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(1);
   if (!out) return hipSuccess;

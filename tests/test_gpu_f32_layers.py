@@ -1,6 +1,7 @@
 """fp32 layers where their kernels can go wrong: rows that are no multiple of a wave's 8 (4 gate) rows, K below and just
 above a wave's 64 elements, hidden sizes that end inside a block of the router projection, segments of 1, 4, 5, 8, 9 and
-more pairs, more pair tiles than workgroups share, and trees on both sides of the fused prologue's limits (experts and tokens)."""
+more pairs, more pair tiles than workgroups share, and trees on both sides of the fused prologue's limits (experts and
+tokens), with segments of several work items."""
 import pytest
 import torch
 
@@ -18,7 +19,7 @@ pytestmark = pytest.mark.gpu
                                          (64, 2, 2, 64, 8, 2), (68, 2, 2, 132, 9, 2), (132, 7, 3, 28, 33, 5),
                                          (100, 4, 2, 52, 300, 3), (48, 300, 5, 20, 11, 40),
                                          (64, 4, 2, 32, 256, 3), (64, 4, 2, 32, 257, 3),
-                                         (300, 5, 3, 332, 1, 4), (260, 3, 3, 516, 2, 3), (256, 2, 2, 256, 3, 2)])
+                                         (68, 9, 3, 44, 700, 7),                                          (300, 5, 3, 332, 1, 4), (260, 3, 3, 516, 2, 3), (256, 2, 2, 256, 3, 2)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_f32_layers(d, N, k, F, M, B, policy):
     print(f"case d={d} N={N} k={k} F={F} M={M} B={B} policy={policy}", flush=True)
