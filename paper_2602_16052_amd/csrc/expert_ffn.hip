@@ -616,28 +616,29 @@ __device__ __forceinline__ void f32_dots(const float *const (&row)[kF32Rows], co
 // caller's arrays.  Ranks and work items come largest first, so that the last round of workgroups is a short one, and work
 // items end at 128 pairs, so that more of them run side by side.  Whole layer of 300 tokens, us, by rank / by ascending
 // segment / by work item: 40 experts of 1024 x 512, top-6, 329 / 349 / 289; 8 of 256 x 1024, top-2, 159 / 155 / 91.
+// kItems: the kernels for work items are their own; as one more choice at run time it cost the others 3 %.
+template <bool kItems>
 __device__ __forceinline__ bool f32_segment(int seg, const int32_t *seg_expert, const int32_t *seg_off, const int4 *items,
                                             const int32_t *perm, const int32_t *rank_count, const int32_t *shortlist,
                                             const int32_t *lists, int list_stride, int M, int N, int k, int &e, int &m,
                                             const int32_t *&plist) {
+  if constexpr (kItems) {
+    if (seg >= items[0].x) return false;
+    const int4 it = items[1 + seg];  // gridDim.y does not exceed the table
+    e = it.y;
+    m = it.w;
+    plist = perm + it.z;
+    return segment_ok(e, it.z, m, (long long)M * k, N);
+  }
   if (rank_count) {
     e = shortlist[seg];
     m = rank_count[seg];
     plist = lists + (size_t)seg * list_stride;
     return e >= 0 && e < N && m > 0 && m <= M;
   }
-  int beg;
-  if (items) {
-    if (seg >= items[0].x) return false;
-    const int4 it = items[1 + seg];  // gridDim.y does not exceed the table
-    e = it.y;
-    beg = it.z;
-    m = it.w;
-  } else {
-    e = seg_expert[seg];
-    beg = seg_off[seg];
-    m = seg_off[seg + 1] - beg;
-  }
+  e = seg_expert[seg];
+  const int beg = seg_off[seg];
+  m = seg_off[seg + 1] - beg;
   plist = perm + beg;
   return segment_ok(e, beg, m, (long long)M * k, N);
 }
@@ -668,7 +669,7 @@ __device__ __forceinline__ void gateup_f32_tile(const float *__restrict__ h, con
 // against a tile of 4 pairs spent a third of the loads and three quarters of the sums on pairs that are not there (one token,
 // 2 experts of 4096 x 14336: 340 us per layer against 290; 8 of 1024 x 2048: 69 / 62).  A kernel of its own, because in one
 // kernel with the larger tiles each costs the other its registers (63 tokens, 8 experts of 512 x 1024: 65 -> 74 us).
-template <bool kFew>
+template <bool kFew, bool kItems>
 __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
     const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
     const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int4 *__restrict__ items,
@@ -676,7 +677,7 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
     const int32_t *__restrict__ lists, int list_stride, int M, int N, int k, int d, int F, float *__restrict__ act) {
   int e, m;
   const int32_t *plist;
-  if (!f32_segment(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
+  if (!f32_segment<kItems>(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
                    plist))
     return;
   const int f0 = (blockIdx.x * kFfnWaves + (int)(threadIdx.x >> 6)) * 4;
@@ -711,7 +712,7 @@ __device__ __forceinline__ void down_f32_tile(const float *__restrict__ act, con
   if (lane % LPS == 0 && j < d && p < m) y[(size_t)pair_at(plist, p, n_pairs) * d + j] = v;
 }
 
-template <bool kFew>
+template <bool kFew, bool kItems>
 __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
     const float *__restrict__ act, const float *__restrict__ w_down, const int32_t *__restrict__ seg_expert,
     const int32_t *__restrict__ seg_off, const int4 *__restrict__ items, const int32_t *__restrict__ perm,
@@ -719,7 +720,7 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
     int list_stride, int M, int N, int k, int d, int F, float *__restrict__ y) {
   int e, m;
   const int32_t *plist;
-  if (!f32_segment(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
+  if (!f32_segment<kItems>(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
                    plist))
     return;
   const int j0 = (blockIdx.x * kFfnWaves + (int)(threadIdx.x >> 6)) * kF32Rows;
@@ -945,7 +946,8 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   const int4 *work = !rank_count && items_ready ? items : nullptr;
   const int rows = work ? cap : n_seg;
   dim3 g1((F + 4 * kFfnWaves - 1) / (4 * kFfnWaves), rows, z);
-  auto gate_up = few ? ffn_gateup_f32_kernel<true> : ffn_gateup_f32_kernel<false>;
+  auto gate_up = work ? (few ? ffn_gateup_f32_kernel<true, true> : ffn_gateup_f32_kernel<false, true>)
+                      : (few ? ffn_gateup_f32_kernel<true, false> : ffn_gateup_f32_kernel<false, false>);
   gate_up<<<g1, kFfnThreads, 0, st>>>(
       static_cast<const float *>(h), static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up),
       seg_expert, seg_off, work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
@@ -953,7 +955,8 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(0);
   dim3 g2((d + kF32Rows * kFfnWaves - 1) / (kF32Rows * kFfnWaves), rows, z);
-  auto down = few ? ffn_down_f32_kernel<true> : ffn_down_f32_kernel<false>;
+  auto down = work ? (few ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
+                   : (few ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
   down<<<g2, kFfnThreads, 0, st>>>(static_cast<const float *>(act), static_cast<const float *>(wt.w_down), seg_expert, seg_off,
                                    work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
   if ((e = hipGetLastError()) != hipSuccess) return e;
