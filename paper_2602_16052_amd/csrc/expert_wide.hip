@@ -197,28 +197,27 @@ __global__ __launch_bounds__(kWideThreads, 2) void ffn_wide_kernel(
         for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       wide_walk<kGateUp, NB>(wa, aoff, x, boff, K, c0, lds, acc);
       const int col = lane & 15, kg = lane >> 4;
+      int pr[NB];  // one round of loads, not one per token tile
+#pragma unroll
+      for (int j = 0; j < NB; ++j) pr[j] = perm[beg + min((2 * j + wc) * 16 + col, m - 1)];
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
-        const int p = (2 * j + wc) * 16 + col;
-        if (p < m) {
-          int pr = perm[beg + p];
-          pr = pr < 0 ? 0 : (pr >= n_pairs ? n_pairs - 1 : pr);
+        pr[j] = pr[j] < 0 ? 0 : (pr[j] >= n_pairs ? n_pairs - 1 : pr[j]);
+        if ((2 * j + wc) * 16 + col < m) {
           if constexpr (kGateUp) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
               const int f = f0 + 32 * wr + 16 * i + 4 * kg;
-              uint16_t o[4];
+              f32x4 o;
 #pragma unroll
-              for (int c = 0; c < 4; ++c) o[c] = float_to_bf16_bits(silu_f(acc[i][j][c]) * acc[i + 2][j][c]);
-              if (f < R)
-                *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + (size_t)pr * R + f) =
-                    uint2{(uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16)};
+              for (int c = 0; c < 4; ++c) o[c] = silu_f(acc[i][j][c]) * acc[i + 2][j][c];
+              if (f < R) store_bf16x4(static_cast<uint16_t *>(out) + (size_t)pr[j] * R + f, o);
             }
           } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int f = f0 + 64 * wr + 16 * i + 4 * kg;
-              if (f < R) *reinterpret_cast<f32x4 *>(static_cast<float *>(out) + (size_t)pr * R + f) = acc[i][j];
+              if (f < R) *reinterpret_cast<f32x4 *>(static_cast<float *>(out) + (size_t)pr[j] * R + f) = acc[i][j];
             }
           }
         }
