@@ -66,21 +66,38 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T
   const int b0 = (int)((long long)part * n_blocks / parts), b1 = (int)((long long)(part + 1) * n_blocks / parts);
   const T *ha = h + (size_t)t * d + g * 8, *wb = w_r + (size_t)e * d + g * 8;
   f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-  constexpr int PB = 4;  // blocks in flight
-  for (int b = b0; b < b1; b += PB) {
-    LogitPiece<T> A[PB], Bv[PB];
+  // Two sets of PB blocks: the loads of one are in flight while the other is multiplied (511 tokens x 64 experts, d = 2048:
+  // 8.2 -> 6.7 us; at 4096 tokens four waves per SIMD hide them anyway, 28 us).
+  constexpr int PB = sizeof(T) == 2 ? 4 : 2;
+  LogitPiece<T> A[2][PB], Bv[2][PB];
+  auto load = [&](int set, int b) {
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
-      const int bb = min(b + u, b1 - 1);
-      A[u].load(ha + (size_t)bb * 32);
-      Bv[u].load(wb + (size_t)bb * 32);
+      const int bb = min(b + u, b1 - 1);  // past the end: the last block again, not multiplied
+      A[set][u].load(ha + (size_t)bb * 32);
+      Bv[set][u].load(wb + (size_t)bb * 32);
     }
+  };
+  auto multiply = [&](int set, int b) {
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
       if (b + u < b1) {  // uniform in the wave
 #pragma unroll
         for (int m = 0; m < 8; ++m)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u].get(m), Bv[u].get(m), acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[set][u].get(m), Bv[set][u].get(m), acc, 0, 0, 0);
+      }
+    }
+  };
+  if (b0 < b1) {
+    load(0, b0);
+    if (b1 - b0 <= PB) {
+      multiply(0, b0);
+    } else {
+      for (int b = b0; b < b1; b += 2 * PB) {
+        load(1, b + PB);
+        multiply(0, b);
+        load(0, b + 2 * PB);
+        multiply(1, b + PB);
       }
     }
   }
