@@ -26,6 +26,9 @@
 // Where its segment comes from: either from the work items that the budget stage has built beside the segment
 // arrays (seg_expert, seg_off, perm; any caller), or - inside the fused layer, for small trees - from the pair lists
 // of the fused prologue.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
 
 namespace moespec {
@@ -80,10 +83,12 @@ __device__ __forceinline__ bool xcd_map(int tiles, int L, int &rank, int &tile) 
 }
 // items[0].x = number of work items L; items[1 + r] = (segment index, expert, offset, size) of item r: the
 // non-empty segments, largest first, each cut into piece_count(size) pieces.  The table has cap + 1 entries.
-__device__ __forceinline__ int4 xcd_item(int tiles, int cap, const int4 *__restrict__ items, int &tile, int &rank) {
+// tiles_of(L, large): the row tiles of an item when there are L of them and large says that the largest has more than 64 pairs.
+template <class TF>
+__device__ __forceinline__ int4 xcd_item(TF tiles_of, int cap, const int4 *__restrict__ items, int &tile, int &rank) {
   int L = items[0].x;
   L = L < 0 ? 0 : (L > cap ? cap : L);
-  return xcd_map(tiles, L, rank, tile) ? items[1 + rank] : int4{-1, -1, 0, 0};
+  return xcd_map(tiles_of(L, L > 0 && items[1].w > 64), L, rank, tile) ? items[1 + rank] : int4{-1, -1, 0, 0};
 }
 // The table above built from segment arrays that did not come from the budget stage.  One workgroup.
 // Only well-formed segments take part (inside the pair table, at most one pair per token), and only as
@@ -154,21 +159,18 @@ constexpr int kLdsBytes = 65536;  // 32 KB of wave-private weight tiles + token 
 // called after the weight loads of the first chunk have been issued.  Loads complete in issue order, so the wait for
 // the (earlier issued) pair ids leaves those weight loads in flight: the expert's first bytes are on their way while
 // the token rows are still being looked up.
-// kPrivate: the waves of the workgroup walk over different parts of K and share nothing: each has token tiles of its own,
-// and nothing in the walk waits for another wave (the caller adds up the waves' sums).
-template <int NT, int U, bool kTail, bool kPrivate, class XF>
+template <int NT, int U, bool kTail, class XF>
 __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt1, int K, int kb, int kl, int ks,
                                          const uint16_t *xbase, XF make_xsrc, unsigned char *lds,
                                          f32x4 (&acc0)[NT], f32x4 (&acc1)[NT]) {
   using C = Chunk<U>;
-  constexpr int IPW = kPrivate ? NT * U : NT * U / 4;  // token-tile loads per wave per chunk (or 4 waves share the tile)
+  constexpr int IPW = NT * U / 4;  // token-tile loads per wave per chunk (4 waves share the tile)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned char *a_lds = lds + wave * 2 * C::TILE;                 // wave-private: two weight tiles
   constexpr int XBUF = NT * 16 * C::RB;
-  unsigned char *x_lds = lds + kFfnWaves * 2 * C::TILE + (kPrivate ? wave * XBUF : 0);  // shared: 2 buffers of NT*16 rows
-  static_assert(!kPrivate || kFfnWaves * (2 * C::TILE + XBUF) <= kLdsBytes, "private token tiles fit the LDS");
+  unsigned char *x_lds = lds + kFfnWaves * 2 * C::TILE;  // shared: 2 buffers of NT*16 rows
   // two token-tile buffers if they fit beside the weight tiles, else one (and a second barrier per chunk)
-  constexpr bool kDoubleX = !kPrivate && kFfnWaves * 2 * C::TILE + 2 * XBUF <= kLdsBytes;
+  constexpr bool kDoubleX = kFfnWaves * 2 * C::TILE + 2 * XBUF <= kLdsBytes;
 
   // global -> register staging
   // uniform base + 32-bit byte offset per lane (a tile is 16 rows of at most 2^20 elements): the loads need
@@ -213,7 +215,7 @@ __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt
     }
 #pragma unroll
     for (int q = 0; q < IPW; ++q) {
-      const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
+      const int g = (wave * IPW + q) * 64 + lane;
       *reinterpret_cast<bf16x8 *>(x_lds + buf * XBUF + C::swz(g / C::CPR, g % C::CPR)) = GX[q];
     }
   };
@@ -275,13 +277,114 @@ __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt
     k += C::KC;
     k = k >= nst * C::KC ? 0 : k;
     if (i + 1 < nst) issue(kb + k);
-    if constexpr (kPrivate) wave_lds_sync();
-    else __syncthreads();  // token tile i complete; also orders this wave's tile writes before its reads
+    __syncthreads();  // token tile i complete; also orders this wave's tile writes before its reads
     compute(kDoubleX ? (i & 1) : 0);
-    if constexpr (kPrivate) wave_lds_sync();
-    else if (!kDoubleX) __syncthreads();  // everybody has read the single token tile before it is overwritten
+    if (!kDoubleX) __syncthreads();  // everybody has read the single token tile before it is overwritten
   }
   __syncthreads();  // the LDS tiles may be reused by the caller's next pass
+}
+
+// The walk of a wave that has a part [kb, kb + kl) of K to itself: it shares nothing with the other waves and waits for none
+// of them (the caller adds up their sums).  Two token tiles at a time go through the LDS, against the chunk of weights parked
+// there, so that a chunk is read from memory once for all NT tiles.  Loads return in the order of their issue: the next
+// chunk of weights is requested after the last tokens of the present one.  make_off(xsrc) is called with the first weights on
+// their way.  Up to two token tiles: it fills xsrc with the byte offsets from xbase of the rows that this lane loads.  More: it fills
+// xoff[0 .. 16 NT), in the LDS, with those of all pairs, and synchronises.
+template <int NT, bool kTail, class XF>
+__device__ __forceinline__ void cut_pass(const uint16_t *wt0, const uint16_t *wt1, int K, int kb, int kl, int ks,
+                                         const uint16_t *xbase, const uint32_t *xoff, XF make_off, unsigned char *lds,
+                                         f32x4 (&acc0)[NT], f32x4 (&acc1)[NT]) {
+  constexpr int U = 4;
+  using C = Chunk<U>;
+  constexpr int G = NT < 2 ? 1 : 2, NG = NT / G, IPW = G * U;  // tiles and loads of a group of tokens
+  static_assert(kFfnWaves * (2 + G) * C::TILE <= kLdsBytes, "private tiles fit the LDS");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  unsigned char *a_lds = lds + wave * (2 + G) * C::TILE, *x_lds = a_lds + 2 * C::TILE;
+  const int lrow = lane / C::CPR, lpc = lane % C::CPR;
+  const uint32_t lane_off = 2u * ((uint32_t)lrow * (uint32_t)K + (uint32_t)lpc * 8u);
+  bf16x8 GA[2][U], GX[IPW];
+  uint32_t xsrc[IPW];
+  auto inside = [&](int k) { return !kTail || k + lpc * 8 < kb + kl; };  // see lds_pass
+  auto issue_w = [&](int k) {
+    const uint32_t back = inside(k) ? 0u : (uint32_t)lpc * 16u;
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const uint32_t off = lane_off + 2u * ((uint32_t)(q * C::RPI) * (uint32_t)K + (uint32_t)k) - back;
+      GA[0][q] = ld_stream(at_bytes(wt0, off));
+      GA[1][q] = ld_stream(at_bytes(wt1, off));
+    }
+  };
+  auto issue_x = [&](int g, int k) {
+    const uint32_t at = 2u * (uint32_t)k + (inside(k) ? (uint32_t)lpc * 16u : 0u);
+#pragma unroll
+    for (int q = 0; q < IPW; ++q)
+      GX[q] = ld_frag(at_bytes(xbase, (NG == 1 ? xsrc[q] : xoff[g * 16 * G + q * C::RPI + lrow]) + at));
+  };
+  auto park_w = [&](int k) {
+    const bool in = inside(k);
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int row = q * C::RPI + lrow;
+      *reinterpret_cast<bf16x8 *>(a_lds + C::swz(row, lpc)) = in ? GA[0][q] : bf16x8{};
+      *reinterpret_cast<bf16x8 *>(a_lds + C::TILE + C::swz(row, lpc)) = in ? GA[1][q] : bf16x8{};
+    }
+  };
+  auto park_x = [&](int k) {
+    const bool in = inside(k);
+#pragma unroll
+    for (int q = 0; q < IPW; ++q)
+      *reinterpret_cast<bf16x8 *>(x_lds + C::swz(q * C::RPI + lrow, lpc)) = in ? GX[q] : bf16x8{};
+  };
+  const int r = lane & 15, kg = lane >> 4;
+  auto compute = [&](int g) {
+    bf16x8 fa0[2], fa1[2], fb[2][G];  // the operands of step u + 1 are read before the matrix instructions of step u
+    auto fetch = [&](int u) {
+      const int pc = 4 * u + kg, st = u & 1;
+      fa0[st] = *reinterpret_cast<const bf16x8 *>(a_lds + C::swz(r, pc));
+      fa1[st] = *reinterpret_cast<const bf16x8 *>(a_lds + C::TILE + C::swz(r, pc));
+#pragma unroll
+      for (int j = 0; j < G; ++j) fb[st][j] = *reinterpret_cast<const bf16x8 *>(x_lds + C::swz(16 * j + r, pc));
+    };
+    fetch(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u + 1 < U) fetch(u + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < G; ++j) {
+        acc0[g * G + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0[u & 1], fb[u & 1][j], acc0[g * G + j], 0, 0, 0);
+        acc1[g * G + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1[u & 1], fb[u & 1][j], acc1[g * G + j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  const int nst = kTail ? (kl + C::KC - 1) / C::KC : kl / C::KC;
+  int k = ((ks % kl) / C::KC) * C::KC;
+  issue_w(kb + k);
+  __builtin_amdgcn_sched_barrier(0);  // keep the weight loads ahead of the wait for the pair ids
+  make_off(xsrc);
+  issue_x(0, kb + k);
+  // one chunk; last: none behind it.  Without a branch around the loads, so that the waits can be counted.
+  auto chunk = [&](auto last_) {
+    constexpr bool last = decltype(last_)::value;
+    int kn = k + C::KC;
+    kn = kn >= nst * C::KC ? 0 : kn;
+    park_w(kb + k);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      park_x(kb + k);
+      if (g + 1 < NG) issue_x(g + 1, kb + k);
+      if (!last && g + 2 >= NG && (NG == 1 || g + 2 == NG)) issue_w(kb + kn);
+      if (!last && g + 1 == NG) issue_x(0, kb + kn);
+      wave_lds_sync();
+      compute(g);
+      wave_lds_sync();
+    }
+    k = kn;
+  };
+  for (int i = 0; i + 1 < nst; ++i) chunk(std::false_type{});
+  chunk(std::true_type{});
+  __syncthreads();  // the caller reuses the LDS
 }
 
 // The workgroup's work item found in the fused prologue's lists: shortlist[r] = expert with rank r in the shortlist
@@ -290,8 +393,10 @@ __device__ __forceinline__ void lds_pass(const uint16_t *wt0, const uint16_t *wt
 // experts in rank order; the workgroup takes the one that xcd_map assigns to it.  Requires B <= kFfnThreads.
 // misc: 8 int32 of LDS scratch.  Called by every thread of the workgroup (it synchronises).  Returns the expert (-1: no
 // work item), its piece of m pairs (list) and the work item's number.
+constexpr int kLargeFlag = 1 << 16;  // above any number of pieces: kSelfMaxExperts of kSelfMaxTokens / kPiecePairs each
+template <class TF>
 __device__ __forceinline__ int listed_segment(const int32_t *__restrict__ rank_count,
-                                              const int32_t *__restrict__ shortlist, int B, int tiles, int32_t *misc,
+                                              const int32_t *__restrict__ shortlist, int B, TF tiles_of, int32_t *misc,
                                               int &m, int &item, int &tile, const int32_t *__restrict__ lists,
                                               int list_stride, const int32_t *&list) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -304,15 +409,18 @@ __device__ __forceinline__ int listed_segment(const int32_t *__restrict__ rank_c
     const int v = __shfl_up(incl, sft, kWave);
     if (lane >= sft) incl += v;
   }
-  if (lane == kWave - 1) misc[1 + wave] = incl;
+  const bool large = __ballot(c > 64) != 0;
+  if (lane == kWave - 1) misc[1 + wave] = incl | (large ? kLargeFlag : 0);
   if (tid == 0) misc[0] = -1;
   __syncthreads();
-  int before = 0, n_items = 0;
+  int before = 0, n_items = 0, flags = 0;
   for (int w = 0; w < kFfnWaves; ++w) {
-    if (w < wave) before += misc[1 + w];
-    n_items += misc[1 + w];
+    const int n = misc[1 + w];
+    if (w < wave) before += n & (kLargeFlag - 1);
+    n_items += n & (kLargeFlag - 1);
+    flags |= n;
   }
-  const bool has_work = xcd_map(tiles, n_items, item, tile);
+  const bool has_work = xcd_map(tiles_of(n_items, (flags & kLargeFlag) != 0), n_items, item, tile);
   const int first = before + incl - q;  // first work item of this thread's expert
   if (has_work && item >= first && item < first + q) {  // one thread at most
     const int len = (c + q - 1) / q, p = item - first;
@@ -328,17 +436,32 @@ __device__ __forceinline__ int listed_segment(const int32_t *__restrict__ rank_c
   return e;
 }
 
+// Whether the 4 waves of a workgroup take a quarter of K each (cut_pass) instead of a quarter of its rows (lds_pass): the same
+// bytes are in flight per workgroup, but there are four times as many of them and a walk is a quarter as long; in exchange
+// every 32 weight rows load the tokens for themselves.  That pays until the workgroups of the other form, `units`, would
+// occupy every second compute unit, and a little longer where a walk by rows is slowed down by more than 64 pairs.  489
+// passes measured (512 to 4096 x 128 to 2048, 1 to 250 tokens, 1 to 85 loaded experts), time by rows / by K: 1.0 to 2.2,
+// mostly 1.5, at up to 120 units; then up to 64 pairs 1.1 to 1.35 at 128 to 135, 0.85 to 0.95 at 140 to 200; more
+// pairs 1.0 to 1.7 at 130 to 160, 0.75 to 1.7 at 160 to 190, 0.8 to 1.0 above 200 (gate/up of 42 experts of 2048 x 192 with up
+// to 126 pairs, 126 units: 37.7 / 20.5 us; of 27 of 2048 x 1024, 432 units: 40 / 52).  How many experts are loaded is known
+// here only: the host's bound, the shortlist, is up to ten times that.
+constexpr int kCutUnits = 132, kCutUnitsLarge = 176;
+__device__ __forceinline__ bool walk_is_cut(int units, bool large, int K, int splits) {
+  return splits == 1 && K >= 4 * 128 && units <= (large ? kCutUnitsLarge : kCutUnits);
+}
+
 // plist: the segment's pairs (flat ids t * k + slot, tokens ascending), in global memory or LDS; n_pairs = M * k.
 __device__ __forceinline__ int pair_at(const int32_t *plist, int p, int n_pairs) {
   const int q = plist[p];
   return q < 0 ? 0 : (q >= n_pairs ? n_pairs - 1 : q);
 }
 
-// The sums of the 4 waves added in wave order; wave j gets the total of token tile j.  Synchronises; the caller may use the
+// The sums of the 4 waves added in wave order; wave w gets the totals of the token tiles w, w + 4.  Synchronises; the caller may use the
 // LDS again afterwards.
 template <int NT>
 __device__ __forceinline__ void add_waves(unsigned char *lds, f32x4 (&a0)[NT], f32x4 (&a1)[NT]) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  static_assert(kFfnWaves * NT * 2 * 64 * sizeof(f32x4) <= kLdsBytes, "the sums fit the LDS");
   f32x4 *part = reinterpret_cast<f32x4 *>(lds);  // [wave][tile][2][lane]
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
@@ -348,7 +471,7 @@ __device__ __forceinline__ void add_waves(unsigned char *lds, f32x4 (&a0)[NT], f
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < NT; ++j)
-    if (j == wave) {
+    if (j % kFfnWaves == wave) {
       a0[j] = part[(j * 2 + 0) * 64 + lane];
       a1[j] = part[(j * 2 + 1) * 64 + lane];
 #pragma unroll
@@ -360,54 +483,68 @@ __device__ __forceinline__ void add_waves(unsigned char *lds, f32x4 (&a0)[NT], f
   __syncthreads();
 }
 
-template <int NT, int U, bool kTail, bool kPrivate>
+// Whether token tile j is this wave's to store (kCut: the waves have shared the tiles out, see add_waves).
+template <bool kCut>
+__device__ __forceinline__ bool own_tile(int j, int wave) { return !kCut || j % kFfnWaves == wave; }
+
+// kCut: cut_pass instead of lds_pass, the waves' sums added up; xoff: 128 words of LDS for it.
+template <int NT, bool kTail, bool kCut>
 __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *wt1, const uint16_t *__restrict__ h,
-                                           const int32_t *plist, int n_pairs, int k, int d, int F, int kb, int kl, int c0,
-                                           int m, int f0, int ks, unsigned char *lds, uint16_t *__restrict__ act) {
-  using C = Chunk<U>;
-  constexpr int IPW = kPrivate ? NT * U : NT * U / 4;
+                                           const int32_t *plist, int n_pairs, int k, int d, int F, int kb, int kl, int m,
+                                           int f0, int ks, unsigned char *lds, uint32_t *xoff, uint16_t *__restrict__ act) {
+  using C = Chunk<4>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int pair[IPW];  // this lane's pair ids, loaded now and turned into row offsets inside lds_pass
-#pragma unroll
-  for (int q = 0; q < IPW; ++q) {
-    const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
-    int p = c0 + g / C::CPR;
-    p = p < m ? p : m - 1;  // pad rows repeat the last token; their columns are never stored
-    pair[q] = plist[p];
-  }
   // 32-bit byte offsets: M * d < 2^31 elements (checked on the host)
-  auto make_xsrc = [&](uint32_t (&xsrc)[IPW]) {
-#pragma unroll
-    for (int q = 0; q < IPW; ++q) {
-      const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
-      const int pr = pair[q] < 0 ? 0 : (pair[q] >= n_pairs ? n_pairs - 1 : pair[q]);
-      xsrc[q] = 2u * ((uint32_t)(pr / k) * (uint32_t)d + (uint32_t)(g % C::CPR) * 8u);
-    }
+  auto row_off = [&](int pr) {
+    pr = pr < 0 ? 0 : (pr >= n_pairs ? n_pairs - 1 : pr);
+    return 2u * ((uint32_t)(pr / k) * (uint32_t)d);
   };
   f32x4 accg[NT], accu[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) accg[j] = accu[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  lds_pass<NT, U, kTail, kPrivate>(wt0, wt1, d, kb, kl, ks, h, make_xsrc, lds, accg, accu);
-  if constexpr (kPrivate) add_waves<NT>(lds, accg, accu);
+  if constexpr (kCut) {
+    constexpr bool kFew = NT <= 2;  // see cut_pass; pad rows repeat the last pair, and their columns are never stored
+    constexpr int kPairs = kFew ? 4 * NT : 1;
+    int pair[kPairs];
+#pragma unroll
+    for (int q = 0; q < kPairs; ++q) pair[q] = plist[min(kFew ? q * C::RPI + lane / C::CPR : (int)threadIdx.x, m - 1)];
+    auto make_off = [&](auto &xsrc) {
+      if constexpr (kFew) {
+#pragma unroll
+        for (int q = 0; q < kPairs; ++q) xsrc[q] = row_off(pair[q]);
+      } else {
+        if (threadIdx.x < 16 * NT) xoff[threadIdx.x] = row_off(pair[0]);
+        __syncthreads();
+      }
+    };
+    cut_pass<NT, kTail>(wt0, wt1, d, kb, kl, ks, h, xoff, make_off, lds, accg, accu);
+    add_waves<NT>(lds, accg, accu);
+  } else {
+    int pair[NT];  // this lane's pair ids, loaded now and turned into row offsets inside lds_pass
+#pragma unroll
+    for (int q = 0; q < NT; ++q) pair[q] = plist[min(((wave * NT + q) * 64 + lane) / C::CPR, m - 1)];
+    auto make_xsrc = [&](uint32_t (&xsrc)[NT]) {
+#pragma unroll
+      for (int q = 0; q < NT; ++q) xsrc[q] = row_off(pair[q]) + (uint32_t)(lane % C::CPR) * 16u;
+    };
+    lds_pass<NT, 4, kTail>(wt0, wt1, d, kb, kl, ks, h, make_xsrc, lds, accg, accu);
+  }
   const int col = lane & 15, kg = lane >> 4;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
-    const int p = c0 + j * 16 + col;
-    if (p < m && (!kPrivate || j == wave)) {
-      uint16_t o[4];
+    const int p = j * 16 + col;
+    if (p < m && own_tile<kCut>(j, wave)) {
+      f32x4 o;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = float_to_bf16_bits(silu_f(accg[j][i]) * accu[j][i]);
-      uint2 pk;
-      pk.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
-      pk.y = (uint32_t)o[2] | ((uint32_t)o[3] << 16);
-      *reinterpret_cast<uint2 *>(act + (size_t)pair_at(plist, p, n_pairs) * F + f0 + 4 * kg) = pk;
+      for (int i = 0; i < 4; ++i) o[i] = silu_f(accg[j][i]) * accu[j][i];
+      store_bf16x4(act + (size_t)pair_at(plist, p, n_pairs) * F + f0 + 4 * kg, o);
     }
   }
 }
 
 // rank_count != NULL: work items from the prologue's lists (items / perm unused; n_seg = B); otherwise items + perm.
-// kPrivate: a workgroup takes 16 gate and the same 16 up rows (down: 32 rows) and its 4 waves a quarter of K each.
-template <bool kTail, bool kPrivate>
+// A workgroup takes 64 gate and the same 64 up rows of an item, or, with its walk cut, 16 and 16.
+template <bool kTail>
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
     const uint16_t *__restrict__ h, const uint16_t *__restrict__ w_gate, const uint16_t *__restrict__ w_up,
     const int4 *__restrict__ items, const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count,
@@ -415,14 +552,20 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
     const int32_t *__restrict__ lists, int list_stride, uint16_t *__restrict__ act) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
   __shared__ int32_t misc[8];
-  const int tiles = kPrivate ? F / 16 : (F / 16 + kFfnWaves - 1) / kFfnWaves;
+  __shared__ uint32_t xoff[kPiecePairs];
+  const int row_tiles = (F / 16 + kFfnWaves - 1) / kFfnWaves;
+  bool cut = false;
+  auto tiles_of = [&](int n_items, bool large) {
+    cut = walk_is_cut(n_items * row_tiles, large, d, 1);
+    return cut ? F / 16 : row_tiles;
+  };
   int tile, rank, e, m;
   const int32_t *plist;
   if (rank_count) {
-    e = listed_segment(rank_count, shortlist, n_seg, tiles, misc, m, rank, tile, lists, list_stride, plist);
+    e = listed_segment(rank_count, shortlist, n_seg, tiles_of, misc, m, rank, tile, lists, list_stride, plist);
     if (e < 0 || e >= N || m <= 0 || m > kPiecePairs) return;
   } else {
-    const int4 it = xcd_item(tiles, cap, items, tile, rank);
+    const int4 it = xcd_item(tiles_of, cap, items, tile, rank);
     e = it.y;
     m = it.w;
     if (it.x < 0 || m > kPiecePairs || !segment_ok(e, it.z, m, (long long)M * k, N)) return;
@@ -431,65 +574,73 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // F is a multiple of 32 but a workgroup covers 64 gate rows: the waves of a last, partial workgroup
   // redo rows of the previous tile (same values, same destination) so that every wave reaches the barriers.
-  int f0 = kPrivate ? tile * 16 : (tile * kFfnWaves + wave) * 16;
+  int f0 = cut ? tile * 16 : (tile * kFfnWaves + wave) * 16;
   f0 = f0 < F ? f0 : F - 16;
   const uint16_t *wt0 = w_gate + ((size_t)e * F + f0) * d;
   const uint16_t *wt1 = w_up + ((size_t)e * F + f0) * d;
-  int kb = 0, kl = d;
-  if (kPrivate) {
-    const int nch = (d + 127) / 128;
-    kb = wave * nch / kFfnWaves * 128;
-    kl = min((wave + 1) * nch / kFfnWaves * 128, d) - kb;
-  }
-  const int ks = k_stagger(5 * e + 3 * tile, kl);
   const int n_pairs = M * k;
-  if constexpr (kPrivate) {
-    for (int c0 = 0; c0 < m; c0 += 32) {
-      if (m - c0 <= 16) gateup_lds<1, 4, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
-      else gateup_lds<2, 4, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, c0, m, f0, ks, lds, act);
-    }
+  if (cut) {
+    const int nch = (d + 127) / 128, kb = wave * nch / kFfnWaves * 128, kl = min((wave + 1) * nch / kFfnWaves * 128, d) - kb;
+    const int ks = k_stagger(5 * e + 3 * tile, kl);
+    if (m <= 16) gateup_lds<1, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, m, f0, ks, lds, xoff, act);
+    else if (m <= 32) gateup_lds<2, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, m, f0, ks, lds, xoff, act);
+    else if (m <= 64) gateup_lds<4, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, m, f0, ks, lds, xoff, act);
+    else gateup_lds<8, kTail, true>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, m, f0, ks, lds, xoff, act);
   } else {
-    if (m <= 16) gateup_lds<1, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, 0, m, f0, ks, lds, act);
-    else if (m <= 32) gateup_lds<2, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, 0, m, f0, ks, lds, act);
-    else if (m <= 64) gateup_lds<4, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, 0, m, f0, ks, lds, act);
-    else gateup_lds<8, 4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, kb, kl, 0, m, f0, ks, lds, act);
+    const int ks = k_stagger(5 * e + 3 * tile, d);
+    if (m <= 16) gateup_lds<1, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, 0, d, m, f0, ks, lds, xoff, act);
+    else if (m <= 32) gateup_lds<2, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, 0, d, m, f0, ks, lds, xoff, act);
+    else if (m <= 64) gateup_lds<4, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, 0, d, m, f0, ks, lds, xoff, act);
+    else gateup_lds<8, kTail, false>(wt0, wt1, h, plist, n_pairs, k, d, F, 0, d, m, f0, ks, lds, xoff, act);
   }
 }
 
-template <int NT, int U, bool kTail, bool kPrivate>
+template <int NT, bool kTail, bool kCut>
 __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt1, const uint16_t *__restrict__ act,
-                                         const int32_t *plist, int n_pairs, int d, int F, int kb, int kl, int c0, int m,
-                                         int j0, int ks, unsigned char *lds, float *__restrict__ y) {
-  using C = Chunk<U>;
-  constexpr int IPW = kPrivate ? NT * U : NT * U / 4;
+                                         const int32_t *plist, int n_pairs, int d, int F, int kb, int kl, int m, int j0,
+                                         int ks, unsigned char *lds, uint32_t *xoff, float *__restrict__ y) {
+  using C = Chunk<4>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int pair[IPW];  // this lane's pair ids, loaded now and turned into row offsets inside lds_pass
-#pragma unroll
-  for (int q = 0; q < IPW; ++q) {
-    const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
-    int p = c0 + g / C::CPR;
-    p = p < m ? p : m - 1;
-    pair[q] = plist[p];
-  }
   // 32-bit byte offsets: M * k * F < 2^31 elements (checked on the host)
-  auto make_xsrc = [&](uint32_t (&xsrc)[IPW]) {
-#pragma unroll
-    for (int q = 0; q < IPW; ++q) {
-      const int g = ((kPrivate ? 0 : wave * IPW) + q) * 64 + lane;
-      const int pr = pair[q] < 0 ? 0 : (pair[q] >= n_pairs ? n_pairs - 1 : pair[q]);
-      xsrc[q] = 2u * ((uint32_t)pr * (uint32_t)F + (uint32_t)(g % C::CPR) * 8u);
-    }
+  auto row_off = [&](int pr) {
+    pr = pr < 0 ? 0 : (pr >= n_pairs ? n_pairs - 1 : pr);
+    return 2u * ((uint32_t)pr * (uint32_t)F);
   };
   f32x4 acc0[NT], acc1[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) acc0[j] = acc1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  lds_pass<NT, U, kTail, kPrivate>(wt0, wt1, F, kb, kl, ks, act, make_xsrc, lds, acc0, acc1);
-  if constexpr (kPrivate) add_waves<NT>(lds, acc0, acc1);
+  if constexpr (kCut) {
+    constexpr bool kFew = NT <= 2;
+    constexpr int kPairs = kFew ? 4 * NT : 1;
+    int pair[kPairs];
+#pragma unroll
+    for (int q = 0; q < kPairs; ++q) pair[q] = plist[min(kFew ? q * C::RPI + lane / C::CPR : (int)threadIdx.x, m - 1)];
+    auto make_off = [&](auto &xsrc) {
+      if constexpr (kFew) {
+#pragma unroll
+        for (int q = 0; q < kPairs; ++q) xsrc[q] = row_off(pair[q]);
+      } else {
+        if (threadIdx.x < 16 * NT) xoff[threadIdx.x] = row_off(pair[0]);
+        __syncthreads();
+      }
+    };
+    cut_pass<NT, kTail>(wt0, wt1, F, kb, kl, ks, act, xoff, make_off, lds, acc0, acc1);
+    add_waves<NT>(lds, acc0, acc1);
+  } else {
+    int pair[NT];  // this lane's pair ids, loaded now and turned into row offsets inside lds_pass
+#pragma unroll
+    for (int q = 0; q < NT; ++q) pair[q] = plist[min(((wave * NT + q) * 64 + lane) / C::CPR, m - 1)];
+    auto make_xsrc = [&](uint32_t (&xsrc)[NT]) {
+#pragma unroll
+      for (int q = 0; q < NT; ++q) xsrc[q] = row_off(pair[q]) + (uint32_t)(lane % C::CPR) * 16u;
+    };
+    lds_pass<NT, 4, kTail>(wt0, wt1, F, kb, kl, ks, act, make_xsrc, lds, acc0, acc1);
+  }
   const int col = lane & 15, kg = lane >> 4;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
-    const int p = c0 + j * 16 + col;
-    if (p < m && (!kPrivate || j == wave)) {
+    const int p = j * 16 + col;
+    if (p < m && own_tile<kCut>(j, wave)) {
       float *dst = y + (size_t)pair_at(plist, p, n_pairs) * d + j0 + 4 * kg;
       *reinterpret_cast<f32x4 *>(dst) = acc0[j];
       *reinterpret_cast<f32x4 *>(dst + 16) = acc1[j];
@@ -497,7 +648,7 @@ __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt
   }
 }
 
-template <bool kTail, bool kPrivate>
+template <bool kTail>
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
     const uint16_t *__restrict__ act, const uint16_t *__restrict__ w_down, const int4 *__restrict__ items,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
@@ -505,44 +656,50 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
     int list_stride, float *__restrict__ y) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
   __shared__ int32_t misc[8];
+  __shared__ uint32_t xoff[kPiecePairs];
   // a work item is (row tile, K split): split sp sums the 128-element chunks [sp n / splits, (sp + 1) n / splits)
   // of F into its own copy of y, which the combine adds up in split order
-  const int tiles = kPrivate ? d / 32 : ((d / 32 + kFfnWaves - 1) / kFfnWaves) * splits;  // kPrivate: splits == 1
+  const int row_tiles = ((d / 32 + kFfnWaves - 1) / kFfnWaves) * splits;
+  bool cut = false;
+  auto tiles_of = [&](int n_items, bool large) {
+    cut = walk_is_cut(n_items * row_tiles, large, F, splits);
+    return cut ? d / 32 : row_tiles;
+  };
   int tile, rank, e, m;
   const int32_t *plist;
   if (rank_count) {
-    e = listed_segment(rank_count, shortlist, n_seg, tiles, misc, m, rank, tile, lists, list_stride, plist);
+    e = listed_segment(rank_count, shortlist, n_seg, tiles_of, misc, m, rank, tile, lists, list_stride, plist);
     if (e < 0 || e >= N || m <= 0 || m > kPiecePairs) return;
   } else {
-    const int4 it = xcd_item(tiles, cap, items, tile, rank);
+    const int4 it = xcd_item(tiles_of, cap, items, tile, rank);
     e = it.y;
     m = it.w;
     if (it.x < 0 || m > kPiecePairs || !segment_ok(e, it.z, m, (long long)M * k, N)) return;
     plist = perm + it.z;
   }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int sp = tile % splits;
-  tile /= splits;
-  int j0 = kPrivate ? tile * 32 : (tile * kFfnWaves + wave) * 32;
+  const int sp = cut ? 0 : tile % splits;
+  if (!cut) tile /= splits;
+  int j0 = cut ? tile * 32 : (tile * kFfnWaves + wave) * 32;
   j0 = j0 < d ? j0 : d - 32;  // see ffn_gateup_lds_kernel
   const uint16_t *wt0 = w_down + ((size_t)e * d + j0) * F;
   const uint16_t *wt1 = wt0 + (size_t)16 * F;
-  const int part = kPrivate ? wave : sp, parts = kPrivate ? kFfnWaves : splits;
+  const int part = cut ? wave : sp, parts = cut ? kFfnWaves : splits;
   const int nch = (F + 127) / 128, kb = (int)((long long)part * nch / parts) * 128;
   const int kl = min((int)((long long)(part + 1) * nch / parts) * 128, F) - kb;
   const int ks = k_stagger(5 * e + sp + 3 * tile, kl);
   const int n_pairs = M * k;
   y += (size_t)sp * n_pairs * d;
-  if constexpr (kPrivate) {
-    for (int c0 = 0; c0 < m; c0 += 32) {
-      if (m - c0 <= 16) down_lds<1, 4, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-      else down_lds<2, 4, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, c0, m, j0, ks, lds, y);
-    }
+  if (cut) {
+    if (m <= 16) down_lds<1, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, m, j0, ks, lds, xoff, y);
+    else if (m <= 32) down_lds<2, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, m, j0, ks, lds, xoff, y);
+    else if (m <= 64) down_lds<4, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, m, j0, ks, lds, xoff, y);
+    else down_lds<8, kTail, true>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, m, j0, ks, lds, xoff, y);
   } else {
-    if (m <= 16) down_lds<1, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, 0, m, j0, ks, lds, y);
-    else if (m <= 32) down_lds<2, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, 0, m, j0, ks, lds, y);
-    else if (m <= 64) down_lds<4, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, 0, m, j0, ks, lds, y);
-    else down_lds<8, 4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, 0, m, j0, ks, lds, y);
+    if (m <= 16) down_lds<1, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, m, j0, ks, lds, xoff, y);
+    else if (m <= 32) down_lds<2, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, m, j0, ks, lds, xoff, y);
+    else if (m <= 64) down_lds<4, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, m, j0, ks, lds, xoff, y);
+    else down_lds<8, kTail, false>(wt0, wt1, act, plist, n_pairs, d, F, kb, kl, m, j0, ks, lds, xoff, y);
   }
 }
 
@@ -860,15 +1017,13 @@ int down_splits(const moespec_desc &ds, int M, int n_seg) {
   return expert_down_wide(ds, M, n_seg) ? 1 : streaming_down_splits(ds, n_seg);
 }
 
-// Whether the 4 waves of a workgroup take a quarter of K each instead of a quarter of its rows: the same bytes are in
-// flight, but a walk is a quarter as long and there are four times as many workgroups, for up to 32 pairs at a time.
-// That pays where the workgroups are few: always with one for every fourth compute unit, and up to one for every second
-// if no segment can need a second round of pairs.  Measured per layer, by rows / by K, us (2048 hidden, top-2 to top-8):
-// 4 experts of width 2048, 32 tokens (128 workgroups) 50 / 41; 4 of 1024, 128 tokens (64) 77 / 68; but 8 of 1024, 64 tokens
-// (128) 54 / 60; 2 of 4096, 128 tokens (128) 92 / 104; 15 of 1024, 63 tokens (240) 60 / 81.
-static bool walk_is_cut(int K, int M, int n_seg, int row_tiles, int splits) {
-  const long long wgs = (long long)n_seg * row_tiles;
-  return splits == 1 && K >= 4 * 128 && (wgs <= 64 || (wgs <= 128 && M <= 32));
+// Workgroups of a streaming pass.  The device picks the form of the walk: room for whole rounds of 8 of n_items items in
+// row tiles, and for kCutUnitsLarge units of which each is up to four (and a last round that is dealt to 8 XCDs).
+static int pass_grid(int row_tiles, int cut_tiles, int n_items, int K, int splits) {
+  const int by_rows = xcd_grid(row_tiles, n_items);
+  if (splits != 1 || K < 4 * 128) return by_rows;
+  const long long by_k = std::min<long long>((long long)xcd_grid(cut_tiles, n_items), 4 * kCutUnitsLarge + kXcds);
+  return std::max<long long>(by_rows, by_k);
 }
 
 hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int n_seg,
@@ -885,6 +1040,8 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   const bool wide_gate_up = !rank_count && expert_ffn_wide(ds, M, n_seg);
   const bool wide_down = !rank_count && expert_down_wide(ds, M, n_seg);
   const int cap = items_capacity(n_seg, M, k);  // work items of the LDS-tiled passes
+  // ... and how many there can be: the prologue's and the budget stage's segments hold every pair once at most
+  const int most = rank_count || items_ready ? (int)std::min<long long>(cap, (long long)M * k) : cap;
   if (ds.dtype == MOESPEC_BF16 && !rank_count && !items_ready) {
     segment_items_kernel<<<1, 256, 0, st>>>(seg_expert, seg_off, n_seg, M, k, cap, items);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -903,22 +1060,18 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
         mark(pass - 1);
         continue;
       }
-      // with few workgroups a pass takes as long as one walk over K: cut it in four
       const int K = pass == 1 ? d : F, row_tiles = pass == 1 ? (F / 16 + kFfnWaves - 1) / kFfnWaves
                                                              : (d / 32 + kFfnWaves - 1) / kFfnWaves * splits;
-      const bool split_k = walk_is_cut(K, M, n_seg, row_tiles, pass == 1 ? 1 : splits), tail = K % 128 != 0;
+      const bool tail = K % 128 != 0;
+      const int grid = pass_grid(row_tiles, pass == 1 ? F / 16 : d / 32, most, K, pass == 1 ? 1 : splits);
       if (pass == 1) {
-        const int grid = xcd_grid(split_k ? F / 16 : row_tiles, cap);
-        auto kern = split_k ? (tail ? ffn_gateup_lds_kernel<true, true> : ffn_gateup_lds_kernel<false, true>)
-                            : (tail ? ffn_gateup_lds_kernel<true, false> : ffn_gateup_lds_kernel<false, false>);
+        auto kern = tail ? ffn_gateup_lds_kernel<true> : ffn_gateup_lds_kernel<false>;
         kern<<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_gate),
                                            static_cast<const uint16_t *>(wt.w_up), items, perm, rank_count, shortlist,
                                            n_seg, cap, M, ds.n_experts, k, d, F, lists, list_stride,
                                            static_cast<uint16_t *>(act));
       } else {
-        const int grid = xcd_grid(split_k ? d / 32 : row_tiles, cap);
-        auto kern = split_k ? (tail ? ffn_down_lds_kernel<true, true> : ffn_down_lds_kernel<false, true>)
-                            : (tail ? ffn_down_lds_kernel<true, false> : ffn_down_lds_kernel<false, false>);
+        auto kern = tail ? ffn_down_lds_kernel<true> : ffn_down_lds_kernel<false>;
         kern<<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(act), static_cast<const uint16_t *>(wt.w_down),
                                            items, perm, rank_count, shortlist, n_seg, cap, M, ds.n_experts, k, d, F,
                                            splits, lists, list_stride, y);

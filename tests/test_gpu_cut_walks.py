@@ -1,6 +1,7 @@
 """Expert passes with so few workgroups that the waves of a workgroup share K instead of the rows: K of exactly four chunks,
-chunks that do not divide by four, a tail in the last wave's part, one and two token tiles, more pairs than one round takes,
-either pass alone in that form; and the shapes just beyond the rule."""
+chunks that do not divide by four, a tail in the last wave's part, one to eight token tiles, either pass alone in that
+form; and the shapes just beyond the rule."""
+import numpy as np
 import pytest
 import torch
 
@@ -30,6 +31,45 @@ def test_cut_walks(d, N, k, F, M, B):
     assert_routing_equal(taps, ref, B)
     assert_out_close(out_to_numpy(out), ref["out"], "bf16")
     assert torch.equal(staged, out)
+
+
+def segment_layer(d, F, sizes, M, seed):
+    """Hand-made segment tables: expert i serves sizes[i] tokens (top-1), rows scattered over the tree."""
+    N = len(sizes)
+    assert sum(sizes) <= M
+    cfg = wl.small_config("cut_sizes", "bf16", d=d, n_experts=N, top_k=1, d_ff=F, M=M, seed=seed)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    rng = np.random.default_rng(seed)
+    tok_ids = np.full((M, 1), -1, dtype=np.int32)
+    tok_ids[rng.permutation(M)[: sum(sizes)], 0] = np.repeat(np.arange(N), sizes)
+    tok_w = np.where(tok_ids >= 0, rng.uniform(0.1, 1.0, (M, 1)), 0.0).astype(np.float32)
+    pairs = [np.flatnonzero(tok_ids.ravel() == i) for i in range(N)]
+    perm = np.full(M, -1, dtype=np.int32)
+    perm[: sum(sizes)] = np.concatenate(pairs)
+    seg_off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    out = mb.moespec_expert_ffn(desc, upload_weights(W), to_device(h), dev(np.arange(N, dtype=np.int32)), dev(seg_off), dev(perm),
+                                dev(tok_ids), dev(tok_w), mb.alloc_workspace(desc, M))
+    torch.cuda.synchronize()
+    W_o = oracle_weights(W)
+    want = O.combine(wl.as_f32(h), tok_ids, tok_w, W_o["w_gate"], W_o["w_up"], W_o["w_down"])
+    assert_out_close(out_to_numpy(out), want, "bf16")
+
+
+@pytest.mark.parametrize("d,F", [(512, 512), (640, 544), (1184, 96), (96, 800)])
+def test_pieces_on_both_sides_of_every_step(d, F):
+    """Pairs where the number of token tiles that a cut walk keeps changes (one group of two tiles, two, four), and segments that
+    are cut into pieces."""
+    print(f"case d={d} F={F}", flush=True)
+    segment_layer(d, F, [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 191], 1100, d + F)
+
+
+@pytest.mark.parametrize("n,size", [(131, 2), (132, 2), (133, 2), (175, 65), (176, 65), (177, 65), (133, 64)])
+def test_units_on_both_sides_of_the_limits(n, size):
+    """n segments of one row tile each, the largest of `size` pairs (one of them, the rest have two): the last number of units
+    whose walks are cut and the first that are not, with up to 64 pairs and with more."""
+    print(f"case n={n} size={size}", flush=True)
+    segment_layer(512, 32, [2] * (n - 1) + [size], 2 * n + size, n + size)
 
 
 @pytest.mark.parametrize("M,B", [(1, 64), (7, 16), (15, 16), (16, 16)])
