@@ -704,6 +704,7 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
 }
 
 // ---- fp32 path ------------------------------------------------------------------------------------------------
+// Vector form, for trees of one or two tokens, and of up to 8 over large weights: a stream of weights.
 // A wave owns 8 weight rows (gate/up: 4 gate rows and the same 4 up rows) and P pairs at a time: lane l adds the
 // products of the elements l, l + 64, ... of K in ascending order, 8 P sums side by side, and the 64 lanes of a sum are
 // folded in the order 32, 16, 8, 4, 2, 1.  The sums are folded together: in each step a lane keeps one half of them and
@@ -892,6 +893,158 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
       if (m - p0 <= kF32Pairs / 2) down_f32_tile<kF32Pairs / 2>(act, wd, plist, p0, m, M * k, d, F, j0, y);
       else down_f32_tile<kF32Pairs>(act, wd, plist, p0, m, M * k, d, F, j0, y);
     }
+  }
+}
+
+// ---- fp32 passes on the matrix cores ----------------------------------------------------------------------------
+// A workgroup owns two tiles of 16 weight rows (gate/up: 16 gate rows and the same 16 up rows) and NP tiles of 16 pairs; its
+// 8 waves take two of every 16 steps of 16 elements of K each.  A lane loads 4 consecutive elements of its row and of its
+// pair per step, which feed 4 v_mfma_f32_16x16x4 (lane (i, g) supplies A[i][g], B[g][i] and receives D[4 g + r][i]); which
+// elements meet in one instruction is immaterial.  Every wave keeps kF32Chains sums side by side that are added pairwise, then
+// the waves' in the order of a tree: 64 short chains, like the 64 lanes of the vector form below, so that the rounding
+// error of a sum is the same (against 64 bits 1.5e-7 and 5.1e-8 before and after, 15 tokens of 128 x 256 and 63 of 512 x
+// 1024 with a residual).
+// What bounds it: the chain of a workgroup, which is about 5 us long (tables, pair ids, loads, sums), times the rounds of
+// workgroups.  One token tile leaves room for two workgroups per compute unit, two tiles for one.  63 tokens over 8 experts of
+// 512 x 1024, top-4, us, vector form / one / two tiles: gate/up 29.9 / 21.1 / 20.9, down 22.6 / 14.5 / 12.7.  A second set
+// of loads in flight changed nothing (its registers cost the second workgroup where one tile is taken).
+constexpr int kMfWaves = 8, kMfThreads = kMfWaves * kWave, kF32Chains = 8, kMfStep = 16;
+
+// v[2][NP] of this wave += its share of K of (rows w[0], w[1]) x (pairs x[0 .. NP)): pointers to this lane's row / pair
+template <int NP>
+__device__ __forceinline__ void f32_mfma_walk(const float *const (&w)[2], const float *const (&x)[NP], int K,
+                                              f32x4 (&v)[2][NP]) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4;
+  const int steps = (K + kMfStep - 1) / kMfStep;
+  f32x4 acc[kF32Chains][2][NP];
+#pragma unroll
+  for (int c = 0; c < kF32Chains; ++c)
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) acc[c][a][p] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int kAhead = 2;  // steps per round, next to each other: whole cache lines
+  for (int s0 = kAhead * wave; s0 < steps; s0 += kAhead * kMfWaves) {
+    f32x4 A[kAhead][2], B[kAhead][NP];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int k = (s0 + u) * kMfStep + 4 * g;
+      const bool in = k < K;  // K is a multiple of 4; lanes past the end multiply zeros
+#pragma unroll
+      for (int a = 0; a < 2; ++a) A[u][a] = in ? *reinterpret_cast<const f32x4 *>(w[a] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int p = 0; p < NP; ++p) B[u][p] = in ? *reinterpret_cast<const f32x4 *>(x[p] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int p = 0; p < NP; ++p)
+            acc[4 * u + m][a][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[u][a][m], B[u][p][m], acc[4 * u + m][a][p], 0, 0, 0);
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      v[a][p] = ((acc[0][a][p] + acc[1][a][p]) + (acc[2][a][p] + acc[3][a][p])) +
+                ((acc[4][a][p] + acc[5][a][p]) + (acc[6][a][p] + acc[7][a][p]));
+}
+
+// part: [kMfWaves][2][NP][kMfPart] floats of LDS.  Calls out(row, pair, sum of the first tile's row, of the second's) for the rows
+// 0 .. 15 and pairs 0 .. 16 NP - 1; 16 consecutive threads have 16 consecutive rows of one pair.
+constexpr int kMfPart = 4 * 68;  // 4 registers of 64 lanes, 68 apart: the threads that read 16 rows of 4 pairs touch all banks
+template <int NP, class F>
+__device__ __forceinline__ void f32_mfma_tile(const float *const (&w)[2], const float *const (&x)[NP], int K, float *part, F out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  f32x4 v[2][NP];
+  f32_mfma_walk<NP>(w, x, K, v);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[((wave * 2 + a) * NP + p) * kMfPart + 68 * r + lane] = v[a][p][r];
+  __syncthreads();
+  if (threadIdx.x < 256 * NP) {
+    const int row = threadIdx.x & 15, pair = (threadIdx.x >> 4) & 15, p = threadIdx.x >> 8;
+    float s[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      float q[kMfWaves];
+#pragma unroll
+      for (int i = 0; i < kMfWaves; ++i) q[i] = part[((i * 2 + a) * NP + p) * kMfPart + 68 * (row & 3) + 16 * (row >> 2) + pair];
+      s[a] = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+    }
+    out(row, 16 * p + pair, s[0], s[1]);
+  }
+  __syncthreads();  // the sums have been read
+}
+
+template <int NP, bool kItems>
+__global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_gateup_f32_mfma_kernel(
+    const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
+    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int4 *__restrict__ items,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
+    const int32_t *__restrict__ lists, int list_stride, int M, int N, int k, int d, int F, float *__restrict__ act) {
+  __shared__ float part[kMfWaves * 2 * NP * kMfPart];
+  int e, m;
+  const int32_t *plist;
+  if (!f32_segment<kItems>(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
+                   plist))
+    return;
+  const int f0 = blockIdx.x * 16, i = threadIdx.x & 15, n_pairs = M * k;
+  const size_t row = ((size_t)e * F + min(f0 + i, F - 1)) * d;  // rows and pairs past the end repeat the last one, never stored
+  const float *const w[2] = {w_gate + row, w_up + row};
+  for (int p0 = blockIdx.z * 16 * NP; p0 < m; p0 += gridDim.z * 16 * NP) {
+    auto run = [&](auto np) {
+      constexpr int T = decltype(np)::value;
+      const float *x[T];
+#pragma unroll
+      for (int p = 0; p < T; ++p) x[p] = h + (size_t)(pair_at(plist, min(p0 + 16 * p + i, m - 1), n_pairs) / k) * d;
+      const float *const(&xc)[T] = x;
+      f32_mfma_tile<T>(w, xc, d, part, [&](int r, int pair, float g, float u) {
+        if (f0 + r < F && p0 + pair < m)
+          act[(size_t)pair_at(plist, p0 + pair, n_pairs) * F + f0 + r] = g / (1.0f + expf(-g)) * u;
+      });
+    };
+    if (NP == 1 || m - p0 <= 16) run(std::integral_constant<int, 1>{});
+    else run(std::integral_constant<int, NP>{});
+  }
+}
+
+template <int NP, bool kItems>
+__global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_down_f32_mfma_kernel(
+    const float *__restrict__ act, const float *__restrict__ w_down, const int32_t *__restrict__ seg_expert,
+    const int32_t *__restrict__ seg_off, const int4 *__restrict__ items, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int M, int N, int k, int d, int F, float *__restrict__ y) {
+  __shared__ float part[kMfWaves * 2 * NP * kMfPart];
+  int e, m;
+  const int32_t *plist;
+  if (!f32_segment<kItems>(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
+                   plist))
+    return;
+  const int j0 = blockIdx.x * 32, i = threadIdx.x & 15, n_pairs = M * k;
+  const float *const w[2] = {w_down + ((size_t)e * d + min(j0 + i, d - 1)) * F, w_down + ((size_t)e * d + min(j0 + 16 + i, d - 1)) * F};
+  for (int p0 = blockIdx.z * 16 * NP; p0 < m; p0 += gridDim.z * 16 * NP) {
+    auto run = [&](auto np) {
+      constexpr int T = decltype(np)::value;
+      const float *x[T];
+#pragma unroll
+      for (int p = 0; p < T; ++p) x[p] = act + (size_t)pair_at(plist, min(p0 + 16 * p + i, m - 1), n_pairs) * F;
+      const float *const(&xc)[T] = x;
+      f32_mfma_tile<T>(w, xc, F, part, [&](int r, int pair, float a, float b) {
+        if (p0 + pair >= m) return;
+        float *dst = y + (size_t)pair_at(plist, p0 + pair, n_pairs) * d + j0 + r;
+        if (j0 + r < d) dst[0] = a;
+        if (j0 + 16 + r < d) dst[16] = b;
+      });
+    };
+    if (NP == 1 || m - p0 <= 16) run(std::integral_constant<int, 1>{});
+    else run(std::integral_constant<int, NP>{});
   }
 }
 
@@ -1093,25 +1246,40 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     mark(2);
     return e;
   }
-  // up to 4 workgroups share the pairs of a segment: enough waves to hide the loads where rows are few
-  const int ptiles = (M + kF32Pairs - 1) / kF32Pairs, z = ptiles < 4 ? ptiles : 4;
   const bool few = M <= 2;
   const int4 *work = !rank_count && items_ready ? items : nullptr;
   const int rows = work ? cap : n_seg;
-  dim3 g1((F + 4 * kFfnWaves - 1) / (4 * kFfnWaves), rows, z);
-  auto gate_up = work ? (few ? ffn_gateup_f32_kernel<true, true> : ffn_gateup_f32_kernel<false, true>)
-                      : (few ? ffn_gateup_f32_kernel<true, false> : ffn_gateup_f32_kernel<false, false>);
-  gate_up<<<g1, kFfnThreads, 0, st>>>(
+  // The matrix cores from three tokens on, unless the weights are so large and the pairs so few that reading them is all there
+  // is (vector / matrix form, us per layer: 64 experts of 1024 x 2048, top-8 of 16, 8 tokens 98 / 104; 8 of 4096 x 4096, 3
+  // tokens 164 / 170, 16 tokens 288 / 191; with less than 2^21 elements per matrix 1.0 to 1.17 times as fast from 3 to 8 tokens).
+  const bool matrix = !few && !(M <= 8 && (long long)d * F >= 1 << 21);
+  // Two token tiles per workgroup read the weights half as often; one tile makes twice as many workgroups, two per compute
+  // unit.  Two tiles where even they come to two workgroups per compute unit (layers of 300 tokens 1.01 to 1.13 times as
+  // fast, 63 tokens over 8 experts of 512 x 1024 1.05; but 58 tokens over 13 experts of 832 x 84 0.89, 21 over 7 of 252 x 256 0.91).
+  const long long mean = (long long)M * k / n_seg;
+  const bool two = matrix && mean > 16 && (long long)((F + 15) / 16) * n_seg * ((mean + 31) / 32) >= 512;
+  // up to 4 workgroups share the pairs of a segment: enough waves to hide the loads where rows are few
+  const int tile = matrix ? (two ? 32 : 16) : kF32Pairs, ptiles = (M + tile - 1) / tile, z = ptiles < 4 ? ptiles : 4;
+  const int wg_rows1 = matrix ? 16 : 4 * kFfnWaves, wg_rows2 = matrix ? 32 : kF32Rows * kFfnWaves;
+  const int threads = matrix ? kMfThreads : kFfnThreads;
+  auto gate_up = matrix ? (two ? (work ? ffn_gateup_f32_mfma_kernel<2, true> : ffn_gateup_f32_mfma_kernel<2, false>)
+                               : (work ? ffn_gateup_f32_mfma_kernel<1, true> : ffn_gateup_f32_mfma_kernel<1, false>))
+                 : work ? (few ? ffn_gateup_f32_kernel<true, true> : ffn_gateup_f32_kernel<false, true>)
+                        : (few ? ffn_gateup_f32_kernel<true, false> : ffn_gateup_f32_kernel<false, false>);
+  dim3 g1((F + wg_rows1 - 1) / wg_rows1, rows, z);
+  gate_up<<<g1, threads, 0, st>>>(
       static_cast<const float *>(h), static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up),
       seg_expert, seg_off, work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
       static_cast<float *>(act));
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(0);
-  dim3 g2((d + kF32Rows * kFfnWaves - 1) / (kF32Rows * kFfnWaves), rows, z);
-  auto down = work ? (few ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
-                   : (few ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
-  down<<<g2, kFfnThreads, 0, st>>>(static_cast<const float *>(act), static_cast<const float *>(wt.w_down), seg_expert, seg_off,
-                                   work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
+  auto down = matrix ? (two ? (work ? ffn_down_f32_mfma_kernel<2, true> : ffn_down_f32_mfma_kernel<2, false>)
+                            : (work ? ffn_down_f32_mfma_kernel<1, true> : ffn_down_f32_mfma_kernel<1, false>))
+              : work ? (few ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
+                     : (few ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
+  dim3 g2((d + wg_rows2 - 1) / wg_rows2, rows, z);
+  down<<<g2, threads, 0, st>>>(static_cast<const float *>(act), static_cast<const float *>(wt.w_down), seg_expert, seg_off,
+                               work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark(1);
   if (!out) return hipSuccess;

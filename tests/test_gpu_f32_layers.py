@@ -19,7 +19,13 @@ pytestmark = pytest.mark.gpu
                                          (64, 2, 2, 64, 8, 2), (68, 2, 2, 132, 9, 2), (132, 7, 3, 28, 33, 5),
                                          (100, 4, 2, 52, 300, 3), (48, 300, 5, 20, 11, 40),
                                          (64, 4, 2, 32, 256, 3), (64, 4, 2, 32, 257, 3),
-                                         (68, 9, 3, 44, 700, 7),                                          (300, 5, 3, 332, 1, 4), (260, 3, 3, 516, 2, 3), (256, 2, 2, 256, 3, 2)])
+                                         (68, 9, 3, 44, 700, 7),
+                                         # tiles of 16 rows and pairs: a K shorter than a step, remainders of rows, pairs and K
+                                         (12, 3, 1, 20, 17, 3), (516, 2, 2, 24, 33, 2), (260, 1, 1, 48, 16, 1),
+                                         # two pair tiles per workgroup; the largest weights of the vector form, and past them
+                                         (36, 2, 2, 4100, 40, 2), (4100, 3, 2, 36, 300, 2), (1028, 2, 1, 2052, 8, 2),
+                                         (1028, 2, 1, 2052, 9, 2), (1028, 2, 2, 2040, 3, 2),
+                                         (300, 5, 3, 332, 1, 4), (260, 3, 3, 516, 2, 3), (256, 2, 2, 256, 3, 2)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_f32_layers(d, N, k, F, M, B, policy):
     print(f"case d={d} N={N} k={k} F={F} M={M} B={B} policy={policy}", flush=True)
