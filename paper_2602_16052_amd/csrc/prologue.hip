@@ -14,6 +14,8 @@
 //
 // Every decision in fp64, ties to the lowest expert id, as in the staged kernels of route.hip / budget.hip, which remain
 // the path of the stage calls, of larger trees (fused_prologue_ok) and of layers whose passes take the grouped form.
+#include <type_traits>
+
 #include "common.h"
 
 namespace moespec {
@@ -52,7 +54,8 @@ template <> struct LogitPiece<float> {
 // = (lane % 16, lane / 16) supplies A[i][g] and B[g][i] and receives D[g + 4 r][i] in accumulator r.  A lane
 // loads 8 consecutive elements of its token row and of its expert row per block; which of the 32
 // elements of a block meet in one instruction is immaterial, the sum over the block is complete after 8 of them.
-template <typename T>
+// kAhead: the loads of the next blocks are in flight while the present ones are multiplied.
+template <typename T, bool kAhead>
 __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T *__restrict__ h, const T *__restrict__ w_r,
                                                                           int M, int N, int d, int n_slices,
                                                                           double *__restrict__ partial) {
@@ -66,10 +69,8 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T
   const int b0 = (int)((long long)part * n_blocks / parts), b1 = (int)((long long)(part + 1) * n_blocks / parts);
   const T *ha = h + (size_t)t * d + g * 8, *wb = w_r + (size_t)e * d + g * 8;
   f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-  // Two sets of PB blocks: the loads of one are in flight while the other is multiplied (511 tokens x 64 experts, d = 2048:
-  // 8.2 -> 6.7 us; at 4096 tokens four waves per SIMD hide them anyway, 28 us).
-  constexpr int PB = sizeof(T) == 2 ? 4 : 2;
-  LogitPiece<T> A[2][PB], Bv[2][PB];
+  constexpr int PB = sizeof(T) == 2 || !kAhead ? 4 : 2, kSets = kAhead ? 2 : 1;  // blocks per set of loads
+  LogitPiece<T> A[kSets][PB], Bv[kSets][PB];
   auto load = [&](int set, int b) {
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
@@ -88,17 +89,22 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T
       }
     }
   };
-  if (b0 < b1) {
-    load(0, b0);
-    if (b1 - b0 <= PB) {
-      multiply(0, b0);
-    } else {
-      for (int b = b0; b < b1; b += 2 * PB) {
-        load(1, b + PB);
-        multiply(0, b);
-        load(0, b + 2 * PB);
-        multiply(1, b + PB);
-      }
+  if constexpr (kAhead) {
+    int b = b0;
+    if (b < b1) load(0, b);
+    for (; b + 2 * PB < b1; b += 2 * PB) {
+      load(1, b + PB);
+      multiply(0, b);
+      load(0, b + 2 * PB);
+      multiply(1, b + PB);
+    }
+    if (b + PB < b1) load(1, b + PB);
+    multiply(0, b);
+    multiply(1, b + PB);
+  } else {
+    for (int b = b0; b < b1; b += PB) {
+      load(0, b);
+      multiply(0, b);
     }
   }
   if (d % 32 != 0 && part == parts - 1) {  // fp32 layers: the last 4 to 28 elements, 4 at a time, one per lane group
@@ -538,14 +544,18 @@ bool mfma_route_ok(const moespec_desc &ds) { return ds.n_experts <= kSelfMaxExpe
 hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int slices,
                          double *partial, hipStream_t st) {
   dim3 grid(((M + 15) / 16) * ((ds.n_experts + 15) / 16), slices);
+  // Loads ahead where a wave has more than one round of them and every workgroup is resident at once with the registers they
+  // take (four per compute unit): 511 tokens x 64 experts, d = 2048, 8.2 -> 6.7 us; but 2588 x 117, d = 640 (1296 workgroups)
+  // 16.0 -> 20.8.
+  const bool ahead = ds.d / 32 > 4 * kLogitWaves * slices && (long long)grid.x * slices <= 768;
+  auto run = [&](auto kern, auto *hp) {
+    using T = std::remove_reference_t<decltype(*hp)>;
+    kern<<<grid, kLogitWaves * kWave, 0, st>>>(hp, static_cast<T *>(wt.w_router), M, ds.n_experts, ds.d, slices, partial);
+  };
   if (ds.dtype == MOESPEC_BF16)
-    logits_mfma_kernel<uint16_t><<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const uint16_t *>(h),
-                                                                    static_cast<const uint16_t *>(wt.w_router), M,
-                                                                    ds.n_experts, ds.d, slices, partial);
+    run(ahead ? logits_mfma_kernel<uint16_t, true> : logits_mfma_kernel<uint16_t, false>, static_cast<const uint16_t *>(h));
   else
-    logits_mfma_kernel<float><<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const float *>(h),
-                                                                 static_cast<const float *>(wt.w_router), M,
-                                                                 ds.n_experts, ds.d, slices, partial);
+    run(ahead ? logits_mfma_kernel<float, true> : logits_mfma_kernel<float, false>, static_cast<const float *>(h));
   return hipGetLastError();
 }
 
