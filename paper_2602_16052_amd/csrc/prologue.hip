@@ -155,8 +155,8 @@ __host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B) 
 // Q = slices of the router projection, NE = ceil(N / 16) = elements of a table row per lane in the softmax (both
 // compile-time so that the short loops unroll: a taken branch costs this hardware about as much as ten fp64
 // operations).  Up to the shortlist the whole workgroup works on the table (16 consecutive lanes share a row and
-// reduce through DPP; rank counts split the rivals of a candidate over the threads with the same index modulo a
-// power of two and add up with integer LDS atomics).  Comparisons are written without short-circuit evaluation and
+// reduce through DPP, 16 lanes share a candidate of the shortlist and split its rivals; a token's rank counts add up with
+// integer LDS atomics).  Comparisons are written without short-circuit evaluation and
 // loops in fixed blocks of four or eight, so that the code stays straight-line.
 template <int Q, int NE>
 __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
@@ -214,6 +214,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
     pos[i] = 0x7fffffff;
     rank[i] = 0;
   }
+  for (int r = tid; r < B; r += nt) S[r] = -1;  // NaN scores: several experts count rank 0, slots stay unfilled
   __syncthreads();
 
   // Eq. (1): 16 lanes per row, 64 rows per round; a lane holds its NE elements of the row in registers
@@ -251,10 +252,6 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
 
   // Eq. (5): s_i = sum_t g_i(h_t).  16 lanes share a column: lane p adds tokens p, p + 16, ... in ascending order
   // and the 16 partial sums are folded through DPP; 64 columns per round.
-  int np2 = 1, np2_log = 0;
-  while (np2 < N) np2 <<= 1, ++np2_log;
-  const int parts = nt >> np2_log;  // N <= 256: at least 4
-  const int ci = tid & (np2 - 1), cp = tid >> np2_log;
   if (ext_shortlist == nullptr || scores_out != nullptr) {
     for (int c0 = 0; c0 < N; c0 += nt / 16) {
       const int col = min(c0 + (tid >> 4), N - 1);
@@ -273,26 +270,25 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   }
   // Section 3.2: the B highest aggregate scores, ties to the lowest id - or the caller's shortlist
   if (ext_shortlist == nullptr) {
-    const int per = (N + parts - 1) / parts;
-    if (ci < N) {
-      const double vi = s[ci];
-      const int j1 = min(N, (cp + 1) * per);
+    // 16 lanes share a candidate and split its rivals: lane p takes p, p + 16, ...; 64 candidates per round
+    for (int c0 = 0; c0 < N; c0 += nt / 16) {
+      const int i = c0 + (tid >> 4);
+      const double vi = s[min(i, N - 1)];
       int c = 0;
-      for (int j = cp * per; j < j1; j += 4) {
+      for (int j = seg; j < N; j += 64) {
         double v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = s[min(j + u, N - 1)];
+        for (int u = 0; u < 4; ++u) v[u] = s[min(j + 16 * u, N - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c += (j + u < j1 && ranks_before(v[u], j + u, vi, ci)) ? 1 : 0;
+        for (int u = 0; u < 4; ++u)
+          c += (int)((j + 16 * u < N) & ((v[u] > vi) | ((v[u] == vi) & (j + 16 * u < i))));
       }
-      if (c) atomicAdd(&rank[ci], c);
-    }
-    for (int r = tid; r < B; r += nt) S[r] = -1;  // NaN scores: several experts count rank 0, slots stay unfilled
-    __syncthreads();
-    if (tid < N && rank[tid] < B) {
-      S[rank[tid]] = tid;
-      pos[tid] = rank[tid];
-      inS[tid] = 1;
+      c = row16_sum(c);
+      if (seg == 0 && i < N && c < B) {
+        S[c] = i;
+        pos[i] = c;
+        inS[i] = 1;
+      }
     }
   } else {
     for (int r = tid; r < B; r += nt) {
@@ -306,7 +302,6 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   }
   for (int j = tid; j < k; j += nt) sel[j] = -1;
   __syncthreads();
-  for (int i = tid; i < N; i += nt) rank[i] = 0;  // reused for this token's candidate ranks below
   // a token's candidates: all experts under truncation (Eq. (7) restricts the natural top-k afterwards), the
   // shortlist in rank order under substitution (Eq. (8)); -1 marks an entry of an external shortlist that is out of
   // range or a repeat, and the padding up to a multiple of 64
@@ -373,7 +368,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
 #pragma unroll
       for (int u = 0; u < 4; ++u) c += (int)((y + u < y1) & (jy[u] >= 0) & before(vy[u], jy[u], v, j));
     }
-    if (c && j >= 0) atomicAdd(&rank[x], c);  // rank[] is zero again here; j >= 0 implies x < n_cand <= N
+    if (c && j >= 0) atomicAdd(&rank[x], c);  // j >= 0 implies x < n_cand <= N
     cand_j = j;
   }
   // the two remaining steps of the token's routing wait for one barrier each; they ride on the barriers of the first
@@ -383,15 +378,14 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   };
   auto token_write = [&]() {
     if (tid < k && own < M) {
-      const double *grow = g + own * NS;
-      double denom = 0.0;  // over the selected set in slot order (before any slot is dropped: Eq. (7))
-      for (int sl = 0; sl < k; ++sl) {
-        const int e = sel[sl];
-        denom += e >= 0 ? grow[e] : 0.0;
-      }
       const int e = sel[tid];
       const bool keep = e >= 0 && inS[e] != 0;  // an unfilled slot (NaN scores) is dropped
-      const double w = keep ? (renorm ? grow[e] / denom : grow[e]) : 0.0;
+      const double ge = e >= 0 ? g[own * NS + e] : 0.0;
+      double denom = 0.0;  // over the selected set in slot order (before any slot is dropped: Eq. (7)); k <= 64: one wave
+      for (int sl = 0; sl < k; ++sl)
+        denom += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(ge), sl),
+                                  __builtin_amdgcn_readlane(__double2loint(ge), sl));
+      const double w = keep ? (renorm ? ge / denom : ge) : 0.0;
       tok_ids[(size_t)own * k + tid] = keep ? e : -1;
       tok_w[(size_t)own * k + tid] = (float)w;
     }
