@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
     int renorm, int sigmoid_gate, const int32_t *__restrict__ ext_shortlist, double *__restrict__ probs_out,
     double *__restrict__ scores_out, int32_t *__restrict__ budget_ids, int32_t *__restrict__ seg_expert,
     int32_t *__restrict__ tok_ids, float *__restrict__ tok_w, int32_t *__restrict__ list_count,
-    int32_t *__restrict__ lists, int list_stride, int table_ready) {
+    int32_t *__restrict__ lists, int list_stride, int table_ready, int list_wgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PrologueLds L = prologue_lds(M, N, k, B);
   double *g = reinterpret_cast<double *>(smem + L.g);        // [M][N + 1] logits, then routing probabilities
@@ -178,7 +178,9 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   uint8_t *inS = smem + L.inS;
   constexpr int nt = kPrologueThreads;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int own = blockIdx.x;  // this workgroup's token; one past the end only builds pair lists
+  // The first list_wgs workgroups build the pair lists and the others take a token each; list_wgs = 0: a workgroup does both.
+  // own: this workgroup's token; below zero or past the end: it only builds pair lists
+  const int own = (int)blockIdx.x - list_wgs;
   const int NS = N + 1;
 
   // logits: the slices of the hidden dimension added in slice order, plus the router bias
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
     }
   }
   __syncthreads();
-  if (probs_out && !table_ready && own < M)  // (a finished table was written where the caller wants it)
+  if (probs_out && !table_ready && own >= 0 && own < M)  // (a finished table was written where the caller wants it)
     for (int i = tid; i < N; i += nt) probs_out[(size_t)own * N + i] = g[own * NS + i];
 
   // Eq. (5): s_i = sum_t g_i(h_t).  16 lanes share a column: lane p adds tokens p, p + 16, ... in ascending order
@@ -318,7 +320,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   }
   // copies for the caller and for the expert passes, written by the last workgroup (on trees of more tokens than
   // shortlisted experts it has no pair list to build)
-  if (own == (int)gridDim.x - 1) {
+  if (blockIdx.x == gridDim.x - 1) {
     for (int i = tid; i < N; i += nt) {
       if (scores_out) scores_out[i] = s[i];
       if (seg_expert && inS[i]) {  // position of expert i among the shortlisted experts in ascending id
@@ -348,7 +350,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   // of candidates that go before it; rank r < k fills slot r.  Thread (x, p): candidate x against the p-th share
   // of the rivals.
   int cand_j = -1;
-  {
+  if (own >= 0) {
     const double *grow = g + min(own, M - 1) * NS;
     int cp2 = 64, cp2_log = 6;  // candidates rounded up to a power of two, at least one wave
     while (cp2 < n_cand) cp2 <<= 1, ++cp2_log;
@@ -390,12 +392,13 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
       tok_w[(size_t)own * k + tid] = (float)w;
     }
   };
-  bool token_done = false;
+  bool token_done = own < 0;
 
-  // Pair lists of the shortlist ranks own, own + gridDim.x, ...: token t is routed to expert e = S[r] iff e ranks among the
+  // Pair lists of this workgroup's shortlist ranks: token t is routed to expert e = S[r] iff e ranks among the
   // first k of t's candidates; its rank is the slot.  16 lanes share a token and split its rivals; 64 tokens per
   // round; the routed tokens of a round are compacted in token order with one ballot per wave.
-  for (int r = own; r < B; r += gridDim.x) {
+  const int list_step = list_wgs ? list_wgs : gridDim.x;
+  for (int r = list_wgs && own >= 0 ? B : (int)blockIdx.x; r < B; r += list_step) {
     const int e = S[r];
     const bool real = (uint32_t)e < (uint32_t)N && pos[e] == r;  // not a repeat, not out of range
     int base = 0;
@@ -586,10 +589,13 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
       if (err != hipSuccess) return err;
     }
     // a workgroup per token, and at least one per shortlist rank: pair lists built one after the other by the same
-    // workgroup cost 0.8 us each (7 tokens, 16 ranks: 11.9 -> 10.3 us)
-    kern<<<M > B ? M : B, kPrologueThreads, smem, st>>>(table, table_bias, M, N, k, B, policy, ds.renorm, sig, ext_shortlist,
+    // workgroup cost 0.8 us each (7 tokens, 16 ranks: 11.9 -> 10.3 us).  Where the compute units suffice, the tokens and the
+    // lists have workgroups of their own (15 tokens x 8 experts 6.8 -> 6.4 us, 7 x 64 10.3 -> 8.6, 63 x 64 10.5 -> 9.7, 127 x 128 12.3
+    // -> 11.7); each loads the whole table, so not in a second round.
+    const int list_wgs = M + B <= 256 ? B : 0;
+    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(table, table_bias, M, N, k, B, policy, ds.renorm, sig, ext_shortlist,
                                             probs_out, scores_out, budget_ids, seg_expert, tok_ids, tok_w, list_count,
-                                            lists, list_stride, split ? 1 : 0);
+                                            lists, list_stride, split ? 1 : 0, list_wgs);
     return hipGetLastError();
   };
   const int ne = (N + 15) / 16;

@@ -72,7 +72,8 @@ def test_units_on_both_sides_of_the_limits(n, size):
     segment_layer(512, 32, [2] * (n - 1) + [size], 2 * n + size, n + size)
 
 
-@pytest.mark.parametrize("M,B", [(1, 64), (7, 16), (15, 16), (16, 16)])
+# ... and the largest tree whose tokens and pair lists have workgroups of their own, and the next
+@pytest.mark.parametrize("M,B", [(1, 64), (7, 16), (15, 16), (16, 16), (200, 56), (200, 57)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_fewer_tokens_than_shortlist_ranks(M, B, policy):
     """The fused prologue then has workgroups without a token, which only build pair lists."""
