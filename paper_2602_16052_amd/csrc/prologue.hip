@@ -3,11 +3,12 @@
 //
 //   logits_mfma_kernel    the router projection w_i . h_t of Eq. (1) for all tokens and experts on the fp64
 //                         matrix cores, as partial sums over slices of the hidden dimension
-//   route_budget_kernel   one workgroup per tree token.  EVERY workgroup rebuilds the whole M x N table of
+//   route_budget_kernel   a workgroup per tree token and one per shortlist rank (on larger trees the same ones for both).
+//                         EVERY workgroup rebuilds the whole M x N table of
 //                         routing probabilities from those partial sums (bias, softmax or sigmoid gate of
 //                         Eq. (1)), the aggregate scores of Eq. (5) and the top-B shortlist (Section 3.2) in its
 //                         LDS - a few thousand exponentials, cheaper than a second pass over global memory and a
-//                         grid-wide wait - then restricts its own token's routing (Eq. (7) / Eq. (8)) and
+//                         grid-wide wait - then restricts its own token's routing (Eq. (7) / Eq. (8)) or
 //                         writes the pair lists of the shortlist ranks it is responsible for: for every loaded
 //                         expert the (token, slot) pairs routed to it, tokens ascending, which is what the
 //                         expert passes consume.
