@@ -21,7 +21,10 @@ pytestmark = pytest.mark.gpu
                                           (5, 257, 8, 64, "softmax"), (2050, 1, 1, 32, "softmax"),
                                           (512, 66, 3, 32, "sigmoid"), (513, 66, 3, 32, "softmax"),
                                           (1, 253, 64, 32, "softmax"), (1025, 8, 2, 1024, "softmax"), (1100, 16, 1, 2048, "sigmoid"),
-                                           (40, 127, 127 // 2, 64, "softmax")])
+                                          # loads ahead in the projection: 4 to 5, 8 to 9, 12 and 16 blocks per wave
+                                          (1100, 64, 4, 544, "softmax"), (1100, 64, 8, 1056, "softmax"), (600, 64, 4, 2080, "softmax"),
+                                          (1030, 64, 2, 1184, "sigmoid"), (500, 100, 8, 4096, "softmax"), (1500, 30, 3, 3104, "softmax"),
+                                          (40, 127, 127 // 2, 64, "softmax")])
 def test_route_stage_edges(M, N, k, d, gate):
     print(f"case M={M} N={N} k={k} d={d} {gate}", flush=True)
     cfg = wl.small_config("route_edge", "bf16", d=d, n_experts=N, top_k=k, d_ff=32, M=M, gate=gate, seed=M + N)
