@@ -25,10 +25,8 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
   return static_cast<uint16_t>(u >> 16);
 }
 
-// For activations that are stored in bf16: the reciprocal instruction (1 ulp) instead of a division.  With it, the conversion
-// instruction below and the pair ids read in one round, the end of a grouped gate/up unit of 128 x 128 sums is a third as many
-// instructions (2048 tokens over 64 experts of 2048 x 1024: 218.5 -> 213 us).
-__device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
+// A division, not the reciprocal instruction: that one gives 0 where 1 + exp(-z) exceeds 2^126 (gates of -87.3 and below).
+__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 // Four floats to bf16 (round-to-nearest-even), stored as 8 bytes.
 __device__ __forceinline__ void store_bf16x4(uint16_t *p, f32x4 v) {
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
