@@ -71,6 +71,12 @@ __device__ __forceinline__ double row16_sum(double v) {
   v += dpp_f64<kDppHalfMirror>(v);
   return v + dpp_f64<kDppMirror>(v);
 }
+__device__ __forceinline__ float row16_sum(float v) {
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kDppXor1, 0xf, 0xf, false));
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kDppXor2, 0xf, 0xf, false));
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kDppHalfMirror, 0xf, 0xf, false));
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kDppMirror, 0xf, 0xf, false));
+}
 __device__ __forceinline__ int row16_sum(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, kDppXor1, 0xf, 0xf, false);
   v += __builtin_amdgcn_update_dpp(0, v, kDppXor2, 0xf, 0xf, false);

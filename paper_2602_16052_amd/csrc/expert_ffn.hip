@@ -983,6 +983,76 @@ __device__ __forceinline__ void f32_mfma_tile(const float *const (&w)[2], const 
   __syncthreads();  // the sums have been read
 }
 
+// A segment of one or two pairs: the tile of the matrix instructions would be nearly empty, and the weights are a stream.  Every
+// wave takes 4 of the workgroup's 32 rows, 16 lanes per row and 4 elements per lane, so that a load covers 64 elements of all 4
+// rows, with 8 steps in flight and nobody to wait for.  s[p] = row . x[p] in every lane of the row; w and x point to this lane's
+// first elements.  64 sums side by side per row here too.  How many pairs a segment has is known on the device only: 64 experts of
+// 1400 x 1400 with one pair each, us, vector kernels / matrix tile / this form: 277 / 304 / 252, with two 280 / 308 / 255.  (With
+// three and four pairs 282 / 315 / 316: the pairs are loaded again for every 4 rows.  Eight rows per wave and K in two
+// halves took 272 for three, but 1 to 8 % longer than the matrix tile in calls of a few workgroups.)
+constexpr int kF32Few = 2;
+__device__ __forceinline__ void f32_few_dots(const float *w, const float *const (&x)[kF32Few], int K, float (&s)[kF32Few]) {
+  const int c = 4 * (threadIdx.x & 15);
+  constexpr int U = 8;  // steps of 64 elements in flight
+  f32x4 acc[kF32Few];
+#pragma unroll
+  for (int p = 0; p < kF32Few; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < K; k0 += 64 * U) {
+    f32x4 wv[U], xv[U][kF32Few];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 64 * u;
+      const bool in = k + c < K;  // K is a multiple of 4; lanes past the end multiply zeros
+      wv[u] = in ? __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(w + k)) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int p = 0; p < kF32Few; ++p) xv[u][p] = in ? *reinterpret_cast<const f32x4 *>(x[p] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int p = 0; p < kF32Few; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[p][i] = fmaf(wv[u][i], xv[u][p][i], acc[p][i]);
+  }
+#pragma unroll
+  for (int p = 0; p < kF32Few; ++p) s[p] = row16_sum((acc[p][0] + acc[p][1]) + (acc[p][2] + acc[p][3]));
+}
+// Whether a segment (or piece) takes that form; the pieces of a segment that was cut take one form, whatever the last one's size.
+template <bool kItems>
+__device__ __forceinline__ bool f32_few(int m, int item, const int4 *items) {
+  if (m > kF32Few) return false;
+  return !kItems || item == 0 || items[item].x != items[1 + item].x;
+}
+
+__device__ __forceinline__ void gateup_f32_few(const float *__restrict__ h, const float *wg, const float *wu, const int32_t *plist,
+                                               int m, int n_pairs, int k, int d, int F, int f0, float *__restrict__ act) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15;
+  const int f = f0 + 2 * wave + ((lane >> 4) & 1);
+  const float *w = (lane < 32 ? wg : wu) + (size_t)min(f, F - 1) * d + 4 * c, *x[kF32Few];
+#pragma unroll
+  for (int p = 0; p < kF32Few; ++p) x[p] = h + (size_t)(pair_at(plist, min(p, m - 1), n_pairs) / k) * d + 4 * c;
+  float s[kF32Few];
+  f32_few_dots(w, x, d, s);
+#pragma unroll
+  for (int p = 0; p < kF32Few; ++p) {
+    const float u = __shfl_xor(s[p], 32, kWave);
+    if (lane < 32 && c == p && f < F && p < m) act[(size_t)pair_at(plist, p, n_pairs) * F + f] = s[p] / (1.0f + expf(-s[p])) * u;
+  }
+}
+
+__device__ __forceinline__ void down_f32_few(const float *__restrict__ act, const float *wd, const int32_t *plist, int m, int n_pairs,
+                                             int d, int F, int j0, float *__restrict__ y) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15, j = j0 + 4 * wave + (lane >> 4);
+  const float *w = wd + (size_t)min(j, d - 1) * F + 4 * c, *x[kF32Few];
+#pragma unroll
+  for (int p = 0; p < kF32Few; ++p) x[p] = act + (size_t)pair_at(plist, min(p, m - 1), n_pairs) * F + 4 * c;
+  float s[kF32Few];
+  f32_few_dots(w, x, F, s);
+#pragma unroll
+  for (int p = 0; p < kF32Few; ++p)
+    if (c == p && j < d && p < m) y[(size_t)pair_at(plist, p, n_pairs) * d + j] = s[p];
+}
+
 template <int NP, bool kItems>
 __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_gateup_f32_mfma_kernel(
     const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
@@ -996,6 +1066,12 @@ __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_gateup_f32_mf
                    plist))
     return;
   const int f0 = blockIdx.x * 16, i = threadIdx.x & 15, n_pairs = M * k;
+  if (f32_few<kItems>(m, blockIdx.y, items)) {
+    if (blockIdx.z != 0) return;
+    const float *wg = w_gate + (size_t)e * F * d, *wu = w_up + (size_t)e * F * d;
+    gateup_f32_few(h, wg, wu, plist, m, n_pairs, k, d, F, f0, act);
+    return;
+  }
   const size_t row = ((size_t)e * F + min(f0 + i, F - 1)) * d;  // rows and pairs past the end repeat the last one, never stored
   const float *const w[2] = {w_gate + row, w_up + row};
   for (int p0 = blockIdx.z * 16 * NP; p0 < m; p0 += gridDim.z * 16 * NP) {
@@ -1028,6 +1104,12 @@ __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_down_f32_mfma
                    plist))
     return;
   const int j0 = blockIdx.x * 32, i = threadIdx.x & 15, n_pairs = M * k;
+  if (f32_few<kItems>(m, blockIdx.y, items)) {
+    if (blockIdx.z != 0) return;
+    const float *wd = w_down + (size_t)e * d * F;
+    down_f32_few(act, wd, plist, m, n_pairs, d, F, j0, y);
+    return;
+  }
   const float *const w[2] = {w_down + ((size_t)e * d + min(j0 + i, d - 1)) * F, w_down + ((size_t)e * d + min(j0 + 16 + i, d - 1)) * F};
   for (int p0 = blockIdx.z * 16 * NP; p0 < m; p0 += gridDim.z * 16 * NP) {
     auto run = [&](auto np) {
@@ -1256,32 +1338,43 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
   // Two token tiles per workgroup read the weights half as often; one tile makes twice as many workgroups, two per compute
   // unit.  Two tiles where even they come to two workgroups per compute unit (layers of 300 tokens 1.01 to 1.13 times as
   // fast, 63 tokens over 8 experts of 512 x 1024 1.05; but 58 tokens over 13 experts of 832 x 84 0.89, 21 over 7 of 252 x 256 0.91).
+  // The gate/up pass decides for both: counted by its own 32-row tiles the down pass takes one tile too early (1 expert of 2532 x 3920,
+  // 93 tokens, 117 -> 143 us; 2 of 364 x 2688, 264 tokens, 109 -> 125; 320 drawn layers 0.996, 25 of them 4 to 18 % slower).
   const long long mean = (long long)M * k / n_seg;
   const bool two = matrix && mean > 16 && (long long)((F + 15) / 16) * n_seg * ((mean + 31) / 32) >= 512;
-  // up to 4 workgroups share the pairs of a segment: enough waves to hide the loads where rows are few
-  const int tile = matrix ? (two ? 32 : 16) : kF32Pairs, ptiles = (M + tile - 1) / tile, z = ptiles < 4 ? ptiles : 4;
-  const int wg_rows1 = matrix ? 16 : 4 * kFfnWaves, wg_rows2 = matrix ? 32 : kF32Rows * kFfnWaves;
-  const int threads = matrix ? kMfThreads : kFfnThreads;
-  auto gate_up = matrix ? (two ? (work ? ffn_gateup_f32_mfma_kernel<2, true> : ffn_gateup_f32_mfma_kernel<2, false>)
-                               : (work ? ffn_gateup_f32_mfma_kernel<1, true> : ffn_gateup_f32_mfma_kernel<1, false>))
-                 : work ? (few ? ffn_gateup_f32_kernel<true, true> : ffn_gateup_f32_kernel<false, true>)
-                        : (few ? ffn_gateup_f32_kernel<true, false> : ffn_gateup_f32_kernel<false, false>);
-  dim3 g1((F + wg_rows1 - 1) / wg_rows1, rows, z);
-  gate_up<<<g1, threads, 0, st>>>(
-      static_cast<const float *>(h), static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up),
-      seg_expert, seg_off, work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
-      static_cast<float *>(act));
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  mark(0);
-  auto down = matrix ? (two ? (work ? ffn_down_f32_mfma_kernel<2, true> : ffn_down_f32_mfma_kernel<2, false>)
+  for (int pass = 1; pass <= 2; ++pass) {
+    const int R = pass == 1 ? F : d, K = pass == 1 ? d : F;
+    // up to 4 workgroups share the pairs of a segment: enough waves to hide the loads where rows are few
+    auto groups = [&](int tile) { return std::min((M + tile - 1) / tile, 4); };
+    const int mf_tile = two ? 32 : 16, mf_rows = 16 * pass, mf_row_tiles = (R + mf_rows - 1) / mf_rows;
+    // Short rows leave half of the 8 waves without a step, and with few pairs per segment the 5 us of a workgroup are all there is:
+    // where workgroups come by the ten thousand the gate/up pass keeps the vector form (layers, us, vector / matrix: 141 of
+    // 200 experts of 88 x 3324, 324 tokens, 247 / 304; 190 of 200 of 72 x 2204, 768 pairs, 222 / 248; 53 of 100 of 76 x 1228, 77
+    // tokens, 59 / 69; but few large segments 94 / 81: 12 of 256 experts of 132 x 624, 177 tokens).  Not the down pass, whose
+    // workgroups have twice the rows (32 of 256 experts of 2900 x 152, 128 tokens 204 / 179).
+    const bool mf = matrix && !(pass == 1 && K <= 160 && mean <= 6 && (long long)mf_row_tiles * rows * groups(mf_tile) >= 24576);
+    const int wg_rows = mf ? mf_rows : pass == 1 ? 4 * kFfnWaves : kF32Rows * kFfnWaves;
+    const dim3 grid((R + wg_rows - 1) / wg_rows, rows, groups(mf ? mf_tile : kF32Pairs));
+    if (pass == 1) {
+      auto kern = mf ? (two ? (work ? ffn_gateup_f32_mfma_kernel<2, true> : ffn_gateup_f32_mfma_kernel<2, false>)
+                            : (work ? ffn_gateup_f32_mfma_kernel<1, true> : ffn_gateup_f32_mfma_kernel<1, false>))
+                  : work ? (few ? ffn_gateup_f32_kernel<true, true> : ffn_gateup_f32_kernel<false, true>)
+                         : (few ? ffn_gateup_f32_kernel<true, false> : ffn_gateup_f32_kernel<false, false>);
+      kern<<<grid, mf ? kMfThreads : kFfnThreads, 0, st>>>(
+          static_cast<const float *>(h), static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up), seg_expert,
+          seg_off, work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, static_cast<float *>(act));
+    } else {
+      auto kern = mf ? (two ? (work ? ffn_down_f32_mfma_kernel<2, true> : ffn_down_f32_mfma_kernel<2, false>)
                             : (work ? ffn_down_f32_mfma_kernel<1, true> : ffn_down_f32_mfma_kernel<1, false>))
-              : work ? (few ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
-                     : (few ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
-  dim3 g2((d + wg_rows2 - 1) / wg_rows2, rows, z);
-  down<<<g2, threads, 0, st>>>(static_cast<const float *>(act), static_cast<const float *>(wt.w_down), seg_expert, seg_off,
-                               work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  mark(1);
+                  : work ? (few ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
+                         : (few ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
+      kern<<<grid, mf ? kMfThreads : kFfnThreads, 0, st>>>(
+          static_cast<const float *>(act), static_cast<const float *>(wt.w_down), seg_expert, seg_off, work, perm, rank_count,
+          shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    mark(pass - 1);
+  }
   if (!out) return hipSuccess;
   if (x_next) {
     combine_scale_kernel<float><<<M, kRmsThreads, 0, st>>>(y, tok_ids, tok_w, static_cast<const float *>(residual), k, d,

@@ -2,6 +2,7 @@
 above a wave's 64 elements, hidden sizes that end inside a block of the router projection, segments of 1, 4, 5, 8, 9 and
 more pairs, more pair tiles than workgroups share, and trees on both sides of the fused prologue's limits (experts and
 tokens), with segments of several work items."""
+import numpy as np
 import pytest
 import torch
 
@@ -40,6 +41,88 @@ def test_f32_layers(d, N, k, F, M, B, policy):
     assert_routing_equal(taps, ref, B)
     assert_out_close(out_to_numpy(out), ref["out"], "f32")
     assert torch.equal(staged, out)
+
+
+def segment_layer(d, F, sizes, k, seed):
+    """Hand-made segment tables: expert i serves sizes[i] pairs, dealt to the tokens in turn; some slots stay empty."""
+    N, M = len(sizes), -(-(sum(sizes) + 3) // k)
+    assert max(sizes) <= M
+    cfg = wl.small_config("f32_sizes", "f32", d=d, n_experts=N, top_k=k, d_ff=F, M=M, seed=seed)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    ids = np.full(M * k, -1, dtype=np.int32)
+    ids[(np.arange(sum(sizes)) % M) * k + np.arange(sum(sizes)) // M] = np.repeat(np.arange(N), sizes)
+    tok_ids = ids.reshape(M, k)
+    tok_w = np.where(tok_ids >= 0, np.random.default_rng(seed).uniform(0.1, 1.0, (M, k)), 0.0).astype(np.float32)
+    perm = np.full(M * k, -1, dtype=np.int32)
+    perm[: sum(sizes)] = np.concatenate([np.flatnonzero(ids == i) for i in range(N)])
+    seg_off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    out = mb.moespec_expert_ffn(desc, upload_weights(W), to_device(h), dev(np.arange(N, dtype=np.int32)), dev(seg_off), dev(perm),
+                                dev(tok_ids), dev(tok_w), mb.alloc_workspace(desc, M))
+    torch.cuda.synchronize()
+    W_o = oracle_weights(W)
+    want = O.combine(wl.as_f32(h), tok_ids, tok_w, W_o["w_gate"], W_o["w_up"], W_o["w_down"])
+    assert_out_close(out_to_numpy(out), want, "f32")
+
+
+@pytest.mark.parametrize("d,F", [(4, 12), (60, 64), (64, 36), (68, 132), (508, 516), (512, 28), (516, 1024), (1028, 508)])
+def test_segments_of_one_and_two_pairs(d, F):
+    """They take a form of their own beside the matrix tiles: rows and K on both sides of its steps of 64 and rounds of 512 elements."""
+    print(f"case d={d} F={F}", flush=True)
+    segment_layer(d, F, [1, 2, 3, 2, 1, 16, 17, 2, 33], 2, d + F)
+
+
+@pytest.mark.parametrize("N,B,M", [(2, 2, 16130), (300, 300, 9), (300, 260, 40)])
+def test_short_segments_and_last_pieces_among_work_items(N, B, M):
+    """Behind the staged prologue: 16130 tokens make 127 pieces of an expert, the last of 2 pairs, which is summed like the
+    others; 300 experts serve a pair or two each."""
+    print(f"case N={N} B={B} M={M}", flush=True)
+    cfg = wl.small_config("f32_items", "f32", d=68, n_experts=N, top_k=2, d_ff=36, M=M, bias_alpha=0.1, seed=M)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    h_d, W_d, ws = to_device(h), upload_weights(W), mb.alloc_workspace(desc, M)
+    ref = O.layer_forward(wl.as_f32(h), oracle_weights(W), 2, cfg.renorm, B, mb.SUBSTITUTE)
+    out, taps = mb.moespec_layer_forward(desc, W_d, h_d, B, mb.SUBSTITUTE, ws, taps=True)
+    staged = mb.moespec_expert_ffn(desc, W_d, h_d, taps["seg_expert"], taps["seg_off"], taps["perm"], taps["tok_ids"],
+                                   taps["tok_w"], ws)
+    torch.cuda.synchronize()
+    assert_routing_equal(taps, ref, B)
+    sizes = np.diff(ref["seg_off"])
+    assert np.any(sizes % 127 == 1 if N == 2 else (sizes > 0) & (sizes <= 2))
+    assert_out_close(out_to_numpy(out), ref["out"], "f32")
+    assert torch.equal(staged, out)
+
+
+def test_one_pair_per_expert_is_a_stream_of_weights():
+    """64 experts with one pair each: sixteen tokens read what two read (304 against 264 us when the pairs of sixteen took a
+    tile of 16 on the matrix cores)."""
+    d, F, N = 1400, 1400, 64
+    gen = torch.Generator(device="cuda").manual_seed(0)
+
+    def normal(*shape):
+        return torch.empty(shape, dtype=torch.float32, device="cuda").normal_(0.0, 0.02, generator=gen)
+
+    def ints(n):
+        return torch.arange(n, dtype=torch.int32, device="cuda")
+
+    W = dict(w_gate=normal(N, F, d), w_up=normal(N, F, d), w_down=normal(N, d, F))
+
+    def best_us(M):
+        k = N // M
+        desc, h = mb.LayerDesc(d, N, k, F, mb.F32, True), normal(M, d)
+        ws, tok_w, out, times = mb.alloc_workspace(desc, M), torch.ones(M, k, device="cuda"), torch.empty_like(h), []
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(8):
+                mb.moespec_expert_ffn(desc, W, h, ints(N), ints(N + 1), ints(N), ints(N).view(M, k), tok_w, ws, out=out)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) * 125.0)
+        return min(times)
+
+    two, sixteen = best_us(2), best_us(16)
+    print(f"two tokens {two:.0f} us, sixteen {sixteen:.0f} us", flush=True)
+    assert sixteen < 1.06 * two
 
 
 def test_one_token_is_a_stream_of_weights():
