@@ -15,8 +15,6 @@
 //
 // Every decision in fp64, ties to the lowest expert id, as in the staged kernels of route.hip / budget.hip, which remain
 // the path of the stage calls, of larger trees (fused_prologue_ok) and of layers whose passes take the grouped form.
-#include <type_traits>
-
 #include "common.h"
 
 namespace moespec {
@@ -70,7 +68,7 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T
   const int b0 = (int)((long long)part * n_blocks / parts), b1 = (int)((long long)(part + 1) * n_blocks / parts);
   const T *ha = h + (size_t)t * d + g * 8, *wb = w_r + (size_t)e * d + g * 8;
   f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-  constexpr int PB = sizeof(T) == 2 || !kAhead ? 4 : 2, kSets = kAhead ? 2 : 1;  // blocks per set of loads
+  constexpr int PB = sizeof(T) == 2 ? 4 : 2, kSets = kAhead ? 2 : 1;  // blocks per set of loads
   LogitPiece<T> A[kSets][PB], Bv[kSets][PB];
   auto load = [&](int set, int b) {
 #pragma unroll
@@ -542,18 +540,18 @@ bool mfma_route_ok(const moespec_desc &ds) { return ds.n_experts <= kSelfMaxExpe
 hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int slices,
                          double *partial, hipStream_t st) {
   dim3 grid(((M + 15) / 16) * ((ds.n_experts + 15) / 16), slices);
-  // Loads ahead where a wave has more than one round of them and every workgroup is resident at once with the registers they
-  // take (four per compute unit): 511 tokens x 64 experts, d = 2048, 8.2 -> 6.7 us; but 2588 x 117, d = 640 (1296 workgroups)
-  // 16.0 -> 20.8.
-  const bool ahead = ds.d / 32 > 4 * kLogitWaves * slices && (long long)grid.x * slices <= 768;
-  auto run = [&](auto kern, auto *hp) {
-    using T = std::remove_reference_t<decltype(*hp)>;
-    kern<<<grid, kLogitWaves * kWave, 0, st>>>(hp, static_cast<T *>(wt.w_router), M, ds.n_experts, ds.d, slices, partial);
-  };
-  if (ds.dtype == MOESPEC_BF16)
-    run(ahead ? logits_mfma_kernel<uint16_t, true> : logits_mfma_kernel<uint16_t, false>, static_cast<const uint16_t *>(h));
+  // Loads ahead, except in bf16 where a wave has two sets of four blocks at most: both are then in flight at once without being
+  // ahead of anything.  Route stage without / with, over 7 to 4096 tokens, 8 to 256 experts, d = 640 to 8192 and 8 to 1552
+  // workgroups (whose number changes nothing): bf16, 5 blocks per wave 0.94 to 0.99, 7 and 8 0.97 to 1.04 (mean 0.99), up to 4 1.01 to
+  // 1.05, 10 and more 1.00 to 1.20; fp32 0.99 to 1.19 (mean 1.00 at 4 blocks, 1.02 to 1.14 elsewhere).
+  const int n_blocks = ds.d / 32, parts = kLogitWaves * slices;
+  if (ds.dtype != MOESPEC_BF16)
+    logits_mfma_kernel<float, true><<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const float *>(h), static_cast<const float *>(wt.w_router),
+                                                                    M, ds.n_experts, ds.d, slices, partial);
   else
-    run(ahead ? logits_mfma_kernel<float, true> : logits_mfma_kernel<float, false>, static_cast<const float *>(h));
+    (n_blocks > 4 * parts && n_blocks <= 8 * parts ? logits_mfma_kernel<uint16_t, false> : logits_mfma_kernel<uint16_t, true>)
+        <<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_router), M,
+                                               ds.n_experts, ds.d, slices, partial);
   return hipGetLastError();
 }
 

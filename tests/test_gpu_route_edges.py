@@ -21,13 +21,27 @@ pytestmark = pytest.mark.gpu
                                           (5, 257, 8, 64, "softmax"), (2050, 1, 1, 32, "softmax"),
                                           (512, 66, 3, 32, "sigmoid"), (513, 66, 3, 32, "softmax"),
                                           (1, 253, 64, 32, "softmax"), (1025, 8, 2, 1024, "softmax"), (1100, 16, 1, 2048, "sigmoid"),
-                                          # loads ahead in the projection: 4 to 5, 8 to 9, 12 and 16 blocks per wave
+                                          # blocks per wave of the projection: 4, 4 to 5, 8 (no loads ahead from 5 to 8), 8 to 9, 12, 16
+                                          (1100, 64, 4, 512, "softmax"), (1100, 64, 4, 1024, "softmax"),
                                           (1100, 64, 4, 544, "softmax"), (1100, 64, 8, 1056, "softmax"), (600, 64, 4, 2080, "softmax"),
                                           (1030, 64, 2, 1184, "sigmoid"), (500, 100, 8, 4096, "softmax"), (1500, 30, 3, 3104, "softmax"),
                                           (40, 127, 127 // 2, 64, "softmax")])
 def test_route_stage_edges(M, N, k, d, gate):
-    print(f"case M={M} N={N} k={k} d={d} {gate}", flush=True)
-    cfg = wl.small_config("route_edge", "bf16", d=d, n_experts=N, top_k=k, d_ff=32, M=M, gate=gate, seed=M + N)
+    check_route(M, N, k, d, gate, "bf16")
+
+
+@pytest.mark.parametrize("M,N,k,d", [(1100, 64, 4, 28), (1100, 64, 8, 36), (1100, 40, 4, 132), (1100, 64, 2, 260), (1100, 64, 4, 392),
+                                     (1100, 64, 6, 516), (1100, 64, 4, 548), (1100, 64, 4, 676), (1100, 64, 8, 1060),
+                                     (600, 64, 4, 2084), (20, 16, 2, 4100)])
+def test_route_stage_fp32_projection(M, N, k, d):
+    """From none to 16 blocks of 32 elements per wave, on both sides of its sets of two blocks, in one slice and in several,
+    with 0 to 28 elements behind the last block."""
+    check_route(M, N, k, d, "softmax", "f32")
+
+
+def check_route(M, N, k, d, gate, dtype):
+    print(f"case M={M} N={N} k={k} d={d} {gate} {dtype}", flush=True)
+    cfg = wl.small_config("route_edge", dtype, d=d, n_experts=N, top_k=k, d_ff=32, M=M, gate=gate, seed=M + N)
     h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
     r = mb.moespec_route(desc, upload_weights(W), to_device(h), mb.alloc_workspace(desc, M))
     counts = mb.moespec_calibration_count(desc, r["topk_ids"], torch.zeros(N, dtype=torch.int64, device="cuda"))
