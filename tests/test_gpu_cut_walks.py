@@ -59,9 +59,14 @@ def segment_layer(d, F, sizes, M, seed):
 @pytest.mark.parametrize("d,F", [(512, 512), (640, 544), (1184, 96), (96, 800)])
 def test_pieces_on_both_sides_of_every_step(d, F):
     """Pairs where the number of token tiles that a cut walk keeps changes (one group of two tiles, two, four), and segments that
-    are cut into pieces."""
+    are cut into pieces.  Empty segments behind them keep the tree out of the grouped form."""
     print(f"case d={d} F={F}", flush=True)
-    segment_layer(d, F, [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 191], 1100, d + F)
+    sizes, M = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 191] + [0] * 25, 1100
+    assert M < 32 * len(sizes)  # fewer pairs per segment than the grouped form asks for
+    pieces = sum(-(-c // 128) for c in sizes)
+    cut = [K >= 512 and pieces * -(-rows // 4) <= 176 for K, rows in ((d, F // 16), (F, d // 32))]  # gate/up, down pass
+    assert cut == [d >= 512, F >= 512]
+    segment_layer(d, F, sizes, M, d + F)
 
 
 @pytest.mark.parametrize("n,size", [(131, 2), (132, 2), (133, 2), (175, 65), (176, 65), (177, 65), (133, 64)])

@@ -23,10 +23,12 @@ pytestmark = pytest.mark.gpu
                                          (68, 9, 3, 44, 700, 7),
                                          # tiles of 16 rows and pairs: a K shorter than a step, remainders of rows, pairs and K
                                          (12, 3, 1, 20, 17, 3), (516, 2, 2, 24, 33, 2), (260, 1, 1, 48, 16, 1),
-                                         # two pair tiles per workgroup; the largest weights of the vector form, and past them
+                                         # long rows of either pass; the largest weights of the vector form, and past them
                                          (36, 2, 2, 4100, 40, 2), (4100, 3, 2, 36, 300, 2), (1028, 2, 1, 2052, 8, 2),
                                          (1028, 2, 1, 2052, 9, 2), (1028, 2, 2, 2040, 3, 2),
-                                         (300, 5, 3, 332, 1, 4), (260, 3, 3, 516, 2, 3), (256, 2, 2, 256, 3, 2)])
+                                         (300, 5, 3, 332, 1, 4), (260, 3, 3, 516, 2, 3), (256, 2, 2, 256, 3, 2),
+                                         # one and two tokens among more experts than the fused prologue takes
+                                         (36, 300, 3, 44, 1, 280), (68, 260, 2, 36, 2, 260)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_f32_layers(d, N, k, F, M, B, policy):
     print(f"case d={d} N={N} k={k} F={F} M={M} B={B} policy={policy}", flush=True)
@@ -41,6 +43,23 @@ def test_f32_layers(d, N, k, F, M, B, policy):
     assert_routing_equal(taps, ref, B)
     assert_out_close(out_to_numpy(out), ref["out"], "f32")
     assert torch.equal(staged, out)
+
+
+@pytest.mark.parametrize("d,N,k,F,M,B", [(36, 2, 2, 4100, 40, 2), (36, 4, 2, 2052, 300, 4), (132, 3, 1, 3076, 290, 3)])
+def test_f32_two_pair_tiles(d, N, k, F, M, B):
+    """Two tiles of 16 pairs per workgroup, with the fused prologue and with the staged one: segments above 128 pairs, tiles and
+    pieces that end after one tile and after two."""
+    assert M * k // B > 16 and -(-F // 16) * B * -(-(M * k // B) // 32) >= 512  # the rule
+    for policy in (mb.TRUNCATE, mb.SUBSTITUTE):
+        test_f32_layers(d, N, k, F, M, B, policy)
+
+
+@pytest.mark.parametrize("d,N,k,F,M,B", [(36, 200, 2, 2052, 20, 200), (160, 128, 1, 1028, 60, 128), (36, 300, 2, 1380, 20, 300)])
+def test_f32_short_rows_by_the_ten_thousand(d, N, k, F, M, B):
+    """Gate/up rows of up to 160 elements and more than 24576 workgroups with few pairs: the vector form in that pass alone, with
+    the prologue's lists and with work items."""
+    assert M * k // B <= 6 and -(-F // 16) * B * min(-(-M // 16), 4) >= 24576  # the rule
+    test_f32_layers(d, N, k, F, M, B, mb.SUBSTITUTE)
 
 
 def segment_layer(d, F, sizes, k, seed):
@@ -89,6 +108,35 @@ def test_short_segments_and_last_pieces_among_work_items(N, B, M):
     sizes = np.diff(ref["seg_off"])
     assert np.any(sizes % 127 == 1 if N == 2 else (sizes > 0) & (sizes <= 2))
     assert_out_close(out_to_numpy(out), ref["out"], "f32")
+    assert torch.equal(staged, out)
+
+
+def test_large_weights_and_many_experts():
+    """Five tokens, more experts than the fused prologue takes, weights of 2^21 elements: the vector form of both passes on work
+    items, against 64 bits and against the same form on segment arrays.  (6.5 GB of weights, made on the GPU.)"""
+    d, F, N, k, M = 1448, 1452, 257, 2, 5
+    assert 2 < M <= 8 and d * F >= 2 ** 21 and N > 256
+    gen = torch.Generator(device="cuda").manual_seed(0)
+
+    def normal(*shape, sigma=0.02):
+        return torch.empty(shape, dtype=torch.float32, device="cuda").normal_(0.0, sigma, generator=gen)
+
+    W = dict(w_router=normal(N, d), b_router=torch.zeros(N, device="cuda"), w_gate=normal(N, F, d), w_up=normal(N, F, d),
+             w_down=normal(N, d, F))
+    desc, h = mb.LayerDesc(d, N, k, F, mb.F32, True), normal(M, d, sigma=1.0)
+    h[1], h[3] = h[0], h[0]  # a segment of three pairs
+    ws = mb.alloc_workspace(desc, M)
+    out, taps = mb.moespec_layer_forward(desc, W, h, N, mb.SUBSTITUTE, ws, taps=True)
+    staged = mb.moespec_expert_ffn(desc, W, h, taps["seg_expert"], taps["seg_off"], taps["perm"], taps["tok_ids"],
+                                   taps["tok_w"], ws)
+    torch.cuda.synchronize()
+    want = torch.zeros(M, d, dtype=torch.float64, device="cuda")
+    for t in range(M):
+        for s in range(k):
+            e, x = int(taps["tok_ids"][t, s]), h[t].double()
+            act = torch.nn.functional.silu(W["w_gate"][e].double() @ x) * (W["w_up"][e].double() @ x)
+            want[t] += taps["tok_w"][t, s].double() * (W["w_down"][e].double() @ act)
+    assert_out_close(out_to_numpy(out), want.cpu().numpy(), "f32")
     assert torch.equal(staged, out)
 
 
