@@ -540,16 +540,20 @@ bool mfma_route_ok(const moespec_desc &ds) { return ds.n_experts <= kSelfMaxExpe
 hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int slices,
                          double *partial, hipStream_t st) {
   dim3 grid(((M + 15) / 16) * ((ds.n_experts + 15) / 16), slices);
-  // Loads ahead, except in bf16 where a wave has two sets of four blocks at most: both are then in flight at once without being
-  // ahead of anything.  Route stage without / with, over 7 to 4096 tokens, 8 to 256 experts, d = 640 to 8192 and 8 to 1552
-  // workgroups (whose number changes nothing): bf16, 5 blocks per wave 0.94 to 0.99, 7 and 8 0.97 to 1.04 (mean 0.99), up to 4 1.01 to
-  // 1.05, 10 and more 1.00 to 1.20; fp32 0.99 to 1.19 (mean 1.00 at 4 blocks, 1.02 to 1.14 elsewhere).
+  // Loads ahead, except in bf16 (sets of four blocks) for five blocks per wave, where most of the second set repeats the last
+  // block, and for up to eight in more workgroups than the registers of two sets leave resident.  Measured inside layers whose
+  // weights pass through the caches in between (replayed by itself, with its operands in the L2, the kernel gains nothing at eight
+  // blocks).  Without / with, bf16: 5 blocks 0.90 to 0.98; 6 to 8 1.02 to 1.13 at up to 456 workgroups (one 0.95), 0.98 to
+  // 1.01 at 648, 0.97 to 0.98 above; 9 and more 1.03 to 1.18, also at 1024; up to 4 1.01 to 1.06 on average.  (511 tokens x 64 experts,
+  // d = 2048: 7.1 -> 6.2 us; 1500 x 64, d = 640: 6.7 -> 7.5.)  fp32 (sets of two): 1.00 to 1.27, 0.96 to 0.98 at 7 and 8 blocks from 648
+  // workgroups on.
   const int n_blocks = ds.d / 32, parts = kLogitWaves * slices;
+  const bool plain = n_blocks > 4 * parts && (n_blocks <= 5 * parts || (n_blocks <= 8 * parts && (long long)grid.x * slices > 700));
   if (ds.dtype != MOESPEC_BF16)
     logits_mfma_kernel<float, true><<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const float *>(h), static_cast<const float *>(wt.w_router),
                                                                     M, ds.n_experts, ds.d, slices, partial);
   else
-    (n_blocks > 4 * parts && n_blocks <= 8 * parts ? logits_mfma_kernel<uint16_t, false> : logits_mfma_kernel<uint16_t, true>)
+    (plain ? logits_mfma_kernel<uint16_t, false> : logits_mfma_kernel<uint16_t, true>)
         <<<grid, kLogitWaves * kWave, 0, st>>>(static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_router), M,
                                                ds.n_experts, ds.d, slices, partial);
   return hipGetLastError();

@@ -21,8 +21,9 @@ pytestmark = pytest.mark.gpu
                                           (5, 257, 8, 64, "softmax"), (2050, 1, 1, 32, "softmax"),
                                           (512, 66, 3, 32, "sigmoid"), (513, 66, 3, 32, "softmax"),
                                           (1, 253, 64, 32, "softmax"), (1025, 8, 2, 1024, "softmax"), (1100, 16, 1, 2048, "sigmoid"),
-                                          # blocks per wave of the projection: 4, 4 to 5, 8 (no loads ahead from 5 to 8), 8 to 9, 12, 16
-                                          (1100, 64, 4, 512, "softmax"), (1100, 64, 4, 1024, "softmax"),
+                                          # blocks per wave of the projection: 4, 5 (no loads ahead), 8 (none above 700 workgroups), 8 to 9, 12, 16
+                                          (1100, 64, 4, 512, "softmax"), (1100, 64, 4, 640, "softmax"), (1100, 64, 4, 1024, "softmax"),
+                                          (2900, 64, 2, 1024, "softmax"),
                                           (1100, 64, 4, 544, "softmax"), (1100, 64, 8, 1056, "softmax"), (600, 64, 4, 2080, "softmax"),
                                           (1030, 64, 2, 1184, "sigmoid"), (500, 100, 8, 4096, "softmax"), (1500, 30, 3, 3104, "softmax"),
                                           (40, 127, 127 // 2, 64, "softmax")])
