@@ -704,13 +704,14 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
 }
 
 // ---- fp32 path ------------------------------------------------------------------------------------------------
-// Vector form, for trees of one or two tokens, and of up to 8 over large weights: a stream of weights.
+// Vector form, for trees of one or two tokens, of up to 8 over large weights, and for the gate/up pass over short rows by the ten
+// thousand with few pairs each: a stream of weights.
 // A wave owns 8 weight rows (gate/up: 4 gate rows and the same 4 up rows) and P pairs at a time: lane l adds the
 // products of the elements l, l + 64, ... of K in ascending order, 8 P sums side by side, and the 64 lanes of a sum are
 // folded in the order 32, 16, 8, 4, 2, 1.  The sums are folded together: in each step a lane keeps one half of them and
 // hands the other half over, so that 8 P sums cost 8 P - 1 exchanges in all and every lane ends with one of them.
-// What bounds it: fp32 multiply-adds (packed fp32 is not used) and their loads, 16 per 64 of them.  One wave per row that
-// walked over the pairs one by one, with 6 exchanges per sum, took 140 + 276 us for 8 experts of 512 x 1024 and 63 tokens.
+// What bounds it: reading the weights; with many pairs the fp32 multiply-adds (packed fp32 is not used) and their loads, 16 per 64 of
+// them, which is why those go to the matrix cores (below).
 constexpr int kF32Rows = 8, kF32Pairs = 8;
 
 // v[0 .. n/2) = the sums of the half of v[0 .. n) that this lane keeps: lanes with bit MASK set keep the upper half
@@ -826,7 +827,7 @@ __device__ __forceinline__ void gateup_f32_tile(const float *__restrict__ h, con
 // kFew: every segment has at most two pairs (trees of one or two tokens), so that the passes are a stream of weights: 8 rows
 // against a tile of 4 pairs spent a third of the loads and three quarters of the sums on pairs that are not there (one token,
 // 2 experts of 4096 x 14336: 340 us per layer against 290; 8 of 1024 x 2048: 69 / 62).  A kernel of its own, because in one
-// kernel with the larger tiles each costs the other its registers (63 tokens, 8 experts of 512 x 1024: 65 -> 74 us).
+// kernel with the larger tiles each costs the other its registers (154 VGPRs against 168 to 170).
 template <bool kFew, bool kItems>
 __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
     const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
@@ -901,12 +902,12 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
 // 8 waves take two of every 16 steps of 16 elements of K each.  A lane loads 4 consecutive elements of its row and of its
 // pair per step, which feed 4 v_mfma_f32_16x16x4 (lane (i, g) supplies A[i][g], B[g][i] and receives D[4 g + r][i]); which
 // elements meet in one instruction is immaterial.  Every wave keeps kF32Chains sums side by side that are added pairwise, then
-// the waves' in the order of a tree: 64 short chains, like the 64 lanes of the vector form below, so that the rounding
-// error of a sum is the same (against 64 bits 1.5e-7 and 5.1e-8 before and after, 15 tokens of 128 x 256 and 63 of 512 x
-// 1024 with a residual).
+// the waves' in the order of a tree: 64 short chains from K = 256 on (below, 8 per 32 elements: a wave without a step
+// adds zeros), like the 64 lanes of the vector form above, so that the rounding error of a sum is the same (against 64 bits
+// 1.4e-7 and 5.1e-8 before and after, 15 tokens of 128 x 256 and 63 of 512 x 1024 with a residual).
 // What bounds it: the chain of a workgroup, which is about 5 us long (tables, pair ids, loads, sums), times the rounds of
 // workgroups.  One token tile leaves room for two workgroups per compute unit, two tiles for one.  63 tokens over 8 experts of
-// 512 x 1024, top-4, us, vector form / one / two tiles: gate/up 29.9 / 21.1 / 20.9, down 22.6 / 14.5 / 12.7.  A second set
+// 512 x 1024, top-4, us, vector form / one / two tiles: gate/up 29.9 / 21.1 / 20.7, down 22.6 / 14.5 / 12.5.  A second set
 // of loads in flight changed nothing (its registers cost the second workgroup where one tile is taken).
 constexpr int kMfWaves = 8, kMfThreads = kMfWaves * kWave, kF32Chains = 8, kMfStep = 16;
 

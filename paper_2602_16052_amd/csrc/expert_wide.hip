@@ -8,8 +8,8 @@
 // (global_load_lds_dwordx4: no registers, no LDS stores), 64 elements (one cache line of every row) per stage in a ring
 // of three 48 KB stages, of which two are in flight.  While one half of a stage is multiplied the operands of the next
 // half are read from LDS into the other register set; one barrier per stage, where the stage just read is refilled.
-// Gate/up + down pass, 2048 tokens x top-8 of 64 experts of 2048 x 1024: 213 + 137 us against 287 + 166 us of the streaming
-// form (511 tokens over 32 experts: 78 + 50 against 99 + 60).  The loads alone take 197 us of the 213 (0.75 GB from memory,
+// Gate/up + down pass, 2048 tokens x top-8 of 64 experts of 2048 x 1024: 218 + 138 us against 287 + 166 us of the streaming
+// form (511 tokens over 32 experts: 79 + 50 against 99 + 60).  The loads alone take 197 us of the 218 (0.75 GB from memory,
 // 2.1 GB into LDS), the LDS reads and matrix instructions alone 122.  With the operands read right before their matrix
 // instructions the gate/up pass took 244 us, with 32 elements (half a line) per stage 255 us.
 // A row of a stage is 128 bytes = 8 pieces of 16; piece c of row r sits in slot c ^ (r & 7), so that 8 lanes that read

@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   int32_t *cand = reinterpret_cast<int32_t *>(smem + L.cand);  // [n_cand, padded to 64] a token's candidates
   int32_t *rank = reinterpret_cast<int32_t *>(smem + L.rank);
   int32_t *pos = reinterpret_cast<int32_t *>(smem + L.pos);  // [N] shortlist rank of every expert
-  volatile int32_t *sel = reinterpret_cast<int32_t *>(smem + L.sel);  // [k] this token's selection (wave 0 only)
+  volatile int32_t *sel = reinterpret_cast<int32_t *>(smem + L.sel);  // [k] this token's selection
   uint8_t *inS = smem + L.inS;
   constexpr int nt = kPrologueThreads;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -317,8 +317,8 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
     }
     cand[x] = j;
   }
-  // copies for the caller and for the expert passes, written by the last workgroup (on trees of more tokens than
-  // shortlisted experts it has no pair list to build)
+  // copies for the caller and for the expert passes, written by the last workgroup: it has no pair list to build where the
+  // lists have workgroups of their own or the tokens outnumber the shortlist
   if (blockIdx.x == gridDim.x - 1) {
     for (int i = tid; i < N; i += nt) {
       if (scores_out) scores_out[i] = s[i];
