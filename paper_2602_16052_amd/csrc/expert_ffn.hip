@@ -1353,7 +1353,7 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     // 200 experts of 88 x 3324, 324 tokens, 247 / 304; 190 of 200 of 72 x 2204, 768 pairs, 222 / 248; 53 of 100 of 76 x 1228, 77
     // tokens, 59 / 69; but few large segments 94 / 81: 12 of 256 experts of 132 x 624, 177 tokens).  Not the down pass, whose
     // workgroups have twice the rows (32 of 256 experts of 2900 x 152, 128 tokens 204 / 179).
-    const bool mf = matrix && !(pass == 1 && K <= 160 && mean <= 6 && (long long)mf_row_tiles * rows * groups(mf_tile) >= 24576);
+    const bool mf = matrix && !(pass == 1 && K <= 160 && mean <= 6 && (long long)mf_row_tiles * n_seg * groups(mf_tile) >= 24576);
     const int wg_rows = mf ? mf_rows : pass == 1 ? 4 * kFfnWaves : kF32Rows * kFfnWaves;
     const dim3 grid((R + wg_rows - 1) / wg_rows, rows, groups(mf ? mf_tile : kF32Pairs));
     if (pass == 1) {

@@ -62,6 +62,15 @@ def test_f32_short_rows_by_the_ten_thousand(d, N, k, F, M, B):
     test_f32_layers(d, N, k, F, M, B, mb.SUBSTITUTE)
 
 
+def test_f32_short_rows_count_the_segments():
+    """Just below that limit by the segments, above it by the room for work items, which only the layer call has: the stage calls
+    add in the same order."""
+    d, N, k, F, M, B = 36, 128, 2, 752, 300, 128
+    tiles, room = -(-F // 16), B + M * k // 128
+    assert M * k // B <= 6 and tiles * B * 4 < 24576 <= tiles * room * 4
+    test_f32_layers(d, N, k, F, M, B, mb.SUBSTITUTE)
+
+
 def segment_layer(d, F, sizes, k, seed):
     """Hand-made segment tables: expert i serves sizes[i] pairs, dealt to the tokens in turn; some slots stay empty."""
     N, M = len(sizes), -(-(sum(sizes) + 3) // k)
