@@ -546,10 +546,10 @@ __device__ __forceinline__ void gateup_lds(const uint16_t *wt0, const uint16_t *
 // A workgroup takes 64 gate and the same 64 up rows of an item, or, with its walk cut, 16 and 16.
 template <bool kTail>
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
-    const uint16_t *__restrict__ h, const uint16_t *__restrict__ w_gate, const uint16_t *__restrict__ w_up,
-    const int4 *__restrict__ items, const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count,
-    const int32_t *__restrict__ shortlist, int n_seg, int cap, int M, int N, int k, int d, int F,
-    const int32_t *__restrict__ lists, int list_stride, uint16_t *__restrict__ act) {
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int n_seg, int cap, int M, int N, int k, int d, int F, const int4 *__restrict__ items,
+    const int32_t *__restrict__ perm, const uint16_t *__restrict__ h, const uint16_t *__restrict__ w_gate,
+    const uint16_t *__restrict__ w_up, uint16_t *__restrict__ act) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
   __shared__ int32_t misc[8];
   __shared__ uint32_t xoff[kPiecePairs];
@@ -650,10 +650,10 @@ __device__ __forceinline__ void down_lds(const uint16_t *wt0, const uint16_t *wt
 
 template <bool kTail>
 __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
-    const uint16_t *__restrict__ act, const uint16_t *__restrict__ w_down, const int4 *__restrict__ items,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
-    int n_seg, int cap, int M, int N, int k, int d, int F, int splits, const int32_t *__restrict__ lists,
-    int list_stride, float *__restrict__ y) {
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int n_seg, int cap, int M, int N, int k, int d, int F, int splits, const int4 *__restrict__ items,
+    const int32_t *__restrict__ perm, const uint16_t *__restrict__ act, const uint16_t *__restrict__ w_down,
+    float *__restrict__ y) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
   __shared__ int32_t misc[8];
   __shared__ uint32_t xoff[kPiecePairs];
@@ -830,10 +830,10 @@ __device__ __forceinline__ void gateup_f32_tile(const float *__restrict__ h, con
 // kernel with the larger tiles each costs the other its registers (154 VGPRs against 168 to 170).
 template <bool kFew, bool kItems>
 __global__ __launch_bounds__(kFfnThreads) void ffn_gateup_f32_kernel(
-    const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
-    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int4 *__restrict__ items,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
-    const int32_t *__restrict__ lists, int list_stride, int M, int N, int k, int d, int F, float *__restrict__ act) {
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int M, int N, int k, int d, int F, const float *__restrict__ w_gate, const float *__restrict__ w_up,
+    const float *__restrict__ h, const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off,
+    const int4 *__restrict__ items, const int32_t *__restrict__ perm, float *__restrict__ act) {
   int e, m;
   const int32_t *plist;
   if (!f32_segment<kItems>(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
@@ -873,10 +873,10 @@ __device__ __forceinline__ void down_f32_tile(const float *__restrict__ act, con
 
 template <bool kFew, bool kItems>
 __global__ __launch_bounds__(kFfnThreads) void ffn_down_f32_kernel(
-    const float *__restrict__ act, const float *__restrict__ w_down, const int32_t *__restrict__ seg_expert,
-    const int32_t *__restrict__ seg_off, const int4 *__restrict__ items, const int32_t *__restrict__ perm,
     const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
-    int list_stride, int M, int N, int k, int d, int F, float *__restrict__ y) {
+    int list_stride, int M, int N, int k, int d, int F, const float *__restrict__ w_down, const float *__restrict__ act,
+    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int4 *__restrict__ items,
+    const int32_t *__restrict__ perm, float *__restrict__ y) {
   int e, m;
   const int32_t *plist;
   if (!f32_segment<kItems>(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
@@ -1056,10 +1056,10 @@ __device__ __forceinline__ void down_f32_few(const float *__restrict__ act, cons
 
 template <int NP, bool kItems>
 __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_gateup_f32_mfma_kernel(
-    const float *__restrict__ h, const float *__restrict__ w_gate, const float *__restrict__ w_up,
-    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int4 *__restrict__ items,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist,
-    const int32_t *__restrict__ lists, int list_stride, int M, int N, int k, int d, int F, float *__restrict__ act) {
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int M, int N, int k, int d, int F, const float *__restrict__ w_gate, const float *__restrict__ w_up,
+    const float *__restrict__ h, const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off,
+    const int4 *__restrict__ items, const int32_t *__restrict__ perm, float *__restrict__ act) {
   __shared__ float part[kMfWaves * 2 * NP * kMfPart];
   int e, m;
   const int32_t *plist;
@@ -1094,10 +1094,10 @@ __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_gateup_f32_mf
 
 template <int NP, bool kItems>
 __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_down_f32_mfma_kernel(
-    const float *__restrict__ act, const float *__restrict__ w_down, const int32_t *__restrict__ seg_expert,
-    const int32_t *__restrict__ seg_off, const int4 *__restrict__ items, const int32_t *__restrict__ perm,
     const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
-    int list_stride, int M, int N, int k, int d, int F, float *__restrict__ y) {
+    int list_stride, int M, int N, int k, int d, int F, const float *__restrict__ w_down, const float *__restrict__ act,
+    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int4 *__restrict__ items,
+    const int32_t *__restrict__ perm, float *__restrict__ y) {
   __shared__ float part[kMfWaves * 2 * NP * kMfPart];
   int e, m;
   const int32_t *plist;
@@ -1302,15 +1302,15 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
       const int grid = pass_grid(row_tiles, pass == 1 ? F / 16 : d / 32, most, K, pass == 1 ? 1 : splits);
       if (pass == 1) {
         auto kern = tail ? ffn_gateup_lds_kernel<true> : ffn_gateup_lds_kernel<false>;
-        kern<<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_gate),
-                                           static_cast<const uint16_t *>(wt.w_up), items, perm, rank_count, shortlist,
-                                           n_seg, cap, M, ds.n_experts, k, d, F, lists, list_stride,
-                                           static_cast<uint16_t *>(act));
+        kern<<<grid, kFfnThreads, 0, st>>>(rank_count, shortlist, lists, list_stride, n_seg, cap, M, ds.n_experts, k, d, F,
+                                           items, perm, static_cast<const uint16_t *>(h),
+                                           static_cast<const uint16_t *>(wt.w_gate),
+                                           static_cast<const uint16_t *>(wt.w_up), static_cast<uint16_t *>(act));
       } else {
         auto kern = tail ? ffn_down_lds_kernel<true> : ffn_down_lds_kernel<false>;
-        kern<<<grid, kFfnThreads, 0, st>>>(static_cast<const uint16_t *>(act), static_cast<const uint16_t *>(wt.w_down),
-                                           items, perm, rank_count, shortlist, n_seg, cap, M, ds.n_experts, k, d, F,
-                                           splits, lists, list_stride, y);
+        kern<<<grid, kFfnThreads, 0, st>>>(rank_count, shortlist, lists, list_stride, n_seg, cap, M, ds.n_experts, k, d, F,
+                                           splits, items, perm, static_cast<const uint16_t *>(act),
+                                           static_cast<const uint16_t *>(wt.w_down), y);
       }
       if ((e = hipGetLastError()) != hipSuccess) return e;
       mark(pass - 1);
@@ -1362,16 +1362,17 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
                   : work ? (few ? ffn_gateup_f32_kernel<true, true> : ffn_gateup_f32_kernel<false, true>)
                          : (few ? ffn_gateup_f32_kernel<true, false> : ffn_gateup_f32_kernel<false, false>);
       kern<<<grid, mf ? kMfThreads : kFfnThreads, 0, st>>>(
-          static_cast<const float *>(h), static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up), seg_expert,
-          seg_off, work, perm, rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, static_cast<float *>(act));
+          rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, static_cast<const float *>(wt.w_gate),
+          static_cast<const float *>(wt.w_up), static_cast<const float *>(h), seg_expert, seg_off, work, perm,
+          static_cast<float *>(act));
     } else {
       auto kern = mf ? (two ? (work ? ffn_down_f32_mfma_kernel<2, true> : ffn_down_f32_mfma_kernel<2, false>)
                             : (work ? ffn_down_f32_mfma_kernel<1, true> : ffn_down_f32_mfma_kernel<1, false>))
                   : work ? (few ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
                          : (few ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
       kern<<<grid, mf ? kMfThreads : kFfnThreads, 0, st>>>(
-          static_cast<const float *>(act), static_cast<const float *>(wt.w_down), seg_expert, seg_off, work, perm, rank_count,
-          shortlist, lists, list_stride, M, ds.n_experts, k, d, F, y);
+          rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F, static_cast<const float *>(wt.w_down),
+          static_cast<const float *>(act), seg_expert, seg_off, work, perm, y);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     mark(pass - 1);

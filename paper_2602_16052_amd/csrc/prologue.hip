@@ -159,11 +159,11 @@ __host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B) 
 // loops in fixed blocks of four or eight, so that the code stays straight-line.
 template <int Q, int NE>
 __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
-    const double *__restrict__ partial, const float *__restrict__ bias, int M, int N, int k, int B, int policy,
-    int renorm, int sigmoid_gate, const int32_t *__restrict__ ext_shortlist, double *__restrict__ probs_out,
-    double *__restrict__ scores_out, int32_t *__restrict__ budget_ids, int32_t *__restrict__ seg_expert,
-    int32_t *__restrict__ tok_ids, float *__restrict__ tok_w, int32_t *__restrict__ list_count,
-    int32_t *__restrict__ lists, int list_stride, int table_ready, int list_wgs) {
+    const double *__restrict__ partial, const float *__restrict__ bias, int M, int N, int k, int B, int list_wgs,
+    int table_ready, int sigmoid_gate, int policy, const int32_t *__restrict__ ext_shortlist, int renorm, int list_stride,
+    double *__restrict__ probs_out, double *__restrict__ scores_out, int32_t *__restrict__ budget_ids,
+    int32_t *__restrict__ seg_expert, int32_t *__restrict__ tok_ids, float *__restrict__ tok_w,
+    int32_t *__restrict__ list_count, int32_t *__restrict__ lists) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PrologueLds L = prologue_lds(M, N, k, B);
   double *g = reinterpret_cast<double *>(smem + L.g);        // [M][N + 1] logits, then routing probabilities
@@ -596,9 +596,9 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
     // lists have workgroups of their own (15 tokens x 8 experts 6.8 -> 6.4 us, 7 x 64 10.3 -> 8.6, 63 x 64 10.5 -> 9.7, 127 x 128 12.3
     // -> 11.7); each loads the whole table, so not in a second round.
     const int list_wgs = M + B <= 256 ? B : 0;
-    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(table, table_bias, M, N, k, B, policy, ds.renorm, sig, ext_shortlist,
-                                            probs_out, scores_out, budget_ids, seg_expert, tok_ids, tok_w, list_count,
-                                            lists, list_stride, split ? 1 : 0, list_wgs);
+    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(
+        table, table_bias, M, N, k, B, list_wgs, split ? 1 : 0, sig, policy, ext_shortlist, ds.renorm, list_stride, probs_out,
+        scores_out, budget_ids, seg_expert, tok_ids, tok_w, list_count, lists);
     return hipGetLastError();
   };
   const int ne = (N + 15) / 16;
