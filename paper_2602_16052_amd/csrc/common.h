@@ -38,11 +38,20 @@ template <> struct Elem<float> {
   static __device__ __forceinline__ float load(const float *p) { return *p; }
   static __device__ __forceinline__ void store(float *p, float v) { *p = v; }
   static __device__ __forceinline__ float stored(float v) { return v; }  // the value a store of v leaves behind
+  // four in a row, the address aligned to their size
+  static __device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+  static __device__ __forceinline__ void store4(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
 };
 template <> struct Elem<uint16_t> {
   static __device__ __forceinline__ float load(const uint16_t *p) { return bf16_bits_to_float(*p); }
   static __device__ __forceinline__ void store(uint16_t *p, float v) { *p = float_to_bf16_bits(v); }
   static __device__ __forceinline__ float stored(float v) { return bf16_bits_to_float(float_to_bf16_bits(v)); }
+  static __device__ __forceinline__ f32x4 load4(const uint16_t *p) {
+    const uint2 b = *reinterpret_cast<const uint2 *>(p);
+    return f32x4{__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u), __uint_as_float(b.y << 16),
+                 __uint_as_float(b.y & 0xffff0000u)};
+  }
+  static __device__ __forceinline__ void store4(uint16_t *p, f32x4 v) { store_bf16x4(p, v); }
 };
 
 // Ranking order used by every selection: larger value first, then lower index.

@@ -1132,77 +1132,68 @@ __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_down_f32_mfma
 }
 
 // ---- combine: out[t] = residual[t] + sum over surviving slots (slot order) of w * y[t*k+slot] ---
-// Four consecutive outputs per thread; y holds `splits` partial copies split_stride floats apart (K-split
-// down pass).  The rows of dropped slots hold stale scratch: they are loaded
-// (valid memory) but never enter the sum.
-// the four outputs j .. j+3 of token t (before storage rounding)
-template <typename T>
+// y holds SP partial copies split_stride floats apart (K-split down pass), added in split order.  The rows of dropped slots
+// hold stale scratch: they are loaded (valid memory) but never enter the sum.
+// The four outputs j .. j+3 of token t (before storage rounding).  What bounds it is one round of cold loads: those of U slots go
+// out together, up to 8 rows (with 4 rows at a time and one by one for the remainder of k it was up to k / 4 + k % 4 rounds).
+template <typename T, int SP, int U>
 __device__ __forceinline__ f32x4 combine_four(const float *__restrict__ y, const int32_t *__restrict__ tok_ids,
                                               const float *__restrict__ tok_w, const T *__restrict__ residual, int t,
-                                              int j, int k, int d, int splits, size_t split_stride) {
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (residual) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = Elem<T>::load(residual + (size_t)t * d + j + i);
-  }
+                                              int j, int k, int d, size_t split_stride) {
   const float *yt = y + (size_t)t * k * d + j;
   const int32_t *ids = tok_ids + (size_t)t * k;
   const float *wt = tok_w + (size_t)t * k;
-  // a pair's row is the sum of its K-split copies, added in split order
-  auto row = [&](const float *p) {
-    f32x4 v = *reinterpret_cast<const f32x4 *>(p);
-    for (int sp = 1; sp < splits; ++sp) v += *reinterpret_cast<const f32x4 *>(p + sp * split_stride);
-    return v;
-  };
-  int s = 0;
-  for (; s + 4 <= k; s += 4) {
-    f32x4 v[4];
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (residual) acc = Elem<T>::load4(residual + (size_t)t * d + j);
+  for (int s0 = 0; s0 < k; s0 += U) {
+    f32x4 v[U][SP];
+    float w[U];
+    int id[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = row(yt + (size_t)(s + u) * d);
+    for (int u = 0; u < U; ++u) {
+      const int s = min(s0 + u, k - 1);  // past the last slot: its row again, not added
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (ids[s + u] >= 0) {
-        const float w = wt[s + u];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = fmaf(w, v[u][i], acc[i]);
-      }
+      for (int sp = 0; sp < SP; ++sp) v[u][sp] = *reinterpret_cast<const f32x4 *>(yt + (size_t)s * d + sp * split_stride);
+      id[u] = ids[s];
+      w[u] = wt[s];
     }
-  }
-  for (; s < k; ++s) {
-    if (ids[s] >= 0) {
-      const f32x4 v = row(yt + (size_t)s * d);
-      const float w = wt[s];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = fmaf(w, v[i], acc[i]);
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u < k && id[u] >= 0) {
+        f32x4 r = v[u][0];
+#pragma unroll
+        for (int sp = 1; sp < SP; ++sp) r += v[u][sp];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = fmaf(w[u], r[i], acc[i]);
+      }
     }
   }
   return acc;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ y, const int32_t *__restrict__ tok_ids,
-                                                      const float *__restrict__ tok_w, const T *__restrict__ residual,
-                                                      int k, int d, int splits, size_t split_stride,
-                                                      T *__restrict__ out) {
+// Workgroups of one wave: the rows of a token are spread over as many compute units as there are.
+constexpr int kCombineThreads = 64;
+template <typename T, int SP, int U>
+__global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float *__restrict__ y, const int32_t *__restrict__ tok_ids,
+                                                                  const float *__restrict__ tok_w, const T *__restrict__ residual,
+                                                                  T *__restrict__ out, int M, int k, int d) {
   const int t = blockIdx.y;
-  const int j = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
+  const int j = (blockIdx.x * kCombineThreads + threadIdx.x) * 4;
   if (j >= d) return;
-  const f32x4 acc = combine_four<T>(y, tok_ids, tok_w, residual, t, j, k, d, splits, split_stride);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) Elem<T>::store(out + (size_t)t * d + j + i, acc[i]);
+  Elem<T>::store4(out + (size_t)t * d + j, combine_four<T, SP, U>(y, tok_ids, tok_w, residual, t, j, k, d, (size_t)M * k * d));
 }
 
 // The combine of a layer inside a stack that scales its layer inputs: one workgroup per token writes the row of the
 // new hidden state and, from the STORED (rounded) values, the next layer's input x = row / rms(row) - with the
 // element-to-thread mapping and summation order of rms_scale_row, so that the result equals, bit for bit, what
 // rms_scale_kernel makes of the stored row.  d <= 8192: a thread holds up to 8 outputs.
-template <typename T>
+template <typename T, int SP, int U>
 __global__ __launch_bounds__(kRmsThreads) void combine_scale_kernel(const float *__restrict__ y,
                                                                     const int32_t *__restrict__ tok_ids,
                                                                     const float *__restrict__ tok_w,
-                                                                    const T *__restrict__ residual, int k, int d,
-                                                                    int splits, size_t split_stride,
-                                                                    T *__restrict__ out, T *__restrict__ x_next) {
+                                                                    const T *__restrict__ residual,
+                                                                    T *__restrict__ out, T *__restrict__ x_next, int M, int k,
+                                                                    int d) {
   __shared__ float part[kRmsThreads];
   const int t = blockIdx.x, tid = threadIdx.x;
   float v[kRmsChunks][4];
@@ -1210,12 +1201,10 @@ __global__ __launch_bounds__(kRmsThreads) void combine_scale_kernel(const float 
   for (int c = 0; c < kRmsChunks; ++c) {
     const int j = (c * kRmsThreads + tid) * 4;
     if (j < d) {
-      const f32x4 acc = combine_four<T>(y, tok_ids, tok_w, residual, t, j, k, d, splits, split_stride);
+      const f32x4 acc = combine_four<T, SP, U>(y, tok_ids, tok_w, residual, t, j, k, d, (size_t)M * k * d);
+      Elem<T>::store4(out + (size_t)t * d + j, acc);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        Elem<T>::store(out + (size_t)t * d + j + i, acc[i]);
-        v[c][i] = Elem<T>::stored(acc[i]);
-      }
+      for (int i = 0; i < 4; ++i) v[c][i] = Elem<T>::stored(acc[i]);
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[c][i] = 0.f;
@@ -1225,10 +1214,33 @@ __global__ __launch_bounds__(kRmsThreads) void combine_scale_kernel(const float 
 #pragma unroll
   for (int c = 0; c < kRmsChunks; ++c) {
     const int j = (c * kRmsThreads + tid) * 4;
-    if (j < d)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) Elem<T>::store(x_next + (size_t)t * d + j + i, v[c][i] * scale);
+    if (j < d) Elem<T>::store4(x_next + (size_t)t * d + j, f32x4{v[c][0] * scale, v[c][1] * scale, v[c][2] * scale, v[c][3] * scale});
   }
+}
+
+template <typename T>
+static hipError_t launch_combine(const moespec_desc &ds, const float *y, const int32_t *tok_ids, const float *tok_w,
+                                 const void *residual, void *out, void *x_next, int M, int splits, hipStream_t st) {
+  const int k = ds.top_k, d = ds.d;
+  auto run = [&](auto sp, auto slots) {
+    constexpr int SP = decltype(sp)::value, U = decltype(slots)::value;
+    if (x_next)
+      combine_scale_kernel<T, SP, U><<<M, kRmsThreads, 0, st>>>(y, tok_ids, tok_w, static_cast<const T *>(residual),
+                                                                static_cast<T *>(out), static_cast<T *>(x_next), M, k, d);
+    else
+      combine_kernel<T, SP, U><<<dim3((d / 4 + kCombineThreads - 1) / kCombineThreads, M), kCombineThreads, 0, st>>>(
+          y, tok_ids, tok_w, static_cast<const T *>(residual), static_cast<T *>(out), M, k, d);
+    return hipGetLastError();
+  };
+  using std::integral_constant;
+  const integral_constant<int, 2> two;
+  const integral_constant<int, 4> four;
+  if constexpr (sizeof(T) == 2) {  // fp32 layers are not split
+    if (splits == kMaxDownSplits) return run(four, two);
+    if (splits == 2) return k <= 2 ? run(two, two) : run(two, four);
+  }
+  const integral_constant<int, 1> one;
+  return k <= 2 ? run(one, two) : k <= 4 ? run(one, four) : run(one, integral_constant<int, 8>{});
 }
 
 // Whether the passes can take their pairs from the prologue's lists.
@@ -1286,7 +1298,6 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     if (trace && trace[i]) (void)hipEventRecord(static_cast<hipEvent_t>(trace[i]), st);
   };
   const int splits = down_splits(ds, M, n_seg);
-  const size_t split_stride = (size_t)M * k * d;
   if (ds.dtype == MOESPEC_BF16) {
     for (int pass = 1; pass <= 2; ++pass) {
       if (pass == 1 ? wide_gate_up : wide_down) {
@@ -1316,16 +1327,7 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
       mark(pass - 1);
     }
     if (!out) return hipSuccess;  // the caller only wants the per-pair outputs y
-    if (x_next) {
-      combine_scale_kernel<uint16_t><<<M, kRmsThreads, 0, st>>>(y, tok_ids, tok_w, static_cast<const uint16_t *>(residual),
-                                                              k, d, splits, split_stride, static_cast<uint16_t *>(out),
-                                                              static_cast<uint16_t *>(x_next));
-    } else {
-      dim3 cgrid((d / 4 + 255) / 256, M);
-      combine_kernel<uint16_t><<<cgrid, 256, 0, st>>>(y, tok_ids, tok_w, static_cast<const uint16_t *>(residual), k, d,
-                                                      splits, split_stride, static_cast<uint16_t *>(out));
-    }
-    e = hipGetLastError();
+    e = launch_combine<uint16_t>(ds, y, tok_ids, tok_w, residual, out, x_next, M, splits, st);
     mark(2);
     return e;
   }
@@ -1378,16 +1380,7 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     mark(pass - 1);
   }
   if (!out) return hipSuccess;
-  if (x_next) {
-    combine_scale_kernel<float><<<M, kRmsThreads, 0, st>>>(y, tok_ids, tok_w, static_cast<const float *>(residual), k, d,
-                                                         1, split_stride, static_cast<float *>(out),
-                                                         static_cast<float *>(x_next));
-  } else {
-    dim3 cgrid((d / 4 + 255) / 256, M);
-    combine_kernel<float><<<cgrid, 256, 0, st>>>(y, tok_ids, tok_w, static_cast<const float *>(residual), k, d, 1,
-                                                 split_stride, static_cast<float *>(out));
-  }
-  e = hipGetLastError();
+  e = launch_combine<float>(ds, y, tok_ids, tok_w, residual, out, x_next, M, 1, st);
   mark(2);
   return e;
 }
