@@ -391,48 +391,57 @@ __device__ __forceinline__ void cut_pass(const uint16_t *wt0, const uint16_t *wt
 // (descending aggregate score, which is also roughly descending segment size), rank_count[r] = number of its surviving
 // pairs, listed at lists + r * list_stride.  The work items are the pieces (piece_count per expert) of the shortlisted
 // experts in rank order; the workgroup takes the one that xcd_map assigns to it.  Requires B <= kFfnThreads.
-// misc: 8 int32 of LDS scratch.  Called by every thread of the workgroup (it synchronises).  Returns the expert (-1: no
-// work item), its piece of m pairs (list) and the work item's number.
-constexpr int kLargeFlag = 1 << 16;  // above any number of pieces: kSelfMaxExperts of kSelfMaxTokens / kPiecePairs each
+// Every wave looks for itself, a lane per rank, with counts of ballots instead of a scan through LDS and two barriers: nothing of
+// the pass is requested before the item is known.  The results are uniform, so that the addresses made of them stay in scalar
+// registers.  Returns the expert (-1: no work item), its piece of m pairs (list) and the work item's number.
 template <class TF>
 __device__ __forceinline__ int listed_segment(const int32_t *__restrict__ rank_count,
-                                              const int32_t *__restrict__ shortlist, int B, TF tiles_of, int32_t *misc,
+                                              const int32_t *__restrict__ shortlist, int B, TF tiles_of,
                                               int &m, int &item, int &tile, const int32_t *__restrict__ lists,
                                               int list_stride, const int32_t *&list) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = tid < B ? rank_count[tid] : 0;
-  const int ex = tid < B ? shortlist[tid] : -1;
-  const int q = c > 0 ? piece_count(c) : 0;
-  int incl = q;  // inclusive scan of the piece counts over the shortlist ranks
+  constexpr int kGroups = kFfnThreads / kWave;  // of 64 ranks
+  const int lane = threadIdx.x & 63;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int c[kGroups], ex[kGroups], first[kGroups], n_items = 0;
+  bool large = false;
 #pragma unroll
-  for (int sft = 1; sft < kWave; sft <<= 1) {
-    const int v = __shfl_up(incl, sft, kWave);
-    if (lane >= sft) incl += v;
+  for (int i = 0; i < kGroups; ++i) {
+    const int r = i * kWave + lane;
+    c[i] = r < B ? rank_count[r] : 0;
+    ex[i] = r < B ? shortlist[r] : -1;
   }
-  const bool large = __ballot(c > 64) != 0;
-  if (lane == kWave - 1) misc[1 + wave] = incl | (large ? kLargeFlag : 0);
-  if (tid == 0) misc[0] = -1;
-  __syncthreads();
-  int before = 0, n_items = 0, flags = 0;
-  for (int w = 0; w < kFfnWaves; ++w) {
-    const int n = misc[1 + w];
-    if (w < wave) before += n & (kLargeFlag - 1);
-    n_items += n & (kLargeFlag - 1);
-    flags |= n;
+#pragma unroll
+  for (int i = 0; i < kGroups; ++i) {
+    first[i] = n_items;
+    if (i * kWave < B) {  // uniform
+      const int q = piece_count(max(c[i], 0));
+      large |= __ballot(c[i] > 64) != 0;
+      for (int bit = 0; __ballot((q >> bit) != 0) != 0; ++bit) {
+        const unsigned long long set = __ballot((q >> bit) & 1);
+        first[i] += __popcll(set & below) << bit;
+        n_items += __popcll(set) << bit;
+      }
+    }
   }
-  const bool has_work = xcd_map(tiles_of(n_items, (flags & kLargeFlag) != 0), n_items, item, tile);
-  const int first = before + incl - q;  // first work item of this thread's expert
-  if (has_work && item >= first && item < first + q) {  // one thread at most
-    const int len = (c + q - 1) / q, p = item - first;
-    misc[0] = ex;
-    misc[5] = p * len;                 // the piece: pairs [lo, lo + m) of the expert's segment
-    misc[6] = min(len, c - p * len);
-    misc[7] = tid;                     // its shortlist rank
+  m = 0;
+  list = lists;
+  int e = -1;
+  if (!xcd_map(tiles_of(n_items, large), n_items, item, tile)) return e;
+#pragma unroll
+  for (int i = 0; i < kGroups; ++i) {
+    if (i * kWave < B) {
+      const int q = piece_count(max(c[i], 0));
+      const unsigned long long hit = __ballot(item >= first[i] && item < first[i] + q);
+      if (hit) {  // one lane
+        const int src = __ffsll((long long)hit) - 1, size = __builtin_amdgcn_readlane(c[i], src);
+        const int pieces = piece_count(size), len = (size + pieces - 1) / pieces;
+        const int lo = (item - __builtin_amdgcn_readlane(first[i], src)) * len;
+        e = __builtin_amdgcn_readlane(ex[i], src);
+        m = min(len, size - lo);
+        list = lists + (size_t)(i * kWave + src) * list_stride + lo;
+      }
+    }
   }
-  __syncthreads();
-  const int e = misc[0];
-  m = e < 0 ? 0 : misc[6];
-  list = e < 0 ? lists : lists + (size_t)misc[7] * list_stride + misc[5];
   return e;
 }
 
@@ -551,7 +560,6 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
     const int32_t *__restrict__ perm, const uint16_t *__restrict__ h, const uint16_t *__restrict__ w_gate,
     const uint16_t *__restrict__ w_up, uint16_t *__restrict__ act) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
-  __shared__ int32_t misc[8];
   __shared__ uint32_t xoff[kPiecePairs];
   const int row_tiles = (F / 16 + kFfnWaves - 1) / kFfnWaves;
   bool cut = false;
@@ -562,7 +570,7 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_gateup_lds_kernel(
   int tile, rank, e, m;
   const int32_t *plist;
   if (rank_count) {
-    e = listed_segment(rank_count, shortlist, n_seg, tiles_of, misc, m, rank, tile, lists, list_stride, plist);
+    e = listed_segment(rank_count, shortlist, n_seg, tiles_of, m, rank, tile, lists, list_stride, plist);
     if (e < 0 || e >= N || m <= 0 || m > kPiecePairs) return;
   } else {
     const int4 it = xcd_item(tiles_of, cap, items, tile, rank);
@@ -655,7 +663,6 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
     const int32_t *__restrict__ perm, const uint16_t *__restrict__ act, const uint16_t *__restrict__ w_down,
     float *__restrict__ y) {
   __shared__ __align__(16) unsigned char lds[kLdsBytes];
-  __shared__ int32_t misc[8];
   __shared__ uint32_t xoff[kPiecePairs];
   // a work item is (row tile, K split): split sp sums the 128-element chunks [sp n / splits, (sp + 1) n / splits)
   // of F into its own copy of y, which the combine adds up in split order
@@ -668,7 +675,7 @@ __global__ __launch_bounds__(kFfnThreads, 2) void ffn_down_lds_kernel(
   int tile, rank, e, m;
   const int32_t *plist;
   if (rank_count) {
-    e = listed_segment(rank_count, shortlist, n_seg, tiles_of, misc, m, rank, tile, lists, list_stride, plist);
+    e = listed_segment(rank_count, shortlist, n_seg, tiles_of, m, rank, tile, lists, list_stride, plist);
     if (e < 0 || e >= N || m <= 0 || m > kPiecePairs) return;
   } else {
     const int4 it = xcd_item(tiles_of, cap, items, tile, rank);
