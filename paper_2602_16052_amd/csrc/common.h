@@ -67,7 +67,7 @@ __device__ __forceinline__ double dpp_f64(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
 }
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140, kDppRor4 = 0x124, kDppRor8 = 0x128;
 __device__ __forceinline__ double row16_max(double v) {
   v = fmax(v, dpp_f64<kDppXor1>(v));
   v = fmax(v, dpp_f64<kDppXor2>(v));
@@ -345,7 +345,7 @@ hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, cons
                          double *partial, hipStream_t st);
 hipError_t launch_gate_rows(const moespec_desc &ds, const moespec_weights &wt, int M, int slices, const double *partial,
                             double *probs, int32_t *topk_ids, float *topk_w, hipStream_t st);
-int logit_slices(const moespec_desc &ds, int M, bool whole_table, int most);
+int logit_slices(const moespec_desc &ds, int M, int most);
 hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int B,
                                  int policy, const int32_t *ext_shortlist, double *partial, double *probs_ws,
                                  double *probs_out,

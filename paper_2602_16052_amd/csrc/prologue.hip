@@ -23,7 +23,7 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 constexpr int kLogitWaves = 4;
 constexpr int kPrologueThreads = 1024;
-constexpr int kSoftmaxSegs = 16;  // threads that share one row of the table in the softmax
+constexpr int kFusedMaxTokens = 256;  // see fused_prologue_ok
 // Tables above this many entries get their softmax in a launch of its own (measured on MI355X: 4032 entries are
 // 0.6 us faster rebuilt in every workgroup, 8128 entries 0.9 us and 16256 entries 2.3 us faster with the extra launch).
 constexpr long long kSplitSoftmaxAbove = 6000;
@@ -33,6 +33,11 @@ template <typename T> struct LogitPiece;
 template <> struct LogitPiece<uint16_t> {
   uint4 v;
   __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint4 *>(p); }
+  // n elements of the row are left (a multiple of 8): zeros past its end
+  __device__ __forceinline__ void load_part(const uint16_t *p, int n) {
+    v = uint4{0, 0, 0, 0};
+    if (n > 0) load(p);
+  }
   __device__ __forceinline__ double get(int m) const {
     const uint32_t word = reinterpret_cast<const uint32_t *>(&v)[m >> 1];
     return (double)__uint_as_float(m & 1 ? (word & 0xffff0000u) : (word << 16));
@@ -43,6 +48,11 @@ template <> struct LogitPiece<float> {
   __device__ __forceinline__ void load(const float *p) {
     v[0] = reinterpret_cast<const float4 *>(p)[0];
     v[1] = reinterpret_cast<const float4 *>(p)[1];
+  }
+  __device__ __forceinline__ void load_part(const float *p, int n) {  // n: a multiple of 4
+    v[0] = v[1] = float4{0.f, 0.f, 0.f, 0.f};
+    if (n > 0) v[0] = reinterpret_cast<const float4 *>(p)[0];
+    if (n > 4) v[1] = reinterpret_cast<const float4 *>(p)[1];
   }
   __device__ __forceinline__ double get(int m) const { return (double)reinterpret_cast<const float *>(v)[m]; }
 };
@@ -123,10 +133,64 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T
   }
 }
 
+// The same for small tables, finished in one launch: logits[t][e] = h[t] . w_r[e] + bias[e].  A workgroup owns 4 tokens x 4
+// experts and the whole hidden dimension, which its 8 waves share in chunks of 128 elements.  v_mfma_f64_4x4x4 multiplies four
+// independent blocks: lane (i, c) = (lane % 4, lane / 4) supplies A[i] and B[i] of its own piece c of the hidden dimension
+// (block c % 4, element c / 4), and D[i][j] of block b arrives in lane 16 i + 4 b + j; the four blocks are added at the end.
+// Sixteen times as many workgroups as 16 x 16 tiles, so that the hidden dimension need not be cut over workgroups and the consumer
+// loads one table instead of up to eight; twice the widening per multiply-add, which matters only where tables are large.
+constexpr int kTableWaves = 8, kTableChunk = 128;
+template <typename T>
+__global__ __launch_bounds__(kTableWaves *kWave) void logits_table_kernel(const T *__restrict__ h, const T *__restrict__ w_r,
+                                                                          const float *__restrict__ bias, int M, int N, int d,
+                                                                          double *__restrict__ logits) {
+  __shared__ double red[kTableWaves][kWave];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int e_tiles = (N + 3) / 4;
+  const int tt = blockIdx.x / e_tiles, et = blockIdx.x % e_tiles;
+  const int i = lane & 3, at = (lane >> 2) * 8;
+  const int t = min(tt * 4 + i, M - 1), e = min(et * 4 + i, N - 1);  // pad rows repeat the last one, never stored
+  const T *ha = h + (size_t)t * d, *wb = w_r + (size_t)e * d;
+  const int n_chunks = (d + kTableChunk - 1) / kTableChunk;
+  double acc[2] = {0.0, 0.0};
+  constexpr int PB = 4;  // chunks in flight
+  for (int c0 = wave; c0 < n_chunks; c0 += PB * kTableWaves) {
+    LogitPiece<T> A[PB], Bv[PB];
+#pragma unroll
+    for (int u = 0; u < PB; ++u) {
+      if (c0 + u * kTableWaves < n_chunks) {  // uniform in the wave
+        const int j = (c0 + u * kTableWaves) * kTableChunk + at;
+        A[u].load_part(ha + j, d - j);
+        Bv[u].load_part(wb + j, d - j);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < PB; ++u) {
+      if (c0 + u * kTableWaves < n_chunks) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+          acc[m & 1] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[u].get(m), Bv[u].get(m), acc[m & 1], 0, 0, 0);
+      }
+    }
+  }
+  red[wave][lane] = acc[0] + acc[1];
+  __syncthreads();
+  if (wave == 0) {
+    double v[kTableWaves];
+#pragma unroll
+    for (int w = 0; w < kTableWaves; ++w) v[w] = red[w][lane];
+    double a = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    a += dpp_f64<kDppRor8>(a);
+    a += dpp_f64<kDppRor4>(a);
+    const int row = tt * 4 + (lane >> 4), col = et * 4 + (lane & 3);
+    if ((lane & 12) == 0 && row < M && col < N) logits[(size_t)row * N + col] = a + (bias ? (double)bias[col] : 0.0);
+  }
+}
+
 // LDS of route_budget_kernel.  Rows of the table are N + 1 doubles apart: lanes that walk down a column (one token
 // per lane) then touch different banks.
 struct PrologueLds {
-  size_t g, s, red, S, cand, rank, pos, sel, inS, total;
+  size_t g, s, count, S, cand, pos, sel, inS, total;
 };
 __host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B) {
   PrologueLds L;
@@ -138,10 +202,9 @@ __host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B) 
   };
   L.g = take(sizeof(double) * (size_t)M * (N + 1));
   L.s = take(sizeof(double) * N);
-  L.red = take(sizeof(double) * kPrologueThreads);
-  L.S = take(sizeof(int32_t) * B);
-  L.cand = take(sizeof(int32_t) * (N + kWave));
-  L.rank = take(sizeof(int32_t) * N);
+  L.count = take(sizeof(int32_t) * 2 * (kPrologueThreads / kWave));
+  L.S = take(sizeof(int32_t) * (B + kWave));
+  L.cand = take(sizeof(int32_t) * (B + kWave));
   L.pos = take(sizeof(int32_t) * N);
   L.sel = take(sizeof(int32_t) * k);
   L.inS = take((size_t)N);
@@ -151,82 +214,70 @@ __host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B) 
 
 // list_count[r] = number of pairs routed to the expert at shortlist rank r after the restriction;
 // lists[r * list_stride + p] = flat id t * k + slot of its p-th pair, tokens ascending.
-// Q = slices of the router projection, NE = ceil(N / 16) = elements of a table row per lane in the softmax (both
-// compile-time so that the short loops unroll: a taken branch costs this hardware about as much as ten fp64
-// operations).  Up to the shortlist the whole workgroup works on the table (16 consecutive lanes share a row and
-// reduce through DPP, 16 lanes share a candidate of the shortlist and split its rivals; a token's rank counts add up with
-// integer LDS atomics).  Comparisons are written without short-circuit evaluation and
-// loops in fixed blocks of four or eight, so that the code stays straight-line.
-template <int Q, int NE>
+// table: logits with their bias, or (kTableReady) the finished routing probabilities, in which case Eq. (1) is skipped.
+// NE = ceil(N / 16) = elements of a table row per lane in the softmax (compile-time so that the short loops unroll: a taken branch
+// costs this hardware about as much as ten fp64 operations).  16 consecutive lanes share a row, a column, a candidate or a token
+// and reduce through DPP; the 64 groups of a round that have nothing to do are skipped wave by wave, because 16 waves share the
+// issue slots of 4 SIMDs (the chain of fp64 operations of a 15 x 8 table took 1.0 us in 16 waves, of which 12 had no row).
+// Comparisons are written without short-circuit evaluation and loops in fixed blocks of four, so that the code stays straight-line.
+enum : int { kTableReady = 1, kSigmoidGate = 2, kTruncate = 4, kRenorm = 8 };
+template <int NE>
 __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
-    const double *__restrict__ partial, const float *__restrict__ bias, int M, int N, int k, int B, int list_wgs,
-    int table_ready, int sigmoid_gate, int policy, const int32_t *__restrict__ ext_shortlist, int renorm, int list_stride,
-    double *__restrict__ probs_out, double *__restrict__ scores_out, int32_t *__restrict__ budget_ids,
-    int32_t *__restrict__ seg_expert, int32_t *__restrict__ tok_ids, float *__restrict__ tok_w,
-    int32_t *__restrict__ list_count, int32_t *__restrict__ lists) {
+    const double *__restrict__ table, int M, int N, int k, int B, int list_wgs, int flags, int list_stride,
+    const int32_t *__restrict__ ext_shortlist, double *__restrict__ probs_out, double *__restrict__ scores_out,
+    int32_t *__restrict__ budget_ids, int32_t *__restrict__ seg_expert, int32_t *__restrict__ tok_ids,
+    float *__restrict__ tok_w, int32_t *__restrict__ list_count, int32_t *__restrict__ lists) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PrologueLds L = prologue_lds(M, N, k, B);
   double *g = reinterpret_cast<double *>(smem + L.g);        // [M][N + 1] logits, then routing probabilities
   double *s = reinterpret_cast<double *>(smem + L.s);        // [N] aggregate scores
-  double *red = reinterpret_cast<double *>(smem + L.red);    // [1024] partial column sums
-  int32_t *S = reinterpret_cast<int32_t *>(smem + L.S);      // [B] shortlist in rank order
-  int32_t *cand = reinterpret_cast<int32_t *>(smem + L.cand);  // [n_cand, padded to 64] a token's candidates
-  int32_t *rank = reinterpret_cast<int32_t *>(smem + L.rank);
+  int32_t *count = reinterpret_cast<int32_t *>(smem + L.count);  // [2][16] pairs per wave of a list (two lists in turn)
+  int32_t *S = reinterpret_cast<int32_t *>(smem + L.S);      // [B] shortlist in rank order, -1 behind it
   int32_t *pos = reinterpret_cast<int32_t *>(smem + L.pos);  // [N] shortlist rank of every expert
-  volatile int32_t *sel = reinterpret_cast<int32_t *>(smem + L.sel);  // [k] this token's selection
+  int32_t *sel = reinterpret_cast<int32_t *>(smem + L.sel);  // [k] this token's selection
   uint8_t *inS = smem + L.inS;
-  constexpr int nt = kPrologueThreads;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int nt = kPrologueThreads, kGroups = nt / 16, kWaves = nt / kWave, kWaveGroups = kGroups / kWaves;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = tid >> 4, seg = tid & 15, group0 = wave * kWaveGroups;  // group0: the first of this wave
+  const bool table_ready = flags & kTableReady, truncate = flags & kTruncate;
   // The first list_wgs workgroups build the pair lists and the others take a token each; list_wgs = 0: a workgroup does both.
   // own: this workgroup's token; below zero or past the end: it only builds pair lists
   const int own = (int)blockIdx.x - list_wgs;
+  const int list_step = list_wgs ? list_wgs : max(M, B), last_wg = (list_wgs ? M + B : max(M, B)) - 1;
   const int NS = N + 1;
 
-  // logits: the slices of the hidden dimension added in slice order, plus the router bias
-  // (table_ready: `partial` already holds the finished routing probabilities, one slice, and Eq. (1) is skipped)
-  const int MN = M * N;
-  const bool fixed_col = nt % N == 0;  // then element tid + u nt always lies in column tid % N
-  const int col0 = tid % N, row0 = tid / N, rows_per_step = nt / N;
-  const double own_bias = (bias && fixed_col) ? (double)bias[col0] : 0.0;
-  for (int x0 = 0; x0 < MN; x0 += 4 * nt) {
-    double v[4][Q];
+  {
+    const int MN = M * N, dt = nt / N, di = nt % N;
+    int t = tid / N, i = tid % N;
+    for (int x0 = 0; x0 < MN; x0 += 4 * nt) {
+      double v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < 4; ++u) v[u] = x0 + u * nt + tid < MN ? table[x0 + u * nt + tid] : 0.0;
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const int x = x0 + u * nt + tid;
-        v[u][q] = x < MN ? partial[(size_t)q * MN + x] : 0.0;
-      }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int x = x0 + u * nt + tid;
-      if (x < MN) {
-        double a = v[u][0];
-#pragma unroll
-        for (int q = 1; q < Q; ++q) a += v[u][q];
-        const int t = fixed_col ? (x0 / nt + u) * rows_per_step + row0 : x / N;
-        const int i = fixed_col ? col0 : x % N;
-        g[t * NS + i] = a + (fixed_col ? own_bias : (bias ? (double)bias[i] : 0.0));
+      for (int u = 0; u < 4; ++u) {
+        if (x0 + u * nt + tid < MN) g[t * NS + i] = v[u];
+        t += dt;
+        i += di;
+        if (i >= N) i -= N, ++t;
       }
     }
   }
   for (int i = tid; i < N; i += nt) {
     inS[i] = 0;
     pos[i] = 0x7fffffff;
-    rank[i] = 0;
   }
-  for (int r = tid; r < B; r += nt) S[r] = -1;  // NaN scores: several experts count rank 0, slots stay unfilled
+  for (int r = tid; r < B + kWave; r += nt) S[r] = -1;  // NaN scores: several experts count rank 0, slots stay unfilled
+  for (int j = tid; j < k; j += nt) sel[j] = -1;
   __syncthreads();
 
   // Eq. (1): 16 lanes per row, 64 rows per round; a lane holds its NE elements of the row in registers
-  const int seg = tid & 15;
-  for (int t0 = 0; t0 < M && !table_ready; t0 += nt / 16) {
-    const int t = t0 + (tid >> 4);
+  for (int t0 = 0; t0 + group0 < M && !table_ready; t0 += kGroups) {
+    const int t = t0 + group;
     double *row = g + (t < M ? t : M - 1) * NS;
     double val[NE];
 #pragma unroll
     for (int u = 0; u < NE; ++u) val[u] = (t < M && seg + 16 * u < N) ? row[seg + 16 * u] : -INFINITY;
-    if (sigmoid_gate) {
+    if (flags & kSigmoidGate) {
 #pragma unroll
       for (int u = 0; u < NE; ++u)
         if (t < M && seg + 16 * u < N) row[seg + 16 * u] = 1.0 / (1.0 + exp(-val[u]));
@@ -251,11 +302,11 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   if (probs_out && !table_ready && own >= 0 && own < M)  // (a finished table was written where the caller wants it)
     for (int i = tid; i < N; i += nt) probs_out[(size_t)own * N + i] = g[own * NS + i];
 
-  // Eq. (5): s_i = sum_t g_i(h_t).  16 lanes share a column: lane p adds tokens p, p + 16, ... in ascending order
-  // and the 16 partial sums are folded through DPP; 64 columns per round.
+  // Eq. (5): s_i = sum_t g_i(h_t).  Lane p of a column adds tokens p, p + 16, ... in ascending order and the 16 partial sums
+  // are folded through DPP; 64 columns per round.
   if (ext_shortlist == nullptr || scores_out != nullptr) {
-    for (int c0 = 0; c0 < N; c0 += nt / 16) {
-      const int col = min(c0 + (tid >> 4), N - 1);
+    for (int c0 = 0; c0 + group0 < N; c0 += kGroups) {
+      const int col = min(c0 + group, N - 1);
       double a = 0.0;
       for (int t = seg; t < M; t += 64) {  // fixed blocks of 4 tokens: the loads go out together
         double v[4];
@@ -265,15 +316,15 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
         for (int u = 0; u < 4; ++u) a += v[u];  // rows past the end add +0.0, which leaves the sum unchanged
       }
       a = row16_sum(a);
-      if (seg == 0 && c0 + (tid >> 4) < N) s[col] = a;
+      if (seg == 0 && c0 + group < N) s[col] = a;
     }
     __syncthreads();
   }
   // Section 3.2: the B highest aggregate scores, ties to the lowest id - or the caller's shortlist
   if (ext_shortlist == nullptr) {
     // 16 lanes share a candidate and split its rivals: lane p takes p, p + 16, ...; 64 candidates per round
-    for (int c0 = 0; c0 < N; c0 += nt / 16) {
-      const int i = c0 + (tid >> 4);
+    for (int c0 = 0; c0 + group0 < N; c0 += kGroups) {
+      const int i = c0 + group;
       const double vi = s[min(i, N - 1)];
       int c = 0;
       for (int j = seg; j < N; j += 64) {
@@ -301,25 +352,24 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
       }
     }
   }
-  for (int j = tid; j < k; j += nt) sel[j] = -1;
   __syncthreads();
   // a token's candidates: all experts under truncation (Eq. (7) restricts the natural top-k afterwards), the
   // shortlist in rank order under substitution (Eq. (8)); -1 marks an entry of an external shortlist that is out of
-  // range or a repeat, and the padding up to a multiple of 64
-  const bool truncate = policy == MOESPEC_TRUNCATE;
+  // range or a repeat, and what lies behind the end
+  const int32_t *cand = S;
   const int n_cand = truncate ? N : B;
-  const int n_cand_pad = (n_cand + kWave - 1) & ~(kWave - 1);
-  for (int x = tid; x < n_cand_pad; x += nt) {
-    int j = -1;
-    if (x < n_cand) {
-      j = truncate ? x : S[x];
-      if (!truncate && !((uint32_t)j < (uint32_t)N && pos[j] == x)) j = -1;
+  if (ext_shortlist != nullptr && !truncate) {
+    int32_t *checked = reinterpret_cast<int32_t *>(smem + L.cand);  // [B + 64]
+    for (int x = tid; x < B + kWave; x += nt) {
+      const int j = S[x];
+      checked[x] = (uint32_t)j < (uint32_t)N && pos[j] == x ? j : -1;
     }
-    cand[x] = j;
+    cand = checked;
+    __syncthreads();
   }
   // copies for the caller and for the expert passes, written by the last workgroup: it has no pair list to build where the
   // lists have workgroups of their own or the tokens outnumber the shortlist
-  if (blockIdx.x == gridDim.x - 1) {
+  if ((int)blockIdx.x == last_wg) {
     for (int i = tid; i < N; i += nt) {
       if (scores_out) scores_out[i] = s[i];
       if (seg_expert && inS[i]) {  // position of expert i among the shortlisted experts in ascending id
@@ -338,45 +388,47 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
       }
     }
   }
-  __syncthreads();
 
   // "x goes before y" in a ranking by (probability descending, id ascending), without short-circuit evaluation
   // (which would turn into divergent control flow)
   auto before = [](double vx, int jx, double vy, int jy) { return (vx > vy) | ((vx == vy) & (jx < jy)); };
+  // The number of a token's candidates that go before expert e with value v, counted by 16 lanes; row: the token's probabilities.
+  auto rank_among = [&](const double *row, double v, int e) {
+    int c = 0;
+    if (truncate) {
+      for (int y = seg; y < N; y += 64) {
+        double vy[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) vy[u] = row[min(y + 16 * u, N - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c += (int)((y + 16 * u < N) & before(vy[u], y + 16 * u, v, e));
+      }
+    } else {
+      for (int y = seg; y < B; y += 64) {
+        int jy[4];
+        double vy[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) jy[u] = cand[min(y + 16 * u, B)];  // entry B: -1
+#pragma unroll
+        for (int u = 0; u < 4; ++u) vy[u] = row[max(jy[u], 0)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c += (int)((jy[u] >= 0) & before(vy[u], jy[u], v, e));
+      }
+    }
+    return row16_sum(c);
+  };
 
   // This token's restricted routing.  Eq. (7) keeps the natural top-k slots that fall inside S with their weights
   // unchanged; Eq. (8) takes the top-k inside S and weights over that selection.  A candidate's rank is the number
-  // of candidates that go before it; rank r < k fills slot r.  Thread (x, p): candidate x against the p-th share
-  // of the rivals.
-  int cand_j = -1;
+  // of candidates that go before it; rank r < k fills slot r.
   if (own >= 0) {
-    const double *grow = g + min(own, M - 1) * NS;
-    int cp2 = 64, cp2_log = 6;  // candidates rounded up to a power of two, at least one wave
-    while (cp2 < n_cand) cp2 <<= 1, ++cp2_log;
-    const int rparts = nt >> cp2_log, x = tid & (cp2 - 1), p = tid >> cp2_log;
-    const int rper = (n_cand + rparts - 1) / rparts;
-    const int j = x < n_cand_pad ? cand[x] : -1;
-    const double v = grow[j < 0 ? 0 : j];
-    const int y1 = min(n_cand, (p + 1) * rper);
-    int c = 0;
-    for (int y = p * rper; y < y1; y += 4) {
-      int jy[4];
-      double vy[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) jy[u] = cand[min(y + u, n_cand_pad - 1)];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) vy[u] = grow[jy[u] < 0 ? 0 : jy[u]];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) c += (int)((y + u < y1) & (jy[u] >= 0) & before(vy[u], jy[u], v, j));
+    const double *row = g + min(own, M - 1) * NS;
+    for (int x0 = 0; x0 + group0 < n_cand; x0 += kGroups) {
+      const int x = x0 + group, j = x >= n_cand ? -1 : truncate ? x : cand[x];
+      const int c = rank_among(row, row[max(j, 0)], j);
+      if (seg == 0 && j >= 0 && c < k) sel[c] = j;
     }
-    if (c && j >= 0) atomicAdd(&rank[x], c);  // j >= 0 implies x < n_cand <= N
-    cand_j = j;
   }
-  // the two remaining steps of the token's routing wait for one barrier each; they ride on the barriers of the first
-  // pair-list round below when this workgroup has one
-  auto token_fill_slots = [&]() {
-    if (tid < n_cand && cand_j >= 0 && rank[tid] < k) sel[rank[tid]] = cand_j;
-  };
   auto token_write = [&]() {
     if (tid < k && own < M) {
       const int e = sel[tid];
@@ -386,7 +438,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
       for (int sl = 0; sl < k; ++sl)
         denom += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(ge), sl),
                                   __builtin_amdgcn_readlane(__double2loint(ge), sl));
-      const double w = keep ? (renorm ? ge / denom : ge) : 0.0;
+      const double w = keep ? (flags & kRenorm ? ge / denom : ge) : 0.0;
       tok_ids[(size_t)own * k + tid] = keep ? e : -1;
       tok_w[(size_t)own * k + tid] = (float)w;
     }
@@ -394,53 +446,52 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   bool token_done = own < 0;
 
   // Pair lists of this workgroup's shortlist ranks: token t is routed to expert e = S[r] iff e ranks among the
-  // first k of t's candidates; its rank is the slot.  16 lanes share a token and split its rivals; 64 tokens per
-  // round; the routed tokens of a round are compacted in token order with one ballot per wave.
-  const int list_step = list_wgs ? list_wgs : gridDim.x;
-  for (int r = list_wgs && own >= 0 ? B : (int)blockIdx.x; r < B; r += list_step) {
+  // first k of t's candidates; its rank is the slot.  A wave takes 4 tokens per round, one behind the other, and its
+  // routed tokens are compacted with one ballot per round; the waves' counts are exchanged once per list.
+  constexpr int kMaxRounds = (kFusedMaxTokens + kGroups - 1) / kGroups;
+  const int rounds = (M + kGroups - 1) / kGroups;
+  int parity = 0;
+  for (int r = list_wgs && own >= 0 ? B : (int)blockIdx.x; r < B; r += list_step, parity ^= 1) {
     const int e = S[r];
     const bool real = (uint32_t)e < (uint32_t)N && pos[e] == r;  // not a repeat, not out of range
-    int base = 0;
-    for (int t0 = 0; t0 < M; t0 += nt / 16) {
-      const int t = min(t0 + (tid >> 4), M - 1);
-      const double *row = g + t * NS;
-      const double ge = row[real ? e : 0];
-      int c = 0;
-      for (int y = seg; y < n_cand; y += 64) {  // rivals seg, seg + 16, ... four at a time
-        int jy[4];
-        double vy[4];
+    const int wave_t0 = wave * kWaveGroups * rounds;
+    int c[kMaxRounds], n_wave = 0;
+    unsigned long long mask[kMaxRounds];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) jy[u] = cand[min(y + 16 * u, n_cand_pad - 1)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) vy[u] = row[jy[u] < 0 ? 0 : jy[u]];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) c += (int)((y + 16 * u < n_cand) & (jy[u] >= 0) & before(vy[u], jy[u], ge, e));
+    for (int rd = 0; rd < kMaxRounds; ++rd) {
+      mask[rd] = 0;
+      c[rd] = 0;
+      const int t0 = wave_t0 + rd * kWaveGroups;
+      if (rd < rounds && t0 < M) {  // uniform in the wave
+        const int t = t0 + (lane >> 4);
+        const double *row = g + min(t, M - 1) * NS;
+        const double ge = row[real ? e : 0];
+        c[rd] = rank_among(row, ge, e);
+        mask[rd] = __ballot(real & (t < M) & (seg == 0) & (c[rd] < k) & (ge == ge));  // NaN ranks nowhere
+        n_wave += __popcll(mask[rd]);
       }
-      c = row16_sum(c);
-      const bool routed = real & (t0 + (tid >> 4) < M) & (seg == 0) & (c < k) & (ge == ge);  // NaN ranks nowhere
-      const unsigned long long mask = __ballot(routed);
-      __syncthreads();  // the wave counts of the previous round have been read (and the rank counts are complete)
-      if (!token_done) token_fill_slots();
-      if (lane == 0) red[wave] = (double)__popcll(mask);
-      __syncthreads();
-      if (!token_done) token_write();
-      token_done = true;
-      int at = base, total = 0;
-#pragma unroll
-      for (int w = 0; w < nt / kWave; ++w) {
-        const int cw = (int)red[w];
-        at += w < wave ? cw : 0;
-        total += cw;
-      }
-      at += __popcll(mask & ((1ull << lane) - 1ull));
-      if (routed) lists[(size_t)r * list_stride + at] = t * k + c;
-      base += total;
     }
-    if (tid == 0) list_count[r] = base;
+    if (lane == 0) count[parity * kWaves + wave] = n_wave;
+    __syncthreads();  // the counts, and the selection of the token
+    if (!token_done) token_write();
+    token_done = true;
+    int at = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const int cw = count[parity * kWaves + w];
+      at += w < wave ? cw : 0;
+      total += cw;
+    }
+#pragma unroll
+    for (int rd = 0; rd < kMaxRounds; ++rd) {
+      if ((mask[rd] >> lane) & 1)
+        lists[(size_t)r * list_stride + at + __popcll(mask[rd] & ((1ull << lane) - 1ull))] =
+            (wave_t0 + rd * kWaveGroups + (lane >> 4)) * k + c[rd];
+      at += __popcll(mask[rd]);
+    }
+    if (tid == 0) list_count[r] = total;
   }
   if (!token_done) {  // a workgroup without a pair list
-    __syncthreads();
-    token_fill_slots();
     __syncthreads();
     token_write();
   }
@@ -506,18 +557,16 @@ __global__ __launch_bounds__(256) void lists_to_segments_kernel(const int32_t *_
 // again, come in rounds, while the staged kernels grow with the tokens alone.  Whole fp32 layer of 4 experts, us, fused
 // less staged: 128 tokens -4, 160 -2, 200 to 256 +1, 300 +2, 400 +5, 512 +16, 1024 +68; of 64 experts, top-8: 128 -5, 256 -5,
 // 300 0; bf16 within 4 up to 256.
-constexpr int kFusedMaxTokens = 256;
 bool fused_prologue_ok(const moespec_desc &ds, int M) {
   if (ds.n_experts > kSelfMaxExperts || M > kFusedMaxTokens) return false;
   return prologue_lds(M, ds.n_experts, ds.top_k, ds.n_experts).total <= 160 * 1024;
 }
 
 // Slices of the hidden dimension (1, 2, 4 or 8, at most `most`): more slices spread the matrix work over more compute units
-// (a wave issues one fp64 matrix instruction per 64 cycles), but the consumer re-reads one partial table per
-// slice: every workgroup of the fused kernel the whole table (whole_table), the row-wise gate kernel one row.
+// (a wave issues one fp64 matrix instruction per 64 cycles), but the row-wise gate kernel re-reads its row once per slice.
 // Picks the count with the smallest estimated sum of the two (rates measured on MI355X: 2.4 GHz, about 150 GB/s
 // from L2 into one compute unit).
-int logit_slices(const moespec_desc &ds, int M, bool whole_table, int most) {
+int logit_slices(const moespec_desc &ds, int M, int most) {
   const double tiles = ((M + 15) / 16) * ((ds.n_experts + 15) / 16), n_blocks = ds.d / 32;
   int best = 1;
   double best_us = 1e30;
@@ -525,7 +574,7 @@ int logit_slices(const moespec_desc &ds, int M, bool whole_table, int most) {
     if (q > 1 && n_blocks < 2.0 * q * kLogitWaves) break;  // at least two 32-element blocks per wave
     const double waves_per_simd = tiles * q * kLogitWaves / 1024.0;  // 256 compute units x 4 SIMDs
     const double mfma_us = (n_blocks / (q * kLogitWaves)) * 8 * 64 / 2400.0 * (waves_per_simd > 1 ? waves_per_simd : 1);
-    const double read_us = q * 8.0 * (whole_table ? M : 1) * ds.n_experts / 150e3;
+    const double read_us = q * 8.0 * ds.n_experts / 150e3;
     if (mfma_us + read_us < best_us) {
       best_us = mfma_us + read_us;
       best = q;
@@ -569,22 +618,28 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
   // Large tables: the routing probabilities are finished row by row in a launch of their own and the last kernel
   // only loads them; small tables: every workgroup of the last kernel rebuilds the table itself.
   const bool split = (long long)M * N > kSplitSoftmaxAbove;
-  const int q = logit_slices(ds, M, !split, kMaxLogitSlices);
-  hipError_t e = launch_logits(ds, wt, h, M, q, partial, st);
-  if (e != hipSuccess) return e;
   const size_t smem = prologue_lds(M, N, k, B).total;
-  const int sig = ds.gate == MOESPEC_GATE_SIGMOID ? 1 : 0;
+  const int flags = (split ? kTableReady : 0) | (ds.gate == MOESPEC_GATE_SIGMOID ? kSigmoidGate : 0) |
+                    (policy == MOESPEC_TRUNCATE ? kTruncate : 0) | (ds.renorm ? kRenorm : 0);
   const double *table = partial;
-  const float *table_bias = wt.b_router;
-  int slices = q;
+  hipError_t e;
   if (split) {
+    const int q = logit_slices(ds, M, kMaxLogitSlices);
+    if ((e = launch_logits(ds, wt, h, M, q, partial, st)) != hipSuccess) return e;
     double *probs = probs_out ? probs_out : probs_ws;
     if ((e = launch_gate_rows(ds, wt, M, q, partial, probs, nullptr, nullptr, st)) != hipSuccess) return e;
     table = probs;
-    table_bias = nullptr;
-    slices = 1;
+  } else {
+    const int tiles = ((M + 3) / 4) * ((N + 3) / 4);
+    if (ds.dtype == MOESPEC_BF16)
+      logits_table_kernel<uint16_t><<<tiles, kTableWaves * kWave, 0, st>>>(
+          static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_router), wt.b_router, M, N, ds.d, partial);
+    else
+      logits_table_kernel<float><<<tiles, kTableWaves * kWave, 0, st>>>(
+          static_cast<const float *>(h), static_cast<const float *>(wt.w_router), wt.b_router, M, N, ds.d, partial);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // instantiation for (slices, elements of a table row per lane = ceil(N / 16) rounded up to a power of two)
+  // instantiation for the elements of a table row per lane: ceil(N / 16) rounded up to a power of two
   auto run = [&](auto kern) -> hipError_t {
     if (smem > 64 * 1024) {  // beyond the default limit of a launch
       hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -596,18 +651,14 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
     // lists have workgroups of their own (15 tokens x 8 experts 6.8 -> 6.4 us, 7 x 64 10.3 -> 8.6, 63 x 64 10.5 -> 9.7, 127 x 128 12.3
     // -> 11.7); each loads the whole table, so not in a second round.
     const int list_wgs = M + B <= 256 ? B : 0;
-    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(
-        table, table_bias, M, N, k, B, list_wgs, split ? 1 : 0, sig, policy, ext_shortlist, ds.renorm, list_stride, probs_out,
-        scores_out, budget_ids, seg_expert, tok_ids, tok_w, list_count, lists);
+    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(table, M, N, k, B, list_wgs, flags, list_stride,
+                                                                            ext_shortlist, probs_out, scores_out, budget_ids,
+                                                                            seg_expert, tok_ids, tok_w, list_count, lists);
     return hipGetLastError();
   };
   const int ne = (N + 15) / 16;
-#define MOESPEC_RB_NE(QQ)                                                                        \
-  (ne <= 1 ? run(route_budget_kernel<QQ, 1>) : ne <= 2 ? run(route_budget_kernel<QQ, 2>)         \
-   : ne <= 4 ? run(route_budget_kernel<QQ, 4>) : ne <= 8 ? run(route_budget_kernel<QQ, 8>)       \
-                                                         : run(route_budget_kernel<QQ, 16>))
-  e = slices == 1 ? MOESPEC_RB_NE(1) : slices == 2 ? MOESPEC_RB_NE(2) : slices == 4 ? MOESPEC_RB_NE(4) : MOESPEC_RB_NE(8);
-#undef MOESPEC_RB_NE
+  e = ne <= 1 ? run(route_budget_kernel<1>) : ne <= 2 ? run(route_budget_kernel<2>) : ne <= 4 ? run(route_budget_kernel<4>)
+      : ne <= 8 ? run(route_budget_kernel<8>) : run(route_budget_kernel<16>);
   if (e != hipSuccess) return e;
   if (seg_off || perm || n_loaded) {
     lists_to_segments_kernel<<<1, 256, 0, st>>>(budget_ids, list_count, lists, list_stride, B, N, M * k, seg_off, perm,

@@ -264,7 +264,7 @@ hipError_t launch_route(const moespec_desc &ds, const moespec_weights &wt, const
   if (mfma_route_ok(ds)) {
     // one slice is accumulated in the caller's table (above kSelfMaxTokens a table of several has the place of y: 1025 tokens
     // x 8 experts of d = 4096 19.3 -> 11.2 us, where the output tiles do not fill the chip)
-    const int slices = logit_slices(ds, M, false, partial_slices);
+    const int slices = logit_slices(ds, M, partial_slices);
     double *logits = slices == 1 ? probs : partial;
     hipError_t e = launch_logits(ds, wt, h, M, slices, logits, st);
     return e != hipSuccess ? e : launch_gate_rows(ds, wt, M, slices, logits, probs, topk_ids, topk_w, st);
