@@ -114,10 +114,10 @@ moespec_status layer_forward(const moespec_desc *desc, const moespec_weights *we
     if (tr && tr[i]) (void)hipEventRecord(static_cast<hipEvent_t>(tr[i]), st);
   };
   mark(0);
-  if (fused_prologue_ok(*desc, M) && expert_ffn_self_segmenting(*desc, M) && !expert_ffn_wide(*desc, M, B)) {
+  if (fused_prologue_ok(*desc, M, B, policy) && expert_ffn_self_segmenting(*desc, M) && !expert_ffn_wide(*desc, M, B)) {
     // Small trees: two launches leave the shortlist, the restricted routing and every loaded expert's pair
     // list; the expert passes pick their work items from those lists.
-    hipError_t e = launch_fused_prologue(*desc, *weights, h, M, B, policy, ext_shortlist, w.partial, w.probs, t.probs,
+    hipError_t e = launch_fused_prologue(*desc, *weights, h, M, B, policy, ext_shortlist, w.partial, w.score_parts, w.y, w.probs, t.probs,
                                          t.scores,
                                          budget_ids, t.seg_expert, tok_ids, tok_w, w.list_count, w.lists, M,
                                          t.seg_off, t.perm, t.n_loaded, st);

@@ -176,6 +176,53 @@ __device__ __forceinline__ void rank_counts(const double *row, int j0, int j1, i
   }
 }
 
+// val[u] = logit of expert lane + 64 u of token t (-inf past the row end): its Q slices in order, plus the router bias.
+template <int Q, int NU>
+__device__ __forceinline__ void load_logits(const double *partial, const float *bias, int M, int N, int t, double (&val)[NU]) {
+  const size_t MN = (size_t)M * N, at = (size_t)t * N;
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int i = (threadIdx.x & 63) + kWave * u;
+    val[u] = -INFINITY;
+    if (i < N) {
+      double v[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[q] = partial[q * MN + at + i];
+      val[u] = v[0];
+#pragma unroll
+      for (int q = 1; q < Q; ++q) val[u] += v[q];
+      val[u] += bias ? (double)bias[i] : 0.0;
+    }
+  }
+}
+
+// Eq. (1) for a row held by a wave: val[u] = logit of expert lane + 64 u (-inf past the row end), replaced by its probability.
+template <int NU>
+__device__ __forceinline__ void gate_of_row(double (&val)[NU], int sigmoid_gate) {
+  if (sigmoid_gate) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) val[u] = 1.0 / (1.0 + exp(-val[u]));
+    return;
+  }
+  auto all_lanes = [](double v, auto op) {  // the 16-lane result of every row of lanes combined across the 4 rows
+    v = op(v, __shfl_xor(v, 16, kWave));
+    return op(v, __shfl_xor(v, 32, kWave));
+  };
+  double m = val[0];
+#pragma unroll
+  for (int u = 1; u < NU; ++u) m = fmax(m, val[u]);
+  m = all_lanes(row16_max(m), [](double a, double b) { return fmax(a, b); });
+  double a = 0.0;
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    val[u] = exp_nonpos(val[u] - m);  // lanes past the row end come out as 0
+    a += val[u];
+  }
+  const double inv = 1.0 / all_lanes(row16_sum(a), [](double x, double y) { return x + y; });
+#pragma unroll
+  for (int u = 0; u < NU; ++u) val[u] *= inv;
+}
+
 // Rank-count selection of the k best of v[0..n).  sel[r] receives the index with rank r < k.  Equivalent to sorting by
 // (value descending, index ascending) and keeping the first k.  v, sel and the scratch rank[n] live in LDS.  Called by
 // every thread of the workgroup (it synchronises); the caller synchronises again before reading sel.  The n x n
@@ -334,9 +381,9 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
 // The fused prologue of the layer call (prologue.hip): router projection on the fp64 matrix cores, then one
 // launch that leaves the shortlist (budget_ids), the restricted routing (tok_ids, tok_w) and, for every shortlist
 // rank r, the pairs routed to its expert (list_count[r]; lists[r * list_stride ..], flat ids t * k + slot, tokens
-// ascending).  partial: [logit_slices, M, N] doubles of scratch.  probs_out, scores_out, seg_expert, seg_off,
+// ascending).  partial: [logit_slices, M, N] doubles of scratch, parts: [64, N], ranks_ws: what fused_prologue_ok asks of y.  probs_out, scores_out, seg_expert, seg_off,
 // perm, n_loaded are optional copies for the caller (the last three cost one more small launch).
-bool fused_prologue_ok(const moespec_desc &ds, int M);
+bool fused_prologue_ok(const moespec_desc &ds, int M, int B, int policy);
 // The two halves of stage 1 for layers of up to kSelfMaxExperts experts (mfma_route_ok): the router projection on
 // the fp64 matrix cores (partial [slices, M, N] out), then bias, gate and - if wanted - the natural top-k, one wave per
 // token (partial may be probs itself when there is one slice).
@@ -347,9 +394,8 @@ hipError_t launch_gate_rows(const moespec_desc &ds, const moespec_weights &wt, i
                             double *probs, int32_t *topk_ids, float *topk_w, hipStream_t st);
 int logit_slices(const moespec_desc &ds, int M, int most);
 hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int B,
-                                 int policy, const int32_t *ext_shortlist, double *partial, double *probs_ws,
-                                 double *probs_out,
-                                 double *scores_out, int32_t *budget_ids, int32_t *seg_expert, int32_t *tok_ids,
+                                 int policy, const int32_t *ext_shortlist, double *partial, double *parts, void *ranks_ws, double *probs_ws,
+                                 double *probs_out, double *scores_out, int32_t *budget_ids, int32_t *seg_expert, int32_t *tok_ids,
                                  float *tok_w, int32_t *list_count, int32_t *lists, int list_stride,
                                  int32_t *seg_off, int32_t *perm, int32_t *n_loaded, hipStream_t st);
 bool expert_ffn_self_segmenting(const moespec_desc &ds, int M);

@@ -24,9 +24,10 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 constexpr int kLogitWaves = 4;
 constexpr int kPrologueThreads = 1024;
 constexpr int kFusedMaxTokens = 256;  // see fused_prologue_ok
-// Tables above this many entries get their softmax in a launch of its own (measured on MI355X: 4032 entries are
-// 0.6 us faster rebuilt in every workgroup, 8128 entries 0.9 us and 16256 entries 2.3 us faster with the extra launch).
-constexpr long long kSplitSoftmaxAbove = 6000;
+// Tables above this many entries get their softmax, and the ranks of their rows, in a launch of their own.  Whole bf16 layer of
+// d = 2048, us, rebuilt in every workgroup / extra launch: 47 x 64 35.8 / 37.1, 63 x 64 37.9 / 39.0, 40 x 128 41.6 / 42.0, 79 x 64
+// 44.3 / 43.8, 93 x 64 45.6 / 44.7, 127 x 64 49.3 / 47.5.
+constexpr long long kSplitSoftmaxAbove = 5500;
 
 // 8 consecutive elements of a row, widened one by one
 template <typename T> struct LogitPiece;
@@ -187,12 +188,71 @@ __global__ __launch_bounds__(kTableWaves *kWave) void logits_table_kernel(const 
   }
 }
 
-// LDS of route_budget_kernel.  Rows of the table are N + 1 doubles apart: lanes that walk down a column (one token
-// per lane) then touch different banks.
+// Larger tables take a launch between the projection and the last one: Eq. (1) row by row, and what the last kernel needs of the
+// table in place of its fp64 values.
+//   ranks[t][i]  (16 bits) the natural rank of expert i for token t: how many experts go before it by (probability descending,
+//                id ascending).  The restricted routings compare ranks only: a rank among the shortlisted experts is the number
+//                of shortlisted experts with a smaller natural one.  kNaNRank where the probability is a NaN, which ranks nowhere.
+//   parts[b][i]  the sum of the probabilities of expert i over the tokens kPartTokens b, ... (Eq. (5))
+// Every workgroup of the last kernel loads a quarter of the bytes, and adds 32 rows at 127 tokens where it added 127.
+// The first workgroups make a part each, a token per wave; the others a token's ranks each: all 4 waves evaluate its row and count
+// against a quarter of the rivals.  That the rows are evaluated twice costs nothing, they lie side by side on compute units that
+// would idle (4 tokens and their part in one workgroup of 16 waves: 6.6 us instead of 4.8 at 127 tokens x 128 experts).
+constexpr int kPartTokens = 4, kRankThreads = 4 * kWave, kNaNRank = 0xffff;
+// Elements from one row of ranks to the next, in memory and in the LDS: 16 bytes more than the row is long, so that the 4 tokens of a
+// wave touch different banks.
+__host__ __device__ inline int rank_row(int N) { return ((N + 7) & ~7) + 8; }
+template <int Q, int NU>
+__global__ __launch_bounds__(kRankThreads) void rank_rows_kernel(const double *__restrict__ partial, const float *__restrict__ bias,
+                                                                 int M, int N, int n_parts, int sigmoid_gate,
+                                                                 double *__restrict__ probs, double *__restrict__ parts,
+                                                                 uint16_t *__restrict__ ranks) {
+  __shared__ double rows[4][NU * kWave];
+  __shared__ int32_t counts[4][NU * kWave];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool part = (int)blockIdx.x < n_parts;
+  const int t = part ? (int)blockIdx.x * kPartTokens + wave : (int)blockIdx.x - n_parts;
+  double val[NU];
+  load_logits<Q, NU>(partial, bias, M, N, min(t, M - 1), val);
+  gate_of_row<NU>(val, sigmoid_gate);
+  if (part) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) rows[wave][lane + kWave * u] = t < M ? val[u] : 0.0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < N; i += kRankThreads)
+      parts[(size_t)blockIdx.x * N + i] = ((rows[0][i] + rows[1][i]) + rows[2][i]) + rows[3][i];
+    return;
+  }
+  if (wave == 0) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int i = lane + kWave * u;
+      rows[0][i] = i < N ? val[u] : kNoRival;
+      if (i < N) probs[(size_t)t * N + i] = val[u];
+    }
+  }
+  __syncthreads();
+  int c[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) c[u] = 0;
+  const int quads = (N + 3) / 4;
+  rank_counts<NU>(rows[0], quads * wave / 4 * 4, quads * (wave + 1) / 4 * 4, lane, 0, val, c);
+#pragma unroll
+  for (int u = 0; u < NU; ++u) counts[wave][lane + kWave * u] = c[u];
+  __syncthreads();
+  for (int i = threadIdx.x; i < N; i += kRankThreads) {
+    const double v = rows[0][i];
+    const int r = (counts[0][i] + counts[1][i]) + (counts[2][i] + counts[3][i]);
+    ranks[(size_t)t * rank_row(N) + i] = (uint16_t)(v == v ? r : kNaNRank);
+  }
+}
+
+// LDS of route_budget_kernel.  Rows of the table are N + 1 doubles apart: lanes that walk down a column (one token per lane) then
+// touch different banks.
 struct PrologueLds {
-  size_t g, s, count, S, cand, pos, sel, inS, total;
+  size_t g, s, red, count, S, cand, pos, sel, inS, total;
 };
-__host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B) {
+__host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B, bool ranked) {
   PrologueLds L;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -200,8 +260,9 @@ __host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B) 
     off += (bytes + 15) & ~(size_t)15;
     return at;
   };
-  L.g = take(sizeof(double) * (size_t)M * (N + 1));
+  L.g = take(ranked ? sizeof(uint16_t) * (size_t)M * rank_row(N) : sizeof(double) * (size_t)M * (N + 1));
   L.s = take(sizeof(double) * N);
+  L.red = take(ranked ? sizeof(double) * kPrologueThreads : 0);
   L.count = take(sizeof(int32_t) * 2 * (kPrologueThreads / kWave));
   L.S = take(sizeof(int32_t) * (B + kWave));
   L.cand = take(sizeof(int32_t) * (B + kWave));
@@ -214,23 +275,27 @@ __host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B) 
 
 // list_count[r] = number of pairs routed to the expert at shortlist rank r after the restriction;
 // lists[r * list_stride + p] = flat id t * k + slot of its p-th pair, tokens ascending.
-// table: logits with their bias, or (kTableReady) the finished routing probabilities, in which case Eq. (1) is skipped.
-// NE = ceil(N / 16) = elements of a table row per lane in the softmax (compile-time so that the short loops unroll: a taken branch
-// costs this hardware about as much as ten fp64 operations).  16 consecutive lanes share a row, a column, a candidate or a token
+// NE > 0: table = logits with their bias; NE = ceil(N / 16) = elements of a table row per lane in the softmax (compile-time so that
+// the short loops unroll: a taken branch costs this hardware about as much as ten fp64 operations).  NE = 0: table = the ranks,
+// beside them probs and parts, all from rank_rows_kernel.  16 consecutive lanes share a row, a column, a candidate or a token
 // and reduce through DPP; the 64 groups of a round that have nothing to do are skipped wave by wave, because 16 waves share the
 // issue slots of 4 SIMDs (the chain of fp64 operations of a 15 x 8 table took 1.0 us in 16 waves, of which 12 had no row).
 // Comparisons are written without short-circuit evaluation and loops in fixed blocks of four, so that the code stays straight-line.
-enum : int { kTableReady = 1, kSigmoidGate = 2, kTruncate = 4, kRenorm = 8 };
+enum : int { kSigmoidGate = 1, kTruncate = 2, kRenorm = 4 };
 template <int NE>
 __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
-    const double *__restrict__ table, int M, int N, int k, int B, int list_wgs, int flags, int list_stride,
-    const int32_t *__restrict__ ext_shortlist, double *__restrict__ probs_out, double *__restrict__ scores_out,
-    int32_t *__restrict__ budget_ids, int32_t *__restrict__ seg_expert, int32_t *__restrict__ tok_ids,
-    float *__restrict__ tok_w, int32_t *__restrict__ list_count, int32_t *__restrict__ lists) {
+    const void *__restrict__ table, int M, int N, int k, int B, int list_wgs, int flags, int list_stride,
+    const int32_t *__restrict__ ext_shortlist, const double *__restrict__ parts, const double *__restrict__ probs,
+    double *__restrict__ probs_out, double *__restrict__ scores_out, int32_t *__restrict__ budget_ids,
+    int32_t *__restrict__ seg_expert, int32_t *__restrict__ tok_ids, float *__restrict__ tok_w,
+    int32_t *__restrict__ list_count, int32_t *__restrict__ lists) {
+  constexpr bool kRanked = NE == 0;
   extern __shared__ __align__(16) unsigned char smem[];
-  const PrologueLds L = prologue_lds(M, N, k, B);
+  const PrologueLds L = prologue_lds(M, N, k, B, kRanked);
   double *g = reinterpret_cast<double *>(smem + L.g);        // [M][N + 1] logits, then routing probabilities
+  uint16_t *nr = reinterpret_cast<uint16_t *>(smem + L.g);   // kRanked: [M][rank_row(N)] natural ranks
   double *s = reinterpret_cast<double *>(smem + L.s);        // [N] aggregate scores
+  double *red = reinterpret_cast<double *>(smem + L.red);    // kRanked: [1024] sums of the parts by group
   int32_t *count = reinterpret_cast<int32_t *>(smem + L.count);  // [2][16] pairs per wave of a list (two lists in turn)
   int32_t *S = reinterpret_cast<int32_t *>(smem + L.S);      // [B] shortlist in rank order, -1 behind it
   int32_t *pos = reinterpret_cast<int32_t *>(smem + L.pos);  // [N] shortlist rank of every expert
@@ -239,20 +304,53 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   constexpr int nt = kPrologueThreads, kGroups = nt / 16, kWaves = nt / kWave, kWaveGroups = kGroups / kWaves;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = tid >> 4, seg = tid & 15, group0 = wave * kWaveGroups;  // group0: the first of this wave
-  const bool table_ready = flags & kTableReady, truncate = flags & kTruncate;
+  const bool truncate = flags & kTruncate;
   // The first list_wgs workgroups build the pair lists and the others take a token each; list_wgs = 0: a workgroup does both.
   // own: this workgroup's token; below zero or past the end: it only builds pair lists
   const int own = (int)blockIdx.x - list_wgs;
   const int list_step = list_wgs ? list_wgs : max(M, B), last_wg = (list_wgs ? M + B : max(M, B)) - 1;
-  const int NS = N + 1;
+  const int NS = N + 1, NR = rank_row(N);
 
-  {
+  const bool want_scores = ext_shortlist == nullptr || scores_out != nullptr;
+  if constexpr (kRanked) {
+    const int total = M * NR / 8;  // pieces of 16 bytes
+    const uint4 *from = static_cast<const uint4 *>(table);
+    uint4 *to = reinterpret_cast<uint4 *>(nr);
+    uint4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = from[min(u * nt + tid, total - 1)];
+    if (want_scores) {  // Eq. (5) from the parts, with the first ranks on their way: a group of threads adds every n_groups-th
+      int cp2 = 64, cp2_log = 6;
+      while (cp2 < N) cp2 <<= 1, ++cp2_log;
+      const int col = tid & (cp2 - 1), n_rows = (M + kPartTokens - 1) / kPartTokens, n_groups = nt >> cp2_log;
+      double a = 0.0;
+      for (int r = tid >> cp2_log; r < n_rows; r += 4 * n_groups) {
+        double x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = col < N && r + u * n_groups < n_rows ? parts[(size_t)(r + u * n_groups) * N + col] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a += x[u];
+      }
+      red[tid] = a;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (u * nt + tid < total) to[u * nt + tid] = v[u];
+    for (int x0 = 4 * nt; x0 < total; x0 += 4 * nt) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = from[min(x0 + u * nt + tid, total - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (x0 + u * nt + tid < total) to[x0 + u * nt + tid] = v[u];
+    }
+  } else {
+    const double *logits = static_cast<const double *>(table);
     const int MN = M * N, dt = nt / N, di = nt % N;
     int t = tid / N, i = tid % N;
     for (int x0 = 0; x0 < MN; x0 += 4 * nt) {
       double v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = x0 + u * nt + tid < MN ? table[x0 + u * nt + tid] : 0.0;
+      for (int u = 0; u < 4; ++u) v[u] = x0 + u * nt + tid < MN ? logits[x0 + u * nt + tid] : 0.0;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         if (x0 + u * nt + tid < MN) g[t * NS + i] = v[u];
@@ -271,52 +369,63 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   __syncthreads();
 
   // Eq. (1): 16 lanes per row, 64 rows per round; a lane holds its NE elements of the row in registers
-  for (int t0 = 0; t0 + group0 < M && !table_ready; t0 += kGroups) {
+  for (int t0 = 0; !kRanked && t0 + group0 < M; t0 += kGroups) {
+    constexpr int NE_ = kRanked ? 1 : NE;
     const int t = t0 + group;
     double *row = g + (t < M ? t : M - 1) * NS;
-    double val[NE];
+    double val[NE_];
 #pragma unroll
-    for (int u = 0; u < NE; ++u) val[u] = (t < M && seg + 16 * u < N) ? row[seg + 16 * u] : -INFINITY;
+    for (int u = 0; u < NE_; ++u) val[u] = (t < M && seg + 16 * u < N) ? row[seg + 16 * u] : -INFINITY;
     if (flags & kSigmoidGate) {
 #pragma unroll
-      for (int u = 0; u < NE; ++u)
+      for (int u = 0; u < NE_; ++u)
         if (t < M && seg + 16 * u < N) row[seg + 16 * u] = 1.0 / (1.0 + exp(-val[u]));
     } else {
       double m = val[0];
 #pragma unroll
-      for (int u = 1; u < NE; ++u) m = fmax(m, val[u]);
+      for (int u = 1; u < NE_; ++u) m = fmax(m, val[u]);
       m = row16_max(m);
       double a = 0.0;
 #pragma unroll
-      for (int u = 0; u < NE; ++u) {
+      for (int u = 0; u < NE_; ++u) {
         val[u] = exp_nonpos(val[u] - m);  // elements past the row end are -inf: they come out as 0
         a += val[u];
       }
       const double inv = 1.0 / row16_sum(a);
 #pragma unroll
-      for (int u = 0; u < NE; ++u)
+      for (int u = 0; u < NE_; ++u)
         if (t < M && seg + 16 * u < N) row[seg + 16 * u] = val[u] * inv;
     }
   }
-  __syncthreads();
-  if (probs_out && !table_ready && own >= 0 && own < M)  // (a finished table was written where the caller wants it)
+  if constexpr (!kRanked) __syncthreads();
+  if (!kRanked && probs_out && own >= 0 && own < M)  // (rank_rows_kernel writes where the caller wants it)
     for (int i = tid; i < N; i += nt) probs_out[(size_t)own * N + i] = g[own * NS + i];
 
-  // Eq. (5): s_i = sum_t g_i(h_t).  Lane p of a column adds tokens p, p + 16, ... in ascending order and the 16 partial sums
-  // are folded through DPP; 64 columns per round.
-  if (ext_shortlist == nullptr || scores_out != nullptr) {
-    for (int c0 = 0; c0 + group0 < N; c0 += kGroups) {
-      const int col = min(c0 + group, N - 1);
-      double a = 0.0;
-      for (int t = seg; t < M; t += 64) {  // fixed blocks of 4 tokens: the loads go out together
-        double v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = t + 16 * u < M ? g[(t + 16 * u) * NS + col] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) a += v[u];  // rows past the end add +0.0, which leaves the sum unchanged
+  // Eq. (5): s_i = sum_t g_i(h_t).  Lane p of a column adds tokens p, p + 16, ... in ascending order and the 16 sums are folded
+  // through DPP; 64 columns per round.
+  if (want_scores) {
+    if constexpr (kRanked) {
+      int cp2 = 64;
+      while (cp2 < N) cp2 <<= 1;
+      if (tid < N) {
+        double a = red[tid];
+        for (int r = cp2; r < nt; r += cp2) a += red[r + tid];
+        s[tid] = a;
       }
-      a = row16_sum(a);
-      if (seg == 0 && c0 + group < N) s[col] = a;
+    } else {
+      for (int c0 = 0; c0 + group0 < N; c0 += kGroups) {
+        const int col = min(c0 + group, N - 1);
+        double a = 0.0;
+        for (int t = seg; t < M; t += 64) {  // fixed blocks of 4 tokens: the loads go out together
+          double v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = t + 16 * u < M ? g[(t + 16 * u) * NS + col] : 0.0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) a += v[u];  // rows past the end add +0.0, which leaves the sum unchanged
+        }
+        a = row16_sum(a);
+        if (seg == 0 && c0 + group < N) s[col] = a;
+      }
     }
     __syncthreads();
   }
@@ -392,48 +501,65 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   // "x goes before y" in a ranking by (probability descending, id ascending), without short-circuit evaluation
   // (which would turn into divergent control flow)
   auto before = [](double vx, int jx, double vy, int jy) { return (vx > vy) | ((vx == vy) & (jx < jy)); };
-  // The number of a token's candidates that go before expert e with value v, counted by 16 lanes; row: the token's probabilities.
-  auto rank_among = [&](const double *row, double v, int e) {
+  // The number of token t's candidates that go before expert e, counted by 16 lanes; -1 (or, unranked, any number) for a NaN.
+  auto rank_among = [&](int t, int e) {
     int c = 0;
-    if (truncate) {
-      for (int y = seg; y < N; y += 64) {
-        double vy[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) vy[u] = row[min(y + 16 * u, N - 1)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) c += (int)((y + 16 * u < N) & before(vy[u], y + 16 * u, v, e));
-      }
-    } else {
+    if constexpr (kRanked) {
+      const uint16_t *row = nr + t * NR;
+      const int own_rank = row[e];
+      if (truncate) return own_rank;
       for (int y = seg; y < B; y += 64) {
-        int jy[4];
-        double vy[4];
+        int jy[4], ry[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) jy[u] = cand[min(y + 16 * u, B)];  // entry B: -1
 #pragma unroll
-        for (int u = 0; u < 4; ++u) vy[u] = row[max(jy[u], 0)];
+        for (int u = 0; u < 4; ++u) ry[u] = row[max(jy[u], 0)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c += (int)((jy[u] >= 0) & before(vy[u], jy[u], v, e));
+        for (int u = 0; u < 4; ++u) c += (int)((jy[u] >= 0) & (ry[u] < own_rank));
       }
+      return row16_sum(c) + (own_rank == kNaNRank ? kNaNRank : 0);
+    } else {
+      const double *row = g + t * NS;
+      const double v = row[e];
+      if (truncate) {
+        for (int y = seg; y < N; y += 64) {
+          double vy[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) vy[u] = row[min(y + 16 * u, N - 1)];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) c += (int)((y + 16 * u < N) & before(vy[u], y + 16 * u, v, e));
+        }
+      } else {
+        for (int y = seg; y < B; y += 64) {
+          int jy[4];
+          double vy[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) jy[u] = cand[min(y + 16 * u, B)];  // entry B: -1
+#pragma unroll
+          for (int u = 0; u < 4; ++u) vy[u] = row[max(jy[u], 0)];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) c += (int)((jy[u] >= 0) & before(vy[u], jy[u], v, e));
+        }
+      }
+      return row16_sum(c) + (v == v ? 0 : kNaNRank);
     }
-    return row16_sum(c);
   };
 
   // This token's restricted routing.  Eq. (7) keeps the natural top-k slots that fall inside S with their weights
   // unchanged; Eq. (8) takes the top-k inside S and weights over that selection.  A candidate's rank is the number
-  // of candidates that go before it; rank r < k fills slot r.
+  // of candidates that go before it; rank r < k fills slot r.  A NaN claims slot 0: its weight makes the token's output NaN.
   if (own >= 0) {
-    const double *row = g + min(own, M - 1) * NS;
     for (int x0 = 0; x0 + group0 < n_cand; x0 += kGroups) {
       const int x = x0 + group, j = x >= n_cand ? -1 : truncate ? x : cand[x];
-      const int c = rank_among(row, row[max(j, 0)], j);
-      if (seg == 0 && j >= 0 && c < k) sel[c] = j;
+      const int c = rank_among(min(own, M - 1), max(j, 0));
+      if (seg == 0 && j >= 0 && (c < k || c >= kNaNRank)) sel[c < k ? c : 0] = j;
     }
   }
   auto token_write = [&]() {
     if (tid < k && own < M) {
       const int e = sel[tid];
       const bool keep = e >= 0 && inS[e] != 0;  // an unfilled slot (NaN scores) is dropped
-      const double ge = e >= 0 ? g[own * NS + e] : 0.0;
+      const double ge = e >= 0 ? (kRanked ? probs[(size_t)own * N + e] : g[own * NS + e]) : 0.0;
       double denom = 0.0;  // over the selected set in slot order (before any slot is dropped: Eq. (7)); k <= 64: one wave
       for (int sl = 0; sl < k; ++sl)
         denom += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(ge), sl),
@@ -464,10 +590,8 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
       const int t0 = wave_t0 + rd * kWaveGroups;
       if (rd < rounds && t0 < M) {  // uniform in the wave
         const int t = t0 + (lane >> 4);
-        const double *row = g + min(t, M - 1) * NS;
-        const double ge = row[real ? e : 0];
-        c[rd] = rank_among(row, ge, e);
-        mask[rd] = __ballot(real & (t < M) & (seg == 0) & (c[rd] < k) & (ge == ge));  // NaN ranks nowhere
+        c[rd] = rank_among(min(t, M - 1), real ? e : 0);
+        mask[rd] = __ballot(real & (t < M) & (seg == 0) & (c[rd] < k));  // NaN ranks nowhere
         n_wave += __popcll(mask[rd]);
       }
     }
@@ -551,15 +675,26 @@ __global__ __launch_bounds__(256) void lists_to_segments_kernel(const int32_t *_
   }
 }
 
-// The fused prologue covers layers whose M x N table of doubles fits the LDS of one workgroup beside the
-// selection scratch, with at most kSelfMaxExperts experts (one thread per shortlist rank in the expert passes) and at most
-// one token per compute unit.  With more tokens the workgroups, each of which loads the whole table and ranks its experts
+// The fused prologue covers layers with at most kSelfMaxExperts experts (one thread per shortlist rank in the expert passes) and at
+// most one token per compute unit.  With more tokens the workgroups, each of which loads the whole table and ranks its experts
 // again, come in rounds, while the staged kernels grow with the tokens alone.  Whole fp32 layer of 4 experts, us, fused
 // less staged: 128 tokens -4, 160 -2, 200 to 256 +1, 300 +2, 400 +5, 512 +16, 1024 +68; of 64 experts, top-8: 128 -5, 256 -5,
 // 300 0; bf16 within 4 up to 256.
-bool fused_prologue_ok(const moespec_desc &ds, int M) {
-  if (ds.n_experts > kSelfMaxExperts || M > kFusedMaxTokens) return false;
-  return prologue_lds(M, ds.n_experts, ds.top_k, ds.n_experts).total <= 160 * 1024;
+// Within that, tables of doubles beyond the LDS came to the staged kernels before ranks took their place.  Under substitution a pair
+// list ranks its expert against the whole shortlist, and where that is long a workgroup has several lists: the staged kernels keep
+// those.  bf16 layers of d = 1024, d_ff = 128, us, staged / fused: 150 x 128 49.0 / 39.6, 256 tokens x 128 experts with 128
+// shortlisted 51.3 / 46.8, 200 x 200 with 100 52.3 / 50.9, but with 200 52.2 / 55.8; 256 x 256 with 64 55.2 / 55.0, with 256 55.5 /
+// 64.6; truncation 200 x 256 53.4 / 52.6, 256 x 256 55.4 / 54.2 to 56.1.
+bool fused_prologue_ok(const moespec_desc &ds, int M, int B, int policy) {
+  const int N = ds.n_experts;
+  if (N > kSelfMaxExperts || M > kFusedMaxTokens) return false;
+  const bool ranked = (long long)M * N > kSplitSoftmaxAbove;
+  // the ranks lie in the place of y: [kMaxDownSplits][M k, d] floats
+  if (ranked && sizeof(uint16_t) * rank_row(N) > sizeof(float) * kMaxDownSplits * ds.top_k * ds.d) return false;
+  if (ranked && prologue_lds(M, N, ds.top_k, N, false).total > 160 * 1024 &&
+      (policy == MOESPEC_TRUNCATE ? M * N > 60000 : N > 128 && M * B > 20480))
+    return false;
+  return prologue_lds(M, N, ds.top_k, N, ranked).total <= 160 * 1024;
 }
 
 // Slices of the hidden dimension (1, 2, 4 or 8, at most `most`): more slices spread the matrix work over more compute units
@@ -609,26 +744,34 @@ hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, cons
 }
 
 hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int B,
-                                 int policy, const int32_t *ext_shortlist, double *partial, double *probs_ws,
-                                 double *probs_out,
-                                 double *scores_out, int32_t *budget_ids, int32_t *seg_expert, int32_t *tok_ids,
+                                 int policy, const int32_t *ext_shortlist, double *partial, double *parts, void *ranks_ws, double *probs_ws,
+                                 double *probs_out, double *scores_out, int32_t *budget_ids, int32_t *seg_expert, int32_t *tok_ids,
                                  float *tok_w, int32_t *list_count, int32_t *lists, int list_stride,
                                  int32_t *seg_off, int32_t *perm, int32_t *n_loaded, hipStream_t st) {
   const int N = ds.n_experts, k = ds.top_k;
   // Large tables: the routing probabilities are finished row by row in a launch of their own and the last kernel
   // only loads them; small tables: every workgroup of the last kernel rebuilds the table itself.
   const bool split = (long long)M * N > kSplitSoftmaxAbove;
-  const size_t smem = prologue_lds(M, N, k, B).total;
-  const int flags = (split ? kTableReady : 0) | (ds.gate == MOESPEC_GATE_SIGMOID ? kSigmoidGate : 0) |
+  const size_t smem = prologue_lds(M, N, k, B, split).total;
+  const int flags = (ds.gate == MOESPEC_GATE_SIGMOID ? kSigmoidGate : 0) |
                     (policy == MOESPEC_TRUNCATE ? kTruncate : 0) | (ds.renorm ? kRenorm : 0);
-  const double *table = partial;
+  double *probs = nullptr;
+  uint16_t *ranks = static_cast<uint16_t *>(ranks_ws);
   hipError_t e;
   if (split) {
     const int q = logit_slices(ds, M, kMaxLogitSlices);
     if ((e = launch_logits(ds, wt, h, M, q, partial, st)) != hipSuccess) return e;
-    double *probs = probs_out ? probs_out : probs_ws;
-    if ((e = launch_gate_rows(ds, wt, M, q, partial, probs, nullptr, nullptr, st)) != hipSuccess) return e;
-    table = probs;
+    probs = probs_out ? probs_out : probs_ws;
+    const int n_parts = (M + kPartTokens - 1) / kPartTokens;
+    auto rank = [&](auto kern) {
+      kern<<<M + n_parts, kRankThreads, 0, st>>>(partial, wt.b_router, M, N, n_parts, flags & kSigmoidGate, probs, parts, ranks);
+      return hipGetLastError();
+    };
+#define MOESPEC_RANK(Q) \
+  (N <= 64 ? rank(rank_rows_kernel<Q, 1>) : N <= 128 ? rank(rank_rows_kernel<Q, 2>) : rank(rank_rows_kernel<Q, 4>))
+    e = q == 1 ? MOESPEC_RANK(1) : q == 2 ? MOESPEC_RANK(2) : q == 4 ? MOESPEC_RANK(4) : MOESPEC_RANK(8);
+#undef MOESPEC_RANK
+    if (e != hipSuccess) return e;
   } else {
     const int tiles = ((M + 3) / 4) * ((N + 3) / 4);
     if (ds.dtype == MOESPEC_BF16)
@@ -651,13 +794,13 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
     // lists have workgroups of their own (15 tokens x 8 experts 6.8 -> 6.4 us, 7 x 64 10.3 -> 8.6, 63 x 64 10.5 -> 9.7, 127 x 128 12.3
     // -> 11.7); each loads the whole table, so not in a second round.
     const int list_wgs = M + B <= 256 ? B : 0;
-    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(table, M, N, k, B, list_wgs, flags, list_stride,
-                                                                            ext_shortlist, probs_out, scores_out, budget_ids,
+    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(split ? static_cast<const void *>(ranks) : partial, M, N, k, B, list_wgs, flags, list_stride,
+                                                                            ext_shortlist, parts, probs, probs_out, scores_out, budget_ids,
                                                                             seg_expert, tok_ids, tok_w, list_count, lists);
     return hipGetLastError();
   };
   const int ne = (N + 15) / 16;
-  e = ne <= 1 ? run(route_budget_kernel<1>) : ne <= 2 ? run(route_budget_kernel<2>) : ne <= 4 ? run(route_budget_kernel<4>)
+  e = split ? run(route_budget_kernel<0>) : ne <= 1 ? run(route_budget_kernel<1>) : ne <= 2 ? run(route_budget_kernel<2>) : ne <= 4 ? run(route_budget_kernel<4>)
       : ne <= 8 ? run(route_budget_kernel<8>) : run(route_budget_kernel<16>);
   if (e != hipSuccess) return e;
   if (seg_off || perm || n_loaded) {

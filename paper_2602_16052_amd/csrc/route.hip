@@ -147,42 +147,9 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
   __shared__ int32_t rank[kShare ? NU * kWave : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = kShare ? blockIdx.x : blockIdx.x * kWaves + wave;
   if (t >= M) return;
-  const size_t MN = (size_t)M * N;
   double val[NU];
-#pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    const int i = lane + kWave * u;
-    double a = -INFINITY;
-    if (i < N) {
-      a = partial[(size_t)t * N + i];
-#pragma unroll
-      for (int q = 1; q < Q; ++q) a += partial[q * MN + (size_t)t * N + i];
-      a += bias ? (double)bias[i] : 0.0;
-    }
-    val[u] = a;
-  }
-  if (sigmoid_gate) {
-#pragma unroll
-    for (int u = 0; u < NU; ++u) val[u] = 1.0 / (1.0 + exp(-val[u]));
-  } else {
-    auto all_lanes = [](double v, auto op) {  // the 16-lane result of every row combined across the 4 rows
-      v = op(v, __shfl_xor(v, 16, kWave));
-      return op(v, __shfl_xor(v, 32, kWave));
-    };
-    double m = val[0];
-#pragma unroll
-    for (int u = 1; u < NU; ++u) m = fmax(m, val[u]);
-    m = all_lanes(row16_max(m), [](double a, double b) { return fmax(a, b); });
-    double a = 0.0;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      val[u] = exp_nonpos(val[u] - m);  // lanes past the row end hold -inf: they come out as 0
-      a += val[u];
-    }
-    const double inv = 1.0 / all_lanes(row16_sum(a), [](double x, double y) { return x + y; });
-#pragma unroll
-    for (int u = 0; u < NU; ++u) val[u] *= inv;
-  }
+  load_logits<Q, NU>(partial, bias, M, N, t, val);
+  gate_of_row<NU>(val, sigmoid_gate);
   if constexpr (kShare) {
     for (int i = threadIdx.x; i < NU * kWave; i += kGateThreads) rank[i] = 0;
     if (wave == 0) {
