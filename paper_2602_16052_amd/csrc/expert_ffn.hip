@@ -1138,6 +1138,182 @@ __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_down_f32_mfma
   }
 }
 
+// The same sums for K up to 768 with the weights held in registers: a workgroup owns NA tiles of 16 rows and passes the segment's
+// pairs by them in tiles of 16, so that the weights are read once per workgroup, all its loads of a tile are in flight together and
+// those of the next tile go out before the sums of the present one are folded.  KA = rounds of 2 steps per wave (K <= 256 KA).
+// The chains are worked off one after the other and added as they end, in the order of f32_mfma_walk (bit-identical): one
+// chain and its partial sums live instead of 8, which leaves the registers for two workgroups per compute unit.
+// Elements past the end of K come from a line of zeros: no branch around a load, so that the waits can be counted.
+// What bounds it: a tile of pairs is a chain of LDS sums and a barrier behind 8 KA matrix instructions per tile of rows; two workgroups
+// take turns.  63 tokens over 8 experts of 512 x 1024: gate/up pass 20.2 -> 16.0 us, layer 42.7 -> 37.9; 57 drawn layers of 64 to
+// 1024 elements and up to 127 tokens 1.03x, up to 1.24x, 0.97x at least.  Up to 768 elements: held for four rounds the weights leave
+// one workgroup per compute unit (down pass above, K = 1024, 12.4 -> 15.3 us; 628 x 872, 11 segments of 2 pairs, layer 25.3 -> 28.2).
+// x_row(id): row of a pair; out(row, pair, its id, sums of the NA tiles' rows).  part: 2 [kMfWaves][NA][kMfPart] floats of LDS.
+constexpr int kF32HeldK = 768;
+__device__ const f32x4 kF32Zeros = {0.f, 0.f, 0.f, 0.f};
+template <int NA, int KA, class X, class F>
+__device__ __forceinline__ void f32_held_tiles(const float *const (&w)[NA], const int32_t *plist, int n_pairs, X x_row, int K, int p0,
+                                               int step, int m, float *part, F out) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15;
+  const int k0 = wave * 2 * kMfStep + 4 * (lane >> 4);
+  const bool whole = ((KA - 1) * kMfWaves + wave) * 2 * kMfStep < K;
+  f32x4 A[KA][2][NA], B[KA][2];
+  auto id_of = [&](int p) { return plist[min(p + i, m - 1)]; };  // pairs past the end repeat the last one, never stored
+  auto load = [&](const float *row, int r, int u) {
+    const int k = k0 + r * (kMfWaves * 2 * kMfStep) + u * kMfStep;
+    const float *p = k < K ? row + k : reinterpret_cast<const float *>(&kF32Zeros);
+    return *(const __attribute__((address_space(1))) f32x4 *)(p);  // both are global memory: no flat load
+  };
+  auto load_pairs = [&](int id) {
+    const float *x = x_row(min(max(id, 0), n_pairs - 1));
+#pragma unroll
+    for (int r = 0; r < KA; ++r)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) B[r][u] = load(x, r, u);
+  };
+  int id = id_of(p0);
+  __builtin_amdgcn_sched_barrier(0);  // loads return in the order of their issue
+#pragma unroll
+  for (int r = 0; r < KA; ++r)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) A[r][u][a] = load(w[a], r, u);
+  int next = id_of(p0 + step);
+  __builtin_amdgcn_sched_barrier(0);  // the weights are on their way before the pair ids are waited for
+  load_pairs(id);
+  int parity = 0;
+  for (int p = p0; p < m; p += step, parity ^= 1) {
+    f32x4 sum[NA];
+    auto chains = [&](auto rounds_) {
+      constexpr int R = decltype(rounds_)::value;
+      f32x4 one[NA], two[NA], four[NA];  // sums of 1, 2 and 4 chains that wait for their neighbours
+#pragma unroll
+      for (int c = 0; c < kF32Chains; ++c) {
+        f32x4 v[NA];
+#pragma unroll
+        for (int a = 0; a < NA; ++a) v[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int a = 0; a < NA; ++a)
+            v[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[r][c >> 2][a][c & 3], B[r][c >> 2][c & 3], v[a], 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+          if ((c & 1) == 0) {
+            one[a] = v[a];
+          } else if ((c & 2) == 0) {
+            two[a] = one[a] + v[a];
+          } else if ((c & 4) == 0) {
+            four[a] = two[a] + (one[a] + v[a]);
+          } else {
+            sum[a] = four[a] + (two[a] + (one[a] + v[a]));
+          }
+        }
+        if (c & 1) {  // two chains at a time, added here: eight side by side would cost the second workgroup its registers
+#pragma unroll
+          for (int a = 0; a < NA; ++a) {
+            if (c == 7) asm volatile("" : "+v"(sum[a]));
+            else if (c == 3) asm volatile("" : "+v"(four[a]));
+            else asm volatile("" : "+v"(two[a]));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    if (whole) chains(std::integral_constant<int, KA>{});
+    else chains(std::integral_constant<int, KA - 1>{});  // this wave has no step in the last round
+    const int present = id;
+    if (p + step < m) {
+      id = next;
+      load_pairs(id);
+      next = id_of(p + 2 * step);
+    }
+    float *mine = part + parity * (kMfWaves * NA * kMfPart);  // two buffers in turn: one barrier per tile
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mine[(wave * NA + a) * kMfPart + 68 * r + lane] = sum[a][r];
+    __syncthreads();
+    if ((wave >> 2) == parity) {  // the two halves of the workgroup take the tiles in turn
+      const int row = threadIdx.x & 15, pair = (threadIdx.x >> 4) & 15;
+      float s[NA];
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        float q[kMfWaves];
+#pragma unroll
+        for (int v = 0; v < kMfWaves; ++v) q[v] = mine[(v * NA + a) * kMfPart + 68 * (row & 3) + 16 * (row >> 2) + pair];
+        s[a] = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+      }
+      out(row, p + pair, min(max(__shfl(present, pair, kWave), 0), n_pairs - 1), s);
+    }
+  }
+}
+
+template <int KA, bool kItems>
+__global__ __launch_bounds__(kMfThreads, 4) void ffn_gateup_f32_held_kernel(
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int M, int N, int k, int d, int F, const float *__restrict__ w_gate, const float *__restrict__ w_up,
+    const float *__restrict__ h, const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off,
+    const int4 *__restrict__ items, const int32_t *__restrict__ perm, float *__restrict__ act) {
+  __shared__ float part[2 * kMfWaves * 2 * kMfPart];
+  int e, m;
+  const int32_t *plist;
+  if (!f32_segment<kItems>(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
+                   plist))
+    return;
+  const int f0 = blockIdx.x * 16, i = threadIdx.x & 15, n_pairs = M * k;
+  if (__builtin_expect(f32_few<kItems>(m, blockIdx.y, items), 0)) {  // its code behind the tiles': 0.3 us of a small call
+    if (blockIdx.z != 0) return;
+    const float *wg = w_gate + (size_t)e * F * d, *wu = w_up + (size_t)e * F * d;
+    gateup_f32_few(h, wg, wu, plist, m, n_pairs, k, d, F, f0, act);
+    return;
+  }
+  if ((int)blockIdx.z * 16 >= m) return;
+  const size_t row = ((size_t)e * F + min(f0 + i, F - 1)) * d;  // rows past the end repeat the last one, never stored
+  const float *const w[2] = {w_gate + row, w_up + row};
+  f32_held_tiles<2, KA>(
+      w, plist, n_pairs, [&](int id) { return h + (size_t)(id / k) * d; }, d, blockIdx.z * 16, gridDim.z * 16, m, part,
+      [&](int r, int pair, int id, const float (&s)[2]) {
+        if (f0 + r < F && pair < m) act[(size_t)id * F + f0 + r] = s[0] / (1.0f + expf(-s[0])) * s[1];
+      });
+}
+
+template <int NA, int KA, bool kItems>
+__global__ __launch_bounds__(kMfThreads, 4) void ffn_down_f32_held_kernel(
+    const int32_t *__restrict__ rank_count, const int32_t *__restrict__ shortlist, const int32_t *__restrict__ lists,
+    int list_stride, int M, int N, int k, int d, int F, const float *__restrict__ w_down, const float *__restrict__ act,
+    const int32_t *__restrict__ seg_expert, const int32_t *__restrict__ seg_off, const int4 *__restrict__ items,
+    const int32_t *__restrict__ perm, float *__restrict__ y) {
+  __shared__ float part[2 * kMfWaves * NA * kMfPart];
+  int e, m;
+  const int32_t *plist;
+  if (!f32_segment<kItems>(blockIdx.y, seg_expert, seg_off, items, perm, rank_count, shortlist, lists, list_stride, M, N, k, e, m,
+                   plist))
+    return;
+  const int j0 = blockIdx.x * 16 * NA, i = threadIdx.x & 15, n_pairs = M * k;
+  if (__builtin_expect(f32_few<kItems>(m, blockIdx.y, items), 0)) {
+    if (blockIdx.z != 0 || (NA == 1 && (blockIdx.x & 1))) return;  // that form takes 32 rows
+    const float *wd = w_down + (size_t)e * d * F;
+    down_f32_few(act, wd, plist, m, n_pairs, d, F, j0, y);
+    return;
+  }
+  if ((int)blockIdx.z * 16 >= m) return;
+  const float *w[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) w[a] = w_down + ((size_t)e * d + min(j0 + 16 * a + i, d - 1)) * F;
+  const float *const(&wc)[NA] = w;
+  f32_held_tiles<NA, KA>(
+      wc, plist, n_pairs, [&](int id) { return act + (size_t)id * F; }, F, blockIdx.z * 16, gridDim.z * 16, m, part,
+      [&](int r, int pair, int id, const float (&s)[NA]) {
+        if (pair >= m) return;
+        float *dst = y + (size_t)id * d + j0 + r;
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+          if (j0 + 16 * a + r < d) dst[16 * a] = s[a];
+      });
+}
+
 // ---- combine: out[t] = residual[t] + sum over surviving slots (slot order) of w * y[t*k+slot] ---
 // y holds SP partial copies split_stride floats apart (K-split down pass), added in split order.  The rows of dropped slots
 // hold stale scratch: they are loaded (valid memory) but never enter the sum.
@@ -1363,6 +1539,39 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     // tokens, 59 / 69; but few large segments 94 / 81: 12 of 256 experts of 132 x 624, 177 tokens).  Not the down pass, whose
     // workgroups have twice the rows (32 of 256 experts of 2900 x 152, 128 tokens 204 / 179).
     const bool mf = matrix && !(pass == 1 && K <= 160 && mean <= 6 && (long long)mf_row_tiles * n_seg * groups(mf_tile) >= 24576);
+    if (mf && K <= kF32HeldK) {
+      const int ka = (K + 255) / 256, pair_tiles = (int)std::min<long long>(std::max<long long>((mean + 15) / 16, 1), 4);
+      // The down pass takes 32 rows, which reads the pairs half as often, where there is still a workgroup for every second compute unit
+      // (layers, us, 32 / 16 rows: 352 x 268 over 17 segments of 2 pairs 19.2 / 19.9, 884 x 88 over 9 of 4 19.5 / 20.3; 84 x 604 over 8
+      // of 35 21.6 / 20.5).
+      const int na = pass == 2 && (long long)((R + 31) / 32) * n_seg * pair_tiles < 128 ? 1 : 2;
+      const int tiles = pass == 1 ? (R + 15) / 16 : (R + 16 * na - 1) / (16 * na);
+      // workgroups share the pairs of a segment until there are two per compute unit
+      int z = 1;
+      while (z < 4 && 16 * z < M && (long long)tiles * n_seg * z < 512) ++z;
+      const dim3 hgrid(tiles, rows, z);
+      auto pick = [&](auto ka_) {
+        constexpr int KA = decltype(ka_)::value;
+        if (pass == 1) {
+          auto kern = work ? ffn_gateup_f32_held_kernel<KA, true> : ffn_gateup_f32_held_kernel<KA, false>;
+          kern<<<hgrid, kMfThreads, 0, st>>>(rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
+                                             static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up),
+                                             static_cast<const float *>(h), seg_expert, seg_off, work, perm, static_cast<float *>(act));
+        } else {
+          auto kern = na == 1 ? (work ? ffn_down_f32_held_kernel<1, KA, true> : ffn_down_f32_held_kernel<1, KA, false>)
+                              : (work ? ffn_down_f32_held_kernel<2, KA, true> : ffn_down_f32_held_kernel<2, KA, false>);
+          kern<<<hgrid, kMfThreads, 0, st>>>(rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
+                                             static_cast<const float *>(wt.w_down), static_cast<const float *>(act), seg_expert,
+                                             seg_off, work, perm, y);
+        }
+      };
+      if (ka == 1) pick(std::integral_constant<int, 1>{});
+      else if (ka == 2) pick(std::integral_constant<int, 2>{});
+      else pick(std::integral_constant<int, 3>{});
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      mark(pass - 1);
+      continue;
+    }
     const int wg_rows = mf ? mf_rows : pass == 1 ? 4 * kFfnWaves : kF32Rows * kFfnWaves;
     const dim3 grid((R + wg_rows - 1) / wg_rows, rows, groups(mf ? mf_tile : kF32Pairs));
     if (pass == 1) {

@@ -1,0 +1,37 @@
+"""fp32 passes with the weights held in registers: the rounds of 256 elements per wave and both sides of their limit (either pass), waves
+without a step in the last round, tiles of rows and pairs that are not full, several tiles of pairs per workgroup and per
+segment, one and two tiles of rows in the down pass, work items, and segments of one or two pairs beside larger ones."""
+import pytest
+import torch
+
+from oracle import moespec_oracle as O
+from paper_2602_16052_amd import binding as mb
+from paper_2602_16052_amd import workloads as wl
+
+from gpu_common import (assert_out_close, assert_routing_equal, desc_of, oracle_weights, out_to_numpy, to_device,
+                        upload_weights)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,N,k,F,M,B", [(32, 2, 1, 252, 3, 2), (256, 2, 2, 28, 16, 2), (260, 2, 2, 36, 17, 2), (288, 3, 1, 20, 33, 2),
+                                         (508, 2, 2, 512, 65, 2), (516, 2, 1, 544, 40, 1), (764, 2, 2, 772, 20, 2),
+                                         (768, 3, 2, 768, 49, 2), (772, 2, 2, 516, 31, 2), (48, 5, 3, 260, 7, 4),
+                                         (2052, 4, 2, 132, 35, 4), (140, 4, 2, 1024, 300, 3), (1040, 8, 2, 300, 270, 8),
+                                         (528, 40, 2, 64, 60, 30)])
+@pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
+def test_f32_held_weights(d, N, k, F, M, B, policy):
+    print(f"case d={d} N={N} k={k} F={F} M={M} B={B} policy={policy}", flush=True)
+    if policy == mb.SUBSTITUTE and B < k:
+        B = k
+    cfg = wl.small_config("held", "f32", d=d, n_experts=N, top_k=k, d_ff=F, M=M, bias_alpha=0.8, seed=d + M)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    h_d, W_d, ws = to_device(h), upload_weights(W), mb.alloc_workspace(desc, M)
+    ref = O.layer_forward(wl.as_f32(h), oracle_weights(W), k, cfg.renorm, B, policy)
+    out, taps = mb.moespec_layer_forward(desc, W_d, h_d, B, policy, ws, taps=True)
+    staged = mb.moespec_expert_ffn(desc, W_d, h_d, taps["seg_expert"], taps["seg_off"], taps["perm"], taps["tok_ids"],
+                                   taps["tok_w"], ws)
+    torch.cuda.synchronize()
+    assert_routing_equal(taps, ref, B)
+    assert_out_close(out_to_numpy(out), ref["out"], "f32")
+    assert torch.equal(staged, out)  # the order of the sums does not depend on the route to the pass
