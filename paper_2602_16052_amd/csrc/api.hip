@@ -128,10 +128,15 @@ moespec_status layer_forward(const moespec_desc *desc, const moespec_weights *we
     return from_hip(e);
   }
   // Other shapes: the budget stage groups the pairs into the segment arrays and work items of the expert passes.
-  hipError_t e = launch_route(*desc, *weights, h, M, probs, nullptr, nullptr, w.partial, w.partial_slices, st);
+  // The sums over blocks of tokens lie in the place of act, which the passes fill later.
+  const size_t act_bytes = (desc->dtype == MOESPEC_BF16 ? 2 : 4) * (size_t)M * desc->top_k * desc->d_ff;
+  int n_parts = gate_parts(*desc, M);
+  if (M <= 128 || (size_t)n_parts * desc->n_experts * sizeof(double) > act_bytes) n_parts = 0;
+  double *parts = n_parts > 0 ? static_cast<double *>(w.act) : nullptr;
+  hipError_t e = launch_route(*desc, *weights, h, M, probs, nullptr, nullptr, w.partial, w.partial_slices, parts, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   e = launch_budget(*desc, probs, M, B, policy, ext_shortlist, t.scores, budget_ids, tok_ids, tok_w, seg_expert,
-                    seg_off, perm, t.n_loaded, w.items, w.score_parts, st);
+                    seg_off, perm, t.n_loaded, w.items, w.score_parts, parts, n_parts, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   mark(1);
   e = launch_expert_ffn(*desc, *weights, h, M, B, seg_expert, seg_off, perm, tok_ids, tok_w, residual, out, w.act,
@@ -175,8 +180,8 @@ moespec_status moespec_route(const moespec_desc *desc, const moespec_weights *we
   if (!h || !probs || !aligned16(h)) return MOESPEC_ERR_INVALID_ARG;
   Workspace w = carve_workspace(*desc, M, ws);
   return from_hip(
-      launch_route(*desc, *weights, h, M, probs, topk_ids, topk_w, w.partial, w.partial_slices,
-                               static_cast<hipStream_t>(hip_stream)));
+      launch_route(*desc, *weights, h, M, probs, topk_ids, topk_w, w.partial, w.partial_slices, nullptr,
+                   static_cast<hipStream_t>(hip_stream)));
 }
 
 moespec_status moespec_budget(const moespec_desc *desc, const double *probs, int32_t M, int32_t B, int32_t policy,
@@ -190,7 +195,7 @@ moespec_status moespec_budget(const moespec_desc *desc, const double *probs, int
   Workspace w = carve_workspace(*desc, M, ws);
   return from_hip(launch_budget(*desc, probs, M, B, policy, ext_shortlist, scores,
                                 budget_ids ? budget_ids : w.budget_ids, tok_ids, tok_w,
-                                seg_expert, seg_off, perm, n_loaded, w.items, w.score_parts,
+                                seg_expert, seg_off, perm, n_loaded, w.items, w.score_parts, nullptr, 0,
                                 static_cast<hipStream_t>(hip_stream)));
 }
 
@@ -332,10 +337,10 @@ moespec_status moespec_oracle_ranking(const moespec_desc *desc, const moespec_we
   Workspace w = carve_workspace(*desc, M, ws);
   const int N = desc->n_experts;
   // natural routing (Eq. (2)): the budgeted path with B = N and truncation keeps every token's top-k
-  hipError_t e = launch_route(*desc, *weights, h, M, w.probs, nullptr, nullptr, w.partial, w.partial_slices, st);
+  hipError_t e = launch_route(*desc, *weights, h, M, w.probs, nullptr, nullptr, w.partial, w.partial_slices, nullptr, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   e = launch_budget(*desc, w.probs, M, N, MOESPEC_TRUNCATE, nullptr, nullptr, w.budget_ids, w.tok_ids, w.tok_w,
-                    w.seg_expert, w.seg_off, w.perm, nullptr, w.items, w.score_parts, st);
+                    w.seg_expert, w.seg_off, w.perm, nullptr, w.items, w.score_parts, nullptr, 0, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;
   e = launch_expert_ffn(*desc, *weights, h, M, N, w.seg_expert, w.seg_off, w.perm, w.tok_ids, w.tok_w, nullptr,
                         nullptr, w.act, w.y, w.items, true, nullptr, nullptr, nullptr, 0, st);

@@ -404,12 +404,15 @@ hipError_t launch_score_parts(const double *probs, int M, int N, double *part, i
 hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int B, int policy,
                          const int32_t *ext_shortlist, double *scores, int32_t *budget_ids, int32_t *tok_ids,
                          float *tok_w, int32_t *seg_expert, int32_t *seg_off, int32_t *perm, int32_t *n_loaded,
-                         int4 *items, double *score_parts, hipStream_t st) {
+                         int4 *items, double *score_parts, const double *parts, int n_parts, hipStream_t st) {
   const int N = ds.n_experts, k = ds.top_k;
   const double *src = probs;
   int n_src = M;
   hipError_t e;
-  if (M > direct_score_rows(N) && (ext_shortlist == nullptr || scores != nullptr)) {
+  if (n_parts > 0) {
+    src = parts;
+    n_src = n_parts;
+  } else if (M > direct_score_rows(N) && (ext_shortlist == nullptr || scores != nullptr)) {
     if ((e = launch_score_parts(probs, M, N, score_parts, &n_src, st)) != hipSuccess) return e;
     src = score_parts;
   }

@@ -356,13 +356,16 @@ inline Workspace carve_workspace(const moespec_desc &ds, int64_t M, void *base) 
 
 // Launchers (defined in the .hip files).  Each returns hipGetLastError() after its launches.
 // topk_ids / topk_w may be NULL.  partial: [partial_slices, M, N] doubles of scratch (partial_slices may be 0).
+// parts (may be NULL; no top-k then): [gate_parts(), N] doubles, the sums of the probabilities over blocks of tokens.
 hipError_t launch_route(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, double *probs,
-                        int32_t *topk_ids, float *topk_w, double *partial, int partial_slices, hipStream_t st);
+                        int32_t *topk_ids, float *topk_w, double *partial, int partial_slices, double *parts, hipStream_t st);
+int gate_parts(const moespec_desc &ds, int M);  // 0: this shape has none
 // score_parts: [kScoreMaxParts, N] doubles of scratch.  scores and n_loaded may be NULL.
+// n_parts > 0: parts [n_parts, N] holds the sums of the probabilities over blocks of tokens already.
 hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int B, int policy,
                          const int32_t *ext_shortlist, double *scores, int32_t *budget_ids, int32_t *tok_ids,
                          float *tok_w, int32_t *seg_expert, int32_t *seg_off, int32_t *perm, int32_t *n_loaded,
-                         int4 *items, double *score_parts, hipStream_t st);
+                         int4 *items, double *score_parts, const double *parts, int n_parts, hipStream_t st);
 // items: table of the work items ([items_capacity(n_seg, M, k) + 1] int4 of scratch: the non-empty segments,
 // those above kPiecePairs pairs cut into pieces); items_ready says that the budget stage has already filled
 // it from the same segment arrays, otherwise it is built first.
@@ -391,7 +394,7 @@ bool mfma_route_ok(const moespec_desc &ds);
 hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int slices,
                          double *partial, hipStream_t st);
 hipError_t launch_gate_rows(const moespec_desc &ds, const moespec_weights &wt, int M, int slices, const double *partial,
-                            double *probs, int32_t *topk_ids, float *topk_w, hipStream_t st);
+                            double *probs, int32_t *topk_ids, float *topk_w, double *parts, hipStream_t st);
 int logit_slices(const moespec_desc &ds, int M, int most);
 hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int B,
                                  int policy, const int32_t *ext_shortlist, double *partial, double *parts, void *ranks_ws, double *probs_ws,
