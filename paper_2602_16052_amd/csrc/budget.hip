@@ -223,14 +223,14 @@ __global__ __launch_bounds__(1024) void budget_kernel(
     for (int u = 0; u < NU; ++u)
       if (member[u] && c[u] < k) sel[c[u]] = lane + kWave * u;
     wave_lds_sync();
+    // weights over the selected set in slot order, before any slot is dropped (Eq. (7)); truncation drops the slots outside S, kept
+    // weights are unchanged
+    const int e = sel[lane];
+    const double ge = lane < k && e >= 0 ? row[e] : 0.0, denom = renorm ? slot_sum(ge, k) : 1.0;
     if (lane < k) {
-      double denom = 0.0;  // over the selected set in slot order, before any slot is dropped (Eq. (7))
-      for (int j = 0; j < k; ++j) denom += sel[j] >= 0 ? row[sel[j]] : 0.0;
-      const int e = sel[lane];
-      const bool keep = e >= 0 && inS[e] != 0;  // truncation drops the slots outside S; kept weights are unchanged
-      const double w = keep ? (renorm ? row[e] / denom : row[e]) : 0.0;
+      const bool keep = e >= 0 && inS[e] != 0;
       tok_ids[(size_t)t * k + lane] = keep ? e : -1;
-      tok_w[(size_t)t * k + lane] = (float)w;
+      tok_w[(size_t)t * k + lane] = (float)(keep ? (renorm ? ge / denom : ge) : 0.0);
     }
     load_row(t + n_waves);
   }
@@ -300,14 +300,14 @@ __global__ __launch_bounds__(1024) void budget_many_kernel(
     __syncthreads();
     if (member && rank[tid] < k) sel[rank[tid]] = tid;
     __syncthreads();
-    if (tid < k) {
-      double denom = 0.0;  // over the selected set in slot order, before any slot is dropped (Eq. (7))
-      for (int j = 0; j < k; ++j) denom += sel[j] >= 0 ? row[sel[j]] : 0.0;
+    if (tid < kWave) {
       const int e = sel[tid];
-      const bool keep = e >= 0 && inS[e] != 0;
-      const double w = keep ? (renorm ? row[e] / denom : row[e]) : 0.0;
-      tok_ids[(size_t)t * k + tid] = keep ? e : -1;
-      tok_w[(size_t)t * k + tid] = (float)w;
+      const double ge = tid < k && e >= 0 ? row[e] : 0.0, denom = renorm ? slot_sum(ge, k) : 1.0;  // as in budget_kernel
+      if (tid < k) {
+        const bool keep = e >= 0 && inS[e] != 0;
+        tok_ids[(size_t)t * k + tid] = keep ? e : -1;
+        tok_w[(size_t)t * k + tid] = (float)(keep ? (renorm ? ge / denom : ge) : 0.0);
+      }
     }
     if (tid < N && t + (int)gridDim.x < M) v = probs[(size_t)(t + gridDim.x) * N + tid];
     __syncthreads();  // the row and the selection have been read
@@ -320,6 +320,10 @@ __global__ __launch_bounds__(1024) void budget_many_kernel(
 // items receives the work items of the expert passes: the non-empty segments ordered by size, largest first (ties:
 // lower segment first), each cut into piece_count(size) pieces of (almost) equal size; items[0].x = number of pieces,
 // items[1 + r] = (segment, expert, offset, size) of piece r - the order in which the expert passes hand them out.
+// kHeld: a thread holds the ids of its token (at most kHeldSlots, one token per thread) from the count to the collection, which
+// otherwise loads them again.
+constexpr int kHeldSlots = 8;
+template <bool kHeld>
 __global__ __launch_bounds__(1024) void group_pairs_kernel(const int32_t *__restrict__ tok_ids, int M, int N, int k,
                                                            int B, const int32_t *__restrict__ seg_expert,
                                                            int32_t *__restrict__ seg_off, int32_t *__restrict__ perm,
@@ -329,27 +333,38 @@ __global__ __launch_bounds__(1024) void group_pairs_kernel(const int32_t *__rest
   __shared__ int32_t wave_cnt[2][16];  // routed tokens per wave, two rounds
   const int nt = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = nt >> 6, i = blockIdx.x;
   const int n_pairs = M * k;
-  for (int e = tid; e < N; e += nt) cnt[e] = 0;
+  int32_t held[kHeld ? kHeldSlots : 1];
+  if constexpr (kHeld) {
+#pragma unroll
+    for (int j = 0; j < kHeldSlots; ++j) held[j] = j < k && tid < M ? tok_ids[(size_t)tid * k + j] : -1;
+  }
+  const int e = seg_expert[i];
+  for (int x = tid; x < N; x += nt) cnt[x] = 0;
   if (tid < 5) tot[tid] = 0;
   __syncthreads();
-  for (int p0 = 0; p0 < n_pairs; p0 += 4 * nt) {
-    int id[4];
+  if constexpr (kHeld) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) id[u] = p0 + u * nt + tid < n_pairs ? tok_ids[p0 + u * nt + tid] : -1;
+    for (int j = 0; j < kHeldSlots; ++j)
+      if (held[j] >= 0) atomicAdd(&cnt[held[j]], 1);
+  } else {
+    for (int p0 = 0; p0 < n_pairs; p0 += 4 * nt) {
+      int id[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (id[u] >= 0) atomicAdd(&cnt[id[u]], 1);
+      for (int u = 0; u < 4; ++u) id[u] = p0 + u * nt + tid < n_pairs ? tok_ids[p0 + u * nt + tid] : -1;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (id[u] >= 0) atomicAdd(&cnt[id[u]], 1);
+    }
   }
   __syncthreads();
-  const int e = seg_expert[i], c = e >= 0 ? cnt[e] : 0;
-  for (int j0 = 0; j0 < B; j0 += nt) {  // uniform trip count
+  const int c = e >= 0 ? cnt[e] : 0;
+  for (int j0 = 0; j0 + (tid & ~63) < B; j0 += nt) {  // uniform in the wave
     const int j = j0 + tid, ej = j < B ? seg_expert[j] : -1, cj = ej >= 0 ? cnt[ej] : 0, q = piece_count(cj);
-    int sum[5] = {j < i ? cj : 0, (cj > c || (cj == c && j < i)) ? q : 0, cj, cj > 0 ? 1 : 0, q};
+    const int sum[5] = {j < i ? cj : 0, (cj > c || (cj == c && j < i)) ? q : 0, cj, cj > 0 ? 1 : 0, q};
 #pragma unroll
     for (int x = 0; x < 5; ++x) {
-#pragma unroll
-      for (int sft = 32; sft >= 1; sft >>= 1) sum[x] += __shfl_xor(sum[x], sft, kWave);
-      if (lane == 0 && sum[x]) atomicAdd(&tot[x], sum[x]);
+      const int s = row16_sum(sum[x]);  // through DPP: six shuffles per sum took 1 us
+      if ((lane & 15) == 0 && s) atomicAdd(&tot[x], s);
     }
   }
   __syncthreads();
@@ -370,7 +385,11 @@ __global__ __launch_bounds__(1024) void group_pairs_kernel(const int32_t *__rest
   for (int t0 = 0, round = 0; base < c && t0 < M; t0 += nt, round ^= 1) {
     const int t = t0 + tid;
     int slot = -1;
-    if (t < M) {
+    if constexpr (kHeld) {
+#pragma unroll
+      for (int j = 0; j < kHeldSlots; ++j)
+        if (held[j] == e) slot = j;
+    } else if (t < M) {
 #pragma unroll 8
       for (int j = 0; j < k; ++j)
         if (tok_ids[(size_t)t * k + j] == e) slot = j;
@@ -433,8 +452,9 @@ hipError_t launch_budget(const moespec_desc &ds, const double *probs, int M, int
   e = N <= 64 ? run(budget_kernel<1>) : N <= 128 ? run(budget_kernel<2>) : !many ? run(budget_kernel<4>)
                                                                                  : run(budget_many_kernel);
   if (e != hipSuccess) return e;
-  group_pairs_kernel<<<B, (int64_t)M * k <= 2048 ? 256 : 1024, 0, st>>>(tok_ids, M, N, k, B, seg_expert, seg_off, perm,
-                                                                       n_loaded, items);
+  const int gt = (int64_t)M * k <= 2048 ? 256 : 1024;
+  (gt == 256 && k <= kHeldSlots && M <= gt ? group_pairs_kernel<true> : group_pairs_kernel<false>)<<<B, gt, 0, st>>>(
+      tok_ids, M, N, k, B, seg_expert, seg_off, perm, n_loaded, items);
   return hipGetLastError();
 }
 

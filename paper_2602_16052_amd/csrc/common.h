@@ -223,6 +223,15 @@ __device__ __forceinline__ void gate_of_row(double (&val)[NU], int sigmoid_gate)
   for (int u = 0; u < NU; ++u) val[u] *= inv;
 }
 
+// v of lane 0 + v of lane 1 + ... + v of lane k - 1, in that order (k <= 64 and uniform; every lane gets the sum): without the LDS
+// reads, one behind the other, of a loop over slots.
+__device__ __forceinline__ double slot_sum(double v, int k) {
+  double a = 0.0;
+  for (int j = 0; j < k; ++j)
+    a += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), j), __builtin_amdgcn_readlane(__double2loint(v), j));
+  return a;
+}
+
 // Rank-count selection of the k best of v[0..n).  sel[r] receives the index with rank r < k.  Equivalent to sorting by
 // (value descending, index ascending) and keeping the first k.  v, sel and the scratch rank[n] live in LDS.  Called by
 // every thread of the workgroup (it synchronises); the caller synchronises again before reading sel.  The n x n

@@ -193,12 +193,11 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
     for (int u = 0; u < NU; ++u)
       if (lane + kWave * u < N && c[u] < k) sel[c[u]] = lane + kWave * u;
     wave_lds_sync();
+    const int e = sel[lane];  // -1 behind the last slot
+    const double ge = lane < k && e >= 0 ? row[e] : 0.0, denom = renorm ? slot_sum(ge, k) : 1.0;
     if (lane < k) {
-      double denom = 0.0;  // in slot order
-      for (int j = 0; j < k; ++j) denom += sel[j] >= 0 ? row[sel[j]] : 0.0;
-      const int e = sel[lane];
       if (topk_ids) topk_ids[(size_t)t * k + lane] = e;
-      if (topk_w) topk_w[(size_t)t * k + lane] = (float)(e < 0 ? 0.0 : (renorm ? row[e] / denom : row[e]));
+      if (topk_w) topk_w[(size_t)t * k + lane] = (float)(e < 0 ? 0.0 : (renorm ? ge / denom : ge));
     }
   }
 }
