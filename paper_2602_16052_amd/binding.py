@@ -181,8 +181,9 @@ def _ptr(t: Optional[torch.Tensor], dtype: Optional[torch.dtype] = None, numel: 
 
 
 def _stream(stream) -> Optional[int]:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    if stream is None:  # the raw handle of torch.cuda.current_stream(), without building the object (2 us of a stage call)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
+    return stream.cuda_stream or None
 
 
 def _weights(desc: LayerDesc, w: Dict[str, torch.Tensor], router: bool, experts: bool) -> Weights:
@@ -213,7 +214,8 @@ def moespec_route(desc: LayerDesc, weights: Dict[str, torch.Tensor], h: torch.Te
     tw = torch.empty((M, k), dtype=torch.float32, device=dev) if want_topk else None
     cd, cw = desc.c(), _weights(desc, weights, True, False)
     st = load_library().moespec_route(ctypes.byref(cd), ctypes.byref(cw), _ptr(h, desc.torch_dtype, M * desc.d, "h"),
-                                      M, _ptr(probs), _ptr(ids), _ptr(tw), _ptr(ws), ws.numel(), _stream(stream))
+                                      M, probs.data_ptr(), ids.data_ptr() if want_topk else None,
+                                      tw.data_ptr() if want_topk else None, _ptr(ws), ws.numel(), _stream(stream))
     _check(st, "moespec_route")
     return dict(probs=probs, topk_ids=ids, topk_w=tw)
 
@@ -231,9 +233,8 @@ def moespec_budget(desc: LayerDesc, probs: torch.Tensor, B: int, policy: int, ws
     cd = desc.c()
     st = load_library().moespec_budget(
         ctypes.byref(cd), _ptr(probs, torch.float64, M * N, "probs"), M, int(B), int(policy),
-        _ptr(ext_shortlist, torch.int32, max(B, 0), "ext_shortlist"), _ptr(out["scores"]), _ptr(out["budget_ids"]),
-        _ptr(out["tok_ids"]), _ptr(out["tok_w"]), _ptr(out["seg_expert"]), _ptr(out["seg_off"]), _ptr(out["perm"]),
-        _ptr(out["n_loaded"]), _ptr(ws), ws.numel(), _stream(stream))
+        _ptr(ext_shortlist, torch.int32, max(B, 0), "ext_shortlist"), *(t.data_ptr() for t in out.values()), _ptr(ws),
+        ws.numel(), _stream(stream))
     _check(st, "moespec_budget")
     return out
 
