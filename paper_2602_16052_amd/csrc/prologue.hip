@@ -134,6 +134,83 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T
   }
 }
 
+// The same in tiles of 32 tokens x 16 TE experts: an operand is widened once for two (TE = 2) instructions of a wave.  What bounds
+// the projection of many tokens is the fp64 unit, which widens as well as it multiplies.  8 waves share the slice, so that a
+// workgroup per compute unit still makes two waves per SIMD (four were slower than the 16 x 16 tiles: no load latency is hidden).
+constexpr int kBlockWaves = 8;
+template <typename T, int TE>
+__global__ __launch_bounds__(kBlockWaves *kWave, 2) void logits_block_kernel(const T *__restrict__ h, const T *__restrict__ w_r, int M,
+                                                                             int N, int d, int n_slices, double *__restrict__ partial) {
+  __shared__ double red[kBlockWaves][2 * TE][256];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int e_tiles = (N + 16 * TE - 1) / (16 * TE);
+  const int tt = blockIdx.x / e_tiles, et = blockIdx.x % e_tiles, q = blockIdx.y;
+  const int i = lane & 15, g = lane >> 4;
+  const int n_blocks = d / 32, parts = n_slices * kBlockWaves, part = q * kBlockWaves + wave;
+  const int b0 = (int)((long long)part * n_blocks / parts), b1 = (int)((long long)(part + 1) * n_blocks / parts);
+  const T *rows[2 + TE];  // pad rows repeat the last one, never stored
+#pragma unroll
+  for (int x = 0; x < 2; ++x) rows[x] = h + (size_t)min(tt * 32 + 16 * x + i, M - 1) * d + g * 8;
+#pragma unroll
+  for (int x = 0; x < TE; ++x) rows[2 + x] = w_r + (size_t)min(et * 16 * TE + 16 * x + i, N - 1) * d + g * 8;
+  f64x4 acc[2][TE];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < TE; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
+  constexpr int PB = 2;  // blocks per set of loads, two sets in turn
+  LogitPiece<T> P[2][PB][2 + TE];
+  auto load = [&](int set, int b) {
+#pragma unroll
+    for (int u = 0; u < PB; ++u)
+#pragma unroll
+      for (int x = 0; x < 2 + TE; ++x) P[set][u][x].load(rows[x] + (size_t)min(b + u, b1 - 1) * 32);  // past the end: the last one again
+  };
+  auto multiply = [&](int set, int b) {
+#pragma unroll
+    for (int u = 0; u < PB; ++u) {
+      if (b + u < b1) {  // uniform in the wave
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          double v[2 + TE];
+#pragma unroll
+          for (int x = 0; x < 2 + TE; ++x) v[x] = P[set][u][x].get(m);
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < TE; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[x], v[2 + y], acc[x][y], 0, 0, 0);
+        }
+      }
+    }
+  };
+  int b = b0;
+  load(0, b);  // every wave has blocks (logits_in_blocks)
+  for (; b + 2 * PB < b1; b += 2 * PB) {
+    load(1, b + PB);
+    multiply(0, b);
+    load(0, b + 2 * PB);
+    multiply(1, b + PB);
+  }
+  if (b + PB < b1) load(1, b + PB);
+  multiply(0, b);
+  multiply(1, b + PB);
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < TE; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][x * TE + y][(g + 4 * r) * 16 + i] = acc[x][y][r];
+  __syncthreads();
+  for (int o = threadIdx.x; o < 2 * TE * 256; o += kBlockWaves * kWave) {
+    const int tile = o >> 8, at = o & 255;
+    double a = red[0][tile][at];
+#pragma unroll
+    for (int w = 1; w < kBlockWaves; ++w) a += red[w][tile][at];
+    const int row = tt * 32 + 16 * (tile / TE) + at / 16, col = et * 16 * TE + 16 * (tile % TE) + at % 16;
+    if (row < M && col < N) partial[((size_t)q * M + row) * N + col] = a;
+  }
+}
+
 // The same for small tables, finished in one launch: logits[t][e] = h[t] . w_r[e] + bias[e].  A workgroup owns 4 tokens x 4
 // experts and the whole hidden dimension, which its 8 waves share in chunks of 128 elements.  v_mfma_f64_4x4x4 multiplies four
 // independent blocks: lane (i, c) = (lane % 4, lane / 4) supplies A[i] and B[i] of its own piece c of the hidden dimension
@@ -697,12 +774,24 @@ bool fused_prologue_ok(const moespec_desc &ds, int M, int B, int policy) {
   return prologue_lds(M, N, ds.top_k, N, ranked).total <= 160 * 1024;
 }
 
+// Tiles of 32 tokens x 32 experts (16 for up to 16 experts) where they and the slices make a workgroup per compute unit, leave every wave four blocks of the
+// hidden dimension, and do not spend on padding what they save.
+static int block_experts(const moespec_desc &ds) { return ds.n_experts > 16 ? 2 : 1; }
+static bool logits_in_blocks(const moespec_desc &ds, int M, int slices) {
+  const int N = ds.n_experts, rows = 16 * block_experts(ds);
+  const long long tiles = (long long)((M + 31) / 32) * ((N + rows - 1) / rows), plain = (long long)((M + 15) / 16) * ((N + 15) / 16);
+  return ds.dtype == MOESPEC_BF16 && tiles * slices >= 256 && ds.d / 32 >= 4 * kBlockWaves * slices &&
+         tiles * 2 * (rows / 16) * 95 <= plain * 100;
+}
+
 // Slices of the hidden dimension (1, 2, 4 or 8, at most `most`): more slices spread the matrix work over more compute units
 // (a wave issues one fp64 matrix instruction per 64 cycles), but the row-wise gate kernel re-reads its row once per slice.
 // Picks the count with the smallest estimated sum of the two (rates measured on MI355X: 2.4 GHz, about 150 GB/s
 // from L2 into one compute unit).
 int logit_slices(const moespec_desc &ds, int M, int most) {
   const double tiles = ((M + 15) / 16) * ((ds.n_experts + 15) / 16), n_blocks = ds.d / 32;
+  for (int q = 1; q <= 2 && q <= most; q *= 2)
+    if (logits_in_blocks(ds, M, q)) return q;
   int best = 1;
   double best_us = 1e30;
   for (int q = 1; q <= kMaxLogitSlices && (q == 1 || q <= most); q *= 2) {
@@ -723,6 +812,14 @@ bool mfma_route_ok(const moespec_desc &ds) { return ds.n_experts <= kSelfMaxExpe
 
 hipError_t launch_logits(const moespec_desc &ds, const moespec_weights &wt, const void *h, int M, int slices,
                          double *partial, hipStream_t st) {
+  if (logits_in_blocks(ds, M, slices)) {
+    const int te = block_experts(ds);
+    const dim3 bgrid(((M + 31) / 32) * ((ds.n_experts + 16 * te - 1) / (16 * te)), slices);
+    auto kern = te == 2 ? logits_block_kernel<uint16_t, 2> : logits_block_kernel<uint16_t, 1>;
+    kern<<<bgrid, kBlockWaves * kWave, 0, st>>>(static_cast<const uint16_t *>(h), static_cast<const uint16_t *>(wt.w_router), M,
+                                                ds.n_experts, ds.d, slices, partial);
+    return hipGetLastError();
+  }
   dim3 grid(((M + 15) / 16) * ((ds.n_experts + 15) / 16), slices);
   // Loads ahead, except in bf16 (sets of four blocks) for five blocks per wave, where most of the second set repeats the last
   // block, and for up to eight in more workgroups than the registers of two sets leave resident.  Measured inside layers whose

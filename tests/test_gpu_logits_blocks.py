@@ -1,0 +1,13 @@
+"""The router projection of many tokens in tiles of 32 tokens x 32 (16) experts: remainders of either, uneven shares of the hidden
+dimension, one slice and two, and shapes that padding keeps in the smaller tiles."""
+import pytest
+
+from test_gpu_route_edges import check_route
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,k,d", [(4100, 64, 8, 1024), (4095, 63, 4, 1056), (8193, 16, 2, 1024), (8200, 9, 2, 1504), (8170, 17, 3, 1248),
+                                     (2050, 61, 8, 2080), (2048, 64, 1, 2336), (4097, 33, 4, 1024)])
+def test_projection_in_blocks(M, N, k, d):
+    check_route(M, N, k, d, "softmax", "bf16")
