@@ -1319,6 +1319,8 @@ __global__ __launch_bounds__(kMfThreads, 4) void ffn_down_f32_held_kernel(
 // hold stale scratch: they are loaded (valid memory) but never enter the sum.
 // The four outputs j .. j+3 of token t (before storage rounding).  What bounds it is one round of cold loads: those of U slots go
 // out together, up to 8 rows (with 4 rows at a time and one by one for the remainder of k it was up to k / 4 + k % 4 rounds).
+// Whole layer of 7 tokens, top-8 of 64 experts of 2048 x 1024: 49.1 -> 47.6 us, with the workgroups of one wave below and
+// kernel arguments preloaded into registers.
 template <typename T, int SP, int U>
 __device__ __forceinline__ f32x4 combine_four(const float *__restrict__ y, const int32_t *__restrict__ tok_ids,
                                               const float *__restrict__ tok_w, const T *__restrict__ residual, int t,

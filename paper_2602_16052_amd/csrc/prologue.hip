@@ -1,11 +1,11 @@
-// Stages 1-3 of Algorithm 1 for the fused layer call on small trees, in two launches with no dependence
+// Stages 1-3 of Algorithm 1 for the fused layer call on small trees, in two or three launches with no dependence
 // between workgroups inside a launch:
 //
-//   logits_mfma_kernel    the router projection w_i . h_t of Eq. (1) for all tokens and experts on the fp64
-//                         matrix cores, as partial sums over slices of the hidden dimension
+//   logits_table_kernel   small tables: the router projection w_i . h_t of Eq. (1) for all tokens and experts on the fp64
+//                         matrix cores, finished
 //   route_budget_kernel   a workgroup per tree token and one per shortlist rank (on larger trees the same ones for both).
 //                         EVERY workgroup rebuilds the whole M x N table of
-//                         routing probabilities from those partial sums (bias, softmax or sigmoid gate of
+//                         routing probabilities from the projection (softmax or sigmoid gate of
 //                         Eq. (1)), the aggregate scores of Eq. (5) and the top-B shortlist (Section 3.2) in its
 //                         LDS - a few thousand exponentials, cheaper than a second pass over global memory and a
 //                         grid-wide wait - then restricts its own token's routing (Eq. (7) / Eq. (8)) or
@@ -13,8 +13,15 @@
 //                         expert the (token, slot) pairs routed to it, tokens ascending, which is what the
 //                         expert passes consume.
 //
+// and for tables too large to be rebuilt by everyone:
+//
+//   logits_mfma_kernel    the projection as partial sums over slices of the hidden dimension
+//   rank_rows_kernel      Eq. (1) row by row, the ranks in every row and sums over a few tokens each
+//   route_budget_kernel   as above from the ranks and those sums
+//
 // Every decision in fp64, ties to the lowest expert id, as in the staged kernels of route.hip / budget.hip, which remain
-// the path of the stage calls, of larger trees (fused_prologue_ok) and of layers whose passes take the grouped form.
+// the path of the stage calls, of larger trees (fused_prologue_ok) and of layers whose passes take the grouped form.  Their
+// projection is here too: logits_mfma_kernel, or logits_block_kernel for many tokens.
 #include "common.h"
 
 namespace moespec {
@@ -137,6 +144,8 @@ __global__ __launch_bounds__(kLogitWaves *kWave) void logits_mfma_kernel(const T
 // The same in tiles of 32 tokens x 16 TE experts: an operand is widened once for two (TE = 2) instructions of a wave.  What bounds
 // the projection of many tokens is the fp64 unit, which widens as well as it multiplies.  8 waves share the slice, so that a
 // workgroup per compute unit still makes two waves per SIMD (four were slower than the 16 x 16 tiles: no load latency is hidden).
+// d = 2048, 64 experts, us, 16 x 16 tiles / these: 4096 tokens 26.6 / 24.2, 2048 tokens 17.3 / 16.1.  (Without the conversions the
+// 16 x 16 tiles would take 24.8; widening with integer operations 32.2.)
 constexpr int kBlockWaves = 8;
 template <typename T, int TE>
 __global__ __launch_bounds__(kBlockWaves *kWave, 2) void logits_block_kernel(const T *__restrict__ h, const T *__restrict__ w_r, int M,
@@ -774,8 +783,9 @@ bool fused_prologue_ok(const moespec_desc &ds, int M, int B, int policy) {
   return prologue_lds(M, N, ds.top_k, N, ranked).total <= 160 * 1024;
 }
 
-// Tiles of 32 tokens x 32 experts (16 for up to 16 experts) where they and the slices make a workgroup per compute unit, leave every wave four blocks of the
-// hidden dimension, and do not spend on padding what they save.
+// Tiles of 32 tokens x 32 experts (16 for up to 16 experts) where they and the slices make a workgroup per compute unit, leave every
+// wave four blocks of the hidden dimension, and do not spend on padding what they save, which is 5 to 10 % (3000 tokens x 100 experts,
+// 128 columns of tiles instead of 112: 0.93 of the speed).
 static int block_experts(const moespec_desc &ds) { return ds.n_experts > 16 ? 2 : 1; }
 static bool logits_in_blocks(const moespec_desc &ds, int M, int slices) {
   const int N = ds.n_experts, rows = 16 * block_experts(ds);
@@ -891,14 +901,18 @@ hipError_t launch_fused_prologue(const moespec_desc &ds, const moespec_weights &
     // lists have workgroups of their own (15 tokens x 8 experts 6.8 -> 6.4 us, 7 x 64 10.3 -> 8.6, 63 x 64 10.5 -> 9.7, 127 x 128 12.3
     // -> 11.7); each loads the whole table, so not in a second round.
     const int list_wgs = M + B <= 256 ? B : 0;
-    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(split ? static_cast<const void *>(ranks) : partial, M, N, k, B, list_wgs, flags, list_stride,
-                                                                            ext_shortlist, parts, probs, probs_out, scores_out, budget_ids,
-                                                                            seg_expert, tok_ids, tok_w, list_count, lists);
+    kern<<<list_wgs ? M + B : (M > B ? M : B), kPrologueThreads, smem, st>>>(
+        split ? static_cast<const void *>(ranks) : partial, M, N, k, B, list_wgs, flags, list_stride, ext_shortlist, parts, probs,
+        probs_out, scores_out, budget_ids, seg_expert, tok_ids, tok_w, list_count, lists);
     return hipGetLastError();
   };
   const int ne = (N + 15) / 16;
-  e = split ? run(route_budget_kernel<0>) : ne <= 1 ? run(route_budget_kernel<1>) : ne <= 2 ? run(route_budget_kernel<2>) : ne <= 4 ? run(route_budget_kernel<4>)
-      : ne <= 8 ? run(route_budget_kernel<8>) : run(route_budget_kernel<16>);
+  e = split     ? run(route_budget_kernel<0>)
+      : ne <= 1 ? run(route_budget_kernel<1>)
+      : ne <= 2 ? run(route_budget_kernel<2>)
+      : ne <= 4 ? run(route_budget_kernel<4>)
+      : ne <= 8 ? run(route_budget_kernel<8>)
+                : run(route_budget_kernel<16>);
   if (e != hipSuccess) return e;
   if (seg_off || perm || n_loaded) {
     lists_to_segments_kernel<<<1, 256, 0, st>>>(budget_ids, list_count, lists, list_stride, B, N, M * k, seg_off, perm,

@@ -203,7 +203,8 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
 }
 
 // Eq. (1) as above and the sums of the probabilities over the tokens of a workgroup, one per wave (Eq. (5)), which spare the budget
-// stage a pass over the table in a launch of its own (4.8 us).  parts[b, i]: workgroup b, added in token order.
+// stage a pass over the table in a launch of its own (4.8 us; layer of 511 tokens x 64 experts, d = 2048, 155.0 -> 152.6 us, of 2048
+// tokens 381.8 -> 379.6).  parts[b, i]: workgroup b, added in token order.
 template <int Q, int NU>
 __global__ __launch_bounds__(1024) void gate_parts_kernel(const double *partial, const float *__restrict__ bias, int M, int N,
                                                           int sigmoid_gate, double *probs, double *__restrict__ parts) {
