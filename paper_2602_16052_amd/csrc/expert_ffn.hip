@@ -1146,10 +1146,16 @@ __global__ __launch_bounds__(kMfThreads, NP == 1 ? 4 : 2) void ffn_down_f32_mfma
 // Elements past the end of K come from a line of zeros: no branch around a load, so that the waits can be counted.
 // What bounds it: a tile of pairs is a chain of LDS sums and a barrier behind 8 KA matrix instructions per tile of rows; two workgroups
 // take turns.  63 tokens over 8 experts of 512 x 1024: gate/up pass 20.2 -> 16.0 us, layer 42.7 -> 37.9; 57 drawn layers of 64 to
-// 1024 elements and up to 127 tokens 1.03x, up to 1.24x, 0.97x at least.  Up to 768 elements: held for four rounds the weights leave
-// one workgroup per compute unit (down pass above, K = 1024, 12.4 -> 15.3 us; 628 x 872, 11 segments of 2 pairs, layer 25.3 -> 28.2).
+// 1024 elements and up to 127 tokens 1.03x, up to 1.24x, 0.97x at least.  Up to 768 elements: held for four rounds the weights of two
+// tiles leave one workgroup per compute unit, and those of one tile read the pairs twice as often (down pass above, K = 1024,
+// 12.4 -> 15.3 us either way; 628 x 872, 11 segments of 2 pairs, layer 25.3 -> 28.2).  But where row tiles and segments make at most 112
+// workgroups, up to four of which share a segment's pairs, the down pass holds one tile of up to 1024 elements: what bounds it there is
+// the time of a workgroup.  Layers, us, streamed / held: 24 workgroups of 64 x 972, 7 pairs per segment 20.2 / 18.2; 35 of 72 x 1004, 21 pairs 28.9 /
+// 24.0; 102 of 260 x 964, 27 pairs 41.4 / 32.9; 32 such layers 1.01 to 1.25x.  124 to 180 workgroups 0.95 to 1.27x, 300 and more 0.92 to
+// 1.06x.  The gate/up pass, which has two tiles at least, gained nothing there (21 layers 0.98 to 1.06x, half of them slower).
 // x_row(id): row of a pair; out(row, pair, its id, sums of the NA tiles' rows).  part: 2 [kMfWaves][NA][kMfPart] floats of LDS.
-constexpr int kF32HeldK = 768;
+constexpr int kF32HeldK = 768, kF32HeldKFew = 1024;
+constexpr long long kF32HeldFew = 112;
 __device__ const f32x4 kF32Zeros = {0.f, 0.f, 0.f, 0.f};
 template <int NA, int KA, class X, class F>
 __device__ __forceinline__ void f32_held_tiles(const float *const (&w)[NA], const int32_t *plist, int n_pairs, X x_row, int K, int p0,
@@ -1541,12 +1547,13 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     // tokens, 59 / 69; but few large segments 94 / 81: 12 of 256 experts of 132 x 624, 177 tokens).  Not the down pass, whose
     // workgroups have twice the rows (32 of 256 experts of 2900 x 152, 128 tokens 204 / 179).
     const bool mf = matrix && !(pass == 1 && K <= 160 && mean <= 6 && (long long)mf_row_tiles * n_seg * groups(mf_tile) >= 24576);
-    if (mf && K <= kF32HeldK) {
+    const bool few_rows = pass == 2 && (long long)((R + 15) / 16) * n_seg <= kF32HeldFew;
+    if (mf && K <= (few_rows ? kF32HeldKFew : kF32HeldK)) {
       const int ka = (K + 255) / 256, pair_tiles = (int)std::min<long long>(std::max<long long>((mean + 15) / 16, 1), 4);
       // The down pass takes 32 rows, which reads the pairs half as often, where there is still a workgroup for every second compute unit
       // (layers, us, 32 / 16 rows: 352 x 268 over 17 segments of 2 pairs 19.2 / 19.9, 884 x 88 over 9 of 4 19.5 / 20.3; 84 x 604 over 8
       // of 35 21.6 / 20.5).
-      const int na = pass == 2 && (long long)((R + 31) / 32) * n_seg * pair_tiles < 128 ? 1 : 2;
+      const int na = pass == 2 && (ka == 4 || (long long)((R + 31) / 32) * n_seg * pair_tiles < 128) ? 1 : 2;
       const int tiles = pass == 1 ? (R + 15) / 16 : (R + 16 * na - 1) / (16 * na);
       // workgroups share the pairs of a segment until there are two per compute unit
       int z = 1;
@@ -1554,22 +1561,27 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
       const dim3 hgrid(tiles, rows, z);
       auto pick = [&](auto ka_) {
         constexpr int KA = decltype(ka_)::value;
-        if (pass == 1) {
+        auto down = [&](auto kern) {
+          kern<<<hgrid, kMfThreads, 0, st>>>(rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
+                                             static_cast<const float *>(wt.w_down), static_cast<const float *>(act), seg_expert,
+                                             seg_off, work, perm, y);
+        };
+        if constexpr (KA == 4) {
+          down(work ? ffn_down_f32_held_kernel<1, KA, true> : ffn_down_f32_held_kernel<1, KA, false>);
+        } else if (pass == 1) {
           auto kern = work ? ffn_gateup_f32_held_kernel<KA, true> : ffn_gateup_f32_held_kernel<KA, false>;
           kern<<<hgrid, kMfThreads, 0, st>>>(rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
                                              static_cast<const float *>(wt.w_gate), static_cast<const float *>(wt.w_up),
                                              static_cast<const float *>(h), seg_expert, seg_off, work, perm, static_cast<float *>(act));
         } else {
-          auto kern = na == 1 ? (work ? ffn_down_f32_held_kernel<1, KA, true> : ffn_down_f32_held_kernel<1, KA, false>)
-                              : (work ? ffn_down_f32_held_kernel<2, KA, true> : ffn_down_f32_held_kernel<2, KA, false>);
-          kern<<<hgrid, kMfThreads, 0, st>>>(rank_count, shortlist, lists, list_stride, M, ds.n_experts, k, d, F,
-                                             static_cast<const float *>(wt.w_down), static_cast<const float *>(act), seg_expert,
-                                             seg_off, work, perm, y);
+          down(na == 1 ? (work ? ffn_down_f32_held_kernel<1, KA, true> : ffn_down_f32_held_kernel<1, KA, false>)
+                       : (work ? ffn_down_f32_held_kernel<2, KA, true> : ffn_down_f32_held_kernel<2, KA, false>));
         }
       };
       if (ka == 1) pick(std::integral_constant<int, 1>{});
       else if (ka == 2) pick(std::integral_constant<int, 2>{});
-      else pick(std::integral_constant<int, 3>{});
+      else if (ka == 3) pick(std::integral_constant<int, 3>{});
+      else pick(std::integral_constant<int, 4>{});
       if ((e = hipGetLastError()) != hipSuccess) return e;
       mark(pass - 1);
       continue;

@@ -35,3 +35,13 @@ def test_f32_held_weights(d, N, k, F, M, B, policy):
     assert_routing_equal(taps, ref, B)
     assert_out_close(out_to_numpy(out), ref["out"], "f32")
     assert torch.equal(staged, out)  # the order of the sums does not depend on the route to the pass
+
+
+@pytest.mark.parametrize("d,N,k,F,M,B", [(64, 3, 2, 772, 5, 3), (20, 4, 2, 800, 70, 4), (36, 5, 3, 1020, 17, 4), (64, 3, 2, 1024, 65, 3),
+                                         (64, 3, 2, 1028, 65, 3), (448, 5, 2, 964, 40, 4), (452, 5, 2, 964, 40, 4),
+                                         (68, 6, 2, 900, 290, 5)])
+@pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
+def test_f32_held_weights_of_few_rows(d, N, k, F, M, B, policy):
+    """The down pass of up to 112 workgroups, which holds up to 1024 elements: both sides of either limit, waves without a step in the
+    fourth round, and segments that four workgroups share."""
+    test_f32_held_weights(d, N, k, F, M, B, policy)
