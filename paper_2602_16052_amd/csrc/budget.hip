@@ -78,11 +78,11 @@ __host__ __device__ inline BudgetLds budget_lds(int N, int B, int threads, int t
   return L;
 }
 
-// s[i] = sum of column i of src [n_src, N], i < N <= nt; kNoRival up to row_stride.  The threads with the same index modulo
-// a power of two >= N share a column, each a contiguous run of rows.  Called by the whole workgroup (it synchronises once;
-// the caller does before it reads s).
+// s[i] = sum of column i of src [n_src, N] as it ranks, i < N <= nt; kNoRival up to row_stride.  scores (may be NULL) receives the
+// sums.  The threads with the same index modulo a power of two >= N share a column, each a contiguous run of rows.  Called by
+// the whole workgroup (it synchronises once; the caller does before it reads s).
 __device__ __forceinline__ void tree_scores(const double *__restrict__ src, int n_src, int N, int row_stride, double *red,
-                                            double *s) {
+                                            double *s, double *__restrict__ scores) {
   const int nt = blockDim.x, tid = threadIdx.x;
   int np2 = 1, np2_log = 0;
   while (np2 < N) np2 <<= 1, ++np2_log;
@@ -104,26 +104,23 @@ __device__ __forceinline__ void tree_scores(const double *__restrict__ src, int 
   if (tid < row_stride) {
     double sum = tid < N ? red[tid] : kNoRival;
     for (int q = 1; tid < N && q < parts; ++q) sum += red[q * np2 + tid];
-    s[tid] = sum;
+    s[tid] = tid < N ? ranking_score(sum) : sum;
+    if (scores && tid < N) scores[tid] = sum;
   }
 }
 
-// The copies of one workgroup for the caller: scores, the shortlist in rank order and in ascending id.  Every wave builds
+// The copies of one workgroup for the caller: the shortlist in rank order and in ascending id.  Every wave builds
 // the membership mask of all experts, 64 at a time; the position of an expert among the shortlisted ones is a population
 // count.
-__device__ __forceinline__ void publish_shortlist(int N, int B, const uint8_t *inS, const int32_t *S, const double *s,
-                                                  double *__restrict__ scores, int32_t *__restrict__ seg_expert,
-                                                  int32_t *__restrict__ budget_ids) {
+__device__ __forceinline__ void publish_shortlist(int N, int B, const uint8_t *inS, const int32_t *S,
+                                                  int32_t *__restrict__ seg_expert, int32_t *__restrict__ budget_ids) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int n_member = 0;  // in the end < B only if an external shortlist repeats or misnames an expert
   for (int i0 = 0; i0 < N; i0 += kWave) {
     const int i = i0 + lane;
     const bool in = i < N && inS[i] != 0;
     const unsigned long long mask = __ballot(in);
-    if (wave == 0) {
-      if (scores && i < N) scores[i] = s[i];
-      if (in) seg_expert[n_member + __popcll(mask & ((1ull << lane) - 1ull))] = i;
-    }
+    if (wave == 0 && in) seg_expert[n_member + __popcll(mask & ((1ull << lane) - 1ull))] = i;
     n_member += __popcll(mask);
   }
   for (int r = tid; r < B; r += blockDim.x) {
@@ -170,10 +167,9 @@ __global__ __launch_bounds__(1024) void budget_kernel(
 
   for (int i = tid; i < N; i += nt) inS[i] = 0;
   if (ext_shortlist == nullptr || scores != nullptr) {
-    tree_scores(src, n_src, N, (int)L.row_stride, red, s);
+    tree_scores(src, n_src, N, (int)L.row_stride, red, s, blockIdx.x == 0 ? scores : nullptr);
   }
   for (int i = tid; i < N; i += nt) rank[i] = 0;
-  for (int r = tid; r < B; r += nt) S[r] = -1;  // stays -1 where NaN scores leave a place of the shortlist unclaimed
   __syncthreads();
   if (ext_shortlist == nullptr) {
     // Section 3.2: the B highest aggregate scores, ties to the lowest id.  Each wave ranks all experts against its share
@@ -202,7 +198,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
   __syncthreads();
 
   if (blockIdx.x == 0) {
-    publish_shortlist(N, B, inS, S, s, scores, seg_expert, budget_ids);
+    publish_shortlist(N, B, inS, S, seg_expert, budget_ids);
   }
 
   const bool truncate = policy == MOESPEC_TRUNCATE;
@@ -275,8 +271,8 @@ __global__ __launch_bounds__(1024) void budget_many_kernel(
     inS[i] = 0;
     rank[i] = 0;
   }
-  for (int r = tid; r < B; r += nt) S[r] = -1;  // see budget_kernel
-  if (ext_shortlist == nullptr || scores != nullptr) tree_scores(src, n_src, N, (int)L.row_stride, red, s);
+  if (ext_shortlist == nullptr || scores != nullptr)
+    tree_scores(src, n_src, N, (int)L.row_stride, red, s, blockIdx.x == 0 ? scores : nullptr);
   __syncthreads();
   if (ext_shortlist == nullptr) {
     rank_in_workgroup(s, N, rank);
@@ -289,7 +285,7 @@ __global__ __launch_bounds__(1024) void budget_many_kernel(
   for (int r = tid; r < B; r += nt)
     if ((uint32_t)S[r] < (uint32_t)N) inS[S[r]] = 1;
   __syncthreads();
-  if (blockIdx.x == 0) publish_shortlist(N, B, inS, S, s, scores, seg_expert, budget_ids);
+  if (blockIdx.x == 0) publish_shortlist(N, B, inS, S, seg_expert, budget_ids);
 
   const bool truncate = policy == MOESPEC_TRUNCATE, member = tid < N && (truncate || inS[tid] != 0);
   for (; t < M; t += gridDim.x) {

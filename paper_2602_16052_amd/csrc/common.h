@@ -59,6 +59,10 @@ __device__ __forceinline__ bool ranks_before(double vj, int j, double vi, int i)
   return vj > vi || (vj == vi && j < i);
 }
 
+// What an aggregate score ranks by (Section 3.2): a NaN, which no comparison would order, goes behind every number, by id.  So B experts
+// claim the B places of the shortlist, one each, whatever the scores: one NaN hidden row makes all of them NaN.
+__device__ __forceinline__ double ranking_score(double s) { return s == s ? s : -INFINITY; }
+
 // ---- 16-lane all-reductions through DPP (no LDS, no barrier).  Every lane of a row of 16 ends with the same
 // bits: each step combines a value with its partner's, and the operations used are commutative.
 template <int CTRL>

@@ -380,7 +380,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   const PrologueLds L = prologue_lds(M, N, k, B, kRanked);
   double *g = reinterpret_cast<double *>(smem + L.g);        // [M][N + 1] logits, then routing probabilities
   uint16_t *nr = reinterpret_cast<uint16_t *>(smem + L.g);   // kRanked: [M][rank_row(N)] natural ranks
-  double *s = reinterpret_cast<double *>(smem + L.s);        // [N] aggregate scores
+  double *s = reinterpret_cast<double *>(smem + L.s);        // [N] aggregate scores, as they rank
   double *red = reinterpret_cast<double *>(smem + L.red);    // kRanked: [1024] sums of the parts by group
   int32_t *count = reinterpret_cast<int32_t *>(smem + L.count);  // [2][16] pairs per wave of a list (two lists in turn)
   int32_t *S = reinterpret_cast<int32_t *>(smem + L.S);      // [B] shortlist in rank order, -1 behind it
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
     inS[i] = 0;
     pos[i] = 0x7fffffff;
   }
-  for (int r = tid; r < B + kWave; r += nt) S[r] = -1;  // NaN scores: several experts count rank 0, slots stay unfilled
+  for (int r = tid; r < B + kWave; r += nt) S[r] = -1;
   for (int j = tid; j < k; j += nt) sel[j] = -1;
   __syncthreads();
 
@@ -496,7 +496,8 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
       if (tid < N) {
         double a = red[tid];
         for (int r = cp2; r < nt; r += cp2) a += red[r + tid];
-        s[tid] = a;
+        s[tid] = ranking_score(a);
+        if (scores_out && (int)blockIdx.x == last_wg) scores_out[tid] = a;
       }
     } else {
       for (int c0 = 0; c0 + group0 < N; c0 += kGroups) {
@@ -510,12 +511,16 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
           for (int u = 0; u < 4; ++u) a += v[u];  // rows past the end add +0.0, which leaves the sum unchanged
         }
         a = row16_sum(a);
-        if (seg == 0 && c0 + group < N) s[col] = a;
+        if (seg == 0 && c0 + group < N) {
+          s[col] = ranking_score(a);
+          if (scores_out && (int)blockIdx.x == last_wg) scores_out[col] = a;
+        }
       }
     }
     __syncthreads();
   }
-  // Section 3.2: the B highest aggregate scores, ties to the lowest id - or the caller's shortlist
+  // Section 3.2: the B highest aggregate scores, ties to the lowest id - or the caller's shortlist.  Every rank is claimed once, so that
+  // inS and pos name the experts of S and no others.
   if (ext_shortlist == nullptr) {
     // 16 lanes share a candidate and split its rivals: lane p takes p, p + 16, ...; 64 candidates per round
     for (int c0 = 0; c0 + group0 < N; c0 += kGroups) {
@@ -566,7 +571,6 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   // lists have workgroups of their own or the tokens outnumber the shortlist
   if ((int)blockIdx.x == last_wg) {
     for (int i = tid; i < N; i += nt) {
-      if (scores_out) scores_out[i] = s[i];
       if (seg_expert && inS[i]) {  // position of expert i among the shortlisted experts in ascending id
         int at = 0;
         for (int j = 0; j < i; ++j) at += inS[j];
