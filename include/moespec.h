@@ -143,6 +143,9 @@ moespec_status moespec_route(const moespec_desc *desc, const moespec_weights *we
  *   perm          [M*k] int32   out  surviving (token, slot) pairs as flat indices t*k+slot, ordered by
  *                                    (expert id, token); entries past seg_off[B] are -1
  *   n_loaded      [1] int32     out  number of non-empty segments = experts loaded (may be NULL)
+ * NaN: a score that is NaN ranks behind every number (ties: lowest id).  Of a token's NaN probabilities the one with the lowest
+ * id inside S, or of all where none is inside, takes slot 0 (its weight is NaN; outside S the slot is dropped); the others
+ * are passed over.
  */
 moespec_status moespec_budget(const moespec_desc *desc, const double *probs, int32_t M, int32_t B,
                               int32_t policy, const int32_t *ext_shortlist,

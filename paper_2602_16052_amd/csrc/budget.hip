@@ -210,7 +210,7 @@ __global__ __launch_bounds__(1024) void budget_kernel(
 #pragma unroll
     for (int u = 0; u < NU; ++u)
       if (lane + kWave * u < (int)L.row_stride) row[lane + kWave * u] = member[u] ? v[u] : kNoRival;
-    sel[lane] = -1;  // stays -1 where an external shortlist names fewer than k experts or a NaN leaves a slot unclaimed
+    sel[lane] = -1;  // stays -1 where an external shortlist names fewer than k experts or NaN values leave a slot unclaimed
     wave_lds_sync();
     int c[NU];
 #pragma unroll
@@ -218,11 +218,12 @@ __global__ __launch_bounds__(1024) void budget_kernel(
     rank_counts<NU>(row, 0, N, lane, 0, v, c);
 #pragma unroll
     for (int u = 0; u < NU; ++u)
-      if (member[u] && c[u] < k) sel[c[u]] = lane + kWave * u;
+      if (member[u] & (c[u] < k) & (v[u] == v[u])) sel[c[u]] = lane + kWave * u;
+    const int nan = nan_claim<NU>(v, member, inS);
     wave_lds_sync();
     // weights over the selected set in slot order, before any slot is dropped (Eq. (7)); truncation drops the slots outside S, kept
     // weights are unchanged
-    const int e = sel[lane];
+    const int e = lane == 0 && nan >= 0 ? nan : sel[lane];
     const double ge = lane < k && e >= 0 ? row[e] : 0.0, denom = renorm ? slot_sum(ge, k) : 1.0;
     if (lane < k) {
       const bool keep = e >= 0 && inS[e] != 0;
@@ -255,6 +256,7 @@ __global__ __launch_bounds__(1024) void budget_many_kernel(
     int32_t *__restrict__ budget_ids, int32_t *__restrict__ seg_expert, int32_t *__restrict__ tok_ids,
     float *__restrict__ tok_w) {
   extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int32_t nan;  // nan_key of the NaN that claims slot 0
   const int nt = blockDim.x, tid = threadIdx.x;
   const BudgetLds L = budget_lds(N, B, nt, 1);
   double *s = reinterpret_cast<double *>(smem + L.s);
@@ -292,13 +294,17 @@ __global__ __launch_bounds__(1024) void budget_many_kernel(
     if (tid < (int)L.row_stride) row[tid] = member ? v : kNoRival;
     if (tid < N) rank[tid] = 0;
     if (tid < kWave) sel[tid] = -1;
+    if (tid == 0) nan = kNoNaN;
     __syncthreads();
     rank_in_workgroup(row, N, rank);
     __syncthreads();
-    if (member && rank[tid] < k) sel[rank[tid]] = tid;
+    if (member) {
+      if (v != v) atomicMin(&nan, nan_key(tid, inS[tid] != 0));
+      else if (rank[tid] < k) sel[rank[tid]] = tid;
+    }
     __syncthreads();
     if (tid < kWave) {
-      const int e = sel[tid];
+      const int e = tid == 0 && nan != kNoNaN ? nan_key_id(nan) : sel[tid];
       const double ge = tid < k && e >= 0 ? row[e] : 0.0, denom = renorm ? slot_sum(ge, k) : 1.0;  // as in budget_kernel
       if (tid < k) {
         const bool keep = e >= 0 && inS[e] != 0;

@@ -236,13 +236,36 @@ __device__ __forceinline__ double slot_sum(double v, int k) {
   return a;
 }
 
+// A token's probabilities that are NaN rank nowhere and nothing ranks behind them, but the token must not come out finite by that: the NaN
+// with the lowest id among the shortlisted experts claims slot 0, or the lowest of all where none is shortlisted.  Its weight makes
+// the token's output NaN, unless the slot is dropped (Eq. (7)).  nan_claim: that id, -1 without a NaN, for a row held by a wave (v[u] =
+// candidate lane + 64 u, or none where member[u] is false).  The loops in LDS use an integer minimum over nan_key(id, listed).
+constexpr int32_t kNaNUnlisted = 1 << 16, kNoNaN = 0x7fffffff;
+__device__ __forceinline__ int32_t nan_key(int id, bool listed) { return listed ? id : id + kNaNUnlisted; }
+__device__ __forceinline__ int nan_key_id(int32_t key) { return key & (kNaNUnlisted - 1); }
+template <int NU>
+__device__ __forceinline__ int nan_claim(const double (&v)[NU], const bool (&member)[NU], const uint8_t *listed) {
+  const int lane = threadIdx.x & 63;
+  int32_t key = kNoNaN;
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const bool nan = member[u] & (v[u] != v[u]);
+    if (__ballot(nan) != 0) {  // uniform
+      const unsigned long long in = __ballot(nan && (listed == nullptr || listed[lane + kWave * u] != 0)), all = __ballot(nan);
+      key = min(key, nan_key(kWave * u + __ffsll((long long)(in ? in : all)) - 1, in != 0));
+    }
+  }
+  return key == kNoNaN ? -1 : nan_key_id(key);
+}
+
 // Rank-count selection of the k best of v[0..n).  sel[r] receives the index with rank r < k.  Equivalent to sorting by
 // (value descending, index ascending) and keeping the first k.  v, sel and the scratch rank[n] live in LDS.  Called by
 // every thread of the workgroup (it synchronises); the caller synchronises again before reading sel.  The n x n
 // comparisons are spread over the whole workgroup: thread (i, part) counts the rivals of candidate i inside its part of
 // the index range and adds its count to rank[i] with an integer LDS atomic (order-independent, hence deterministic).
-// Every slot of sel is first set to -1: when a value is NaN no comparison holds, several candidates then
-// count rank 0 and some slots are never claimed; those stay -1 (an unfilled slot) instead of stale LDS.
+// Every slot of sel is first set to -1: NaN values rank nowhere, so that slots may stay unfilled.  The lowest NaN claims slot 0: until
+// every value has been looked at the slot holds kNaNMark less its index.
+constexpr int32_t kNaNMark = 1 << 30;
 __device__ inline void select_topk(const double *v, int n, int k, int32_t *sel, int32_t *rank) {
   const int nt = blockDim.x, tid = threadIdx.x;
   int np2 = 1;
@@ -256,14 +279,23 @@ __device__ inline void select_topk(const double *v, int n, int k, int32_t *sel, 
     const int part = np2 <= nt ? tid / np2 : 0;
     const int j0 = part * chunk, j1 = min(n, j0 + chunk);
     const double vi = v[i];
+    if (vi != vi) {
+      atomicMax(&sel[0], kNaNMark - i);
+      continue;
+    }
     int cnt = 0;
 #pragma unroll 4
     for (int j = j0; j < j1; ++j) cnt += ranks_before(v[j], j, vi, i) ? 1 : 0;
     if (cnt) atomicAdd(&rank[i], cnt);
   }
   __syncthreads();
-  for (int x = tid; x < n; x += nt)
-    if (rank[x] < k) sel[rank[x]] = x;
+  for (int x = tid; x < n; x += nt) {
+    if (v[x] != v[x]) {
+      if (sel[0] == kNaNMark - x) sel[0] = x;
+    } else if (rank[x] < k && (rank[x] > 0 || sel[0] < 0)) {  // slot 0 is claimed by one value of either kind
+      sel[rank[x]] = x;
+    }
+  }
 }
 
 // Mixing weights of the slots sel[0..k): raw g or g / sum over the slots (summed in slot order).

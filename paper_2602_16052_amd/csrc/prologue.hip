@@ -353,7 +353,7 @@ __host__ __device__ inline PrologueLds prologue_lds(int M, int N, int k, int B, 
   L.S = take(sizeof(int32_t) * (B + kWave));
   L.cand = take(sizeof(int32_t) * (B + kWave));
   L.pos = take(sizeof(int32_t) * N);
-  L.sel = take(sizeof(int32_t) * k);
+  L.sel = take(sizeof(int32_t) * (k + 1));
   L.inS = take((size_t)N);
   L.total = off;
   return L;
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   int32_t *count = reinterpret_cast<int32_t *>(smem + L.count);  // [2][16] pairs per wave of a list (two lists in turn)
   int32_t *S = reinterpret_cast<int32_t *>(smem + L.S);      // [B] shortlist in rank order, -1 behind it
   int32_t *pos = reinterpret_cast<int32_t *>(smem + L.pos);  // [N] shortlist rank of every expert
-  int32_t *sel = reinterpret_cast<int32_t *>(smem + L.sel);  // [k] this token's selection
+  int32_t *sel = reinterpret_cast<int32_t *>(smem + L.sel);  // [k] this token's selection; [1] nan_key of the NaN that claims slot 0
   uint8_t *inS = smem + L.inS;
   constexpr int nt = kPrologueThreads, kGroups = nt / 16, kWaves = nt / kWave, kWaveGroups = kGroups / kWaves;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
     pos[i] = 0x7fffffff;
   }
   for (int r = tid; r < B + kWave; r += nt) S[r] = -1;
-  for (int j = tid; j < k; j += nt) sel[j] = -1;
+  for (int j = tid; j <= k; j += nt) sel[j] = j < k ? -1 : kNoNaN;
   __syncthreads();
 
   // Eq. (1): 16 lanes per row, 64 rows per round; a lane holds its NE elements of the row in registers
@@ -591,7 +591,7 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
   // "x goes before y" in a ranking by (probability descending, id ascending), without short-circuit evaluation
   // (which would turn into divergent control flow)
   auto before = [](double vx, int jx, double vy, int jy) { return (vx > vy) | ((vx == vy) & (jx < jy)); };
-  // The number of token t's candidates that go before expert e, counted by 16 lanes; -1 (or, unranked, any number) for a NaN.
+  // The number of token t's candidates that go before expert e, counted by 16 lanes; kNaNRank or more where its probability is a NaN.
   auto rank_among = [&](int t, int e) {
     int c = 0;
     if constexpr (kRanked) {
@@ -637,18 +637,22 @@ __global__ __launch_bounds__(kPrologueThreads) void route_budget_kernel(
 
   // This token's restricted routing.  Eq. (7) keeps the natural top-k slots that fall inside S with their weights
   // unchanged; Eq. (8) takes the top-k inside S and weights over that selection.  A candidate's rank is the number
-  // of candidates that go before it; rank r < k fills slot r.  A NaN claims slot 0: its weight makes the token's output NaN.
+  // of candidates that go before it; rank r < k fills slot r.  A NaN claims slot 0 (nan_claim), decided when all candidates are through.
   if (own >= 0) {
     for (int x0 = 0; x0 + group0 < n_cand; x0 += kGroups) {
       const int x = x0 + group, j = x >= n_cand ? -1 : truncate ? x : cand[x];
       const int c = rank_among(min(own, M - 1), max(j, 0));
-      if (seg == 0 && j >= 0 && (c < k || c >= kNaNRank)) sel[c < k ? c : 0] = j;
+      if (seg == 0 && j >= 0) {
+        if (c < k) sel[c] = j;
+        else if (c >= kNaNRank) atomicMin(&sel[k], nan_key(j, inS[j] != 0));
+      }
     }
   }
   auto token_write = [&]() {
     if (tid < k && own < M) {
-      const int e = sel[tid];
-      const bool keep = e >= 0 && inS[e] != 0;  // an unfilled slot (NaN scores) is dropped
+      const int32_t nan = sel[k];
+      const int e = tid == 0 && nan != kNoNaN ? nan_key_id(nan) : sel[tid];
+      const bool keep = e >= 0 && inS[e] != 0;  // an unfilled slot is dropped
       const double ge = e >= 0 ? (kRanked ? probs[(size_t)own * N + e] : g[own * NS + e]) : 0.0;
       double denom = 0.0;  // over the selected set in slot order (before any slot is dropped: Eq. (7)); k <= 64: one wave
       for (int sl = 0; sl < k; ++sl)

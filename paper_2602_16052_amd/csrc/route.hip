@@ -175,7 +175,10 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
     double *row = rows[kShare ? 0 : wave];
     int32_t *sel = sels[kShare ? 0 : wave];
     int c[NU];
-    sel[lane] = -1;  // stays -1 where a NaN leaves a slot unclaimed
+    sel[lane] = -1;  // stays -1 where NaN values leave a slot unclaimed
+    bool real[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) real[u] = lane + kWave * u < N;
     if constexpr (kShare) {
 #pragma unroll
       for (int u = 0; u < NU; ++u) c[u] = rank[lane + kWave * u];
@@ -191,9 +194,10 @@ __global__ __launch_bounds__(kGateThreads) void gate_rows_kernel(const double *p
     }
 #pragma unroll
     for (int u = 0; u < NU; ++u)
-      if (lane + kWave * u < N && c[u] < k) sel[c[u]] = lane + kWave * u;
+      if (real[u] & (c[u] < k) & (val[u] == val[u])) sel[c[u]] = lane + kWave * u;
+    const int nan = nan_claim<NU>(val, real, nullptr);
     wave_lds_sync();
-    const int e = sel[lane];  // -1 behind the last slot
+    const int e = lane == 0 && nan >= 0 ? nan : sel[lane];  // -1 behind the last slot
     const double ge = lane < k && e >= 0 ? row[e] : 0.0, denom = renorm ? slot_sum(ge, k) : 1.0;
     if (lane < k) {
       if (topk_ids) topk_ids[(size_t)t * k + lane] = e;

@@ -31,6 +31,26 @@ def oracle_weights(W):
     return {key: (wl.as_f32(val) if val is not None else None) for key, val in W.items()}
 
 
+def routing_with_nan(g, k, S, policy, renorm):
+    """(ids, weights) of the restricted routing of probabilities g[M, N] that may be NaN inside the shortlist S.  Numbers rank among
+    themselves; the lowest NaN candidate inside S, or the lowest of all where none is inside, has slot 0."""
+    M, N = g.shape
+    ids, w = np.full((M, k), -1, dtype=np.int32), np.zeros((M, k))
+    for t in range(M):
+        cand = range(N) if policy == mb.TRUNCATE else S
+        sel = sorted((i for i in cand if not np.isnan(g[t, i])), key=lambda i: (-g[t, i], i))[:k]
+        nan = sorted((i not in S, i) for i in cand if np.isnan(g[t, i]))
+        if nan:
+            sel[:1] = [nan[0][1]]
+        denom = 0.0
+        for e in sel:
+            denom += g[t, e]
+        for s, e in enumerate(sel):
+            if e in S:
+                ids[t, s], w[t, s] = e, g[t, e] / denom if renorm else g[t, e]
+    return ids, w
+
+
 def out_to_numpy(out: torch.Tensor) -> np.ndarray:
     return out.float().cpu().numpy().astype(np.float64)
 

@@ -10,7 +10,7 @@ from oracle import moespec_oracle as O
 from paper_2602_16052_amd import binding as mb
 from paper_2602_16052_amd import workloads as wl
 
-from gpu_common import (assert_out_close, assert_routing_equal, desc_of, oracle_weights, out_to_numpy, to_device,
+from gpu_common import (assert_out_close, assert_routing_equal, desc_of, oracle_weights, out_to_numpy, routing_with_nan, to_device,
                         upload_weights)
 
 pytestmark = pytest.mark.gpu
@@ -78,9 +78,9 @@ def test_equal_probabilities_go_to_the_lowest_id(dtype, d, N, k, M, B):
 @pytest.mark.parametrize("gate", ["softmax", "sigmoid"])
 @pytest.mark.parametrize("dtype,d,N,k,M,B", [SMALL[8], LARGE[0], LARGE[6]])
 def test_a_nan_expert_claims_a_slot_and_no_pair(dtype, d, N, k, M, B, gate):
-    """A router bias that is NaN: under softmax every probability is NaN, under sigmoid that of one expert.  A caller's shortlist
-    keeps the selection defined: the NaN expert claims slot 0 (whose weight makes the token's output NaN) where it is in the
-    candidates, and is in no pair list; the output of a token is finite exactly where none of its slots is NaN."""
+    """A router bias that is NaN: under softmax every probability is NaN, under sigmoid that of one expert.  A NaN candidate claims slot
+    0 (whose weight makes the token's output NaN unless the slot is dropped), and is in no pair list; the output of a token is finite
+    exactly where none of its slots is NaN."""
     bad = 5
 
     def nan_bias(h, W):
@@ -90,15 +90,18 @@ def test_a_nan_expert_claims_a_slot_and_no_pair(dtype, d, N, k, M, B, gate):
         ext = [i for i in range(B + 1) if i != bad] + ([bad] if with_bad else [])
         for cfg, h, W, policy, out, plain, taps in run(dtype, d, N, k, M, B, gate, ext=ext, spoil=nan_bias):
             ids, w = taps["tok_ids"].cpu().numpy(), taps["tok_w"].cpu().numpy()
+            want_ids, want_w = routing_with_nan(taps["probs"].cpu().numpy(), k, ext, policy, cfg.renorm)
+            assert np.array_equal(ids, want_ids)
+            np.testing.assert_allclose(w, want_w, rtol=1e-6, atol=1e-12)  # NaN in the same places
+            assert torch.equal(out.view(torch.uint8), plain.view(torch.uint8))
             off, seg = taps["seg_off"].cpu().numpy(), taps["seg_expert"].cpu().numpy()
             sizes = {int(e): int(off[i + 1] - off[i]) for i, e in enumerate(seg) if e >= 0}
             assert sizes.get(bad, 0) == 0
-            if gate == "softmax":
-                assert sum(sizes.values()) == 0 and np.all(np.isnan(w[ids >= 0]))
-            elif policy == mb.SUBSTITUTE and not with_bad:
-                assert np.all(np.isfinite(w)) and np.all(np.isfinite(out_to_numpy(out)))
-            elif with_bad:
-                assert np.all(np.isnan(w[:, 0]) | (ids[:, 0] != bad))
             rows = np.isnan(out_to_numpy(out)).any(axis=1)
-            if gate == "sigmoid":
-                assert np.array_equal(rows, np.isnan(w).any(axis=1))
+            assert np.array_equal(rows, np.isnan(w).any(axis=1))
+            if gate == "softmax":
+                assert sum(sizes.values()) == 0 and np.all(rows)
+            elif with_bad:
+                assert np.all(ids[:, 0] == bad) and np.all(rows)
+            elif policy == mb.SUBSTITUTE:
+                assert not np.any(rows)
