@@ -20,11 +20,11 @@ pytestmark = pytest.mark.gpu
                                          (2052, 4, 2, 132, 35, 4), (140, 4, 2, 1024, 300, 3), (1040, 8, 2, 300, 270, 8),
                                          (528, 40, 2, 64, 60, 30)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
-def test_f32_held_weights(d, N, k, F, M, B, policy):
+def test_f32_held_weights(d, N, k, F, M, B, policy, alpha=0.8):
     print(f"case d={d} N={N} k={k} F={F} M={M} B={B} policy={policy}", flush=True)
     if policy == mb.SUBSTITUTE and B < k:
         B = k
-    cfg = wl.small_config("held", "f32", d=d, n_experts=N, top_k=k, d_ff=F, M=M, bias_alpha=0.8, seed=d + M)
+    cfg = wl.small_config("held", "f32", d=d, n_experts=N, top_k=k, d_ff=F, M=M, bias_alpha=alpha, seed=d + M)
     h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
     h_d, W_d, ws = to_device(h), upload_weights(W), mb.alloc_workspace(desc, M)
     ref = O.layer_forward(wl.as_f32(h), oracle_weights(W), k, cfg.renorm, B, policy)
@@ -45,3 +45,12 @@ def test_f32_held_weights_of_few_rows(d, N, k, F, M, B, policy):
     """The down pass of up to 112 workgroups, which holds up to 1024 elements: both sides of either limit, waves without a step in the
     fourth round, and segments that four workgroups share."""
     test_f32_held_weights(d, N, k, F, M, B, policy)
+
+
+@pytest.mark.parametrize("d,N,k,F,M,B", [(48, 64, 1, 60, 80, 64), (96, 64, 2, 520, 120, 50), (48, 128, 1, 256, 200, 128), (516, 60, 1, 48, 255, 40),
+                                         (36, 256, 2, 708, 363, 256), (108, 256, 1, 148, 700, 128), (64, 64, 8, 260, 200, 64)])
+@pytest.mark.parametrize("alpha", [0.2, 4.0])
+@pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
+def test_f32_held_long_segments(d, N, k, F, M, B, alpha, policy):
+    """Many short segments and, with alpha = 4, one of nearly all tokens (or its pieces), which up to four workgroups share."""
+    test_f32_held_weights(d, N, k, F, M, B, policy, alpha)
