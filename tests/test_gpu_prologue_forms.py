@@ -19,9 +19,11 @@ SMALL = [("bf16", 32, 1, 1, 1, 1), ("bf16", 96, 5, 2, 3, 4), ("bf16", 160, 7, 3,
          ("f32", 132, 9, 4, 17, 6), ("f32", 1028, 3, 1, 4, 2), ("bf16", 4256, 6, 2, 9, 5), ("f32", 4612, 4, 2, 5, 3),
          ("bf16", 64, 87, 8, 63, 40), ("bf16", 64, 21, 4, 255, 12), ("bf16", 128, 256, 6, 21, 200), ("f32", 72, 22, 3, 250, 7)]
 LARGE = [("bf16", 64, 88, 8, 63, 40), ("bf16", 64, 22, 4, 255, 12), ("bf16", 32, 251, 6, 24, 130), ("bf16", 64, 234, 8, 256, 80),
-         # with a long shortlist the staged kernels under substitution alone; the staged kernels
          ("bf16", 64, 200, 8, 255, 200), ("bf16", 64, 256, 8, 256, 256),
-         ("bf16", 128, 129, 8, 127, 64), ("f32", 72, 31, 3, 201, 11), ("bf16", 2048, 64, 8, 129, 16), ("f32", 36, 200, 2, 131, 70)]
+         ("bf16", 128, 129, 8, 127, 64), ("f32", 72, 31, 3, 201, 11), ("bf16", 2048, 64, 8, 129, 16), ("f32", 36, 200, 2, 131, 70),
+         # beyond the LDS as doubles: fused, under truncation alone (table, shortlist), staged (as two above)
+         ("bf16", 64, 128, 8, 256, 128), ("f32", 36, 100, 4, 210, 30), ("f32", 36, 200, 2, 160, 75), ("bf16", 64, 140, 6, 250, 40),
+         ("f32", 36, 200, 2, 160, 76), ("bf16", 64, 141, 8, 256, 46)]
 
 
 def run(dtype, d, N, k, M, B, gate="softmax", ext=None, spoil=None):
