@@ -213,14 +213,20 @@ template <int Q, int NU>
 __global__ __launch_bounds__(1024) void gate_parts_kernel(const double *partial, const float *__restrict__ bias, int M, int N,
                                                           int sigmoid_gate, double *probs, double *__restrict__ parts) {
   __shared__ double rows[16][NU * kWave];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6, t = blockIdx.x * n_waves + wave;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+  const int t = blockIdx.x * n_waves + wave;
   double val[NU];
-  load_logits<Q, NU>(partial, bias, M, N, min(t, M - 1), val);
-  gate_of_row<NU>(val, sigmoid_gate);
+  if (t < M) {  // uniform in the wave; partial may be probs: a row belongs to one wave
+    load_logits<Q, NU>(partial, bias, M, N, t, val);
+    gate_of_row<NU>(val, sigmoid_gate);
+  } else {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) val[u] = 0.0;
+  }
 #pragma unroll
   for (int u = 0; u < NU; ++u) {
     const int i = lane + kWave * u;
-    rows[wave][i] = t < M ? val[u] : 0.0;
+    rows[wave][i] = val[u];
     if (i < N && t < M) probs[(size_t)t * N + i] = val[u];
   }
   __syncthreads();
