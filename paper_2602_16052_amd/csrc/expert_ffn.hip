@@ -1559,12 +1559,15 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     // workgroups have twice the rows (32 of 256 experts of 2900 x 152, 128 tokens 204 / 179).
     const bool mf = matrix && !(pass == 1 && K <= 160 && mean <= 6 && (long long)mf_row_tiles * n_seg * groups(mf_tile) >= 24576);
     const bool few_rows = pass == 2 && (long long)((R + 15) / 16) * n_seg <= kF32HeldFew;
-    if (mf && K <= (few_rows ? kF32HeldKFew : kF32HeldK)) {
-      const int ka = (K + 255) / 256, pair_tiles = (int)std::min<long long>(std::max<long long>((mean + 15) / 16, 1), 4);
-      // The down pass takes 32 rows, which reads the pairs half as often, where there is still a workgroup for every second compute unit
-      // (layers, us, 32 / 16 rows: 352 x 268 over 17 segments of 2 pairs 19.2 / 19.9, 884 x 88 over 9 of 4 19.5 / 20.3; 84 x 604 over 8
-      // of 35 21.6 / 20.5).
-      const int na = pass == 2 && (ka == 4 || (long long)((R + 31) / 32) * n_seg * pair_tiles < 128) ? 1 : 2;
+    const int ka = (K + 255) / 256, pair_tiles = (int)std::min<long long>(std::max<long long>((mean + 15) / 16, 1), 4);
+    // The down pass takes 32 rows, which reads the pairs half as often, where there is still a workgroup for every second compute unit
+    // (layers, us, 32 / 16 rows: 352 x 268 over 17 segments of 2 pairs 19.2 / 19.9, 884 x 88 over 9 of 4 19.5 / 20.3; 84 x 604 over 8
+    // of 35 21.6 / 20.5).
+    const int na = pass == 2 && (ka == 4 || (long long)((R + 31) / 32) * n_seg * pair_tiles < 128) ? 1 : 2;
+    // Up to 16 tokens make one tile of pairs, for which nothing is held: the streaming form then, except where the down pass gains
+    // workgroups by its 16 rows (held / streaming, 122 gate/up passes 1.01x, 78 down passes of 32 rows 1.03x, of 8192 x 64 over 128
+    // segments 51.7 / 44.8 us; 58 of 16 rows 0.87x).
+    if (mf && K <= (few_rows ? kF32HeldKFew : kF32HeldK) && (M > 16 || na == 1)) {
       const int tiles = pass == 1 ? (R + 15) / 16 : (R + 16 * na - 1) / (16 * na);
       // workgroups share the pairs of a segment until there are two per compute unit
       int z = 1;
