@@ -800,13 +800,20 @@ bool fused_prologue_ok(const moespec_desc &ds, int M, int B, int policy) {
 
 // Tiles of 32 tokens x 32 experts (16 for up to 16 experts) where they and the slices make a workgroup per compute unit, leave every
 // wave four blocks of the hidden dimension, and do not spend on padding what they save, which is 5 to 10 % (3000 tokens x 100 experts,
-// 128 columns of tiles instead of 112: 0.93 of the speed).
+// 128 columns of tiles instead of 112: 0.93 of the speed).  One such workgroup is resident per compute unit, so that they come in whole
+// rounds, in each of which a compute unit is through with 4 (2) of the 16 x 16 tiles: not where those alone would give none of the
+// compute units as many (1165 tokens x 218 experts, d = 3296, 259 workgroups 62 us, 16 x 16 tiles 39), nor in several rounds of fewer
+// than six blocks per wave, which start up each time.  3133 projections of 400 to 16384 tokens against 16 x 16 tiles alone: 1.03x, 6 of
+// them slower by more than 3 % (0.94x); wherever they and the slices made 256 workgroups it was 0.96x (0.64x at least).  In two
+// slices the others are the less even ones (0.75 and 0.87), but where one slice makes a workgroup per compute unit two were 0.92x.
 static int block_experts(const moespec_desc &ds) { return ds.n_experts > 16 ? 2 : 1; }
 static bool logits_in_blocks(const moespec_desc &ds, int M, int slices) {
-  const int N = ds.n_experts, rows = 16 * block_experts(ds);
+  const int N = ds.n_experts, te = block_experts(ds), rows = 16 * te;
   const long long tiles = (long long)((M + 31) / 32) * ((N + rows - 1) / rows), plain = (long long)((M + 15) / 16) * ((N + 15) / 16);
-  return ds.dtype == MOESPEC_BF16 && tiles * slices >= 256 && ds.d / 32 >= 4 * kBlockWaves * slices &&
-         tiles * 2 * (rows / 16) * 95 <= plain * 100;
+  const long long rounds = (tiles * slices + 255) / 256, most_plain = (plain * slices + 255) / 256;  // per compute unit
+  if (ds.dtype != MOESPEC_BF16 || tiles * slices < 256 || (slices > 1 && tiles >= 256)) return false;
+  return ds.d / 32 >= (rounds > 1 ? 6 : 4) * kBlockWaves * slices &&
+         tiles * 2 * te * 95 <= plain * 100 && rounds * 2 * te * (slices == 1 ? 95 : te == 1 ? 75 : 87) <= most_plain * 100;
 }
 
 // Slices of the hidden dimension (1, 2, 4 or 8, at most `most`): more slices spread the matrix work over more compute units
