@@ -115,8 +115,8 @@ moespec_status layer_forward(const moespec_desc *desc, const moespec_weights *we
   };
   mark(0);
   if (fused_prologue_ok(*desc, M, B, policy) && expert_ffn_self_segmenting(*desc, M) && !expert_ffn_wide(*desc, M, B)) {
-    // Small trees: two launches leave the shortlist, the restricted routing and every loaded expert's pair
-    // list; the expert passes pick their work items from those lists.
+    // Small trees: two launches (three for tables above 5500 entries) leave the shortlist, the restricted routing and every
+    // loaded expert's pair list; the expert passes pick their work items from those lists.
     hipError_t e = launch_fused_prologue(*desc, *weights, h, M, B, policy, ext_shortlist, w.partial, w.score_parts, w.y, w.probs, t.probs,
                                          t.scores,
                                          budget_ids, t.seg_expert, tok_ids, tok_w, w.list_count, w.lists, M,
@@ -132,6 +132,7 @@ moespec_status layer_forward(const moespec_desc *desc, const moespec_weights *we
   const size_t act_bytes = (desc->dtype == MOESPEC_BF16 ? 2 : 4) * (size_t)M * desc->top_k * desc->d_ff;
   int n_parts = gate_parts(*desc, M);
   if (M <= 128 || (size_t)n_parts * desc->n_experts * sizeof(double) > act_bytes) n_parts = 0;
+  if (ext_shortlist != nullptr && t.scores == nullptr) n_parts = 0;  // nothing reads the sums
   double *parts = n_parts > 0 ? static_cast<double *>(w.act) : nullptr;
   hipError_t e = launch_route(*desc, *weights, h, M, probs, nullptr, nullptr, w.partial, w.partial_slices, parts, st);
   if (e != hipSuccess) return MOESPEC_ERR_HIP;

@@ -41,6 +41,24 @@ def test_sums_beside_the_gate(M, N, k, F, gate, dtype):
     layer(dtype, 32, N, k, F, M, max(k, N // 3), mb.SUBSTITUTE, gate)
 
 
+@pytest.mark.parametrize("dtype,M,N,k", [("bf16", 257, 64, 4), ("f32", 300, 200, 2), ("bf16", 2049, 17, 3)])
+@pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
+def test_shortlist_of_the_caller(dtype, M, N, k, policy):
+    """Sums over tokens are only made where the scores are handed out."""
+    print(f"case {dtype} N={N} k={k} M={M} policy={policy}", flush=True)
+    cfg = wl.small_config("staged_ext", dtype, d=64, n_experts=N, top_k=k, d_ff=64, M=M, bias_alpha=0.8, seed=M + N)
+    h, W, desc = wl.hidden_states(cfg), wl.layer_weights(cfg), desc_of(cfg)
+    ext = list(range(N - 1, N // 2, -1))
+    h_d, W_d, ws, ext_d = to_device(h), upload_weights(W), mb.alloc_workspace(desc, M), torch.tensor(ext, dtype=torch.int32, device="cuda")
+    ref = O.layer_forward(wl.as_f32(h), oracle_weights(W), k, cfg.renorm, len(ext), policy, ext_shortlist=ext)
+    plain = mb.moespec_layer_forward(desc, W_d, h_d, len(ext), policy, ws, ext_shortlist=ext_d)
+    out, taps = mb.moespec_layer_forward(desc, W_d, h_d, len(ext), policy, ws, ext_shortlist=ext_d, taps=True)
+    torch.cuda.synchronize()
+    assert_routing_equal(taps, ref, len(ext))
+    assert_out_close(out_to_numpy(out), ref["out"], dtype)
+    assert torch.equal(out, plain)
+
+
 @pytest.mark.parametrize("M,k", [(256, 8), (255, 7), (1, 8), (257, 7), (227, 9), (256, 9)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_pairs_grouped(M, k, policy):
