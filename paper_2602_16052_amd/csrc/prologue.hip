@@ -774,14 +774,14 @@ __global__ __launch_bounds__(256) void lists_to_segments_kernel(const int32_t *_
 // again, come in rounds, while the staged kernels grow with the tokens alone.  Whole fp32 layer of 4 experts, us, fused
 // less staged: 128 tokens -4, 160 -2, 200 to 256 +1, 300 +2, 400 +5, 512 +16, 1024 +68; of 64 experts, top-8: 128 -5, 256 -5,
 // 300 0; bf16 within 4 up to 256.
-// Tables that as doubles would not fit the LDS (the ranks do) have more than 20000 entries, and there the fused form pays only in part.
-// Its prologue saves 4 to 8 us up to 128 experts; with more the last kernel, where every workgroup loads all ranks and, under
-// substitution, ranks an expert against the whole shortlist, takes that back: -4 us at 57000 entries.  And its expert passes look up
-// their item in the lists: 1.15 us per 1000 workgroups of bf16 passes (8192 x 32, 256 experts, 90 tokens, down pass 80 / 117 us).
-// Line by layers of 60 to 256 tokens and 80 to 256 experts, either policy, budgets of 1/16 to all: over 379 bf16 layers the side taken
-// is 0.2 % slower than the better one on average, 5 % at most; staged alone is 3.1 % (24 %), fused alone 3.2 % (36 %).  Over 133
-// fp32 layers, where the lists also hold segments that the staged form cuts in pieces of 128 pairs, 1.3 % (24 %) against 3.5 % (29 %)
-// and 6.3 % (51 %).
+// Tables that as doubles would not leave the LDS room for other work (above 151 KB; the ranks do) have more than 18500 entries, and
+// there the fused form pays only in part (90 x 208, d = 1120, 183 shortlisted 45.1 us staged, 47.7 fused).  Its prologue saves 4 to 8
+// us up to 128 experts; with more the last kernel, where every workgroup loads all ranks and, under substitution, ranks an expert
+// against the whole shortlist, takes that back: -4 us at 57000 entries.  And its expert passes look up their item in the lists: 1.15
+// us per 1000 workgroups of bf16 passes (8192 x 32, 256 experts, 90 tokens, down pass 80 / 117 us). Line by layers of 60 to 256 tokens
+// and 80 to 256 experts, either policy, budgets of 1/16 to all: over 379 bf16 layers the side taken is 0.2 % slower than the better
+// one on average, 5 % at most; staged alone is 3.1 % (24 %), fused alone 3.2 % (36 %).  Over 133 fp32 layers, where the lists also
+// hold segments that the staged form cuts in pieces of 128 pairs, 1.3 % (24 %) against 3.5 % (29 %) and 6.3 % (51 %).
 static bool fused_beyond_lds(const moespec_desc &ds, int M, int B, int policy) {
   const int N = ds.n_experts;
   const long long pass_wgs = (long long)B * ((ds.d_ff + 63) / 64 + (ds.d + 127) / 128);
@@ -794,7 +794,7 @@ bool fused_prologue_ok(const moespec_desc &ds, int M, int B, int policy) {
   const bool ranked = (long long)M * N > kSplitSoftmaxAbove;
   // the ranks lie in the place of y: [kMaxDownSplits][M k, d] floats
   if (ranked && sizeof(uint16_t) * rank_row(N) > sizeof(float) * kMaxDownSplits * ds.top_k * ds.d) return false;
-  if (ranked && prologue_lds(M, N, ds.top_k, N, false).total > 160 * 1024 && !fused_beyond_lds(ds, M, B, policy)) return false;
+  if (ranked && prologue_lds(M, N, ds.top_k, N, false).total > 151 * 1024 && !fused_beyond_lds(ds, M, B, policy)) return false;
   return prologue_lds(M, N, ds.top_k, N, ranked).total <= 160 * 1024;
 }
 

@@ -23,7 +23,9 @@ LARGE = [("bf16", 64, 88, 8, 63, 40), ("bf16", 64, 22, 4, 255, 12), ("bf16", 32,
          ("bf16", 128, 129, 8, 127, 64), ("f32", 72, 31, 3, 201, 11), ("bf16", 2048, 64, 8, 129, 16), ("f32", 36, 200, 2, 131, 70),
          # beyond the LDS as doubles: fused, under truncation alone (table, shortlist), staged (as two above)
          ("bf16", 64, 128, 8, 256, 128), ("f32", 36, 100, 4, 210, 30), ("f32", 36, 200, 2, 160, 75), ("bf16", 64, 140, 6, 250, 40),
-         ("f32", 36, 200, 2, 160, 76), ("bf16", 64, 141, 8, 256, 46)]
+         ("f32", 36, 200, 2, 160, 76), ("bf16", 64, 141, 8, 256, 46),
+         # just within it: the same choice
+         ("bf16", 64, 208, 8, 90, 183), ("f32", 36, 140, 3, 140, 130)]
 
 
 def run(dtype, d, N, k, M, B, gate="softmax", ext=None, spoil=None):
