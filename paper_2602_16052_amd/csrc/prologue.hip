@@ -778,12 +778,15 @@ __global__ __launch_bounds__(256) void lists_to_segments_kernel(const int32_t *_
 // there the fused form pays only in part (90 x 208, d = 1120, 183 shortlisted 45.1 us staged, 47.7 fused).  Its prologue saves 4 to 8
 // us up to 128 experts; with more the last kernel, where every workgroup loads all ranks and, under substitution, ranks an expert
 // against the whole shortlist, takes that back: -4 us at 57000 entries.  And its expert passes look up their item in the lists: 1.15
-// us per 1000 workgroups of bf16 passes (8192 x 32, 256 experts, 90 tokens, down pass 80 / 117 us). Line by layers of 60 to 256 tokens
+// us per 1000 workgroups of bf16 passes (8192 x 32, 256 experts, 90 tokens, down pass 80 / 117 us).  Line by layers of 60 to 256 tokens
 // and 80 to 256 experts, either policy, budgets of 1/16 to all: over 379 bf16 layers the side taken is 0.2 % slower than the better
-// one on average, 5 % at most; staged alone is 3.1 % (24 %), fused alone 3.2 % (36 %).  Over 133 fp32 layers, where the lists also
-// hold segments that the staged form cuts in pieces of 128 pairs, 1.3 % (24 %) against 3.5 % (29 %) and 6.3 % (51 %).
+// one on average, 5 % at most; staged alone is 3.1 % (24 %), fused alone 3.2 % (36 %).  fp32 segments of more than 128 tokens are cut
+// in pieces by the staged kernels only, and where routing concentrates that decides: 5385 drawn layers of 129 to 256 tokens against
+// the kernels before the fused form reached them, fused 1.141x (0.77x at worst, 127 slower by more than 5 %; top-1 1.09x), staged
+// 1.147x (0.91x, 1; top-1 1.11x).
 static bool fused_beyond_lds(const moespec_desc &ds, int M, int B, int policy) {
   const int N = ds.n_experts;
+  if (ds.dtype == MOESPEC_F32 && M > kPiecePairs) return false;
   const long long pass_wgs = (long long)B * ((ds.d_ff + 63) / 64 + (ds.d + 127) / 128);
   if (N <= 128) return pass_wgs <= 4000;
   return pass_wgs <= 3000 && (policy == MOESPEC_TRUNCATE ? M * N <= 36000 : M * N <= 32000 && M * B <= 12000);

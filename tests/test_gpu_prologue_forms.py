@@ -25,7 +25,9 @@ LARGE = [("bf16", 64, 88, 8, 63, 40), ("bf16", 64, 22, 4, 255, 12), ("bf16", 32,
          ("bf16", 64, 128, 8, 256, 128), ("f32", 36, 100, 4, 210, 30), ("f32", 36, 200, 2, 160, 75), ("bf16", 64, 140, 6, 250, 40),
          ("f32", 36, 200, 2, 160, 76), ("bf16", 64, 141, 8, 256, 46),
          # just within it: the same choice
-         ("bf16", 64, 208, 8, 90, 183), ("f32", 36, 140, 3, 140, 130)]
+         ("bf16", 64, 208, 8, 90, 183), ("f32", 36, 140, 3, 140, 130),
+         # fp32 layers that stay fused, on either side of the limit of its tokens
+         ("f32", 36, 200, 2, 128, 70), ("f32", 36, 146, 4, 127, 30), ("f32", 36, 146, 4, 129, 30)]
 
 
 def run(dtype, d, N, k, M, B, gate="softmax", ext=None, spoil=None):
