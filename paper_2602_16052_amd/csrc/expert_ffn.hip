@@ -1566,12 +1566,17 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
     const int na = pass == 2 && (ka == 4 || (long long)((R + 31) / 32) * n_seg * pair_tiles < 128) ? 1 : 2;
     // Up to 16 tokens make one tile of pairs, for which nothing is held: the streaming form then, except where the down pass gains
     // workgroups by its 16 rows (held / streaming, 122 gate/up passes 1.01x, 78 down passes of 32 rows 1.03x, of 8192 x 64 over 128
-    // segments 51.7 / 44.8 us; 58 of 16 rows 0.87x).
-    if (mf && K <= (few_rows ? kF32HeldKFew : kF32HeldK) && (M > 16 || na == 1)) {
-      const int tiles = pass == 1 ? (R + 15) / 16 : (R + 16 * na - 1) / (16 * na);
+    // segments 51.7 / 44.8 us; 58 of 16 rows 0.87x).  Segments of less than four pairs make little more than a tile each, and with one
+    // workgroup per segment in one or two rounds (512 to 1023) the longest of them decide, which the streaming form shares out: held
+    // / streaming, layers, 280 such gate/up passes 1.02x (0.93 to 1.11x); in more workgroups what each costs decides, from 2048 on 0.91x.
+    // 244 such down passes 1.01x (0.91 to 1.12x): held.
+    const int tiles = pass == 1 ? (R + 15) / 16 : (R + 16 * na - 1) / (16 * na);
+    const long long held_wgs = (long long)tiles * n_seg;
+    const bool reused = M > 16 && !(pass == 1 && mean < 4 && held_wgs >= 512 && held_wgs < 1024);
+    if (mf && K <= (few_rows ? kF32HeldKFew : kF32HeldK) && (reused || na == 1)) {
       // workgroups share the pairs of a segment until there are two per compute unit
       int z = 1;
-      while (z < 4 && 16 * z < M && (long long)tiles * n_seg * z < 512) ++z;
+      while (z < 4 && 16 * z < M && held_wgs * z < 512) ++z;
       // Routing concentrates, and a segment (or a piece of one) is then far longer than the mean, the only length known here: where one
       // could have five tiles of pairs or more and six times the mean, more workgroups stand by for it, and segments of the mean length
       // keep to one.  Layers, us, without / with them: 464 x 192, 50 of 100 experts, 249 tokens, top-2 69.9 / 44.1; 196 x 256, 64 of
@@ -1582,7 +1587,7 @@ hipError_t launch_expert_ffn(const moespec_desc &ds, const moespec_weights &wt, 
       const int usual = (int)std::min<long long>((std::max<long long>(mean, 1) + 15) / 16, longest);
       int parts = z;
       if (longest >= 5 && longest >= 6 * usual)
-        while (parts < groups(16) && (long long)tiles * n_seg * (parts + 1) <= 4096) ++parts;
+        while (parts < groups(16) && held_wgs * (parts + 1) <= 4096) ++parts;
       const int k_walk = k | (parts > z ? 16 * usual : 16) << 8;
       const dim3 hgrid(tiles, rows, parts);
       auto pick = [&](auto ka_) {

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
                                          (768, 3, 2, 768, 49, 2), (772, 2, 2, 516, 31, 2), (48, 5, 3, 260, 7, 4),
                                          (2052, 4, 2, 132, 35, 4), (140, 4, 2, 1024, 300, 3), (1040, 8, 2, 300, 270, 8),
                                          (528, 40, 2, 64, 60, 30), (32, 2, 1, 252, 18, 2), (256, 2, 2, 28, 17, 2), (48, 5, 3, 260, 19, 4),
-                                         (1056, 6, 2, 36, 16, 6)])
+                                         (1056, 6, 2, 36, 16, 6), (36, 40, 2, 208, 60, 40), (36, 40, 2, 208, 60, 39)])
 @pytest.mark.parametrize("policy", [mb.TRUNCATE, mb.SUBSTITUTE])
 def test_f32_held_weights(d, N, k, F, M, B, policy, alpha=0.8):
     print(f"case d={d} N={N} k={k} F={F} M={M} B={B} policy={policy}", flush=True)
